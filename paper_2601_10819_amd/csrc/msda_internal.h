@@ -81,7 +81,6 @@ struct TileArgs {
     int32_t NL, B, C, G;
     int64_t R;
     int32_t lps_shift;            // log2(C / chans_per_lane)
-    int32_t waves;                // narrower lane groups: waves sharing each tile's records (set by the launcher)
     uint64_t magic;               // sample -> anchor: s / (P*N*L) == (s * magic) >> magic_shift
     int32_t magic_shift;
 };
@@ -131,7 +130,6 @@ struct BatchArgs {
     // tiled reduction
     const uint32_t* vals;
     const uint32_t* off;
-    int32_t waves;                // narrower lane groups: as TileArgs::waves
     uint32_t tile_begin, tile_split, tile_end;  // as TileArgs
 };
 

@@ -146,50 +146,25 @@ __device__ __forceinline__ void add_sample(float (&acc)[TH][TW][CPL], float4 f, 
     }
 }
 
-// Dispatch on the cell position pos = DY * 5 + DX of a 4x4 tile's 5x5 cells
-// (uniform within the lane group) to the static accumulation: a switch, which
-// the compiler lowers to a jump table.
-template <int CPL>
-__device__ __forceinline__ void add_sample_at(int pos, float (&acc)[4][4][CPL], float4 f,
-                                              float wv, const float* gv) {
-#define MSDA_CELL_CASE(P) \
-    case P: add_sample<(P) / 5, (P) % 5, 4, 4, CPL>(acc, f, wv, gv); break;
-    switch (pos) {
-        MSDA_CELL_CASE(0) MSDA_CELL_CASE(1) MSDA_CELL_CASE(2) MSDA_CELL_CASE(3) MSDA_CELL_CASE(4)
-        MSDA_CELL_CASE(5) MSDA_CELL_CASE(6) MSDA_CELL_CASE(7) MSDA_CELL_CASE(8) MSDA_CELL_CASE(9)
-        MSDA_CELL_CASE(10) MSDA_CELL_CASE(11) MSDA_CELL_CASE(12) MSDA_CELL_CASE(13)
-        MSDA_CELL_CASE(14) MSDA_CELL_CASE(15) MSDA_CELL_CASE(16) MSDA_CELL_CASE(17)
-        MSDA_CELL_CASE(18) MSDA_CELL_CASE(19) MSDA_CELL_CASE(20) MSDA_CELL_CASE(21)
-        MSDA_CELL_CASE(22) MSDA_CELL_CASE(23) MSDA_CELL_CASE(24)
-        default: break;
-    }
-#undef MSDA_CELL_CASE
-}
-
-// One sample of a statically known cell (DY, DX): the arithmetic of the
-// switch's case (DY * 5 + DX).
+// One sample of a statically known cell (DY, DX).
 template <int DY, int DX, int CPL>
 __device__ __forceinline__ void cell_sample(float (&acc)[4][4][CPL], float4 f, float wv,
                                             const float* gv) {
     add_sample<DY, DX, 4, 4, CPL>(acc, f, wv, gv);
 }
 
-// Floats per record-table entry: the 4 bilinear factors, the anchor, the
-// cell position, 2 spare, then the G weights (16-byte multiple, so the
-// factors load as one vector).
+// Floats per record-table entry: the 4 bilinear factors, the anchor, 3
+// spare, then the G weights (16-byte multiple, so the factors load as one
+// vector).
 __host__ __device__ inline int tile_entry_floats(int G) { return 8 + ((G + 3) & ~3); }
 
 // Cell boundaries of a tile's TH+1 cell rows, (TW+2) per row.
-constexpr int kBndPerGroup = (kTileH + 1) * (kTileW + 2);
+constexpr int kBndPerWave = (kTileH + 1) * (kTileW + 2);
 
-// LDS bytes of the boundary slots: one per lane group of every wave.
-__host__ __device__ inline size_t bnd_lds_bytes(int waves, int lps_shift) {
-    const size_t groups = (size_t)waves * (size_t)(64 >> lps_shift);
-    return (groups * kBndPerGroup * 4 + 15) & ~(size_t)15;
+// LDS bytes of the boundary slots: one per wave.
+__host__ __device__ inline size_t bnd_lds_bytes(int waves) {
+    return ((size_t)waves * kBndPerWave * 4 + 15) & ~(size_t)15;
 }
-
-// Records handled per group of grad_out loads in flight.
-constexpr int kGoBatch = 8;
 
 // Everything one tile's reduction needs (from the single-call or the
 // batched tables).
@@ -224,25 +199,29 @@ __device__ __forceinline__ const float* go_row(const TileView& v, float anchor_b
     return v.grad_out + (size_t)an * (u32)v.C;
 }
 
-// The reduction of one tile by a group of lps lanes (grp-th group of its
-// wave, lane sl within it); `waves` waves of the block share its records,
-// this wave being the wt-th of them (waves == 1: wt == 0, and the other
-// waves of the block reduce tiles of their own).
-// CELLS (whole-wave groups only): walk each chunk's records cell by cell in
-// a static loop over the tile's 5x5 cells, so every record's corner ->
-// pixel map is a compile-time constant (no per-record dispatch); records of
-// a cell are consecutive in the sorted order, so the visiting order, and
-// the sums, are those of the flat walk.
-template <class OT, int CPL, bool WHOLE_WAVE, bool CELLS, int QB = 4>
-__device__ __forceinline__ void tile_reduce(const TileView& v, const int lps, const int spw,
-                                            const int grp, const int sl, const int waves,
-                                            const int wt,
-                                            u32* bnd_lds, float* work) {
+// The reduction of one tile by `waves` waves of the block that share its
+// records, this wave being the wt-th of them (waves == 1: wt == 0, and the
+// other waves of the block reduce tiles of their own).
+//
+// A record takes 1 << lps_shift lanes (C / CPL), so a wave walks 64 >>
+// lps_shift records of a cell at a time, one per sub-wave (WHOLE: lps_shift
+// is 6). Each chunk's records are walked cell by cell in a static loop over
+// the tile's 5x5 cells, so every record's corner -> pixel map is a
+// compile-time constant (no per-record dispatch); records of a cell are
+// consecutive in the sorted order. QB: records of a sub-wave whose grad_out
+// rows are loaded together.
+template <class OT, int CPL, bool WHOLE, int QB>
+__device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shift,
+                                            const int waves, const int wt, u32* bnd_lds,
+                                            float* work) {
     constexpr int TH = kTileH, TW = kTileW;
     // the wave index is uniform: chunk bounds and cell runs below stay scalar
     const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
+    const int spw = WHOLE ? 1 : 64 >> lps_shift;            // sub-waves
+    const int sub = WHOLE ? 0 : lane >> lps_shift;
+    const int sl = WHOLE ? lane : lane & ((1 << lps_shift) - 1);
     const int stride = tile_entry_floats(v.G);      // floats per record-table entry
-    float* tab = work + (size_t)wave * 64 * stride + (size_t)(lane - sl) * stride;
+    float* tab = work + (size_t)wave * 64 * stride;
     const bool active = v.active;
     const int H = v.H, W = v.W, ty = v.ty, tx = v.tx;
     const u32 cbase = v.cbase;
@@ -250,11 +229,13 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps, co
     const int g = c0 / (v.C / v.G);
 
     // The tile's cells are TH+1 rows of TW+1 consecutive cells; each row's
-    // records are one contiguous range of the sorted order. The group stores
+    // records are one contiguous range of the sorted order. The wave stores
     // the (TH+1) x (TW+2) cell boundaries of those rows in its LDS slot.
-    constexpr int NB = kBndPerGroup;
-    u32* bslot = bnd_lds + ((size_t)wave * spw + (size_t)grp) * NB;
-    for (int k = sl; k < NB; k += lps) {
+    constexpr int NB = kBndPerWave;
+    u32* bslot = bnd_lds + (size_t)wave * NB;
+    static_assert(NB <= 64, "one boundary per lane");
+    if (lane < NB) {
+        const int k = lane;
         const int dy = k / (TW + 2), dx = k % (TW + 2);
         u32 bv = 0u;
         if (active && ty + dy <= H) {
@@ -286,14 +267,14 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps, co
 #pragma unroll
             for (int i = 0; i < CPL; ++i) acc[py][px][i] = 0.f;
 
-    // The tile's records as one flat list, in chunks of lps; chunk k goes to
-    // wave k % waves. Each lane of the group fills one table entry (all the
-    // chunk's loads in flight together), then the group walks the chunk.
-    for (u32 base = (u32)(wt * lps); base < total; base += (u32)(waves * lps)) {
-        const int n = (int)min((u32)lps, total - base);
-        if (sl < n) {
-            // flat index -> (row dy, sorted position e) -> cell position dx
-            u32 f = base + (u32)sl;
+    // The tile's records as one flat list, in chunks of 64; chunk k goes to
+    // wave k % waves. Each lane fills one table entry (all the chunk's loads
+    // in flight together), then the wave walks the chunk.
+    for (u32 base = (u32)(wt * 64); base < total; base += (u32)(waves * 64)) {
+        const int n = (int)min(64u, total - base);
+        if (lane < n) {
+            // flat index -> (row dy, sorted position e)
+            u32 f = base + (u32)lane;
             int dy = 0;
 #pragma unroll
             for (int k = 0; k < TH; ++k)
@@ -302,13 +283,9 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps, co
 #pragma unroll
             for (int k = 1; k <= TH; ++k)
                 if (dy == k) e = rs[k] + f;
-            int dx = 0;
-#pragma unroll
-            for (int k = 1; k <= TW; ++k)
-                if (e >= bslot[dy * (TW + 2) + k]) dx = k;
             const u32 s = min(v.vals[e], v.nrec - 1u);
             const float2 fr = v.frac[s];
-            float* ent = tab + sl * stride;
+            float* ent = tab + lane * stride;
             // the scene-local sample (clamped into the scene: an inconsistent
             // sort could only give wrong sums, never a read outside it)
             const u32 ls = s - v.sample_offset < v.sample_count ? s - v.sample_offset : 0u;
@@ -332,30 +309,29 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps, co
             *reinterpret_cast<float4*>(ent) =
                 make_float4(hy * hx, hy * fr.x, fr.y * hx, fr.y * fr.x);
             ent[4] = __uint_as_float(an);
-            ent[5] = __int_as_float(dy * (TW + 1) + dx);
         }
         // LDS accesses of one wave are performed in order; keep the compiler
         // from hoisting the reads above the writes
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if constexpr (CELLS && WHOLE_WAVE) {
-            // flat index of each row's first record, then each cell's run
-            // clipped to this chunk [base, base + n)
-            u32 f0 = 0;
-            static_for<TH + 1>([&](auto dyc) {
-                constexpr int DY = decltype(dyc)::value;
-                const u32 rlen = (u32)uniform((int)rn[DY]);
-                if (rlen) {
-                    const u32 rstart = (u32)uniform((int)rs[DY]);
-                    static_for<TW + 1>([&](auto dxc) {
-                        constexpr int DX = decltype(dxc)::value;
-                        const u32 e0 = (u32)uniform((int)bslot[DY * (TW + 2) + DX]);
-                        const u32 e1 = (u32)uniform((int)bslot[DY * (TW + 2) + DX + 1]);
-                        const u32 lo = max(f0 + (e0 - rstart), base);
-                        const u32 hi = min(f0 + (e1 - rstart), base + (u32)n);
-                        int qq = (int)lo - (int)base;
-                        const int qe = (int)hi - (int)base;
+        // flat index of each row's first record, then each cell's run
+        // clipped to this chunk [base, base + n)
+        u32 f0 = 0;
+        static_for<TH + 1>([&](auto dyc) {
+            constexpr int DY = decltype(dyc)::value;
+            const u32 rlen = (u32)uniform((int)rn[DY]);
+            if (rlen) {
+                const u32 rstart = (u32)uniform((int)rs[DY]);
+                static_for<TW + 1>([&](auto dxc) {
+                    constexpr int DX = decltype(dxc)::value;
+                    const u32 e0 = (u32)uniform((int)bslot[DY * (TW + 2) + DX]);
+                    const u32 e1 = (u32)uniform((int)bslot[DY * (TW + 2) + DX + 1]);
+                    const u32 lo = max(f0 + (e0 - rstart), base);
+                    const u32 hi = min(f0 + (e1 - rstart), base + (u32)n);
+                    int qq = (int)lo - (int)base;
+                    const int qe = (int)hi - (int)base;
+                    if constexpr (WHOLE) {
                         for (; qq + QB <= qe; qq += QB) {
                             float gv[QB][CPL];
 #pragma unroll
@@ -377,37 +353,32 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps, co
                             cell_sample<DY, DX, CPL>(acc, *reinterpret_cast<const float4*>(ent),
                                                      ent[8 + g], gv);
                         }
-                    });
-                }
-                f0 += rlen;
-            });
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            continue;
-        }
-        int q = 0;
-        for (; q + kGoBatch <= n; q += kGoBatch) {
-            float gv[kGoBatch][CPL];
+                    } else {
+                        // sub-wave s takes the run's records s, s + spw, ...;
+                        // past the run's end it loads its last record's row
+                        // again and adds nothing
+                        for (; qq < qe; qq += QB * spw) {
+                            float gv[QB][CPL];
+                            const float* ent[QB];
 #pragma unroll
-            for (int k = 0; k < kGoBatch; ++k) {
-                const float* ent = tab + (q + k) * stride;
-                load_go<CPL>(v.grad_out + (size_t)__float_as_uint(ent[4]) * v.C + c0, gv[k]);
-            }
+                            for (int k = 0; k < QB; ++k) {
+                                ent[k] = tab + min(qq + k * spw + sub, qe - 1) * stride;
+                                load_go<CPL>(v.grad_out +
+                                                 (size_t)__float_as_uint(ent[k][4]) * v.C + c0,
+                                             gv[k]);
+                            }
 #pragma unroll
-            for (int k = 0; k < kGoBatch; ++k) {
-                const float* ent = tab + (q + k) * stride;
-                add_sample_at<CPL>(__float_as_int(ent[5]), acc,
-                                   *reinterpret_cast<const float4*>(ent), ent[8 + g], gv[k]);
+                            for (int k = 0; k < QB; ++k)
+                                if (qq + k * spw + sub < qe)
+                                    cell_sample<DY, DX, CPL>(
+                                        acc, *reinterpret_cast<const float4*>(ent[k]),
+                                        ent[k][8 + g], gv[k]);
+                        }
+                    }
+                });
             }
-        }
-        for (; q < n; ++q) {
-            const float* ent = tab + q * stride;
-            float gv[CPL];
-            load_go<CPL>(v.grad_out + (size_t)__float_as_uint(ent[4]) * v.C + c0, gv);
-            add_sample_at<CPL>(__float_as_int(ent[5]), acc, *reinterpret_cast<const float4*>(ent),
-                               ent[8 + g], gv);
-        }
+            f0 += rlen;
+        });
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -444,13 +415,30 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps, co
         }
     }
     if (wt != 0 || !active) return;
+    if constexpr (!WHOLE) {
+        // the sub-waves' sums, in every sub-wave
+        auto fold = [&](auto&& sum) {
+#pragma unroll
+            for (int py = 0; py < TH; ++py)
+#pragma unroll
+                for (int px = 0; px < TW; ++px)
+#pragma unroll
+                    for (int i = 0; i < CPL; ++i) acc[py][px][i] = sum(acc[py][px][i]);
+        };
+        for (int m = 1 << lps_shift; m < 8; m <<= 1)
+            fold([&](float x) { return x + xor_shuffle(x, m); });
+        if (lps_shift <= 3) fold([](float x) { return x + dpp<0x128>(x); });   // row_ror:8
+        if (lps_shift <= 4) fold([](float x) { return swap16_sum(x); });
+        fold([](float x) { return swap32_sum(x); });
+    }
     const int start = v.start;
 #pragma unroll
     for (int py = 0; py < TH; ++py) {
 #pragma unroll
         for (int px = 0; px < TW; ++px) {
             const int y = ty + py, x = tx + px;
-            if (y < H && x < W) {
+            // each sub-wave stores its share of the pixels
+            if (y < H && x < W && (WHOLE || ((py * TW + px) & (spw - 1)) == (sub & (TH * TW - 1)))) {
                 const size_t row = v.row_base + (size_t)(start + y * W + x);
                 store_row<OT, CPL>(v.grad_feat, row * (size_t)v.C + (size_t)c0, acc[py][px]);
             }
@@ -461,24 +449,18 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps, co
 // The tile of id gt (ids run over batch items first, then processing slots
 // within [tile_begin, tile_end)) by `waves` waves of the block, this wave the
 // wt-th of them.
-template <class OT, int CPL, bool WHOLE_WAVE, bool CELLS, int QB = 4>
+template <class OT, int CPL, bool WHOLE, int QB>
 __device__ __forceinline__ void gfeat_tile_body(const TileArgs& t, const u32 gt, const int waves,
                                                 const int wt) {
     static_assert(kTileH == 4 && kTileW == 4, "the cell dispatch is written for 4x4 tiles");
-    // LDS: per lane group its tile's cell boundaries; per wave a record table
-    // (64 entries of bilinear factors, anchor, cell position and G weights);
-    // after the records, the waves' partial sums reuse the record tables'
-    // space.
+    // LDS: per wave its tile's cell boundaries and a record table (64 entries
+    // of bilinear factors, anchor and G weights); after the records, the
+    // waves' partial sums reuse the record tables' space.
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int TH = kTileH, TW = kTileW;
-    const int lane = threadIdx.x & 63;
-    const int lps = WHOLE_WAVE ? 64 : 1 << t.lps_shift;
-    const int spw = WHOLE_WAVE ? 1 : 64 >> t.lps_shift;
-    const int grp = WHOLE_WAVE ? 0 : lane >> t.lps_shift;
-    const int sl = WHOLE_WAVE ? lane : lane & (lps - 1);   // lane within its tile's group
     u32* bnd_lds = reinterpret_cast<u32*>(smem_raw);
     float* work = reinterpret_cast<float*>(smem_raw +
-                                           bnd_lds_bytes((int)(blockDim.x >> 6), t.lps_shift));
+                                           bnd_lds_bytes((int)(blockDim.x >> 6)));
 
     const u32 span = t.tile_end - t.tile_begin;
     TileView v;
@@ -517,18 +499,22 @@ __device__ __forceinline__ void gfeat_tile_body(const TileArgs& t, const u32 gt,
     v.vscale = t.view_scale;
     v.N = t.N;
     v.L = t.L;
-    tile_reduce<OT, CPL, WHOLE_WAVE, CELLS, QB>(v, lps, spw, grp, sl, waves, wt, bnd_lds, work);
+    tile_reduce<OT, CPL, WHOLE, QB>(v, t.lps_shift, waves, wt, bnd_lds, work);
 }
 
-// Whole-wave lane groups (C = 64 * CPL): at most 128 VGPRs, i.e. 4 waves per
-// SIMD. The reduction waits on record and grad_out loads, and a fourth wave
-// hides more of that than the few registers it spills cost (measured on the
-// 64-camera scene: light tiles 0.28 -> 0.24 ms, coarse 0.19 -> 0.18 ms).
-// Narrower groups keep the compiler's choice (they would spill heavily).
-// QB: records whose grad_out rows are loaded together in the cell walk; 2
-// for the one-wave light tiles (fewer registers: no spills at 128), 4 for
-// the coarse tiles (measured: light 0.248 -> 0.234 ms with 2, coarse 0.180
-// -> 0.191 ms).
+// At most 128 VGPRs, i.e. 4 waves per SIMD. The reduction waits on record
+// and grad_out loads, and a fourth wave hides more of that than the few
+// registers it spills cost (measured on the 64-camera scene: light tiles 0.28
+// -> 0.24 ms, coarse 0.19 -> 0.18 ms). QB: 2 for the one-wave light tiles
+// (fewer registers: no spills at 128), 4 for whole-wave coarse tiles
+// (measured: light 0.248 -> 0.234 ms with 2, coarse 0.180 -> 0.191 ms).
+//
+// Narrower records (C < 64 * CPL) share the wave as sub-waves of one tile
+// rather than taking tiles of their own, which left a run-time dispatch on
+// the cell per record and, on small problems, too few waves: 2 cameras of
+// 128 x 224, C = 64, 128 anchors 144 -> 30 us, 32 cameras of 256 x 448, 900
+// anchors, C = 128 285 -> 165 us, C = 64 317 -> 150 us. 8 waves per coarse
+// tile instead of 4: 20, 184 and 162 us.
 //
 // One launch for both kinds of tiles: the coarse tiles (ids below
 // (tile_split - tile_begin) * B) first, a block of 4 waves each, then the
@@ -536,42 +522,29 @@ __device__ __forceinline__ void gfeat_tile_body(const TileArgs& t, const u32 gt,
 // around the long coarse ones instead of waiting for them to drain.
 constexpr int kTileBlockWaves = 4;
 
-template <class OT, int CPL>
-__global__ void __launch_bounds__(64 * kTileBlockWaves) __attribute__((amdgpu_waves_per_eu(4, 8)))
-gfeat_tile_kernel(TileArgs t) {
+template <class OT, int CPL, bool WHOLE>
+__global__ void __launch_bounds__(64 * kTileBlockWaves)
+    __attribute__((amdgpu_waves_per_eu(4, 8))) gfeat_tile_kernel(TileArgs t) {
     constexpr int BW = kTileBlockWaves;
     const u32 heavy = (t.tile_split - t.tile_begin) * (u32)t.B;
     const int wave = uniform((int)(threadIdx.x >> 6));
     if (blockIdx.x < heavy)
-        gfeat_tile_body<OT, CPL, true, true, 4>(t, blockIdx.x, BW, wave);
+        gfeat_tile_body<OT, CPL, WHOLE, WHOLE ? 4 : 2>(t, blockIdx.x, BW, wave);
     else
-        gfeat_tile_body<OT, CPL, true, true, 2>(
+        gfeat_tile_body<OT, CPL, WHOLE, 2>(
             t, heavy + (blockIdx.x - heavy) * (u32)BW + (u32)wave, 1, 0);
-}
-
-// Narrower lane groups: spw tiles per wave, t.waves waves sharing them.
-template <class OT, int CPL>
-__global__ void __launch_bounds__(256) gfeat_tile_group_kernel(TileArgs t) {
-    const int spw = 64 >> t.lps_shift;
-    const u32 gt = blockIdx.x * (u32)spw + (u32)((threadIdx.x & 63) >> t.lps_shift);
-    gfeat_tile_body<OT, CPL, false, false>(t, gt, t.waves, (int)(threadIdx.x >> 6));
 }
 
 // Batched tiled reduction: tiles of all scenes' regions in slot order; the
 // tile of id gt (from tile_begin) by `waves` waves, this wave the wt-th.
-template <class OT, int CPL, bool WHOLE_WAVE, int QB = 4>
+template <class OT, int CPL, bool WHOLE, int QB>
 __device__ __forceinline__ void gfeat_tile_batched_body(const BatchArgs& b, const u32 gt,
                                                         const int waves, const int wt) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int TH = kTileH, TW = kTileW;
-    const int lane = threadIdx.x & 63;
-    const int lps = WHOLE_WAVE ? 64 : 1 << b.lps_shift;
-    const int spw = WHOLE_WAVE ? 1 : 64 >> b.lps_shift;
-    const int grp = WHOLE_WAVE ? 0 : lane >> b.lps_shift;
-    const int sl = WHOLE_WAVE ? lane : lane & (lps - 1);
     u32* bnd_lds = reinterpret_cast<u32*>(smem_raw);
     float* work = reinterpret_cast<float*>(smem_raw +
-                                           bnd_lds_bytes((int)(blockDim.x >> 6), b.lps_shift));
+                                           bnd_lds_bytes((int)(blockDim.x >> 6)));
 
     TileView v;
     v.active = gt < b.tile_end - b.tile_begin;
@@ -606,8 +579,7 @@ __device__ __forceinline__ void gfeat_tile_batched_body(const BatchArgs& b, cons
     v.vscale = nullptr;
     v.N = 1;
     v.L = 1;
-    tile_reduce<OT, CPL, WHOLE_WAVE, WHOLE_WAVE, QB>(v, lps, spw, grp, sl, waves, wt, bnd_lds,
-                                                     work);
+    tile_reduce<OT, CPL, WHOLE, QB>(v, b.lps_shift, waves, wt, bnd_lds, work);
 }
 
 // As gfeat_tile_kernel: the heavy tiles ([tile_begin, tile_split)) 4 waves
@@ -615,24 +587,17 @@ __device__ __forceinline__ void gfeat_tile_batched_body(const BatchArgs& b, cons
 // grad_out rows in flight: with the batch's scene lookups, 4 for the heavy
 // tiles spilled 64 bytes under the 128-VGPR cap (the 12-scene batch's step:
 // 9.37 ms with 4, 9.22 ms with 2).
-template <class OT, int CPL>
-__global__ void __launch_bounds__(64 * kTileBlockWaves) __attribute__((amdgpu_waves_per_eu(4, 8)))
-gfeat_tile_batched_kernel(BatchArgs b) {
+template <class OT, int CPL, bool WHOLE>
+__global__ void __launch_bounds__(64 * kTileBlockWaves)
+    __attribute__((amdgpu_waves_per_eu(4, 8))) gfeat_tile_batched_kernel(BatchArgs b) {
     constexpr int BW = kTileBlockWaves;
     const u32 heavy = b.tile_split - b.tile_begin;
     const int wave = uniform((int)(threadIdx.x >> 6));
     if (blockIdx.x < heavy)
-        gfeat_tile_batched_body<OT, CPL, true, 2>(b, blockIdx.x, BW, wave);
+        gfeat_tile_batched_body<OT, CPL, WHOLE, 2>(b, blockIdx.x, BW, wave);
     else
-        gfeat_tile_batched_body<OT, CPL, true, 2>(
+        gfeat_tile_batched_body<OT, CPL, WHOLE, 2>(
             b, heavy + (blockIdx.x - heavy) * (u32)BW + (u32)wave, 1, 0);
-}
-
-template <class OT, int CPL>
-__global__ void __launch_bounds__(256) gfeat_tile_batched_group_kernel(BatchArgs b) {
-    const int spw = 64 >> b.lps_shift;
-    const u32 gt = blockIdx.x * (u32)spw + (u32)((threadIdx.x & 63) >> b.lps_shift);
-    gfeat_tile_batched_body<OT, CPL, false>(b, gt, b.waves, (int)(threadIdx.x >> 6));
 }
 
 // ---------------------------------------------------------------- launchers
@@ -641,84 +606,51 @@ __global__ void __launch_bounds__(256) gfeat_tile_batched_group_kernel(BatchArgs
 // of the record tables and the partial sums (coarse tiles: waves/2 halves of
 // a tile's accumulators).
 template <int CPL>
-static size_t tile_lds_bytes(int waves, int lps_shift, int G, bool coarse) {
+static size_t tile_lds_bytes(int waves, int G, bool coarse) {
     const size_t part = coarse ? (size_t)(waves / 2) * kTileH * kTileW * CPL * 64 * 4 : 0;
     const size_t tables = (size_t)waves * 64 * tile_entry_floats(G) * sizeof(float);
-    return bnd_lds_bytes(waves, lps_shift) + (part > tables ? part : tables);
+    return bnd_lds_bytes(waves) + (part > tables ? part : tables);
 }
 
-// Whole-wave groups: one launch of gfeat_tile_kernel over [tile_begin,
-// tile_end) (coarse up to tile_split). Narrower groups: two launches of the
-// group kernel, 4 waves per coarse tile group, 1 per light one.
-template <class OT, int CPL>
-static hipError_t tile_launch(const TileArgs& t0, hipStream_t s) {
-    const u32 B = (u32)t0.B;
-    if (t0.lps_shift == 6) {
-        const u32 heavy = (t0.tile_split - t0.tile_begin) * B;
-        const u32 light = (t0.tile_end - t0.tile_split) * B;
-        constexpr int BW = kTileBlockWaves;
-        const u32 blocks = heavy + (light + BW - 1) / BW;
-        if (blocks == 0) return hipSuccess;
-        const size_t lds = tile_lds_bytes<CPL>(BW, 6, t0.G, heavy > 0);
-        mark_begin("gfeat_tile_kernel", s);
-        hipLaunchKernelGGL((gfeat_tile_kernel<OT, CPL>), dim3(blocks), dim3(64 * BW), lds, s,
-                           t0);
-        mark_end(s);
-        return hipGetLastError();
-    }
-    const u32 split[3] = {t0.tile_begin, t0.tile_split, t0.tile_end};
-    for (int part = 0; part < 2; ++part) {
-        TileArgs t = t0;
-        t.tile_begin = split[part];
-        t.tile_end = split[part + 1];
-        t.waves = part == 0 ? 4 : 1;
-        const u32 spw = 64u >> t.lps_shift;
-        const u32 blocks = ((t.tile_end - t.tile_begin) * B + spw - 1) / spw;
-        if (blocks == 0) continue;
-        const size_t lds = tile_lds_bytes<CPL>(t.waves, t.lps_shift, t.G, t.waves > 1);
-        mark_begin(t.waves > 1 ? "gfeat_tile_kernel_coarse" : "gfeat_tile_kernel", s);
-        hipLaunchKernelGGL((gfeat_tile_group_kernel<OT, CPL>), dim3(blocks),
-                           dim3(64 * t.waves), lds, s, t);
-        mark_end(s);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+// One launch over [tile_begin, tile_end), coarse up to tile_split.
+template <class OT, int CPL, bool WHOLE>
+static hipError_t tile_launch_of(const TileArgs& t, hipStream_t s) {
+    constexpr u32 BW = kTileBlockWaves;
+    const u32 heavy = (t.tile_split - t.tile_begin) * (u32)t.B;
+    const u32 light = (t.tile_end - t.tile_split) * (u32)t.B;
+    const u32 blocks = heavy + (light + BW - 1) / BW;
+    if (blocks == 0) return hipSuccess;
+    mark_begin("gfeat_tile_kernel", s);
+    hipLaunchKernelGGL((gfeat_tile_kernel<OT, CPL, WHOLE>), dim3(blocks), dim3(64 * BW),
+                       tile_lds_bytes<CPL>(BW, t.G, heavy > 0), s, t);
+    mark_end(s);
+    return hipGetLastError();
 }
 
 template <class OT, int CPL>
-static hipError_t tile_batched_launch(const BatchArgs& b0, hipStream_t s) {
-    if (b0.lps_shift == 6) {
-        const u32 heavy = b0.tile_split - b0.tile_begin;
-        const u32 light = b0.tile_end - b0.tile_split;
-        constexpr int BW = kTileBlockWaves;
-        const u32 blocks = heavy + (light + BW - 1) / BW;
-        if (blocks == 0) return hipSuccess;
-        const size_t lds = tile_lds_bytes<CPL>(BW, 6, b0.G, heavy > 0);
-        mark_begin("gfeat_tile_batched", s);
-        hipLaunchKernelGGL((gfeat_tile_batched_kernel<OT, CPL>), dim3(blocks), dim3(64 * BW), lds,
-                           s, b0);
-        mark_end(s);
-        return hipGetLastError();
-    }
-    const u32 split[3] = {b0.tile_begin, b0.tile_split, b0.tile_end};
-    for (int part = 0; part < 2; ++part) {
-        BatchArgs b = b0;
-        b.tile_begin = split[part];
-        b.tile_end = split[part + 1];
-        b.waves = part == 0 ? 4 : 1;
-        const u32 spw = 64u >> b.lps_shift;
-        const u32 blocks = (b.tile_end - b.tile_begin + spw - 1) / spw;
-        if (blocks == 0) continue;
-        const size_t lds = tile_lds_bytes<CPL>(b.waves, b.lps_shift, b.G, b.waves > 1);
-        mark_begin(b.waves > 1 ? "gfeat_tile_batched_coarse" : "gfeat_tile_batched", s);
-        hipLaunchKernelGGL((gfeat_tile_batched_group_kernel<OT, CPL>), dim3(blocks),
-                           dim3(64 * b.waves), lds, s, b);
-        mark_end(s);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+static hipError_t tile_launch(const TileArgs& t, hipStream_t s) {
+    return t.lps_shift == 6 ? tile_launch_of<OT, CPL, true>(t, s)
+                            : tile_launch_of<OT, CPL, false>(t, s);
+}
+
+template <class OT, int CPL, bool WHOLE>
+static hipError_t tile_batched_launch_of(const BatchArgs& b, hipStream_t s) {
+    constexpr u32 BW = kTileBlockWaves;
+    const u32 heavy = b.tile_split - b.tile_begin;
+    const u32 light = b.tile_end - b.tile_split;
+    const u32 blocks = heavy + (light + BW - 1) / BW;
+    if (blocks == 0) return hipSuccess;
+    mark_begin("gfeat_tile_batched", s);
+    hipLaunchKernelGGL((gfeat_tile_batched_kernel<OT, CPL, WHOLE>), dim3(blocks), dim3(64 * BW),
+                       tile_lds_bytes<CPL>(BW, b.G, heavy > 0), s, b);
+    mark_end(s);
+    return hipGetLastError();
+}
+
+template <class OT, int CPL>
+static hipError_t tile_batched_launch(const BatchArgs& b, hipStream_t s) {
+    return b.lps_shift == 6 ? tile_batched_launch_of<OT, CPL, true>(b, s)
+                            : tile_batched_launch_of<OT, CPL, false>(b, s);
 }
 
 hipError_t launch_gfeat_tiles_batched(const BatchArgs& b, int out_dtype, int cpl, hipStream_t s) {
