@@ -111,9 +111,9 @@ typedef enum msda_dtype {
 #define MSDA_ORDER_VIEW 2   /* the (batch item, camera) x anchor work is cut, camera-
                                major, into 8 equal ranges, one per XCD, so each XCD's
                                L2 holds the pyramids of a few cameras at a time; each
-                               wave takes one anchor over its cameras in a range. The
-                               forward then adds 8 partial sums per anchor in a fixed
-                               order and needs a workspace (msda_forward_ws)           */
+                               wave takes one anchor over a few cameras. The forward
+                               then adds an anchor's partial sums in a fixed order and
+                               needs a workspace (msda_forward_ws)                     */
 
 /* Launch shape. A zero field means "choose". */
 typedef struct msda_tile {
@@ -169,8 +169,8 @@ msda_status msda_forward(const void* feat, const int32_t* spatial_shapes,
  * least 8 (batch item, camera) views. Same results contract as
  * msda_forward; the two orders add the samples in different orders, each
  * fixed (deterministic).
- * workspace: device, 256-byte aligned, at least
- * msda_forward_workspace_size(desc) bytes (may be NULL when that is 0).
+ * workspace: device, 256-byte aligned, msda_forward_workspace_size(desc)
+ * bytes, or fewer as said there (may be NULL when that is 0).
  * Returns MSDA_ERR_WORKSPACE if it is missing or too small.
  */
 msda_status msda_forward_ws(const void* feat, const int32_t* spatial_shapes,
@@ -178,9 +178,12 @@ msda_status msda_forward_ws(const void* feat, const int32_t* spatial_shapes,
                             const float* weights, float* out, void* workspace,
                             size_t workspace_bytes, const msda_desc* desc, void* stream);
 
-/* Bytes of device workspace msda_forward_ws needs for desc: 8*B*A*C*4 when
- * the forward runs in view order (chosen or requested), plus B*A*G*8 (the
- * softmax statistics) with MSDA_WEIGHT_LOGITS, each part rounded up to 256. */
+/* Bytes of device workspace for msda_forward_ws: R*B*A*C*4 when the forward
+ * runs in view order (chosen or requested), R = 8 for Ncam < 16, else Ncam
+ * rounded down to a multiple of 8, at most 64; plus B*A*G*8 (the softmax
+ * statistics) with MSDA_WEIGHT_LOGITS, each part rounded up to 256. A
+ * workspace of R = 8's size is enough: the same sums are then formed in
+ * more launches. */
 size_t msda_forward_workspace_size(const msda_desc* desc);
 
 /*
@@ -194,8 +197,8 @@ size_t msda_forward_workspace_size(const msda_desc* desc);
  * Every call on one GPU shares that array and leaves its contents behind:
  * calls that overlap on one GPU (on two streams, or from two threads without
  * ordering) race and may return wrong results; order them on one stream.
- * Returns MSDA_ERR_UNSUPPORTED, before any HIP call, when
- * msda_forward_workspace_size(desc) exceeds MSDA_NOALLOC_SCRATCH_BYTES (for
+ * Returns MSDA_ERR_UNSUPPORTED, before any HIP call, when the least
+ * workspace (R = 8) exceeds MSDA_NOALLOC_SCRATCH_BYTES (for
  * the view order: B*A*C > 1,048,576 less the statistics' share; the anchor
  * order, msda_tile.order = MSDA_ORDER_ANCHOR, needs none), MSDA_ERR_HIP if
  * the device or the array cannot be looked up.
@@ -400,15 +403,14 @@ size_t msda_batched_workspace_size(const msda_batch* batch, int32_t backward);
 
 /*
  * Forward of every scene of the batch in one launch per pass. Work order
- * (msda_batch.tile->order): view order by default -- each scene's (camera,
- * anchor) items are split over the 8 XCD slots exactly as a single call with
- * B = 1 splits them, one wave per (slot, anchor) row, then one kernel adds
- * the slots' partial sums in slot order, so every scene's result is bitwise
- * the single call's in view order; MSDA_ORDER_ANCHOR: persistent workgroups
- * stride over all anchors of all scenes (bitwise the single call's in
- * anchor order). workspace: device, 256-byte aligned, >=
- * msda_batched_workspace_size(batch, 0) (it includes the view order's
- * 8 * anchors * C FP32 partial sums in either order). Validation as for
+ * (msda_batch.tile->order): view order by default -- each scene's partial
+ * rows are those of a single call with B = 1, one wave per (row, anchor),
+ * then one kernel adds an anchor's rows in order, so every scene's result is
+ * bitwise the single call's in view order; MSDA_ORDER_ANCHOR: persistent
+ * workgroups stride over all anchors of all scenes (bitwise the single
+ * call's in anchor order). workspace: device, 256-byte aligned, >=
+ * msda_batched_workspace_size(batch, 0) (it includes the view order's FP32
+ * partial rows, R * anchors * C per scene, in either order). Validation as for
  * msda_forward, per scene; in addition at most 4096 (camera, level)
  * regions over all scenes.
  */

@@ -430,18 +430,27 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
     int cpl = 0, waves = 0;
     msda_status st = prepare(desc, order, &a, &cpl, &waves);
     if (st != MSDA_OK) return st;
-    // the view-order forward runs fastest with one wave (one anchor row) per
-    // workgroup (measured on the 64-camera workload in FP32 and BF16)
-    if (order == MSDA_ORDER_VIEW && !(desc->tile && desc->tile->waves_per_anchor)) waves = 1;
+    // (a chosen wave count of the view order: see fwd_chunk_samples for its LDS)
+    if (order == MSDA_ORDER_VIEW && !(desc->tile && desc->tile->waves_per_anchor)) waves = 4;
     // sampling_loc, weights and out hold zero elements when A == 0 and may be NULL then
     if (!feat || !spatial_shapes || !level_start_index ||
         (a.A > 0 && (!sampling_loc || !weights || !out)))
         return fail(MSDA_ERR_INVALID_ARGUMENT, "a required device pointer is NULL");
     if (!aligned(feat, 16)) return fail(MSDA_ERR_UNSUPPORTED, "feat must be 16-byte aligned");
-    const size_t part_bytes = order == MSDA_ORDER_VIEW
-                                  ? (size_t)msda::kSlots * a.B * a.A * a.C * sizeof(float) : 0;
-    const size_t stats_off = align256(part_bytes);
-    const size_t need = stats_off + stats_bytes(desc);
+    // the partial rows: as many as the workspace has room for, from the
+    // minimum up to all of them (the sums are the same; fewer rows take more
+    // launches), then the softmax statistics
+    const size_t row_bytes = (size_t)a.B * a.A * a.C * sizeof(float);
+    const size_t stats = stats_bytes(desc);
+    int part_rows = 0;
+    if (order == MSDA_ORDER_VIEW) {
+        part_rows = std::max(msda::fwd_rows(a.N), msda::kMinFwdRows);
+        while (part_rows > msda::kMinFwdRows &&
+               align256(part_rows * row_bytes) + stats > workspace_bytes)
+            --part_rows;
+    }
+    const size_t stats_off = align256(part_rows * row_bytes);
+    const size_t need = stats_off + stats;
     if (need && !has_ws)
         return fail(MSDA_ERR_WORKSPACE, "weight logits need a workspace (msda_forward_ws)");
     if (need && (!workspace || workspace_bytes < need || !aligned(workspace, 256)))
@@ -469,8 +478,7 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
     a.out = out;
     const hipError_t e =
         order == MSDA_ORDER_VIEW
-            ? msda::launch_forward_view(a, desc->feat_dtype, cpl, waves,
-                                        msda::lds_bytes_view(a, waves),
+            ? msda::launch_forward_view(a, desc->feat_dtype, cpl, waves, part_rows,
                                         static_cast<float*>(workspace), (hipStream_t)stream)
             : msda::launch_forward(a, desc->feat_dtype, cpl, waves, msda::lds_bytes_for(a, waves),
                                    (hipStream_t)stream);
@@ -493,14 +501,28 @@ msda_status msda_forward_ws(const void* feat, const int32_t* spatial_shapes,
                         workspace, workspace_bytes, true, desc, stream);
 }
 
-size_t msda_forward_workspace_size(const msda_desc* d) {
+// Workspace of the forward with the given number of partial rows per batch
+// item in view order.
+static size_t forward_bytes(const msda_desc* d, int part_rows) {
     if (!d || d->batch < 1 || d->num_cams < 1 || d->channels < 1 || d->num_anchors < 0) return 0;
     const size_t part = resolve_order(d, true) == MSDA_ORDER_VIEW
-                            ? (size_t)msda::kSlots * (size_t)d->batch * (size_t)d->num_anchors *
+                            ? (size_t)part_rows * (size_t)d->batch * (size_t)d->num_anchors *
                                   (size_t)d->channels * sizeof(float)
                             : 0;
     return align256(part) + stats_bytes(d);
 }
+
+size_t msda_forward_workspace_size(const msda_desc* d) {
+    return forward_bytes(d, d ? std::max(msda::fwd_rows(d->num_cams), msda::kMinFwdRows) : 0);
+}
+
+}  // extern "C"
+
+size_t msda::forward_min_workspace(const msda_desc* d) {
+    return forward_bytes(d, msda::kMinFwdRows);
+}
+
+extern "C" {
 
 // The backward gather in the chosen order. In view order each wave takes
 // one anchor over a group of cameras: 2 for 1- and 2-byte features, 1 for
@@ -1109,8 +1131,8 @@ msda_status msda_quantize_fp8(const float* feat_f32, const int32_t* spatial_shap
 namespace {
 
 struct BatchWs {
-    size_t anchor_start, sample_start, region_start, cell_start, slot_scene, slot_region,
-        tile_start, magic, magic_shift, keys_a, keys_b, vals_a, vals_b, frac, off, scratch, part,
+    size_t anchor_start, sample_start, region_start, row_start, cell_start, slot_scene,
+        slot_region, tile_start, magic, magic_shift, keys_a, keys_b, vals_a, vals_b, frac, off, scratch, part,
         wstats, wscratch, w32, total;
 };
 
@@ -1131,6 +1153,7 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
     w.anchor_start = take((S + 1) * 4);
     w.sample_start = take((S + 1) * 4);
     w.region_start = take((S + 1) * 4);
+    w.row_start = take((S + 1) * 8);
     w.cell_start = take(regions * 4);
     w.slot_scene = take(regions * 4);
     w.slot_region = take(regions * 4);
@@ -1157,6 +1180,7 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
 // Sizes of a validated batch.
 struct BatchPlan {
     uint64_t anchors, samples, regions, cells, tiles, heavy_tiles;
+    uint64_t fwd_rows;            // view-order forward: rows over all scenes and anchors
     int max_regions_per_scene, max_cams;
     int cpl, waves;
     int64_t max_batch_bytes;
@@ -1212,6 +1236,7 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
         if (!aligned(sc.feat, 16))
             return fail(MSDA_ERR_UNSUPPORTED, "scene %d: feat must be 16-byte aligned", s);
         p->anchors += (uint64_t)sc.num_anchors;
+        p->fwd_rows += (uint64_t)sc.num_anchors * (uint64_t)msda::fwd_rows(sc.num_cams);
         p->samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams * b->num_levels;
         p->regions += (uint64_t)sc.num_cams * b->num_levels;
         p->max_regions_per_scene = std::max(p->max_regions_per_scene, sc.num_cams * b->num_levels);
@@ -1278,9 +1303,9 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
     p->order = req == MSDA_ORDER_ANCHOR ? MSDA_ORDER_ANCHOR : MSDA_ORDER_VIEW;
     p->view_cams = p->max_cams / msda::kSlots + 2;
     const int tw = b->tile ? b->tile->waves_per_anchor : 0;
-    p->view_waves_fwd = tw ? tw : 1;
+    p->view_waves_fwd = tw ? tw : 4;
     p->view_waves_bwd = tw ? tw : 4;
-    p->part_bytes = (uint64_t)msda::kSlots * p->anchors * (uint64_t)b->channels * sizeof(float);
+    p->part_bytes = p->fwd_rows * (uint64_t)b->channels * sizeof(float);
     if (p->order == MSDA_ORDER_VIEW) {
         const int J = msda::max_pairs_per_chunk(b->num_levels, b->groups);
         const int wmax = std::max(p->view_waves_fwd, p->view_waves_bwd);
@@ -1305,6 +1330,7 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, char* ws, const Ba
     a->t.anchor_start = reinterpret_cast<uint32_t*>(ws + w.anchor_start);
     a->t.sample_start = reinterpret_cast<uint32_t*>(ws + w.sample_start);
     a->t.region_start = reinterpret_cast<uint32_t*>(ws + w.region_start);
+    a->t.row_start = reinterpret_cast<uint64_t*>(ws + w.row_start);
     a->t.cell_start = reinterpret_cast<uint32_t*>(ws + w.cell_start);
     a->t.slot_scene = reinterpret_cast<uint32_t*>(ws + w.slot_scene);
     a->t.slot_region = reinterpret_cast<uint32_t*>(ws + w.slot_region);
@@ -1312,6 +1338,7 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, char* ws, const Ba
     a->t.magic = reinterpret_cast<uint64_t*>(ws + w.magic);
     a->t.magic_shift = reinterpret_cast<uint32_t*>(ws + w.magic_shift);
     a->total_anchors = (uint32_t)p.anchors;
+    a->total_rows = p.fwd_rows;
     a->total_samples = (uint32_t)p.samples;
     a->total_cells = (uint32_t)p.cells;
     a->total_regions = (uint32_t)p.regions;
@@ -1473,10 +1500,8 @@ msda_status msda_forward_batched(const msda_batch* b, void* workspace, size_t wo
     if ((st = batch_weight_prep(b, static_cast<char*>(workspace), w, false, &a, s)) != MSDA_OK)
         return st;
     if (p.order == MSDA_ORDER_VIEW) {
-        const size_t vlds = msda::batch_view_lds(p.view_cams, b->num_levels, a.pairs_per_chunk,
-                                                 b->groups, p.view_waves_fwd);
         e = msda::launch_forward_batched_view(
-            a, b->feat_dtype, p.cpl, p.view_waves_fwd, vlds,
+            a, b->feat_dtype, p.cpl, p.view_waves_fwd,
             reinterpret_cast<float*>(static_cast<char*>(workspace) + w.part), s);
     } else {
         e = msda::launch_forward_batched(a, b->feat_dtype, p.cpl, p.waves,

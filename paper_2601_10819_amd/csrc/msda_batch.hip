@@ -43,11 +43,14 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
     __syncthreads();
     if (tid == 0) {
         u32 a = 0, smp = 0, reg = 0;
+        u64 rows = 0;
         for (int s = 0; s < S; ++s) {
             b.t.anchor_start[s] = a;
             b.t.sample_start[s] = smp;
             b.t.region_start[s] = reg;
             rstart[s] = reg;
+            b.t.row_start[s] = rows;
+            rows += (u64)fwd_rows((int)s_cams[s]) * s_anchors[s];
             a += s_anchors[s];
             const u32 per_anchor = (u32)b.P * s_cams[s] * (u32)L;
             smp += s_anchors[s] * per_anchor;
@@ -62,6 +65,7 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
         b.t.anchor_start[S] = a;
         b.t.sample_start[S] = smp;
         b.t.region_start[S] = reg;
+        b.t.row_start[S] = rows;
         rstart[S] = reg;
     }
     __syncthreads();

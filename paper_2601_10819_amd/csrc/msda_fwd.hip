@@ -6,21 +6,21 @@
 // its waves split the anchor's (keypoint, camera) pairs in chunks and the
 // waves' partial sums are added in a fixed order at the end.
 //
-// View order (msda_fwd_view_kernel): the (view, anchor) items are cut into
-// one contiguous range per XCD (see slot_span); each wave sums one anchor
-// over its views in the slot and writes a per-slot partial row, and
-// fwd_view_reduce adds the slots' partials in slot order. Both orders are
+// View order (msda_fwd_view_kernel): the rows -- a run of cameras, see
+// fwd_rows -- of every anchor are cut, camera-major, into one contiguous
+// range per XCD; each wave sums one anchor over one row and writes a partial
+// row, and fwd_rows_reduce adds an anchor's rows in order. Both orders are
 // deterministic.
 //
-// In both, a wave stages a chunk of pairs -- the pairs' weights and the
-// corner taps of their samples, one sample per lane, so the coordinate
-// arithmetic is done once per sample rather than once per lane of a sample
-// -- then each group of C/CPL lanes takes a pair and issues the corner
-// loads of all its levels before using them.
+// In both, a wave stages its samples one per lane, so the coordinate
+// arithmetic is done once per sample rather than once per lane of a sample,
+// then each group of C/CPL lanes takes a sample at a time and issues several
+// samples' corner loads before using them.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "msda_gather.h"
+#include "msda_rows.h"
 
 namespace msda {
 
@@ -114,78 +114,63 @@ __global__ void __launch_bounds__(512) msda_fwd_kernel(OpArgs a) {
     fwd_anchor<FT, CPL>(a, (int)blockIdx.x, geo, work);
 }
 
-// View order: workgroup w serves slot w % kSlots; its waves take
-// consecutive rows of the slot. Each wave writes its row's partial sum
-// (zeros for an empty row) to part[slot][b*A + a].
+// The XCD slot x of a workgroup (the hardware hands workgroups to the XCDs
+// round-robin) takes the x-th of kSlots equal ranges of T units: this wave's
+// unit, or T.
+__device__ __forceinline__ u64 slot_unit(u64 T, u32 block, int wave, int nwaves) {
+    const u32 x = block % kSlots;
+    const u64 u = T * x / kSlots + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
+    return u < T * (x + 1) / kSlots ? u : T;
+}
+
+// Quotient of the wave-uniform u by d.
+__device__ __forceinline__ u64 uniform_div(u64 u, u32 d) {
+    return u >> 32 ? u / d : (u64)((u32)u / d);
+}
+
+// View order: rows [row0, row0 + nrows) of every batch item, of `rows` in
+// all; unit (b*nrows + j)*A + a, the partial row of that index in part.
 template <class FT, int CPL>
-__global__ void __launch_bounds__(512) msda_fwd_view_kernel(OpArgs a, float* part) {
+__global__ void __launch_bounds__(512) msda_fwd_view_kernel(OpArgs a, int rows, int row0,
+                                                            int nrows, int chunk, float* part) {
     extern __shared__ __align__(16) unsigned char smem[];
-    Geo* geo = reinterpret_cast<Geo*>(smem);
-    unsigned char* work = smem + (size_t)a.N * a.L * sizeof(Geo);
-    stage_geometry(geo, a);
-    __syncthreads();                       // the only block-wide barrier
-
-    const int x = (int)(blockIdx.x % kSlots);
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
-    const int64_t r = (int64_t)(blockIdx.x / kSlots) * nwaves + wave;
-    const SlotSpan span = slot_span(x, a.B, a.N, a.A);
-    if (r >= slot_rows(span, a.A)) return;
-    ViewRow row = view_row(span, r, a.N, a.A);
-    // every field is the same across the wave (r is per wave)
-    row.b = uniform(row.b);
-    row.a = uniform(row.a);
-    row.n_lo = uniform(row.n_lo);
-    row.nv = uniform(row.nv);
-
-    const int LG = a.L * a.G;
-    const int J = a.pairs_per_chunk;
+    const u64 T = (u64)a.B * (u32)nrows * (u32)a.A;
+    const u64 u = slot_unit(T, blockIdx.x, wave, nwaves);
+    if (u >= T) return;
+    const u32 r = (u32)uniform((int)uniform_div(u, (u32)a.A));
+    const int an = uniform((int)(u - (u64)r * (u32)a.A));
+    const int b = (int)(r / (u32)nrows), j = row0 + (int)(r % (u32)nrows);
+    const int n_lo = (int)((u64)a.N * (u32)j / (u32)rows);
+    const int n_hi = (int)((u64)a.N * (u32)(j + 1) / (u32)rows);
     const Lanes q = lanes_of<FT, CPL>(a);
-    const StageSlot st = stage_slot(work, wave, J, a.L, a.G);
-    const int ba = row.b * a.A + row.a;
-    const int npairs = a.P * a.N;
-    const float* gl = a.loc + (size_t)ba * npairs * 2;
-    const WSrc gw = anchor_weights(a, (size_t)ba, (size_t)npairs * LG);
-    const u32 row_bytes = (u32)a.C * FT::kBytes;
     const rsrc_t feat = make_rsrc(
-        static_cast<const char*>(a.feat) + (size_t)row.b * a.batch_bytes, a.batch_bytes);
-    const ViewOrder order{a.N, a.P, row.n_lo};
-    const RecordSink none{};
-
+        static_cast<const char*>(a.feat) + (size_t)b * a.batch_bytes, a.batch_bytes);
     float acc[CPL];
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) acc[i] = 0.f;
-    const int nk = row.nv * a.P;
-    for (int k0 = 0; k0 < nk; k0 += J) {
-        const int nj = min(J, nk - k0);
-        stage_chunk<FT::kBytes == 1, false>(st, order, k0, nj, gw, gl, geo, a.L, LG, row_bytes,
-                                            q.lane, none);
-        fwd_chunk<FT, CPL>(st, nj, a.L, a.G, q, feat, acc);
-        end_chunk();
-    }
-    reduce_subwaves<CPL>(q, acc);
+    row_sum<FT, CPL>(a, (size_t)b * a.A + an, feat, n_lo, n_hi, q, chunk,
+                     smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
     if (q.sub == 0) {
-        float* dst = part + ((size_t)x * a.B * a.A + ba) * a.C + q.c0;
+        float* dst = part + ((size_t)r * a.A + an) * a.C + q.c0;
 #pragma unroll
         for (int i = 0; i < CPL; ++i) dst[i] = acc[i];
     }
 }
 
-// out[i] = sum over the slots that touch i's batch item of part[slot][i],
-// in slot order; four floats per thread (C % 4 == 0) or one.
+// out[b][i] = the sum of batch item b's partial rows in row order (added to
+// out with `more`: the rows after those already in it); four floats per
+// thread (C % 4 == 0) or one.
 template <int V>
-__global__ void __launch_bounds__(256) fwd_view_reduce(const float* part, float* out, int B,
-                                                       int N, int A, int C) {
-    const size_t total = (size_t)B * A * C;
+__global__ void __launch_bounds__(256) fwd_rows_reduce(const float* part, float* out, int B,
+                                                       int rows, size_t AC, bool more) {
     const size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
-    if (i >= total) return;
-    const int b = (int)(i / ((size_t)A * C));
+    if (i >= (size_t)B * AC) return;
+    const size_t b = i / AC;
+    const float* p = part + b * rows * AC + (i - b * AC);
     float s[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) s[v] = 0.f;
-    for (int x = 0; x < kSlots; ++x) {
-        const SlotSpan span = slot_span(x, B, N, A);
-        if (b < span.b_first || b > span.b_last) continue;
-        const float* p = part + (size_t)x * total + i;
+    for (int v = 0; v < V; ++v) s[v] = more ? out[i + v] : 0.f;
+#pragma unroll 8
+    for (int x = 0; x < rows; ++x, p += AC) {
         if constexpr (V == 4) {
             const float4 t = *reinterpret_cast<const float4*>(p);
             s[0] += t.x; s[1] += t.y; s[2] += t.z; s[3] += t.w;
@@ -217,61 +202,48 @@ __global__ void __launch_bounds__(512) msda_fwd_batched_kernel(BatchArgs b) {
     }
 }
 
-// Batched forward in view order: workgroup w serves XCD slot w % kSlots;
-// each wave takes one global anchor g over its scene's cameras in that slot
-// (the single call's slot split of the scene), stages just those cameras'
-// geometry in its own LDS slice and writes the row's partial sum (zeros for
-// an anchor with no cameras in the slot) to part[slot][g]. Per anchor the
-// arithmetic is the single call's view order.
-template <class FT, int CPL>
-__global__ void __launch_bounds__(512) msda_fwd_batched_view_kernel(BatchArgs b, float* part) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int x = (int)(blockIdx.x % kSlots);
-    const int wave = wave_index(), nwaves = blockDim.x >> 6;
-    const u32 g = (blockIdx.x / kSlots) * (u32)nwaves + (u32)wave;
-    if (g >= b.total_anchors) return;
-    unsigned char* mine =
-        smem + (size_t)wave * batch_view_wave_bytes(b.view_cams, b.L, b.pairs_per_chunk, b.G);
-    Geo* geo = reinterpret_cast<Geo*>(mine);
-    unsigned char* work =
-        mine + (((size_t)b.view_cams * b.L * sizeof(Geo) + 15) & ~(size_t)15);
-    const BatchRow row = batch_row(b, x, g);
-    const OpArgs a = scene_view(b, row.s, FT::kBytes);
-    const Lanes q = lanes_of<FT, CPL>(a);
-    stage_geometry_range(geo, a, row.n_lo, row.nv, q.lane);
-
-    const int LG = a.L * a.G;
-    const int J = a.pairs_per_chunk;
-    const StageSlot st = stage_slot(work, 0, J, a.L, a.G);
-    const int npairs = a.P * a.N;
-    const float* gl = a.loc + (size_t)row.a * npairs * 2;
-    const WSrc gw = anchor_weights(a, (size_t)row.a, (size_t)npairs * LG);
-    const u32 row_bytes = (u32)a.C * FT::kBytes;
-    const rsrc_t feat = make_rsrc(a.feat, a.batch_bytes);
-    const ViewOrder order{a.N, a.P, row.n_lo, row.n_lo};
-    const RecordSink none{};
-
-    float acc[CPL];
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) acc[i] = 0.f;
-    const int nk = row.nv * a.P;
-    for (int k0 = 0; k0 < nk; k0 += J) {
-        const int nj = min(J, nk - k0);
-        stage_chunk<FT::kBytes == 1, false>(st, order, k0, nj, gw, gl, geo, a.L, LG, row_bytes,
-                                            q.lane, none);
-        fwd_chunk<FT, CPL>(st, nj, a.L, a.G, q, feat, acc);
-        end_chunk();
+// The scene of a view-order row index: the last s with start[s] <= u.
+__device__ __forceinline__ int scene_of_row(const u64* start, int S, u64 u) {
+    int lo = 0, hi = S - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (start[mid] <= u) lo = mid; else hi = mid - 1;
     }
-    reduce_subwaves<CPL>(q, acc);
+    return uniform(lo);
+}
+
+// Batched forward in view order: the units of all scenes, scene by scene,
+// cut into one range per XCD. Per anchor the arithmetic is the single call's
+// view order with B = 1.
+template <class FT, int CPL>
+__global__ void __launch_bounds__(512) msda_fwd_batched_view_kernel(BatchArgs b, int chunk,
+                                                                    float* part) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int wave = wave_index(), nwaves = blockDim.x >> 6;
+    const u64 u = slot_unit(b.total_rows, blockIdx.x, wave, nwaves);
+    if (u >= b.total_rows) return;
+    const int s = scene_of_row(b.t.row_start, b.S, u);
+    const OpArgs a = scene_view(b, s, FT::kBytes);
+    const u64 v = u - b.t.row_start[s];
+    const int j = uniform((int)uniform_div(v, (u32)a.A));
+    const int an = uniform((int)(v - (u64)(u32)j * (u32)a.A));
+    const int rows = fwd_rows(a.N);
+    const int n_lo = (int)((u64)a.N * (u32)j / (u32)rows);
+    const int n_hi = (int)((u64)a.N * (u32)(j + 1) / (u32)rows);
+    const Lanes q = lanes_of<FT, CPL>(a);
+    const rsrc_t feat = make_rsrc(a.feat, a.batch_bytes);
+    float acc[CPL];
+    row_sum<FT, CPL>(a, (size_t)an, feat, n_lo, n_hi, q, chunk,
+                     smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
     if (q.sub == 0) {
-        float* dst = part + ((size_t)x * b.total_anchors + g) * b.C + q.c0;
+        float* dst = part + u * (u32)b.C + q.c0;
 #pragma unroll
         for (int i = 0; i < CPL; ++i) dst[i] = acc[i];
     }
 }
 
-// out of global anchor g = sum over the slots of part[slot][g], in slot
-// order, written to its scene's output; V floats per thread.
+// out of global anchor g = the sum of its partial rows in row order, written
+// to its scene's output; V floats per thread.
 template <int V>
 __global__ void __launch_bounds__(256) fwd_batched_view_reduce(BatchArgs b, const float* part) {
     const size_t total = (size_t)b.total_anchors * b.C;
@@ -280,11 +252,15 @@ __global__ void __launch_bounds__(256) fwd_batched_view_reduce(BatchArgs b, cons
     const u32 g = (u32)(i / (size_t)b.C);
     const int c = (int)(i - (size_t)g * b.C);
     const int sc = scene_of(b.t.anchor_start, b.S, g);
+    const u32 a = g - b.t.anchor_start[sc];
+    const size_t AC = (size_t)b.scenes[sc].num_anchors * b.C;
+    const int rows = fwd_rows(b.scenes[sc].num_cams);
+    const float* p = part + (b.t.row_start[sc] + a) * (u32)b.C + c;
     float s[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) s[v] = 0.f;
-    for (int x = 0; x < kSlots; ++x) {
-        const float* p = part + (size_t)x * total + i;
+#pragma unroll 8
+    for (int x = 0; x < rows; ++x, p += AC) {
         if constexpr (V == 4) {
             const float4 t = *reinterpret_cast<const float4*>(p);
             s[0] += t.x; s[1] += t.y; s[2] += t.z; s[3] += t.w;
@@ -292,7 +268,7 @@ __global__ void __launch_bounds__(256) fwd_batched_view_reduce(BatchArgs b, cons
             s[0] += p[0];
         }
     }
-    float* out = b.scenes[sc].out + (size_t)(g - b.t.anchor_start[sc]) * b.C + c;
+    float* out = b.scenes[sc].out + (size_t)a * b.C + c;
     if constexpr (V == 4) {
         *reinterpret_cast<float4*>(out) = make_float4(s[0], s[1], s[2], s[3]);
     } else {
@@ -300,14 +276,20 @@ __global__ void __launch_bounds__(256) fwd_batched_view_reduce(BatchArgs b, cons
     }
 }
 
+// Blocks of `waves` waves over T units in kSlots ranges.
+static unsigned slot_blocks(u64 T, int waves) {
+    const u64 per_slot = (T + kSlots - 1) / kSlots;
+    return (unsigned)(kSlots * ((per_slot + (u64)waves - 1) / (u64)waves));
+}
+
 template <class FT, int CPL>
-static hipError_t fwd_batched_view_launch(const BatchArgs& b, int waves, size_t lds, float* part,
+static hipError_t fwd_batched_view_launch(const BatchArgs& b, int waves, float* part,
                                           hipStream_t s) {
-    const unsigned blocks =
-        (unsigned)(kSlots * (((size_t)b.total_anchors + waves - 1) / (size_t)waves));
+    const int chunk = fwd_chunk_samples(waves, b.G);
     mark_begin("msda_fwd_batched_view_kernel", s);
-    hipLaunchKernelGGL((msda_fwd_batched_view_kernel<FT, CPL>), dim3(blocks), dim3(64 * waves),
-                       lds, s, b, part);
+    hipLaunchKernelGGL((msda_fwd_batched_view_kernel<FT, CPL>),
+                       dim3(slot_blocks(b.total_rows, waves)), dim3(64 * waves),
+                       (size_t)waves * row_lds_bytes(chunk, b.G), s, b, chunk, part);
     mark_end(s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -344,27 +326,32 @@ static hipError_t fwd_launch(const OpArgs& a, int waves, size_t lds, hipStream_t
 }
 
 template <class FT, int CPL>
-static hipError_t fwd_view_launch(const OpArgs& a, int waves, size_t lds, float* part,
+static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, float* part,
                                   hipStream_t s) {
-    const int64_t rows = max_slot_rows(a.B, a.N, a.A);
-    const unsigned blocks = (unsigned)(kSlots * ((rows + waves - 1) / waves));
-    mark_begin("msda_fwd_view_kernel", s);
-    hipLaunchKernelGGL((msda_fwd_view_kernel<FT, CPL>), dim3(blocks), dim3(64 * waves), lds, s,
-                       a, part);
-    mark_end(s);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const size_t total = (size_t)a.B * a.A * a.C;
-    mark_begin("fwd_view_reduce", s);
-    if (a.C % 4 == 0) {
-        hipLaunchKernelGGL(fwd_view_reduce<4>, dim3((unsigned)((total / 4 + 255) / 256)),
-                           dim3(256), 0, s, part, a.out, a.B, a.N, a.A, a.C);
-    } else {
-        hipLaunchKernelGGL(fwd_view_reduce<1>, dim3((unsigned)((total + 255) / 256)), dim3(256),
-                           0, s, part, a.out, a.B, a.N, a.A, a.C);
+    const int rows = fwd_rows(a.N), chunk = fwd_chunk_samples(waves, a.G);
+    const size_t AC = (size_t)a.A * a.C, total = AC * a.B;
+    for (int row0 = 0; row0 < rows; row0 += part_rows) {
+        const int nrows = part_rows < rows - row0 ? part_rows : rows - row0;
+        mark_begin("msda_fwd_view_kernel", s);
+        hipLaunchKernelGGL((msda_fwd_view_kernel<FT, CPL>),
+                           dim3(slot_blocks((u64)a.B * (u32)nrows * (u32)a.A, waves)),
+                           dim3(64 * waves), (size_t)waves * row_lds_bytes(chunk, a.G), s, a, rows,
+                           row0, nrows, chunk, part);
+        mark_end(s);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        mark_begin("fwd_view_reduce", s);
+        if (a.C % 4 == 0) {
+            hipLaunchKernelGGL(fwd_rows_reduce<4>, dim3((unsigned)((total / 4 + 255) / 256)),
+                               dim3(256), 0, s, part, a.out, a.B, nrows, AC, row0 > 0);
+        } else {
+            hipLaunchKernelGGL(fwd_rows_reduce<1>, dim3((unsigned)((total + 255) / 256)),
+                               dim3(256), 0, s, part, a.out, a.B, nrows, AC, row0 > 0);
+        }
+        mark_end(s);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    mark_end(s);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 // Instantiations by (dtype, channels per lane).
@@ -391,8 +378,8 @@ hipError_t launch_forward_batched(const BatchArgs& b, int dtype, int cpl, int wa
 }
 
 hipError_t launch_forward_batched_view(const BatchArgs& b, int dtype, int cpl, int waves,
-                                       size_t lds, float* part, hipStream_t s) {
-    MSDA_FOR_EACH_LAYOUT(fwd_batched_view_launch, b, waves, lds, part, s)
+                                       float* part, hipStream_t s) {
+    MSDA_FOR_EACH_LAYOUT(fwd_batched_view_launch, b, waves, part, s)
 }
 
 hipError_t launch_forward(const OpArgs& a, int dtype, int cpl, int waves, size_t lds,
@@ -400,9 +387,9 @@ hipError_t launch_forward(const OpArgs& a, int dtype, int cpl, int waves, size_t
     MSDA_FOR_EACH_LAYOUT(fwd_launch, a, waves, lds, s)
 }
 
-hipError_t launch_forward_view(const OpArgs& a, int dtype, int cpl, int waves, size_t lds,
+hipError_t launch_forward_view(const OpArgs& a, int dtype, int cpl, int waves, int part_rows,
                                float* part, hipStream_t s) {
-    MSDA_FOR_EACH_LAYOUT(fwd_view_launch, a, waves, lds, part, s)
+    MSDA_FOR_EACH_LAYOUT(fwd_view_launch, a, waves, part_rows, part, s)
 }
 
 }  // namespace msda

@@ -97,6 +97,7 @@ struct BatchTables {
     uint32_t* anchor_start;       // [S+1] first anchor (over all scenes) of each scene
     uint32_t* sample_start;       // [S+1] first sample / record of each scene
     uint32_t* region_start;       // [S+1] first region of each scene
+    uint64_t* row_start;          // [S+1] first view-order forward row of each scene
     uint32_t* cell_start;         // [regions] first cell of each region (global)
     uint32_t* slot_scene;         // [regions] scene of each slot
     uint32_t* slot_region;        // [regions] region (within its scene) of each slot
@@ -111,6 +112,7 @@ struct BatchArgs {
     const float* level_scale;
     BatchTables t;
     uint32_t total_anchors;
+    uint64_t total_rows;          // view-order forward rows: sum of fwd_rows(Ncam) * A
     uint32_t total_samples;
     uint32_t total_cells;
     uint32_t total_regions;
@@ -205,14 +207,26 @@ __host__ __device__ inline ViewRow view_row(const SlotSpan& s, int64_t r, int N,
     return v;
 }
 
-// The largest slot_rows over the slots (sizes the grid of a view launch).
-inline int64_t max_slot_rows(int B, int N, int A) {
-    int64_t m = 0;
-    for (int x = 0; x < kSlots; ++x) {
-        const int64_t r = slot_rows(slot_span(x, B, N, A), A);
-        if (r > m) m = r;
-    }
-    return m;
+// The view-order forward's work: partial row j of a batch item with N cameras
+// covers cameras [N*j/rows, N*(j+1)/rows), and one wave sums one anchor over
+// one row. Rows are as short as the workspace's 8 rows per batch item allow
+// to grow: one camera for a multiple of 8 up to 64 cameras (a wave per camera
+// took 0.325 ms at the 64-camera scene in BF16, 2 cameras 0.332, 4 0.366, 8
+// 0.385; FP32 0.577, 0.649, 0.752), and at most 64 rows so that the
+// workspace stays bounded.
+constexpr int kMinFwdRows = 8, kMaxFwdRows = 64;
+
+__host__ __device__ inline int fwd_rows(int N) {
+    return N < kMinFwdRows ? N : N >= kMaxFwdRows ? kMaxFwdRows : N / 8 * 8;
+}
+
+// Samples a wave stages at a time: 64 while `waves` waves' staging fits 64
+// KiB, else the largest power of two that does. At least 64 / lanes per
+// sample, since G is at most the lanes per sample.
+inline int fwd_chunk_samples(int waves, int G) {
+    int c = 64;
+    while (c > 1 && (size_t)waves * (size_t)c * (16 + 16 * (size_t)G) > 65536) c /= 2;
+    return c;
 }
 
 // Launchers return hipSuccess or the launch error. They enqueue only.
@@ -221,9 +235,10 @@ hipError_t launch_forward(const OpArgs& a, int dtype, int cpl, int waves, size_t
 hipError_t launch_backward(const OpArgs& a, int dtype, int cpl, int waves, size_t lds_bytes,
                            hipStream_t s);
 // View order: `waves` waves per workgroup, each its own row. The forward
-// writes per-slot partial sums to part ([kSlots][B*A][C] FP32) and adds
-// them into out in slot order.
-hipError_t launch_forward_view(const OpArgs& a, int dtype, int cpl, int waves, size_t lds_bytes,
+// writes partial rows to part and adds them into out in row order, part_rows
+// (>= min(fwd_rows(N), kMinFwdRows)) rows [B][part_rows][A][C] FP32 at a
+// time; the sums do not depend on part_rows.
+hipError_t launch_forward_view(const OpArgs& a, int dtype, int cpl, int waves, int part_rows,
                                float* part, hipStream_t s);
 hipError_t launch_backward_view(const OpArgs& a, int dtype, int cpl, int waves, size_t lds_bytes,
                                 hipStream_t s);
@@ -326,11 +341,12 @@ hipError_t launch_backward_batched(const BatchArgs& b, int dtype, int cpl, int w
                                    size_t lds_bytes, hipStream_t s);
 // Batched gathers in view order: one wave per (XCD slot, global anchor)
 // row; grid kSlots * ceil(total_anchors / waves); LDS waves *
-// batch_view_wave_bytes. The forward's per-slot partials go to part
-// ([kSlots][total_anchors][C] FP32) and are added into each scene's out.
+// batch_view_wave_bytes. The forward takes one wave per partial row of every
+// scene (total_rows anchor rows, fwd_rows(Ncam) per anchor), written to part
+// ([total_rows][C] FP32, scenes in order) and added into each scene's out.
 size_t batch_view_lds(int view_cams, int L, int J, int G, int waves);
 hipError_t launch_forward_batched_view(const BatchArgs& b, int dtype, int cpl, int waves,
-                                       size_t lds, float* part, hipStream_t s);
+                                       float* part, hipStream_t s);
 hipError_t launch_backward_batched_view(const BatchArgs& b, int dtype, int cpl, int waves,
                                         size_t lds, hipStream_t s);
 hipError_t launch_gfeat_tiles_batched(const BatchArgs& b, int out_dtype, int cpl, hipStream_t s);
@@ -354,6 +370,10 @@ int max_pairs_per_chunk(int L, int G);
 
 // Benchmark instrumentation (msda_set_kernel_events): called around every
 // kernel launch; records the caller's events when enabled, else does nothing.
+// The least workspace msda_forward_ws takes for d: kMinFwdRows partial rows
+// per batch item in view order, where msda_forward_workspace_size has room for all.
+size_t forward_min_workspace(const msda_desc* d);
+
 // Sets the thread's last-error message (msda_last_error) and returns st.
 msda_status set_error(msda_status st, const char* message);
 

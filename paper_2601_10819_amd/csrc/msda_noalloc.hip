@@ -46,7 +46,7 @@ extern "C" msda_status msda_forward_noalloc(const void* feat, const int32_t* spa
                                             float* out, const msda_desc* desc, void* stream) {
     if (!desc) return msda::set_error(MSDA_ERR_INVALID_ARGUMENT, "desc is NULL");
     // the size check comes first: no HIP call for an input that cannot fit
-    const size_t need = msda_forward_workspace_size(desc);
+    const size_t need = msda::forward_min_workspace(desc);
     if (need > kScratchBytes)
         return failf(MSDA_ERR_UNSUPPORTED,
                      "msda_forward_noalloc: this input needs %zu bytes of scratch, more than the "
