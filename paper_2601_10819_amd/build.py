@@ -17,7 +17,7 @@ SOURCES = [os.path.join(CSRC, f) for f in
             "msda_util.hip", "msda_vis.hip", "msda_softmax.hip", "msda_noalloc.hip",
             "msda_api.cpp")]
 HEADERS = [os.path.join(CSRC, "msda_internal.h"), os.path.join(CSRC, "msda_common.h"),
-           os.path.join(CSRC, "msda_gather.h"),
+           os.path.join(CSRC, "msda_rows.h"), os.path.join(CSRC, "msda_grads.h"),
            os.path.join(ROOT, "include", "msda.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -202,10 +202,8 @@ msda_status prepare(const msda_desc* d, int order, msda::OpArgs* a, int* cpl_out
     a->R = d->rows;
     a->batch_bytes = (uint32_t)batch_bytes;
     a->lps_shift = log2i(d->channels / cpl);
-    a->pairs_per_chunk = msda::max_pairs_per_chunk(d->num_levels, d->groups);
 
     const int64_t npairs = (int64_t)d->num_points * d->num_cams;
-    const int64_t nchunks = (npairs + a->pairs_per_chunk - 1) / a->pairs_per_chunk;
     int waves = 0;
     if (d->tile && d->tile->waves_per_anchor) {
         waves = d->tile->waves_per_anchor;
@@ -215,14 +213,12 @@ msda_status prepare(const msda_desc* d, int order, msda::OpArgs* a, int* cpl_out
         waves = 4;
     } else {
         // Aim for about 8 waves per SIMD across the chip (256 CUs x 4 SIMDs),
-        // but no more waves than the anchor has staging chunks.
+        // with at least 4 pairs each.
         const int64_t blocks = (int64_t)d->batch * d->num_anchors;
         waves = 1;
-        while (waves < 8 && blocks * waves * 2 <= 8192 && waves * 2 <= nchunks) waves *= 2;
+        while (waves < 8 && blocks * waves * 2 <= 8192 && waves * 2 * 4 <= npairs) waves *= 2;
     }
-    auto lds_of = [&](int w) {
-        return order == MSDA_ORDER_VIEW ? msda::lds_bytes_view(*a, w) : msda::lds_bytes_for(*a, w);
-    };
+    auto lds_of = [&](int w) { return msda::gather_lds_bytes(w, d->channels, d->groups); };
     // a chosen (not requested) wave count shrinks until the staging fits
     // 64 KiB (a quarter of the CU's LDS or less: 4 workgroups per CU); a
     // requested one may use what the device allows a workgroup
@@ -430,8 +426,6 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
     int cpl = 0, waves = 0;
     msda_status st = prepare(desc, order, &a, &cpl, &waves);
     if (st != MSDA_OK) return st;
-    // (a chosen wave count of the view order: see fwd_chunk_samples for its LDS)
-    if (order == MSDA_ORDER_VIEW && !(desc->tile && desc->tile->waves_per_anchor)) waves = 4;
     // sampling_loc, weights and out hold zero elements when A == 0 and may be NULL then
     if (!feat || !spatial_shapes || !level_start_index ||
         (a.A > 0 && (!sampling_loc || !weights || !out)))
@@ -480,8 +474,7 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
         order == MSDA_ORDER_VIEW
             ? msda::launch_forward_view(a, desc->feat_dtype, cpl, waves, part_rows,
                                         static_cast<float*>(workspace), (hipStream_t)stream)
-            : msda::launch_forward(a, desc->feat_dtype, cpl, waves, msda::lds_bytes_for(a, waves),
-                                   (hipStream_t)stream);
+            : msda::launch_forward(a, desc->feat_dtype, cpl, waves, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "msda_forward launch");
     return ok();
 }
@@ -524,17 +517,11 @@ size_t msda::forward_min_workspace(const msda_desc* d) {
 
 extern "C" {
 
-// The backward gather in the chosen order. In view order each wave takes
-// one anchor over a group of cameras: 2 for 1- and 2-byte features, 1 for
-// FP32 (measured at 64 cameras: BF16 0.457 ms with 2 against 0.478 with 1
-// and 0.470 with 4; FP32 0.709 ms with 1 against 0.754 with 2).
-static hipError_t launch_gather(const msda::OpArgs& a0, int order, int dtype, int cpl, int waves,
+// The backward gather in the chosen order.
+static hipError_t launch_gather(const msda::OpArgs& a, int order, int dtype, int cpl, int waves,
                                 hipStream_t s) {
-    msda::OpArgs a = a0;
-    a.view_cams = dtype == MSDA_F32 ? 1 : 2;
-    if (order == MSDA_ORDER_VIEW)
-        return msda::launch_backward_view(a, dtype, cpl, waves, msda::lds_bytes_view(a, waves), s);
-    return msda::launch_backward(a, dtype, cpl, waves, msda::lds_bytes_for(a, waves), s);
+    return order == MSDA_ORDER_VIEW ? msda::launch_backward_view(a, dtype, cpl, waves, s)
+                                    : msda::launch_backward(a, dtype, cpl, waves, s);
 }
 
 // Extra workspace of the visible-view form: the scanned flags (V + 1 words),
@@ -815,7 +802,7 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
                                                 reinterpret_cast<uint32_t*>(ws + VW.partial),
                                                 s)) != hipSuccess ||
                 (e = msda::launch_backward_visible(
-                     a, desc->feat_dtype, cpl, waves, msda::lds_bytes_view(a, waves), items,
+                     a, desc->feat_dtype, cpl, waves, items,
                      place, place + V,
                      grad_feat ? reinterpret_cast<uint32_t*>(ws + W.vals_a) : nullptr, vt,
                      item_dot, s)) != hipSuccess)
@@ -1008,8 +995,7 @@ static msda_status forward_visible_impl(const void* feat, const int32_t* spatial
                                               reinterpret_cast<uint32_t*>(ws + vw.partial), s);
     if (e == hipSuccess && fused) e = msda::launch_view_scale(visible, score, a.B * a.A, a.N, vt, s);
     if (e == hipSuccess)
-        e = msda::launch_forward_visible(a, desc->feat_dtype, cpl, waves,
-                                         msda::lds_bytes_view(a, waves), items, place + V, place,
+        e = msda::launch_forward_visible(a, desc->feat_dtype, cpl, waves, items, place + V, place,
                                          visible, vt, reinterpret_cast<float*>(ws + part_off), s);
     if (e != hipSuccess) return hip_fail(e, "msda_forward_visible launch");
     return ok();
@@ -1180,13 +1166,12 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
 // Sizes of a validated batch.
 struct BatchPlan {
     uint64_t anchors, samples, regions, cells, tiles, heavy_tiles;
-    uint64_t fwd_rows;            // view-order forward: rows over all scenes and anchors
-    int max_regions_per_scene, max_cams;
+    uint64_t fwd_rows, bwd_rows;  // view-order units of all scenes
+    int max_cams;
     int cpl, waves;
     int64_t max_batch_bytes;
     int order;                    // MSDA_ORDER_ANCHOR or MSDA_ORDER_VIEW
-    int view_cams;                // view order: cameras of a row at most
-    int view_waves_fwd, view_waves_bwd;
+    int view_waves;               // view order: waves per workgroup
     uint64_t part_bytes;          // view-order forward partials
     uint64_t max_ap;              // the largest A_s * P
     bool keys_fit;                // every region's cells fit the bucket sort's keys
@@ -1237,9 +1222,10 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
             return fail(MSDA_ERR_UNSUPPORTED, "scene %d: feat must be 16-byte aligned", s);
         p->anchors += (uint64_t)sc.num_anchors;
         p->fwd_rows += (uint64_t)sc.num_anchors * (uint64_t)msda::fwd_rows(sc.num_cams);
+        p->bwd_rows += (uint64_t)sc.num_anchors *
+                       (uint64_t)msda::bwd_rows(sc.num_cams, b->num_points);
         p->samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams * b->num_levels;
         p->regions += (uint64_t)sc.num_cams * b->num_levels;
-        p->max_regions_per_scene = std::max(p->max_regions_per_scene, sc.num_cams * b->num_levels);
         p->max_cams = std::max(p->max_cams, sc.num_cams);
         p->max_batch_bytes = std::max<int64_t>(p->max_batch_bytes, bb);
         uint64_t cells = 0, tiles = 0;
@@ -1295,30 +1281,22 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
     msda_status stt = prepare(&d, MSDA_ORDER_ANCHOR, &a, &p->cpl, &p->waves);
     if (stt != MSDA_OK) return stt;
     // work order: view order (one camera range per XCD) unless anchor order
-    // is asked for; each scene is split over the XCD slots as a single call
-    // with B = 1 would be, and a row covers at most max_cams / 8 + 2 cameras
+    // is asked for; each scene's units are those of a single call with B = 1
     const int req = b->tile ? b->tile->order : MSDA_ORDER_AUTO;
     if (req != MSDA_ORDER_AUTO && req != MSDA_ORDER_ANCHOR && req != MSDA_ORDER_VIEW)
         return fail(MSDA_ERR_UNSUPPORTED, "unknown order %d", req);
     p->order = req == MSDA_ORDER_ANCHOR ? MSDA_ORDER_ANCHOR : MSDA_ORDER_VIEW;
-    p->view_cams = p->max_cams / msda::kSlots + 2;
     const int tw = b->tile ? b->tile->waves_per_anchor : 0;
-    p->view_waves_fwd = tw ? tw : 4;
-    p->view_waves_bwd = tw ? tw : 4;
+    p->view_waves = tw ? tw : 4;
+    while (!tw && p->view_waves > 1 &&
+           msda::gather_lds_bytes(p->view_waves, b->channels, b->groups) > 65536)
+        p->view_waves /= 2;
     p->part_bytes = p->fwd_rows * (uint64_t)b->channels * sizeof(float);
-    if (p->order == MSDA_ORDER_VIEW) {
-        const int J = msda::max_pairs_per_chunk(b->num_levels, b->groups);
-        const int wmax = std::max(p->view_waves_fwd, p->view_waves_bwd);
-        const size_t need = msda::batch_view_lds(p->view_cams, b->num_levels, J, b->groups, wmax);
-        if (need > 65536)
-            return fail(MSDA_ERR_UNSUPPORTED, "view-order batched launch needs %zu bytes of LDS",
-                        need);
-    }
     return MSDA_OK;
 }
 
-void fill_batch_args(const msda_batch* b, const BatchPlan& p, char* ws, const BatchWs& w,
-                     msda::BatchArgs* a) {
+void fill_batch_args(const msda_batch* b, const BatchPlan& p, bool backward, char* ws,
+                     const BatchWs& w, msda::BatchArgs* a) {
     *a = msda::BatchArgs{};
     a->scenes = b->scenes;
     a->S = b->num_scenes;
@@ -1338,14 +1316,11 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, char* ws, const Ba
     a->t.magic = reinterpret_cast<uint64_t*>(ws + w.magic);
     a->t.magic_shift = reinterpret_cast<uint32_t*>(ws + w.magic_shift);
     a->total_anchors = (uint32_t)p.anchors;
-    a->total_rows = p.fwd_rows;
+    a->total_rows = backward ? p.bwd_rows : p.fwd_rows;
     a->total_samples = (uint32_t)p.samples;
     a->total_cells = (uint32_t)p.cells;
     a->total_regions = (uint32_t)p.regions;
     a->lps_shift = log2i(b->channels / p.cpl);
-    a->pairs_per_chunk = msda::max_pairs_per_chunk(b->num_levels, b->groups);
-    a->max_regions_per_scene = p.max_regions_per_scene;
-    a->view_cams = p.view_cams;
 }
 
 // The weight-flag buffers of a batch (all zero without a weight flag).
@@ -1426,16 +1401,6 @@ msda_status batch_softmax_grad(const msda_batch* b, char* ws, const BatchWs& w, 
     return MSDA_OK;
 }
 
-size_t batch_lds(const msda_batch* b, const BatchPlan& p) {
-    msda::OpArgs o = {};
-    o.N = p.max_cams;
-    o.L = b->num_levels;
-    o.G = b->groups;
-    o.C = b->channels;
-    o.pairs_per_chunk = msda::max_pairs_per_chunk(b->num_levels, b->groups);
-    return msda::lds_bytes_for(o, p.waves);
-}
-
 int persistent_blocks(uint64_t items, int waves) {
     const uint64_t cap = 256ull * (uint64_t)(16 / waves);     // 256 CUs, ~16 waves each
     return (int)std::max<uint64_t>(1, std::min(items, cap));
@@ -1489,10 +1454,8 @@ msda_status msda_forward_batched(const msda_batch* b, void* workspace, size_t wo
     if (!workspace || workspace_bytes < w.total)
         return fail(MSDA_ERR_WORKSPACE, "workspace of %zu bytes needed", w.total);
     if (!aligned(workspace, 256)) return fail(MSDA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-    const size_t lds = batch_lds(b, p);
-    if (lds > 65536) return fail(MSDA_ERR_UNSUPPORTED, "batched launch needs %zu bytes of LDS", lds);
     msda::BatchArgs a;
-    fill_batch_args(b, p, static_cast<char*>(workspace), w, &a);
+    fill_batch_args(b, p, false, static_cast<char*>(workspace), w, &a);
     const hipStream_t s = (hipStream_t)stream;
     hipError_t e = msda::launch_batch_tables(a, false, s);
     if (e != hipSuccess) return hip_fail(e, "batch tables");
@@ -1501,11 +1464,11 @@ msda_status msda_forward_batched(const msda_batch* b, void* workspace, size_t wo
         return st;
     if (p.order == MSDA_ORDER_VIEW) {
         e = msda::launch_forward_batched_view(
-            a, b->feat_dtype, p.cpl, p.view_waves_fwd,
+            a, b->feat_dtype, p.cpl, p.view_waves,
             reinterpret_cast<float*>(static_cast<char*>(workspace) + w.part), s);
     } else {
         e = msda::launch_forward_batched(a, b->feat_dtype, p.cpl, p.waves,
-                                         persistent_blocks(p.anchors, p.waves), lds, s);
+                                         persistent_blocks(p.anchors, p.waves), s);
     }
     if (e != hipSuccess) return hip_fail(e, "msda_forward_batched launch");
     return ok();
@@ -1558,12 +1521,10 @@ msda_status msda_backward_batched(const msda_batch* b, void* workspace, size_t w
     if (!workspace || workspace_bytes < w.total)
         return fail(MSDA_ERR_WORKSPACE, "workspace of %zu bytes needed", w.total);
     if (!aligned(workspace, 256)) return fail(MSDA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-    const size_t lds = batch_lds(b, p);
-    if (lds > 65536) return fail(MSDA_ERR_UNSUPPORTED, "batched launch needs %zu bytes of LDS", lds);
 
     char* ws = static_cast<char*>(workspace);
     msda::BatchArgs a;
-    fill_batch_args(b, p, ws, w, &a);
+    fill_batch_args(b, p, true, ws, w, &a);
     const hipStream_t s = (hipStream_t)stream;
     hipError_t e = msda::launch_batch_tables(a, true, s);
     if (e != hipSuccess) return hip_fail(e, "batch tables");
@@ -1597,14 +1558,10 @@ msda_status msda_backward_batched(const msda_batch* b, void* workspace, size_t w
     }
     if (p.anchors > 0 && (gf || gl || gw)) {
         if (p.order == MSDA_ORDER_VIEW) {
-            const size_t vlds = msda::batch_view_lds(p.view_cams, b->num_levels,
-                                                     a.pairs_per_chunk, b->groups,
-                                                     p.view_waves_bwd);
-            e = msda::launch_backward_batched_view(a, b->feat_dtype, p.cpl, p.view_waves_bwd,
-                                                   vlds, s);
+            e = msda::launch_backward_batched_view(a, b->feat_dtype, p.cpl, p.view_waves, s);
         } else {
             e = msda::launch_backward_batched(a, b->feat_dtype, p.cpl, p.waves,
-                                              persistent_blocks(p.anchors, p.waves), lds, s);
+                                              persistent_blocks(p.anchors, p.waves), s);
         }
         if (e != hipSuccess) return hip_fail(e, "msda_backward_batched launch");
     }

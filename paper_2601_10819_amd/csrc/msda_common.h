@@ -130,24 +130,8 @@ __device__ __forceinline__ u32 bf16x2_rne(float lo, float hi) {
 
 // ---------------------------------------------------------------- geometry
 
-// One (camera, level) region: its size, first row, first bilinear cell (for
-// the sorted grad_feat records; 0 when unused) and the FP8 level scale (1
-// for other storage types).
-struct Geo { int H, W, start; float scale; u32 cstart, pad0, pad1, pad2; };
-
-__device__ __forceinline__ void stage_geometry(Geo* geo, const OpArgs& a) {
-    const int NL = a.N * a.L;
-    for (int i = threadIdx.x; i < NL; i += blockDim.x) {
-        Geo g;
-        g.H = a.shapes[2 * i];
-        g.W = a.shapes[2 * i + 1];
-        g.start = a.starts[i];
-        g.scale = a.level_scale ? a.level_scale[i % a.L] : 1.f;
-        g.cstart = a.cell_start ? a.cell_start[i] : 0u;
-        g.pad0 = g.pad1 = g.pad2 = 0u;
-        geo[i] = g;
-    }
-}
+// One (camera, level) region: its size and first row.
+struct Geo { int H, W, start; };
 
 // Integer part and fraction of t = u*n - 0.5 along one axis of a level with n
 // pixels, and whether -1 < t < n. u*n is split exactly into p + e, the floor
@@ -302,55 +286,14 @@ __device__ __forceinline__ float xor_sum(float v, int mask) {
     return v + xor_shuffle(v, mask);
 }
 
-// Per-lane registers' worth of weights staged per wave step.
-constexpr int kStageWords = 8;
-
-// The 4 corner taps of one sample as staged in LDS: byte offsets of the
-// corner rows within the batch item (kOOB outside; each lane adds its own
-// channel offset) and the bilinear weights (times the FP8 level scale).
-struct alignas(16) Taps { u32 off[4]; float cw[4]; };
-
-__host__ __device__ constexpr size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
-
-// One wave's LDS staging slot for a chunk of up to J (keypoint, camera)
-// pairs of one anchor: per pair its index p*N + n among the anchor's pairs
-// and its camera, its L*G weights, and the taps of its L samples; for the
-// backward also each sample's location-derivative factors
-// (W(1-ly), W ly, H(1-lx), H lx): d(blend)/dx = W((1-ly)(F01-F00) +
-// ly(F11-F10)) and d(blend)/dy = H((1-lx)(F10-F00) + lx(F11-F01)).
-struct StageSlot {
-    u32* src;
-    u32* cam;
-    float* w;
-    Taps* taps;
-    float4* dk;
-};
-
-// Levels per pair in the staged taps: L rounded up to a multiple of 4, so the
-// forward issues the loads of 4 levels at a time without a branch (a padded
-// level's taps point outside the feature and weigh 0).
-__host__ __device__ constexpr int padded_levels(int L) { return (L + 3) & ~3; }
-
-// Every part starts 16-byte aligned (taps are read as 16-byte words), and so
-// does every wave's slot.
-__host__ __device__ constexpr size_t wave_stage_bytes(int J, int L, int G) {
-    return align16((size_t)J * 8) + align16((size_t)J * L * G * 4) +
-           (size_t)J * padded_levels(L) * sizeof(Taps) +
-           (size_t)J * padded_levels(L) * sizeof(float4);
+// Quotients of 0 <= i <= i_max by d: by the multiplier of div_magic where that
+// is exact (i_max * d < 2^32, d > 1), else (0) by division.
+__device__ __forceinline__ u32 div_magic(int d, int64_t i_max) {
+    return d > 1 && (u64)i_max * (u32)d >> 32 == 0 ? 0xffffffffu / (u32)d + 1u : 0u;
 }
 
-__device__ __forceinline__ StageSlot stage_slot(unsigned char* work, int wave, int J, int L,
-                                                int G) {
-    unsigned char* p = work + (size_t)wave * wave_stage_bytes(J, L, G);
-    StageSlot s;
-    s.src = reinterpret_cast<u32*>(p);
-    s.cam = s.src + J;
-    p += align16((size_t)J * 8);
-    s.w = reinterpret_cast<float*>(p);
-    p += align16((size_t)J * L * G * 4);
-    s.taps = reinterpret_cast<Taps*>(p);
-    s.dk = reinterpret_cast<float4*>(s.taps + (size_t)J * padded_levels(L));
-    return s;
+__device__ __forceinline__ int div_by(int i, int d, u32 m) {
+    return m ? (int)__umulhi((u32)i, m) : i / d;
 }
 
 // Makes this wave's LDS writes visible to its later reads: LDS accesses of
@@ -361,53 +304,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-
-// Pair orders: the k-th pair a wave processes -> (index p*N + n, camera n).
-// Anchor order walks the anchor's pairs as stored (keypoint-major); view
-// order walks cameras [n_lo, n_lo + nv) one after the other, every
-// keypoint of a camera before the next camera.
-struct AnchorOrder {
-    int N;
-    __device__ __forceinline__ void operator()(int k, u32* src, u32* cam) const {
-        *src = (u32)k;
-        *cam = (u32)(k % N);
-    }
-};
-
-struct ViewOrder {
-    int N, P, n_lo;
-    int geo_lo = 0;     // first camera of the staged geometry (a wave's own slice)
-    __device__ __forceinline__ void operator()(int k, u32* src, u32* cam) const {
-        const int q = k / P, p = k - q * P;
-        *cam = (u32)(n_lo + q - geo_lo);
-        *src = (u32)(p * N + n_lo + q);
-    }
-};
-
-// Where the backward writes its grad_feat records (key = bilinear cell,
-// frac = (lx, ly)) while staging. The sample (pair src, level l) has the
-// index s = base + src*L + l; its fractions go to frac[s]. Dense records
-// (val == nullptr): the record is key[s] and its value is s. Compacted
-// records (the visible-view form): the k-th pair the wave processes writes
-// record r = cbase + k*L + l, key[r] and val[r] = s. key == nullptr: none.
-//
-// Bucketed records (bucket_ap != 0, the dense single call): the record of
-// pair src = p*N + n, level l goes to bucket (b, n, l) at slot a*P + p,
-// i.e. key[bucket_base + (n*L + l)*bucket_ap + p] with bucket_base =
-// b*N*L*bucket_ap + a*P, and its key is the local cell of the region
-// ((H+1)(W+1) outside the level); frac is still written at s.
-struct RecordSink {
-    u32* key;
-    float2* frac;
-    u32 base;            // first sample of the anchor
-    u32 cell_base;       // first cell of the batch item
-    u32 no_cell;         // key of a sample outside its level
-    u32* val;            // compacted records' values, or nullptr
-    u32 cbase;           // compacted: first record of the wave's item
-    u32 bucket_ap;       // bucketed: A*P records per bucket (0: not bucketed)
-    u32 bucket_base;     // bucketed: b*N*L*A*P + a*P
-    u32 N;               // bucketed: cameras
-};
 
 // One anchor's weights as the gathers stage them: FP32 or bfloat16 storage,
 // and optionally logits turned into the per-group softmax on the fly
@@ -441,83 +337,6 @@ __device__ __forceinline__ WSrc anchor_weights(const OpArgs& a, size_t ba, size_
     return WSrc(p, a.wstats ? a.wstats + ba * (size_t)a.G : nullptr, a.G, a.w_bf16 != 0);
 }
 
-// Stages pairs [k0, k0 + nj) (in the wave's pair order) of the anchor whose
-// weights / locations start at gw / gl: pair table, weights (coalesced
-// within each pair's L*G run), and one sample's taps per lane. Ends with
-// the slot readable by the whole wave.
-template <bool SCALE_TAPS, bool FRACS, class Order>
-__device__ __forceinline__ void stage_chunk(const StageSlot& s, const Order& order, int k0, int nj,
-                                            const WSrc& gw, const float* gl, const Geo* geo,
-                                            int L, int LG, u32 row_bytes, int lane,
-                                            const RecordSink& rec) {
-    if (lane < nj) {
-        u32 src, cam;
-        order(k0 + lane, &src, &cam);
-        s.src[lane] = src;
-        s.cam[lane] = cam;
-    }
-    wave_lds_sync();
-    const int nw = nj * LG;
-#pragma unroll
-    for (int t = 0; t < kStageWords; ++t) {
-        const int i = t * 64 + lane;
-        if (i < nw) {
-            const int jj = i / LG;
-            s.w[i] = gw.raw((size_t)s.src[jj] * LG + (i - jj * LG));
-        }
-    }
-    if (gw.stats) {
-        // logits -> softmax weights: each lane rewrites the entries it staged
-        for (int i = lane; i < nw; i += 64) s.w[i] = gw.softmax(s.w[i], i & (gw.G - 1));
-    }
-    const int Lp = padded_levels(L);
-    for (int i = lane; i < nj * Lp; i += 64) {
-        const int jj = i / Lp, l = i - jj * Lp;
-        Taps t;
-        if (l >= L) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                t.off[c] = kOOB;
-                t.cw[c] = 0.f;
-            }
-            s.taps[i] = t;
-            if constexpr (FRACS) s.dk[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            continue;
-        }
-        const u32 src = s.src[jj];
-        const Geo gm = geo[s.cam[jj] * L + l];
-        const Corners cr = corners_of(gl[2 * src], gl[2 * src + 1], gm, row_bytes, 0u);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            t.off[c] = cr.off[c];
-            t.cw[c] = SCALE_TAPS ? cr.cw[c] * gm.scale : cr.cw[c];
-        }
-        s.taps[i] = t;
-        if constexpr (FRACS) {
-            const float fw = (float)gm.W, fh = (float)gm.H;
-            s.dk[i] = make_float4(fw * (1.f - cr.ly), fw * cr.ly, fh * (1.f - cr.lx), fh * cr.lx);
-            if (rec.key) {
-                const u32 smp = rec.base + src * (u32)L + (u32)l;
-                const u32 local = cr.valid ? (u32)(cr.y0 + 1) * (u32)(gm.W + 1) + (u32)(cr.x0 + 1)
-                                           : (u32)(gm.H + 1) * (u32)(gm.W + 1);
-                const u32 key = cr.valid ? rec.cell_base + gm.cstart + local : rec.no_cell;
-                if (rec.bucket_ap) {
-                    const u32 p = src / rec.N, n = src - p * rec.N;
-                    rec.key[rec.bucket_base + (n * (u32)L + (u32)l) * rec.bucket_ap + p] = local;
-                } else if (rec.val) {
-                    const u32 r = rec.cbase + (u32)(k0 + jj) * (u32)L + (u32)l;
-                    rec.key[r] = key;
-                    rec.val[r] = smp;
-                } else {
-                    rec.key[smp] = key;
-                }
-                rec.frac[smp] = make_float2(cr.lx, cr.ly);
-            }
-        }
-    }
-    wave_lds_sync();
-}
-
 // Lane layout of one wave: CPL channels per lane, C/CPL lanes per sample.
 struct Lanes {
     int lane, lps, spw, sub, c0, g;
@@ -537,9 +356,6 @@ __device__ __forceinline__ Lanes lanes_of(const OpArgs& a) {
     return q;
 }
 
-// Ends a chunk: the next staging may overwrite the slot.
-__device__ __forceinline__ void end_chunk() { wave_lds_sync(); }
-
 // Inclusive scan across the 256 threads of a block (4 waves); returns the
 // thread's inclusive sum and the block total in *total.
 __device__ __forceinline__ u32 block_inclusive_scan(u32 v, u32* lds4, u32* total) {
@@ -558,6 +374,36 @@ __device__ __forceinline__ u32 block_inclusive_scan(u32 v, u32* lds4, u32* total
     return v + before;
 }
 
+// ---------------------------------------------------------------- view order
+
+// The XCD slot x of a workgroup (the hardware hands workgroups to the XCDs
+// round-robin) takes the x-th of kSlots equal ranges of T units: this wave's
+// unit, or T.
+__device__ __forceinline__ u64 slot_unit(u64 T, u32 block, int wave, int nwaves) {
+    const u32 x = block % kSlots;
+    const u64 u = T * x / kSlots + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
+    return u < T * (x + 1) / kSlots ? u : T;
+}
+
+// Unit u of a view-order launch as (row, anchor), units row-major: both the
+// same across the wave.
+struct RowUnit { u32 row; int a; };
+
+__device__ __forceinline__ RowUnit row_unit(u64 u, int A) {
+    const u64 r = u >> 32 ? u / (u32)A : (u64)((u32)u / (u32)A);
+    RowUnit t;
+    t.row = (u32)uniform((int)r);
+    t.a = uniform((int)(u - r * (u32)A));
+    return t;
+}
+
+// Cameras [lo, hi) of row j of `rows`.
+struct CamRange { int lo, hi; };
+
+__device__ __forceinline__ CamRange row_cams(int N, int j, int rows) {
+    return CamRange{(int)((u64)N * (u32)j / (u32)rows), (int)((u64)N * (u32)(j + 1) / (u32)rows)};
+}
+
 // ---------------------------------------------------------------- batched form
 
 // The scene of a batch item index: the last s with start[s] <= item (start
@@ -569,6 +415,16 @@ __device__ __forceinline__ int scene_of(const u32* start, int S, u32 item) {
         if (start[mid] <= item) lo = mid; else hi = mid - 1;
     }
     return lo;
+}
+
+// The same for a row index (start: 64-bit prefix table), wave-uniform.
+__device__ __forceinline__ int scene_of_row(const u64* start, int S, u64 u) {
+    int lo = 0, hi = S - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (start[mid] <= u) lo = mid; else hi = mid - 1;
+    }
+    return uniform(lo);
 }
 
 // Scene s of a batch as a single-call argument set with B = 1.
@@ -607,61 +463,7 @@ __device__ __forceinline__ OpArgs scene_view(const BatchArgs& b, int s, int feat
     a.R = sc.rows;
     a.batch_bytes = (u32)(sc.rows * (int64_t)b.C * feat_bytes);
     a.lps_shift = b.lps_shift;
-    a.pairs_per_chunk = b.pairs_per_chunk;
     return a;
-}
-
-// A row of the batched view order: one anchor of one scene over that
-// scene's cameras in XCD slot x, the single call's slot split of the scene
-// with B = 1. nv = 0: the anchor has no cameras in the slot.
-struct BatchRow {
-    int s, a, n_lo, nv;
-};
-
-__device__ __forceinline__ BatchRow batch_row(const BatchArgs& b, int x, u32 g) {
-    BatchRow r;
-    r.s = scene_of(b.t.anchor_start, b.S, g);
-    r.a = (int)(g - b.t.anchor_start[r.s]);
-    const int N = b.scenes[r.s].num_cams, A = b.scenes[r.s].num_anchors;
-    const SlotSpan span = slot_span(x, 1, N, A);
-    r.n_lo = 0;
-    r.nv = 0;
-    if (slot_rows(span, A) > 0) {
-        const ViewRow v = view_row(span, r.a, N, A);
-        r.n_lo = v.n_lo;
-        r.nv = v.nv;
-    }
-    // every field is the same across the wave (g is per wave)
-    r.s = uniform(r.s);
-    r.a = uniform(r.a);
-    r.n_lo = uniform(r.n_lo);
-    r.nv = uniform(r.nv);
-    return r;
-}
-
-// Bytes of one wave's LDS in the batched view order: the geometry of its
-// row's cameras (at most view_cams) and its staging slot.
-__host__ __device__ inline size_t batch_view_wave_bytes(int view_cams, int L, int J, int G) {
-    return (((size_t)view_cams * L * sizeof(Geo) + 15) & ~(size_t)15) +
-           wave_stage_bytes(J, L, G);
-}
-
-// The geometry of cameras [n_lo, n_lo + nv) of `a` into one wave's slice
-// (entry (n - n_lo) * L + l), then readable by the whole wave.
-__device__ __forceinline__ void stage_geometry_range(Geo* geo, const OpArgs& a, int n_lo, int nv,
-                                                     int lane) {
-    for (int i = lane; i < nv * a.L; i += 64) {
-        const int l = i % a.L, r = (n_lo + i / a.L) * a.L + l;
-        Geo g;
-        g.H = a.shapes[2 * r];
-        g.W = a.shapes[2 * r + 1];
-        g.start = a.starts[r];
-        g.scale = a.level_scale ? a.level_scale[l] : 1.f;
-        g.cstart = a.cell_start ? a.cell_start[r] : 0u;
-        g.pad0 = g.pad1 = g.pad2 = 0u;
-        geo[i] = g;
-    }
-    wave_lds_sync();
 }
 
 // Quotient of n < 2^30 by the divisor whose magic is (m, shift): exact

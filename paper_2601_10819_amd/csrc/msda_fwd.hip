@@ -3,8 +3,8 @@
 // bilinear sample.
 //
 // Anchor order (msda_fwd_kernel): one workgroup per (batch item, anchor);
-// its waves split the anchor's (keypoint, camera) pairs in chunks and the
-// waves' partial sums are added in a fixed order at the end.
+// its waves split the anchor's samples and the waves' partial sums are added
+// in a fixed order at the end.
 //
 // View order (msda_fwd_view_kernel): the rows -- a run of cameras, see
 // fwd_rows -- of every anchor are cut, camera-major, into one contiguous
@@ -19,67 +19,29 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "msda_gather.h"
 #include "msda_rows.h"
 
 namespace msda {
 
-int max_pairs_per_chunk(int L, int G) {
-    int j = (kStageWords * 64) / (L * G);
-    if (j > 32) j = 32;
-    return j < 1 ? 1 : j;
-}
-
-size_t lds_bytes_for(const OpArgs& a, int waves) {
-    const size_t geo = (size_t)a.N * a.L * sizeof(Geo);
-    const size_t stage = (size_t)waves * wave_stage_bytes(a.pairs_per_chunk, a.L, a.G);
-    const size_t red = (size_t)waves * a.C * sizeof(float);
-    return geo + (stage > red ? stage : red);
-}
-
-size_t batch_view_lds(int view_cams, int L, int J, int G, int waves) {
-    return (size_t)waves * batch_view_wave_bytes(view_cams, L, J, G);
-}
-
-size_t lds_bytes_view(const OpArgs& a, int waves) {
-    return (size_t)a.N * a.L * sizeof(Geo) +
-           (size_t)waves * wave_stage_bytes(a.pairs_per_chunk, a.L, a.G);
-}
-
 // The forward of one anchor (index ba = b*A + a of `a`) by the whole
-// workgroup in anchor order; the geometry of `a` is already staged in geo.
-// Called by every thread of the block (it ends with block-wide barriers).
+// workgroup in anchor order. Called by every thread of the block (it ends
+// with block-wide barriers).
 template <class FT, int CPL>
-__device__ __forceinline__ void fwd_anchor(const OpArgs& a, const int ba, const Geo* geo,
-                                           unsigned char* work) {
-    const int LG = a.L * a.G;
-    const int J = a.pairs_per_chunk;
+__device__ __forceinline__ void fwd_anchor(const OpArgs& a, const int ba, int chunk,
+                                           unsigned char* smem) {
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
     const Lanes q = lanes_of<FT, CPL>(a);
-    const StageSlot st = stage_slot(work, wave, J, a.L, a.G);
     const int b = ba / a.A;
-    const int npairs = a.P * a.N;
-    const float* gl = a.loc + (size_t)ba * npairs * 2;
-    const WSrc gw = anchor_weights(a, (size_t)ba, (size_t)npairs * LG);
-    const u32 row_bytes = (u32)a.C * FT::kBytes;
     const rsrc_t feat = make_rsrc(static_cast<const char*>(a.feat) + (size_t)b * a.batch_bytes,
                                   a.batch_bytes);
-    const AnchorOrder order{a.N};
-    const RecordSink none{};
-
+    // equal runs of samples, of whole chunks of 64 where there are several
+    const int total = a.P * a.N * a.L;
+    int per = (total + nwaves - 1) / nwaves;
+    if (per > 64) per = (per + 63) & ~63;
+    const int s_lo = (int)min((int64_t)total, (int64_t)wave * per);
     float acc[CPL];
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) acc[i] = 0.f;
-    const int nchunks = (npairs + J - 1) / J;
-    for (int k = wave; k < nchunks; k += nwaves) {
-        const int k0 = k * J;
-        const int nj = min(J, npairs - k0);
-        stage_chunk<FT::kBytes == 1, false>(st, order, k0, nj, gw, gl, geo, a.L, LG, row_bytes,
-                                            q.lane, none);
-        fwd_chunk<FT, CPL>(st, nj, a.L, a.G, q, feat, acc);
-        end_chunk();
-    }
-    reduce_subwaves<CPL>(q, acc);
+    row_sum<FT, CPL>(a, (size_t)ba, feat, s_lo, min(total, s_lo + per), q, chunk,
+                     smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
 
     float* out = a.out + (size_t)ba * a.C;
     if (nwaves == 1) {
@@ -89,8 +51,8 @@ __device__ __forceinline__ void fwd_anchor(const OpArgs& a, const int ba, const 
         }
         return;
     }
-    float* red = reinterpret_cast<float*>(work);
-    __syncthreads();                       // every wave is done with its staging slot
+    float* red = reinterpret_cast<float*>(smem);
+    __syncthreads();                       // every wave is done with its staging
     if (q.sub == 0) {
 #pragma unroll
         for (int i = 0; i < CPL; ++i) red[wave * a.C + q.c0 + i] = acc[i];
@@ -101,31 +63,20 @@ __device__ __forceinline__ void fwd_anchor(const OpArgs& a, const int ba, const 
         for (int w = 0; w < nwaves; ++w) s += red[w * a.C + c];   // fixed order
         out[c] = s;
     }
-    __syncthreads();                       // work is free again
+    __syncthreads();                       // smem is free again
+}
+
+// LDS of an anchor-order workgroup: the waves' staging, then their sums.
+static size_t anchor_lds_bytes(int waves, int chunk, int C, int G) {
+    const size_t stage = (size_t)waves * row_lds_bytes(chunk, G);
+    const size_t red = (size_t)waves * C * sizeof(float);
+    return stage > red ? stage : red;
 }
 
 template <class FT, int CPL>
-__global__ void __launch_bounds__(512) msda_fwd_kernel(OpArgs a) {
+__global__ void __launch_bounds__(512) msda_fwd_kernel(OpArgs a, int chunk) {
     extern __shared__ __align__(16) unsigned char smem[];
-    Geo* geo = reinterpret_cast<Geo*>(smem);
-    unsigned char* work = smem + (size_t)a.N * a.L * sizeof(Geo);
-    stage_geometry(geo, a);
-    __syncthreads();
-    fwd_anchor<FT, CPL>(a, (int)blockIdx.x, geo, work);
-}
-
-// The XCD slot x of a workgroup (the hardware hands workgroups to the XCDs
-// round-robin) takes the x-th of kSlots equal ranges of T units: this wave's
-// unit, or T.
-__device__ __forceinline__ u64 slot_unit(u64 T, u32 block, int wave, int nwaves) {
-    const u32 x = block % kSlots;
-    const u64 u = T * x / kSlots + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
-    return u < T * (x + 1) / kSlots ? u : T;
-}
-
-// Quotient of the wave-uniform u by d.
-__device__ __forceinline__ u64 uniform_div(u64 u, u32 d) {
-    return u >> 32 ? u / d : (u64)((u32)u / d);
+    fwd_anchor<FT, CPL>(a, (int)blockIdx.x, chunk, smem);
 }
 
 // View order: rows [row0, row0 + nrows) of every batch item, of `rows` in
@@ -138,19 +89,18 @@ __global__ void __launch_bounds__(512) msda_fwd_view_kernel(OpArgs a, int rows, 
     const u64 T = (u64)a.B * (u32)nrows * (u32)a.A;
     const u64 u = slot_unit(T, blockIdx.x, wave, nwaves);
     if (u >= T) return;
-    const u32 r = (u32)uniform((int)uniform_div(u, (u32)a.A));
-    const int an = uniform((int)(u - (u64)r * (u32)a.A));
-    const int b = (int)(r / (u32)nrows), j = row0 + (int)(r % (u32)nrows);
-    const int n_lo = (int)((u64)a.N * (u32)j / (u32)rows);
-    const int n_hi = (int)((u64)a.N * (u32)(j + 1) / (u32)rows);
+    const RowUnit t = row_unit(u, a.A);
+    const int b = (int)(t.row / (u32)nrows);
+    const CamRange n = row_cams(a.N, row0 + (int)(t.row % (u32)nrows), rows);
     const Lanes q = lanes_of<FT, CPL>(a);
     const rsrc_t feat = make_rsrc(
         static_cast<const char*>(a.feat) + (size_t)b * a.batch_bytes, a.batch_bytes);
+    const int NS = a.P * a.L;
     float acc[CPL];
-    row_sum<FT, CPL>(a, (size_t)b * a.A + an, feat, n_lo, n_hi, q, chunk,
+    row_sum<FT, CPL>(a, (size_t)b * a.A + t.a, feat, n.lo * NS, n.hi * NS, q, chunk,
                      smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
     if (q.sub == 0) {
-        float* dst = part + ((size_t)r * a.A + an) * a.C + q.c0;
+        float* dst = part + u * (u32)a.C + q.c0;
 #pragma unroll
         for (int i = 0; i < CPL; ++i) dst[i] = acc[i];
     }
@@ -186,30 +136,15 @@ __global__ void __launch_bounds__(256) fwd_rows_reduce(const float* part, float*
 }
 
 // Batched forward: persistent workgroups stride over the anchors of all
-// scenes; each restages its scene's geometry before the anchor.
+// scenes.
 template <class FT, int CPL>
-__global__ void __launch_bounds__(512) msda_fwd_batched_kernel(BatchArgs b) {
+__global__ void __launch_bounds__(512) msda_fwd_batched_kernel(BatchArgs b, int chunk) {
     extern __shared__ __align__(16) unsigned char smem[];
-    Geo* geo = reinterpret_cast<Geo*>(smem);
-    unsigned char* work = smem + (size_t)b.max_regions_per_scene * sizeof(Geo);
     for (u32 item = blockIdx.x; item < b.total_anchors; item += gridDim.x) {
         const int s = scene_of(b.t.anchor_start, b.S, item);
         const OpArgs a = scene_view(b, s, FT::kBytes);
-        __syncthreads();                    // the previous anchor is done with geo and work
-        stage_geometry(geo, a);
-        __syncthreads();
-        fwd_anchor<FT, CPL>(a, (int)(item - b.t.anchor_start[s]), geo, work);
+        fwd_anchor<FT, CPL>(a, (int)(item - b.t.anchor_start[s]), chunk, smem);
     }
-}
-
-// The scene of a view-order row index: the last s with start[s] <= u.
-__device__ __forceinline__ int scene_of_row(const u64* start, int S, u64 u) {
-    int lo = 0, hi = S - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (start[mid] <= u) lo = mid; else hi = mid - 1;
-    }
-    return uniform(lo);
 }
 
 // Batched forward in view order: the units of all scenes, scene by scene,
@@ -224,16 +159,13 @@ __global__ void __launch_bounds__(512) msda_fwd_batched_view_kernel(BatchArgs b,
     if (u >= b.total_rows) return;
     const int s = scene_of_row(b.t.row_start, b.S, u);
     const OpArgs a = scene_view(b, s, FT::kBytes);
-    const u64 v = u - b.t.row_start[s];
-    const int j = uniform((int)uniform_div(v, (u32)a.A));
-    const int an = uniform((int)(v - (u64)(u32)j * (u32)a.A));
-    const int rows = fwd_rows(a.N);
-    const int n_lo = (int)((u64)a.N * (u32)j / (u32)rows);
-    const int n_hi = (int)((u64)a.N * (u32)(j + 1) / (u32)rows);
+    const RowUnit t = row_unit(u - b.t.row_start[s], a.A);
+    const CamRange n = row_cams(a.N, (int)t.row, fwd_rows(a.N));
     const Lanes q = lanes_of<FT, CPL>(a);
     const rsrc_t feat = make_rsrc(a.feat, a.batch_bytes);
+    const int NS = a.P * a.L;
     float acc[CPL];
-    row_sum<FT, CPL>(a, (size_t)an, feat, n_lo, n_hi, q, chunk,
+    row_sum<FT, CPL>(a, (size_t)t.a, feat, n.lo * NS, n.hi * NS, q, chunk,
                      smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
     if (q.sub == 0) {
         float* dst = part + u * (u32)b.C + q.c0;
@@ -276,12 +208,6 @@ __global__ void __launch_bounds__(256) fwd_batched_view_reduce(BatchArgs b, cons
     }
 }
 
-// Blocks of `waves` waves over T units in kSlots ranges.
-static unsigned slot_blocks(u64 T, int waves) {
-    const u64 per_slot = (T + kSlots - 1) / kSlots;
-    return (unsigned)(kSlots * ((per_slot + (u64)waves - 1) / (u64)waves));
-}
-
 template <class FT, int CPL>
 static hipError_t fwd_batched_view_launch(const BatchArgs& b, int waves, float* part,
                                           hipStream_t s) {
@@ -307,20 +233,21 @@ static hipError_t fwd_batched_view_launch(const BatchArgs& b, int waves, float* 
 }
 
 template <class FT, int CPL>
-static hipError_t fwd_batched_launch(const BatchArgs& b, int waves, int blocks, size_t lds,
-                                     hipStream_t s) {
+static hipError_t fwd_batched_launch(const BatchArgs& b, int waves, int blocks, hipStream_t s) {
+    const int chunk = fwd_chunk_samples(waves, b.G);
     mark_begin("msda_fwd_batched_kernel", s);
-    hipLaunchKernelGGL((msda_fwd_batched_kernel<FT, CPL>), dim3(blocks), dim3(64 * waves), lds, s,
-                       b);
+    hipLaunchKernelGGL((msda_fwd_batched_kernel<FT, CPL>), dim3(blocks), dim3(64 * waves),
+                       anchor_lds_bytes(waves, chunk, b.C, b.G), s, b, chunk);
     mark_end(s);
     return hipGetLastError();
 }
 
 template <class FT, int CPL>
-static hipError_t fwd_launch(const OpArgs& a, int waves, size_t lds, hipStream_t s) {
+static hipError_t fwd_launch(const OpArgs& a, int waves, hipStream_t s) {
+    const int chunk = fwd_chunk_samples(waves, a.G);
     mark_begin("msda_fwd_kernel", s);
     hipLaunchKernelGGL((msda_fwd_kernel<FT, CPL>), dim3((unsigned)(a.B * a.A)),
-                       dim3(64 * waves), lds, s, a);
+                       dim3(64 * waves), anchor_lds_bytes(waves, chunk, a.C, a.G), s, a, chunk);
     mark_end(s);
     return hipGetLastError();
 }
@@ -373,8 +300,8 @@ static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, flo
     }
 
 hipError_t launch_forward_batched(const BatchArgs& b, int dtype, int cpl, int waves, int blocks,
-                                  size_t lds, hipStream_t s) {
-    MSDA_FOR_EACH_LAYOUT(fwd_batched_launch, b, waves, blocks, lds, s)
+                                  hipStream_t s) {
+    MSDA_FOR_EACH_LAYOUT(fwd_batched_launch, b, waves, blocks, s)
 }
 
 hipError_t launch_forward_batched_view(const BatchArgs& b, int dtype, int cpl, int waves,
@@ -382,9 +309,8 @@ hipError_t launch_forward_batched_view(const BatchArgs& b, int dtype, int cpl, i
     MSDA_FOR_EACH_LAYOUT(fwd_batched_view_launch, b, waves, part, s)
 }
 
-hipError_t launch_forward(const OpArgs& a, int dtype, int cpl, int waves, size_t lds,
-                          hipStream_t s) {
-    MSDA_FOR_EACH_LAYOUT(fwd_launch, a, waves, lds, s)
+hipError_t launch_forward(const OpArgs& a, int dtype, int cpl, int waves, hipStream_t s) {
+    MSDA_FOR_EACH_LAYOUT(fwd_launch, a, waves, s)
 }
 
 hipError_t launch_forward_view(const OpArgs& a, int dtype, int cpl, int waves, int part_rows,

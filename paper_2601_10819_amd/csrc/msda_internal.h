@@ -44,13 +44,10 @@ struct OpArgs {
     int64_t R;
     uint32_t batch_bytes;         // R * C * sizeof(feat element) (<= kOOB, under 4 GiB)
     int32_t lps_shift;            // log2(lanes per sample) = log2(C / chans_per_lane)
-    int32_t pairs_per_chunk;      // (keypoint, camera) pairs staged per wave step
     // Bucketed records (dense single call): 0, or A*P -- the record of
     // sample (b, a, p, n, l) then goes to bucket (b, n, l) at a*P + p, its
     // key the local cell of region (n, l) (see launch_bucket_sort).
     uint32_t rec_bucket_ap;
-    // Backward view order: cameras of one anchor per wave (>= 1).
-    int32_t view_cams;
 };
 
 // The tiled grad_feat reduction over records sorted by bilinear cell.
@@ -97,7 +94,7 @@ struct BatchTables {
     uint32_t* anchor_start;       // [S+1] first anchor (over all scenes) of each scene
     uint32_t* sample_start;       // [S+1] first sample / record of each scene
     uint32_t* region_start;       // [S+1] first region of each scene
-    uint64_t* row_start;          // [S+1] first view-order forward row of each scene
+    uint64_t* row_start;          // [S+1] first view-order unit of each scene
     uint32_t* cell_start;         // [regions] first cell of each region (global)
     uint32_t* slot_scene;         // [regions] scene of each slot
     uint32_t* slot_region;        // [regions] region (within its scene) of each slot
@@ -112,14 +109,11 @@ struct BatchArgs {
     const float* level_scale;
     BatchTables t;
     uint32_t total_anchors;
-    uint64_t total_rows;          // view-order forward rows: sum of fwd_rows(Ncam) * A
+    uint64_t total_rows;          // view-order units: sum of fwd_rows (bwd_rows) * A
     uint32_t total_samples;
     uint32_t total_cells;
     uint32_t total_regions;
     int32_t lps_shift;            // log2(C / chans_per_lane)
-    int32_t pairs_per_chunk;
-    int32_t max_regions_per_scene;   // LDS sizing of the geometry table
-    int32_t view_cams;            // view order: cameras of a row at most (geometry slice)
     uint32_t* rec_key;            // backward, grad_feat records (or nullptr)
     float2* rec_frac;
     int32_t rec_bucketed;         // records written per (scene, region) bucket (launch_bucket_sort_batched)
@@ -151,63 +145,21 @@ struct ProjArgs {
 
 // ---------------------------------------------------------------- view order
 //
-// In view order the work of a call -- every (view, anchor) item, a view
-// being one (batch item, camera), P*L samples each -- is cut, view-major,
-// into kSlots contiguous ranges of equal size. Slot x runs on the workgroups
-// whose index is x modulo kSlots: the hardware hands workgroups to the
-// chip's kSlots XCDs round-robin, so slot x stays on one XCD and its L2
-// holds the pyramids of the few cameras the slot is working through instead
-// of every camera's. A wave takes one "row" of its slot: one anchor of a
-// batch item the slot touches, over the anchor's views inside the slot
-// (possibly none at the slot's edges).
+// In view order the work of a call is cut, camera-major, into kSlots
+// contiguous ranges of equal size. Range x runs on the workgroups whose index
+// is x modulo kSlots: the hardware hands workgroups to the chip's kSlots XCDs
+// round-robin, so a range stays on one XCD and its L2 holds the pyramids of
+// the few cameras the range is working through instead of every camera's. A
+// unit of work, one wave's, is one anchor over a row of cameras.
 constexpr int kSlots = 8;
 
-struct SlotSpan {
-    int64_t lo, hi;               // items [lo, hi), item = (b*N + n)*A + a
-    int32_t b_first, b_last;      // batch items touched (b_last < b_first: none)
-};
-
-__host__ __device__ inline SlotSpan slot_span(int x, int B, int N, int A) {
-    const int64_t T = (int64_t)B * N * A;
-    SlotSpan s;
-    s.lo = T * x / kSlots;
-    s.hi = T * (x + 1) / kSlots;
-    if (s.hi <= s.lo) {
-        s.b_first = 1;
-        s.b_last = 0;
-    } else {
-        s.b_first = (int32_t)(s.lo / A / N);
-        s.b_last = (int32_t)((s.hi - 1) / A / N);
-    }
-    return s;
+// Workgroups of `waves` waves for T units, a multiple of kSlots.
+inline unsigned slot_blocks(uint64_t T, int waves) {
+    const uint64_t per_slot = (T + kSlots - 1) / kSlots;
+    return (unsigned)(kSlots * ((per_slot + (uint64_t)waves - 1) / (uint64_t)waves));
 }
 
-// Rows of slot x: (batch items touched) * A.
-__host__ __device__ inline int64_t slot_rows(const SlotSpan& s, int A) {
-    return s.b_last < s.b_first ? 0 : (int64_t)(s.b_last - s.b_first + 1) * A;
-}
-
-struct ViewRow {
-    int32_t b, a;                 // batch item and anchor
-    int32_t n_lo, nv;             // cameras [n_lo, n_lo + nv) of this row (nv may be 0)
-};
-
-// Row r (< slot_rows) of slot span s.
-__host__ __device__ inline ViewRow view_row(const SlotSpan& s, int64_t r, int N, int A) {
-    ViewRow v;
-    v.b = s.b_first + (int32_t)(r / A);
-    v.a = (int32_t)(r % A);
-    // items of anchor a lie at views v with v*A + a in [lo, hi)
-    int64_t v0 = (s.lo - v.a + A - 1) / A, v1 = (s.hi - v.a + A - 1) / A;
-    const int64_t first = (int64_t)v.b * N, last = first + N;
-    if (v0 < first) v0 = first;
-    if (v1 > last) v1 = last;
-    v.n_lo = (int32_t)(v0 - first);
-    v.nv = v1 > v0 ? (int32_t)(v1 - v0) : 0;
-    return v;
-}
-
-// The view-order forward's work: partial row j of a batch item with N cameras
+// The forward: partial row j of a batch item with N cameras
 // covers cameras [N*j/rows, N*(j+1)/rows), and one wave sums one anchor over
 // one row. Rows are as short as the workspace's 8 rows per batch item allow
 // to grow: one camera for a multiple of 8 up to 64 cameras (a wave per camera
@@ -220,7 +172,16 @@ __host__ __device__ inline int fwd_rows(int N) {
     return N < kMinFwdRows ? N : N >= kMaxFwdRows ? kMaxFwdRows : N / 8 * 8;
 }
 
-// Samples a wave stages at a time: 64 while `waves` waves' staging fits 64
+// The backward, whose rows need no combining: one camera per row, or as many
+// as hold kMinRowPairs pairs where anchors have few keypoints.
+constexpr int kMinRowPairs = 7;
+
+__host__ __device__ inline int bwd_rows(int N, int P) {
+    const int cams = P >= kMinRowPairs ? 1 : (kMinRowPairs + P - 1) / P;
+    return (N + cams - 1) / cams;
+}
+
+// Samples a wave of the forward stages at a time: 64 while `waves` waves' staging fits 64
 // KiB, else the largest power of two that does. At least 64 / lanes per
 // sample, since G is at most the lanes per sample.
 inline int fwd_chunk_samples(int waves, int G) {
@@ -230,18 +191,15 @@ inline int fwd_chunk_samples(int waves, int G) {
 }
 
 // Launchers return hipSuccess or the launch error. They enqueue only.
-hipError_t launch_forward(const OpArgs& a, int dtype, int cpl, int waves, size_t lds_bytes,
-                          hipStream_t s);
-hipError_t launch_backward(const OpArgs& a, int dtype, int cpl, int waves, size_t lds_bytes,
-                           hipStream_t s);
-// View order: `waves` waves per workgroup, each its own row. The forward
+hipError_t launch_forward(const OpArgs& a, int dtype, int cpl, int waves, hipStream_t s);
+hipError_t launch_backward(const OpArgs& a, int dtype, int cpl, int waves, hipStream_t s);
+// View order: `waves` waves per workgroup, each its own unit. The forward
 // writes partial rows to part and adds them into out in row order, part_rows
 // (>= min(fwd_rows(N), kMinFwdRows)) rows [B][part_rows][A][C] FP32 at a
 // time; the sums do not depend on part_rows.
 hipError_t launch_forward_view(const OpArgs& a, int dtype, int cpl, int waves, int part_rows,
                                float* part, hipStream_t s);
-hipError_t launch_backward_view(const OpArgs& a, int dtype, int cpl, int waves, size_t lds_bytes,
-                                hipStream_t s);
+hipError_t launch_backward_view(const OpArgs& a, int dtype, int cpl, int waves, hipStream_t s);
 hipError_t launch_gfeat_tiles(const TileArgs& t, int out_dtype, int cpl, hipStream_t s);
 // cell_start[N*L], tile_start[N*L + 1] and tile_region[N*L] from the shapes.
 hipError_t launch_region_tables(const int32_t* shapes, int32_t N, int32_t L, uint32_t* cell_start,
@@ -303,12 +261,12 @@ hipError_t launch_visible_items(const uint8_t* visible, int B, int N, int A, uin
                                 uint32_t* place, uint32_t* items, uint32_t* rec_count,
                                 uint32_t* scan_partial, hipStream_t s);
 // vt (or nullptr): the fused form's per-view weights [B][A][N].
-hipError_t launch_forward_visible(const OpArgs& a, int dtype, int cpl, int waves, size_t lds,
+hipError_t launch_forward_visible(const OpArgs& a, int dtype, int cpl, int waves,
                                   const uint32_t* items, const uint32_t* count,
                                   const uint32_t* place, const uint8_t* visible, const float* vt,
                                   float* part, hipStream_t s);
 // item_dot (or nullptr): per item, <grad_out, the anchor's feature in the view>.
-hipError_t launch_backward_visible(const OpArgs& a, int dtype, int cpl, int waves, size_t lds,
+hipError_t launch_backward_visible(const OpArgs& a, int dtype, int cpl, int waves,
                                    const uint32_t* items, const uint32_t* place,
                                    const uint32_t* count, uint32_t* rec_val, const float* vt,
                                    float* item_dot, hipStream_t s);
@@ -336,19 +294,16 @@ int sort_passes(uint32_t max_key);
 
 hipError_t launch_batch_tables(const BatchArgs& b, bool backward, hipStream_t s);
 hipError_t launch_forward_batched(const BatchArgs& b, int dtype, int cpl, int waves, int blocks,
-                                  size_t lds_bytes, hipStream_t s);
+                                  hipStream_t s);
 hipError_t launch_backward_batched(const BatchArgs& b, int dtype, int cpl, int waves, int blocks,
-                                   size_t lds_bytes, hipStream_t s);
-// Batched gathers in view order: one wave per (XCD slot, global anchor)
-// row; grid kSlots * ceil(total_anchors / waves); LDS waves *
-// batch_view_wave_bytes. The forward takes one wave per partial row of every
-// scene (total_rows anchor rows, fwd_rows(Ncam) per anchor), written to part
-// ([total_rows][C] FP32, scenes in order) and added into each scene's out.
-size_t batch_view_lds(int view_cams, int L, int J, int G, int waves);
+                                   hipStream_t s);
+// Batched gathers in view order: one wave per unit of every scene, scenes in
+// order. The forward's partial rows go to part ([total_rows][C] FP32) and are
+// added into each scene's out.
 hipError_t launch_forward_batched_view(const BatchArgs& b, int dtype, int cpl, int waves,
                                        float* part, hipStream_t s);
 hipError_t launch_backward_batched_view(const BatchArgs& b, int dtype, int cpl, int waves,
-                                        size_t lds, hipStream_t s);
+                                        hipStream_t s);
 hipError_t launch_gfeat_tiles_batched(const BatchArgs& b, int out_dtype, int cpl, hipStream_t s);
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
@@ -361,12 +316,8 @@ hipError_t launch_quantize_fp8(const float* x, const int32_t* shapes, const int3
                                uint32_t* amax_ws, hipStream_t s);
 hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 
-// LDS bytes of a forward/backward launch: geometry table + per-wave staging
-// (or the cross-wave reduction area, whichever is larger).
-size_t lds_bytes_for(const OpArgs& a, int waves);
-// The same for a view-order launch (staging only).
-size_t lds_bytes_view(const OpArgs& a, int waves);
-int max_pairs_per_chunk(int L, int G);
+// The most LDS a gather's workgroup of `waves` waves takes.
+size_t gather_lds_bytes(int waves, int C, int G);
 
 // Benchmark instrumentation (msda_set_kernel_events): called around every
 // kernel launch; records the caller's events when enabled, else does nothing.

@@ -1,10 +1,10 @@
-// The view-order forward's unit of work: one anchor over a short run of
-// cameras, by one wave. Shared by the single call and the batched form.
+// The forwards' unit of work: a run of one anchor's samples, by one wave.
+// Shared by every work order.
 //
 // What bounds it: the corner rows' path through the vector cache. At the
 // 64-camera scene in BF16 a kernel that only loads the same rows takes 0.28
 // ms of this one's 0.32 (21 TB/s; rows that stay in one XCD's 4 MB L2 come at
-// 29 TB/s). So the units run camera by camera -- an XCD's waves work on one
+// 29 TB/s). So in view order the units run camera by camera -- an XCD's waves work on one
 // camera's pyramid at a time -- and the work around the loads is kept off the
 // waves' critical path: 16 corner loads in flight per wave, the corner
 // weights multiplied out once per sample and group while staging, no
@@ -25,11 +25,6 @@ __host__ __device__ constexpr size_t row_lds_bytes(int chunk, int G) {
 
 // Rounds of samples whose corner loads are issued together.
 constexpr int kRowRounds = 4;
-
-// i / d for i * d < 2^32 (m = 0xffffffff / d + 1).
-__device__ __forceinline__ int div_by(int i, int d, u32 m) {
-    return d == 1 ? i : (int)__umulhi((u32)i, m);
-}
 
 // U rounds of staged samples from round t (64 / lanes-per-sample samples
 // each): the corner loads of all U, then their multiply-adds.
@@ -60,39 +55,47 @@ __device__ __forceinline__ void row_rounds(const Lanes& q, rsrc_t feat, int t, i
     }
 }
 
-// The sum of anchor `ba`'s samples in cameras [n_lo, n_hi) over the lane's
-// channels, the same in every sub-wave. The samples (camera-major, then
-// keypoint, then level) go through LDS `chunk` at a time (a power of two from
+// Sums the per-sample partials of a wave's sub-waves (samples that share
+// channels): a butterfly over the sub-wave index.
+template <int CPL>
+__device__ __forceinline__ void reduce_subwaves(const Lanes& q, float* acc) {
+    for (int s = q.lps; s < 64; s <<= 1) {
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) acc[i] = xor_sum(acc[i], s);
+    }
+}
+
+// The sum of samples [s_lo, s_hi) of anchor `ba` over the lane's channels, the
+// same in every sub-wave. The anchor's samples are numbered camera-major,
+// then keypoint, then level; they go through LDS `chunk` at a time (a power of two from
 // the sub-waves' count to 64; it does not change the sum's order), one per
 // lane: corner offsets, and per group the corner weights times the sample's
 // weight (and the FP8 level scale). Geometry is read from memory: a camera's
 // few words stay in the caches, and nothing is staged block-wide.
 template <class FT, int CPL>
-__device__ __forceinline__ void row_sum(const OpArgs& a, size_t ba, rsrc_t feat, int n_lo,
-                                        int n_hi, const Lanes& q, int chunk, unsigned char* lds,
+__device__ __forceinline__ void row_sum(const OpArgs& a, size_t ba, rsrc_t feat, int s_lo,
+                                        int s_hi, const Lanes& q, int chunk, unsigned char* lds,
                                         float* acc) {
     const int L = a.L, G = a.G, P = a.P, LG = L * G, npairs = P * a.N;
     const float* gl = a.loc + ba * npairs * 2;
     const WSrc gw = anchor_weights(a, ba, (size_t)npairs * LG);
     const u32 row_bytes = (u32)a.C * FT::kBytes;
-    const int NS = P * L, total = (n_hi - n_lo) * NS;
-    // quotients by multiplication while they are exact, else by division
-    const bool small = (int64_t)total * NS < (int64_t)1 << 32;
-    const u32 mL = 0xffffffffu / (u32)L + 1u, mNS = 0xffffffffu / (u32)NS + 1u;
+    const int NS = P * L;
+    const u32 mL = div_magic(L, NS), mNS = div_magic(NS, s_hi);
     u32x4* const s_off = reinterpret_cast<u32x4*>(lds);
     float4* const s_w = reinterpret_cast<float4*>(s_off + chunk);
 #pragma unroll
     for (int i = 0; i < CPL; ++i) acc[i] = 0.f;
-    for (int i0 = 0; i0 < total; i0 += chunk) {
-        const int i = i0 + q.lane, ns = min(chunk, total - i0);
+    for (int i0 = s_lo; i0 < s_hi; i0 += chunk) {
+        const int i = i0 + q.lane, ns = min(chunk, s_hi - i0);
         // lanes past the last sample stage zeros that read no memory
         const bool live = q.lane < ns;
         u32x4 off = {kOOB, kOOB, kOOB, kOOB};
         float4 cw = make_float4(0.f, 0.f, 0.f, 0.f);
         size_t wb = 0;
         if (live) {
-            const int v = small ? div_by(i, NS, mNS) : i / NS, k = i - v * NS;
-            const int p = small ? div_by(k, L, mL) : k / L, l = k - p * L, n = n_lo + v;
+            const int n = div_by(i, NS, mNS), k = i - n * NS;
+            const int p = div_by(k, L, mL), l = k - p * L;
             const size_t src = (size_t)p * a.N + n;
             const int r = n * L + l;
             Geo gm = {};

@@ -22,7 +22,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "msda_gather.h"
+#include "msda_grads.h"
+#include "msda_rows.h"
 
 namespace msda {
 
@@ -193,38 +194,17 @@ __device__ __forceinline__ void for_each_visible_item(const OpArgs& a, const u32
 
 template <class FT, int CPL>
 __global__ void __launch_bounds__(512) msda_fwd_visible_kernel(OpArgs a, const u32* items,
-                                                               const u32* count, float* part) {
+                                                               const u32* count, int chunk,
+                                                               float* part) {
     extern __shared__ __align__(16) unsigned char smem[];
-    Geo* geo = reinterpret_cast<Geo*>(smem);
-    unsigned char* work = smem + (size_t)a.N * a.L * sizeof(Geo);
-    stage_geometry(geo, a);
-    __syncthreads();                       // the only block-wide barrier
-
-    const int LG = a.L * a.G;
-    const int J = a.pairs_per_chunk;
     const Lanes q = lanes_of<FT, CPL>(a);
-    const StageSlot st = stage_slot(work, wave_index(), J, a.L, a.G);
-    const u32 row_bytes = (u32)a.C * FT::kBytes;
-    const int npairs = a.P * a.N;
-    const RecordSink none{};
+    unsigned char* lds = smem + (size_t)wave_index() * row_lds_bytes(chunk, a.G);
+    const int NS = a.P * a.L;
     for_each_visible_item(a, items, count, [&](u32 i, int b, int an, int n) {
-        const int ba = b * a.A + an;
-        const float* gl = a.loc + (size_t)ba * npairs * 2;
-        const WSrc gw = anchor_weights(a, (size_t)ba, (size_t)npairs * LG);
         const rsrc_t feat = make_rsrc(static_cast<const char*>(a.feat) + (size_t)b * a.batch_bytes,
                                       a.batch_bytes);
-        const ViewOrder order{a.N, a.P, n};
         float acc[CPL];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-        for (int k0 = 0; k0 < a.P; k0 += J) {
-            const int nj = min(J, a.P - k0);
-            stage_chunk<FT::kBytes == 1, false>(st, order, k0, nj, gw, gl, geo, a.L, LG,
-                                                row_bytes, q.lane, none);
-            fwd_chunk<FT, CPL>(st, nj, a.L, a.G, q, feat, acc);
-            end_chunk();
-        }
-        reduce_subwaves<CPL>(q, acc);
+        row_sum<FT, CPL>(a, (size_t)b * a.A + an, feat, n * NS, (n + 1) * NS, q, chunk, lds, acc);
         if (q.sub == 0) {
             float* dst = part + (size_t)i * a.C + q.c0;
 #pragma unroll
@@ -299,41 +279,28 @@ __global__ void __launch_bounds__(512) msda_bwd_visible_kernel(OpArgs a, const u
                                                                u32* rec_val, const float* vt,
                                                                float* item_dot) {
     extern __shared__ __align__(16) unsigned char smem[];
-    Geo* geo = reinterpret_cast<Geo*>(smem);
-    unsigned char* work = smem + (size_t)a.N * a.L * sizeof(Geo);
-    stage_geometry(geo, a);
-    __syncthreads();                       // the only block-wide barrier
-
-    const int J = a.pairs_per_chunk;
     const Lanes q = lanes_of<FT, CPL>(a);
-    const StageSlot st = stage_slot(work, wave_index(), J, a.L, a.G);
+    unsigned char* lds = smem + (size_t)wave_index() * grads_lds_bytes(a.G);
+    const u32 mP = div_magic(a.P, a.P);
     for_each_visible_item(a, items, count, [&](u32 i, int b, int an, int n) {
-        float go[CPL];
-        BwdAnchor x = bwd_anchor_ctx<FT, CPL>(a, b * a.A + an, q, go);
+        GradAnchor x = grad_anchor<FT>(a, b, an);
         if (a.rec_bucket_ap) {
             // records per (b, n, l) bucket (launch_bucket_sort's visible-view
             // layout): the cnt visible anchors of (b, n) from item s0 on,
-            // level-major; stage_chunk adds (n*L + l)*bucket_ap + p, so the
-            // base drops n*L*bucket_ap (modulo 2^32)
+            // level-major; stage_grads adds (n*L + l)*ap + p, so the base
+            // drops n*L*ap (modulo 2^32)
             const u32 bn = (u32)(b * a.N + n), P = (u32)a.P, L = (u32)a.L;
             const u32 s0 = place[(size_t)bn * a.A];
-            x.rec.bucket_ap = (place[(size_t)(bn + 1) * a.A] - s0) * P;
-            x.rec.bucket_base = s0 * P * L + (i - s0) * P - (u32)n * L * x.rec.bucket_ap;
-            x.rec.val = nullptr;
+            x.rec.ap = (place[(size_t)(bn + 1) * a.A] - s0) * P;
+            x.rec.bucket_base = s0 * P * L + (i - s0) * P - (u32)n * L * x.rec.ap;
         } else {
             x.rec.val = rec_val;
             x.rec.cbase = i * (u32)(a.P * a.L);
         }
-        const ViewOrder order{a.N, a.P, n};
         const float scale = vt ? vt[((size_t)b * a.A + an) * a.N + n] : 1.f;
         float dot = 0.f;
-        for (int k0 = 0; k0 < a.P; k0 += J) {
-            const int nj = min(J, a.P - k0);
-            stage_chunk<false, true>(st, order, k0, nj, x.gw, x.gl, geo, a.L, a.L * a.G,
-                                     (u32)a.C * FT::kBytes, q.lane, x.rec);
-            bwd_chunk<FT, CPL>(a, st, nj, geo, q, x, go, scale, item_dot ? &dot : nullptr);
-            end_chunk();
-        }
+        grads_of<FT, CPL>(a, x, ViewOrder{a.P, n, mP}, 0, a.P, q, lds, scale,
+                          item_dot ? &dot : nullptr);
         if (item_dot) {
             dot = group_sum(dot, 64);
             if (q.lane == 0) item_dot[i] = dot;
@@ -349,12 +316,14 @@ static unsigned visible_blocks(int waves) {
 }
 
 template <class FT, int CPL>
-static hipError_t fwd_visible_launch(const OpArgs& a, int waves, size_t lds, const u32* items,
+static hipError_t fwd_visible_launch(const OpArgs& a, int waves, const u32* items,
                                      const u32* count, const u32* place, const uint8_t* visible,
                                      const float* vt, float* part, hipStream_t s) {
+    const int chunk = fwd_chunk_samples(waves, a.G);
     mark_begin("msda_fwd_visible_kernel", s);
     hipLaunchKernelGGL((msda_fwd_visible_kernel<FT, CPL>), dim3(visible_blocks(waves)),
-                       dim3(64 * waves), lds, s, a, items, count, part);
+                       dim3(64 * waves), (size_t)waves * row_lds_bytes(chunk, a.G), s, a, items,
+                       count, chunk, part);
     mark_end(s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -367,12 +336,13 @@ static hipError_t fwd_visible_launch(const OpArgs& a, int waves, size_t lds, con
 }
 
 template <class FT, int CPL>
-static hipError_t bwd_visible_launch(const OpArgs& a, int waves, size_t lds, const u32* items,
+static hipError_t bwd_visible_launch(const OpArgs& a, int waves, const u32* items,
                                      const u32* place, const u32* count, u32* rec_val,
                                      const float* vt, float* item_dot, hipStream_t s) {
     mark_begin("msda_bwd_visible_kernel", s);
     hipLaunchKernelGGL((msda_bwd_visible_kernel<FT, CPL>), dim3(visible_blocks(waves)),
-                       dim3(64 * waves), lds, s, a, items, place, count, rec_val, vt, item_dot);
+                       dim3(64 * waves), (size_t)waves * grads_lds_bytes(a.G), s, a, items, place,
+                       count, rec_val, vt, item_dot);
     mark_end(s);
     return hipGetLastError();
 }
@@ -395,14 +365,14 @@ hipError_t launch_visible_items(const uint8_t* visible, int B, int N, int A, u32
     return hipGetLastError();
 }
 
-hipError_t launch_forward_visible(const OpArgs& a, int dtype, int cpl, int waves, size_t lds,
+hipError_t launch_forward_visible(const OpArgs& a, int dtype, int cpl, int waves,
                                   const u32* items, const u32* count, const u32* place,
                                   const uint8_t* visible, const float* vt, float* part,
                                   hipStream_t s) {
     switch (dtype * 100 + cpl) {
 #define MSDA_CASE(D, T, K) \
         case D * 100 + K: \
-            return fwd_visible_launch<T, K>(a, waves, lds, items, count, place, visible, vt, \
+            return fwd_visible_launch<T, K>(a, waves, items, count, place, visible, vt, \
                                             part, s);
         MSDA_CASE(kF32, TF32, 1) MSDA_CASE(kF32, TF32, 2) MSDA_CASE(kF32, TF32, 4)
         MSDA_CASE(kBF16, TBF16, 2) MSDA_CASE(kBF16, TBF16, 4) MSDA_CASE(kBF16, TBF16, 8)
@@ -413,13 +383,13 @@ hipError_t launch_forward_visible(const OpArgs& a, int dtype, int cpl, int waves
     }
 }
 
-hipError_t launch_backward_visible(const OpArgs& a, int dtype, int cpl, int waves, size_t lds,
+hipError_t launch_backward_visible(const OpArgs& a, int dtype, int cpl, int waves,
                                    const u32* items, const u32* place, const u32* count,
                                    u32* rec_val, const float* vt, float* item_dot, hipStream_t s) {
     switch (dtype * 100 + cpl) {
 #define MSDA_CASE(D, T, K) \
         case D * 100 + K: \
-            return bwd_visible_launch<T, K>(a, waves, lds, items, place, count, rec_val, vt, \
+            return bwd_visible_launch<T, K>(a, waves, items, place, count, rec_val, vt, \
                                             item_dot, s);
         MSDA_CASE(kF32, TF32, 1) MSDA_CASE(kF32, TF32, 2) MSDA_CASE(kF32, TF32, 4)
         MSDA_CASE(kBF16, TBF16, 2) MSDA_CASE(kBF16, TBF16, 4) MSDA_CASE(kBF16, TBF16, 8)
