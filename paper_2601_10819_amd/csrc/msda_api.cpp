@@ -1222,6 +1222,9 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
             return fail(MSDA_ERR_UNSUPPORTED, "scene %d: feat must be 16-byte aligned", s);
         p->anchors += (uint64_t)sc.num_anchors;
         p->fwd_rows += (uint64_t)sc.num_anchors * (uint64_t)msda::fwd_rows(sc.num_cams);
+        // sized as for the single call: at least kMinFwdRows rows an anchor
+        p->part_bytes += (uint64_t)sc.num_anchors *
+                         (uint64_t)std::max(msda::fwd_rows(sc.num_cams), msda::kMinFwdRows);
         p->bwd_rows += (uint64_t)sc.num_anchors *
                        (uint64_t)msda::bwd_rows(sc.num_cams, b->num_points);
         p->samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams * b->num_levels;
@@ -1291,7 +1294,7 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
     while (!tw && p->view_waves > 1 &&
            msda::gather_lds_bytes(p->view_waves, b->channels, b->groups) > 65536)
         p->view_waves /= 2;
-    p->part_bytes = p->fwd_rows * (uint64_t)b->channels * sizeof(float);
+    p->part_bytes *= (uint64_t)b->channels * sizeof(float);
     return MSDA_OK;
 }
 
