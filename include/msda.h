@@ -166,11 +166,15 @@ msda_status msda_forward(const void* feat, const int32_t* spatial_shapes,
  * msda_forward (the same operator, Sec. 3.1/3.2) with a workspace, which lets
  * the library use view order
  * (MSDA_ORDER_VIEW) for the forward: the library's choice for inputs with at
- * least 8 (batch item, camera) views. Same results contract as
- * msda_forward; the two orders add the samples in different orders, each
+ * least 8 (batch item, camera) views, and for 3 to 7 views of more than 32 MB
+ * of feature maps (all batch items), 24,576 (keypoint, camera) pairs or more
+ * and partial rows within MSDA_NOALLOC_SCRATCH_BYTES. Same results contract
+ * as msda_forward; the two orders add the samples in different orders, each
  * fixed (deterministic).
  * workspace: device, 256-byte aligned, msda_forward_workspace_size(desc)
- * bytes, or fewer as said there (may be NULL when that is 0).
+ * bytes, or fewer as said there (may be NULL when that is 0). With fewer than
+ * 8 views, unless view order is asked for, the anchor order's workspace (none,
+ * or the softmax statistics) is enough too, and then that order is taken.
  * Returns MSDA_ERR_WORKSPACE if it is missing or too small.
  */
 msda_status msda_forward_ws(const void* feat, const int32_t* spatial_shapes,

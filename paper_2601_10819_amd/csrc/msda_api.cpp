@@ -139,14 +139,80 @@ msda_status check_regions(const msda_desc* d, int64_t* batch_bytes_out) {
     return MSDA_OK;
 }
 
+size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// Fused weight generation: the softmax statistics (forward and backward)
+// and the FP32 weights the backward works on.
+// The statistics [B*A][G] float2, then the per-chunk partials they are
+// merged from (reused for the backward's per-chunk group sums).
+size_t stats_only_bytes(const msda_desc* d) {
+    return align256((size_t)d->batch * (size_t)(d->num_anchors > 0 ? d->num_anchors : 0) *
+                    (size_t)d->groups * sizeof(float2));
+}
+
+size_t stats_bytes(const msda_desc* d) {
+    if (!(d->flags & MSDA_WEIGHT_LOGITS)) return 0;
+    const int BA = d->batch * (d->num_anchors > 0 ? d->num_anchors : 0);
+    return stats_only_bytes(d) +
+           align256(msda::softmax_scratch_bytes(
+               BA, d->num_points * d->num_cams * d->num_levels, d->groups));
+}
+
+// The partial rows of a view-order forward: `rows` per (batch item, anchor).
+size_t part_bytes(const msda_desc* d, int rows) {
+    return align256((size_t)rows * (size_t)d->batch * (size_t)d->num_anchors *
+                    (size_t)d->channels * sizeof(float));
+}
+
+// Fewer views than XCDs, and still view order: the feature maps are larger
+// than the chip's L2s together (8 x 4 MB). In anchor order every L2 then
+// sees all of the maps go by; in view order an XCD has one camera's. Six
+// cameras of 256 x 704, 900 anchors, 256 channels: FP32 (92 MB) forward 102
+// -> 67 us and backward gather 104 -> 73 us, BF16 (46 MB) 50 -> 38 and 51 ->
+// 40; two cameras of 256 x 448 (FP32, 20 MB) 26 -> 24 and 27 -> 29, BF16 16
+// -> 18: below the line the L2s hold the maps in either order. And there is
+// enough to cut: with 200 anchors (15,600 pairs) FP32 stays at 27 us and BF16
+// goes from 17 to 19, with 400 49 -> 38 and 27 -> 24; one camera has nothing
+// to gain (512 x 1408, 4000 anchors: 70 -> 72 and 33 -> 37). The last
+// condition keeps the partial rows within what msda_forward_noalloc holds, so
+// that it and msda_forward_ws keep one order for one desc.
+bool few_views_in_view_order(const msda_desc* d) {
+    constexpr int64_t kMinViews = 3, kMinViewBytes = 32 << 20;
+    constexpr double kMinViewPairs = 24576;
+    if (d->batch < 1 || d->num_cams < 1 || d->channels < 1 || d->num_anchors < 0 ||
+        (int64_t)d->batch * d->num_cams < kMinViews)
+        return false;
+    const int eb = d->feat_dtype == MSDA_F32 ? 4 : d->feat_dtype == MSDA_FP8_E4M3 ? 1 : 2;
+    const double pairs = (double)d->batch * d->num_anchors * d->num_cams * d->num_points;
+    return d->rows > kMinViewBytes / ((int64_t)d->batch * d->channels * eb) &&
+           pairs >= kMinViewPairs &&
+           part_bytes(d, msda::kMinFwdRows) + stats_bytes(d) <= MSDA_NOALLOC_SCRATCH_BYTES;
+}
+
 // The gathers' work order: explicit, else view order once there are at
-// least kSlots (batch item, camera) views to spread over the XCDs. A
-// forward without a workspace always runs in anchor order.
+// least kSlots (batch item, camera) views to spread over the XCDs, or fewer
+// of large maps. A forward without a workspace always runs in anchor order.
 int resolve_order(const msda_desc* d, bool can_view) {
     const int o = d->tile ? d->tile->order : MSDA_ORDER_AUTO;
     if (o != MSDA_ORDER_AUTO) return o;
     const int64_t views = (int64_t)d->batch * d->num_cams;
-    return can_view && views >= msda::kSlots ? MSDA_ORDER_VIEW : MSDA_ORDER_ANCHOR;
+    return can_view && (views >= msda::kSlots || few_views_in_view_order(d)) ? MSDA_ORDER_VIEW
+                                                                              : MSDA_ORDER_ANCHOR;
+}
+
+// msda_forward_ws: with fewer views than XCDs the view order is the library's
+// own choice and a caller may pass the workspace of the anchor order (none,
+// or the statistics' share) instead.
+int resolve_forward_order(const msda_desc* d, const void* ws, size_t ws_bytes) {
+    const int order = resolve_order(d, true);
+    const bool chosen = !d->tile || d->tile->order == MSDA_ORDER_AUTO;
+    if (order != MSDA_ORDER_VIEW || !chosen ||
+        (int64_t)d->batch * d->num_cams >= msda::kSlots)
+        return order;
+    return ws && (uintptr_t)ws % 256 == 0 &&
+                   ws_bytes >= part_bytes(d, msda::kMinFwdRows) + stats_bytes(d)
+               ? order
+               : MSDA_ORDER_ANCHOR;
 }
 
 // LDS one workgroup may use on the current device (160 KB on gfx950), the
@@ -238,25 +304,6 @@ msda_status hip_fail(hipError_t e, const char* what) {
 }
 
 bool aligned(const void* p, size_t n) { return ((uintptr_t)p % n) == 0; }
-
-size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
-
-// Fused weight generation: the softmax statistics (forward and backward)
-// and the FP32 weights the backward works on.
-// The statistics [B*A][G] float2, then the per-chunk partials they are
-// merged from (reused for the backward's per-chunk group sums).
-size_t stats_only_bytes(const msda_desc* d) {
-    return align256((size_t)d->batch * (size_t)(d->num_anchors > 0 ? d->num_anchors : 0) *
-                    (size_t)d->groups * sizeof(float2));
-}
-
-size_t stats_bytes(const msda_desc* d) {
-    if (!(d->flags & MSDA_WEIGHT_LOGITS)) return 0;
-    const int BA = d->batch * (d->num_anchors > 0 ? d->num_anchors : 0);
-    return stats_only_bytes(d) +
-           align256(msda::softmax_scratch_bytes(
-               BA, d->num_points * d->num_cams * d->num_levels, d->groups));
-}
 
 // Workspace of the sorted grad_feat form: record keys (x2 for the sort),
 // values (x2), fractions, per-cell offsets, region tables and the sort's
@@ -418,7 +465,8 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
                                 size_t workspace_bytes, bool has_ws, const msda_desc* desc,
                                 void* stream) {
     if (!desc) return fail(MSDA_ERR_INVALID_ARGUMENT, "desc is NULL");
-    const int order = resolve_order(desc, has_ws);
+    const int order = has_ws ? resolve_forward_order(desc, workspace, workspace_bytes)
+                             : resolve_order(desc, false);
     if (order == MSDA_ORDER_VIEW && !has_ws)
         return fail(MSDA_ERR_WORKSPACE, "the view-order forward needs a workspace "
                                         "(msda_forward_ws)");
@@ -434,16 +482,15 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
     // the partial rows: as many as the workspace has room for, from the
     // minimum up to all of them (the sums are the same; fewer rows take more
     // launches), then the softmax statistics
-    const size_t row_bytes = (size_t)a.B * a.A * a.C * sizeof(float);
     const size_t stats = stats_bytes(desc);
     int part_rows = 0;
     if (order == MSDA_ORDER_VIEW) {
         part_rows = std::max(msda::fwd_rows(a.N), msda::kMinFwdRows);
         while (part_rows > msda::kMinFwdRows &&
-               align256(part_rows * row_bytes) + stats > workspace_bytes)
+               part_bytes(desc, part_rows) + stats > workspace_bytes)
             --part_rows;
     }
-    const size_t stats_off = align256(part_rows * row_bytes);
+    const size_t stats_off = part_bytes(desc, part_rows);
     const size_t need = stats_off + stats;
     if (need && !has_ws)
         return fail(MSDA_ERR_WORKSPACE, "weight logits need a workspace (msda_forward_ws)");
@@ -498,11 +545,8 @@ msda_status msda_forward_ws(const void* feat, const int32_t* spatial_shapes,
 // item in view order.
 static size_t forward_bytes(const msda_desc* d, int part_rows) {
     if (!d || d->batch < 1 || d->num_cams < 1 || d->channels < 1 || d->num_anchors < 0) return 0;
-    const size_t part = resolve_order(d, true) == MSDA_ORDER_VIEW
-                            ? (size_t)part_rows * (size_t)d->batch * (size_t)d->num_anchors *
-                                  (size_t)d->channels * sizeof(float)
-                            : 0;
-    return align256(part) + stats_bytes(d);
+    const bool view = resolve_order(d, true) == MSDA_ORDER_VIEW;
+    return part_bytes(d, view ? part_rows : 0) + stats_bytes(d);
 }
 
 size_t msda_forward_workspace_size(const msda_desc* d) {
