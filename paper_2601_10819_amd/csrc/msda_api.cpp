@@ -141,21 +141,11 @@ msda_status check_regions(const msda_desc* d, int64_t* batch_bytes_out) {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Fused weight generation: the softmax statistics (forward and backward)
-// and the FP32 weights the backward works on.
-// The statistics [B*A][G] float2, then the per-chunk partials they are
-// merged from (reused for the backward's per-chunk group sums).
-size_t stats_only_bytes(const msda_desc* d) {
-    return align256((size_t)d->batch * (size_t)(d->num_anchors > 0 ? d->num_anchors : 0) *
-                    (size_t)d->groups * sizeof(float2));
-}
-
+// Fused weight generation, forward: the softmax statistics [B*A][G] float2.
 size_t stats_bytes(const msda_desc* d) {
     if (!(d->flags & MSDA_WEIGHT_LOGITS)) return 0;
-    const int BA = d->batch * (d->num_anchors > 0 ? d->num_anchors : 0);
-    return stats_only_bytes(d) +
-           align256(msda::softmax_scratch_bytes(
-               BA, d->num_points * d->num_cams * d->num_levels, d->groups));
+    return align256((size_t)d->batch * (size_t)(d->num_anchors > 0 ? d->num_anchors : 0) *
+                    (size_t)d->groups * sizeof(float2));
 }
 
 // The partial rows of a view-order forward: `rows` per (batch item, anchor).
@@ -503,10 +493,8 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
     if (desc->flags & MSDA_WEIGHT_LOGITS) {
         char* base = static_cast<char*>(workspace) + stats_off;
         float2* stats = reinterpret_cast<float2*>(base);
-        float2* part = reinterpret_cast<float2*>(base + stats_only_bytes(desc));
-        const hipError_t e = msda::launch_softmax_stats(weights, wbf16, a.B * a.A,
-                                                        a.P * a.N * a.L, a.G, part, stats,
-                                                        (hipStream_t)stream);
+        const hipError_t e = msda::launch_softmax(weights, wbf16, a.B * a.A, a.P * a.N * a.L,
+                                                  a.G, stats, nullptr, (hipStream_t)stream);
         if (e != hipSuccess) return hip_fail(e, "softmax statistics");
         a.wstats = stats;
     }
@@ -635,7 +623,7 @@ static size_t weights_f32_bytes(const msda_desc* d) {
 
 size_t msda_backward_workspace_size(const msda_desc* d) {
     if (!d || d->batch < 1 || d->rows < 1 || d->channels < 1 || d->num_anchors < 0) return 0;
-    return align256(base_backward_bytes(d)) + stats_bytes(d) + weights_f32_bytes(d);
+    return align256(base_backward_bytes(d)) + weights_f32_bytes(d);
 }
 
 // The backward, dense (visible == nullptr) or over the visible views only.
@@ -707,10 +695,10 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     }
     const size_t sorted_need = grad_feat ? base_backward_bytes(desc) : 0;
     const VisibleWs VW = visible_layout(desc, align256(sorted_need));
-    // weight flags: softmax statistics and FP32 weights after the rest
+    // weight flags: the FP32 weights after the rest
     const size_t base_need = visible && a.A > 0 ? VW.total : sorted_need;
     const size_t wx_off = align256(base_need);
-    const size_t wx_bytes = a.A > 0 ? stats_bytes(desc) + weights_f32_bytes(desc) : 0;
+    const size_t wx_bytes = a.A > 0 ? weights_f32_bytes(desc) : 0;
     const size_t need = wx_bytes ? wx_off + wx_bytes : base_need;
     if (need) {
         if (!workspace || workspace_bytes < need)
@@ -733,25 +721,20 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     const bool logits = (desc->flags & MSDA_WEIGHT_LOGITS) && a.A > 0;
     const float* weff = weights;
     float* w32 = nullptr;
-    float2* part = nullptr;
     if (wx_bytes) {
-        float2* stats = logits ? reinterpret_cast<float2*>(ws + wx_off) : nullptr;
-        part = reinterpret_cast<float2*>(ws + wx_off + stats_only_bytes(desc));
-        w32 = reinterpret_cast<float*>(ws + wx_off + stats_bytes(desc));
-        const bool wbf16 = desc->flags & MSDA_WEIGHTS_BF16;
-        const int PNL = a.P * a.N * a.L;
-        if ((logits && (e = msda::launch_softmax_stats(weights, wbf16, a.B * a.A, PNL, a.G, part,
-                                                       stats, s)) != hipSuccess) ||
-            (e = msda::launch_weights_f32(weights, wbf16, stats, a.B * a.A, PNL, a.G, w32, s)) !=
-                hipSuccess)
+        w32 = reinterpret_cast<float*>(ws + wx_off);
+        const int BA = a.B * a.A, PNL = a.P * a.N * a.L;
+        e = logits ? msda::launch_softmax(weights, desc->flags & MSDA_WEIGHTS_BF16, BA, PNL, a.G,
+                                          nullptr, w32, s)
+                   : msda::launch_weights_f32(weights, BA, PNL, a.G, w32, s);
+        if (e != hipSuccess)
             return hip_fail(e, "weights from logits");
         weff = w32;
     }
     auto finish = [&]() -> msda_status {
         if (logits && grad_weights) {
             const hipError_t ee = msda::launch_softmax_grad(w32, grad_weights, a.B * a.A,
-                                                            a.P * a.N * a.L, a.G,
-                                                            reinterpret_cast<float*>(part), s);
+                                                            a.P * a.N * a.L, a.G, s);
             if (ee != hipSuccess) return hip_fail(ee, "gradient through the softmax");
         }
         return ok();
@@ -966,7 +949,7 @@ size_t msda_backward_fused_workspace_size(const msda_desc* d) {
 size_t msda_backward_visible_workspace_size(const msda_desc* d) {
     if (!d || d->batch < 1 || d->rows < 1 || d->channels < 1 || d->num_anchors < 0) return 0;
     const size_t base = visible_layout(d, align256(base_backward_bytes(d))).total;
-    const size_t extra = stats_bytes(d) + weights_f32_bytes(d);
+    const size_t extra = weights_f32_bytes(d);
     return extra ? align256(base) + extra : base;
 }
 
@@ -1029,9 +1012,8 @@ static msda_status forward_visible_impl(const void* feat, const int32_t* spatial
     a.w_bf16 = wbf16;
     if (desc->flags & MSDA_WEIGHT_LOGITS) {
         float2* stats = reinterpret_cast<float2*>(ws + stats_off);
-        float2* spart = reinterpret_cast<float2*>(ws + stats_off + stats_only_bytes(desc));
-        const hipError_t es = msda::launch_softmax_stats(weights, wbf16, a.B * a.A,
-                                                         a.P * a.N * a.L, a.G, spart, stats, s);
+        const hipError_t es = msda::launch_softmax(weights, wbf16, a.B * a.A, a.P * a.N * a.L,
+                                                   a.G, stats, nullptr, s);
         if (es != hipSuccess) return hip_fail(es, "softmax statistics");
         a.wstats = stats;
     }
@@ -1163,14 +1145,13 @@ namespace {
 struct BatchWs {
     size_t anchor_start, sample_start, region_start, row_start, cell_start, slot_scene,
         slot_region, tile_start, magic, magic_shift, keys_a, keys_b, vals_a, vals_b, frac, off, scratch, part,
-        wstats, wscratch, w32, total;
+        wstats, w32, total;
 };
 
-// Weight-flag buffers of a batch: softmax statistics per anchor of every
-// scene, one softmax scratch (the per-scene launches run in stream order and
-// share it), and for the backward the FP32 weights of every sample.
+// Weight-flag buffers of a batch: forward, softmax statistics per anchor of
+// every scene; backward, the FP32 weights of every sample.
 struct BatchWeights {
-    uint64_t stats_bytes, scratch_bytes, w32_bytes;
+    uint64_t stats_bytes, w32_bytes;
 };
 
 // part_bytes: the view-order forward's per-slot partial sums (always part of
@@ -1201,7 +1182,6 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
     }
     if (part_bytes) w.part = take(part_bytes);
     if (wb.stats_bytes) w.wstats = take(wb.stats_bytes);
-    if (wb.scratch_bytes) w.wscratch = take(wb.scratch_bytes);
     if (wb.w32_bytes) w.w32 = take(wb.w32_bytes);
     w.total = at;
     return w;
@@ -1373,32 +1353,21 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, bool backward, cha
 // The weight-flag buffers of a batch (all zero without a weight flag).
 BatchWeights batch_weights(const msda_batch* b, const BatchPlan& p, bool backward) {
     BatchWeights w{};
-    if (b->flags & MSDA_WEIGHT_LOGITS) {
+    if (!backward && (b->flags & MSDA_WEIGHT_LOGITS))
         w.stats_bytes = p.anchors * (uint64_t)b->groups * sizeof(float2);
-        for (int sc = 0; sc < b->num_scenes; ++sc) {
-            const msda_scene& h = b->host_scenes[sc];
-            if (h.num_anchors > 0)
-                w.scratch_bytes = std::max<uint64_t>(
-                    w.scratch_bytes,
-                    msda::softmax_scratch_bytes(h.num_anchors,
-                                                b->num_points * h.num_cams * b->num_levels,
-                                                b->groups));
-        }
-    }
     if (backward && (b->flags & kWeightFlags)) w.w32_bytes = p.samples * (uint64_t)b->groups * 4;
     return w;
 }
 
-// Under a weight flag, per scene with anchors (in stream order): the softmax
-// statistics of its logits, and for the backward its FP32 weights (softmax
+// Under a weight flag, per scene with anchors (in stream order): forward, the
+// softmax statistics of its logits; backward, its FP32 weights (softmax
 // weights, or BF16 weights widened) at its samples' place, which the
 // batched kernels then read in place of the scene's weights.
 msda_status batch_weight_prep(const msda_batch* b, char* ws, const BatchWs& w, bool backward,
                               msda::BatchArgs* a, hipStream_t s) {
     const bool logits = b->flags & MSDA_WEIGHT_LOGITS, wbf16 = b->flags & MSDA_WEIGHTS_BF16;
     if (!logits && !wbf16) return MSDA_OK;
-    float2* stats = logits ? reinterpret_cast<float2*>(ws + w.wstats) : nullptr;
-    float2* part = logits ? reinterpret_cast<float2*>(ws + w.wscratch) : nullptr;
+    float2* stats = logits && !backward ? reinterpret_cast<float2*>(ws + w.wstats) : nullptr;
     float* w32 = backward ? reinterpret_cast<float*>(ws + w.w32) : nullptr;
     const int G = b->groups;
     uint64_t a0 = 0, s0 = 0;
@@ -1406,14 +1375,14 @@ msda_status batch_weight_prep(const msda_batch* b, char* ws, const BatchWs& w, b
         const msda_scene& h = b->host_scenes[sc];
         const int A = h.num_anchors, PNL = b->num_points * h.num_cams * b->num_levels;
         if (A > 0) {
-            float2* st = logits ? stats + a0 * G : nullptr;
             hipError_t e = hipSuccess;
-            if (logits && (e = msda::launch_softmax_stats(h.weights, wbf16, A, PNL, G, part, st,
-                                                          s)) != hipSuccess)
-                return hip_fail(e, "batched softmax statistics");
-            if (w32 && (e = msda::launch_weights_f32(h.weights, wbf16, st, A, PNL, G,
-                                                     w32 + s0 * G, s)) != hipSuccess)
-                return hip_fail(e, "batched FP32 weights");
+            if (logits)
+                e = msda::launch_softmax(h.weights, wbf16, A, PNL, G,
+                                         stats ? stats + a0 * G : nullptr,
+                                         w32 ? w32 + s0 * G : nullptr, s);
+            else if (w32)
+                e = msda::launch_weights_f32(h.weights, A, PNL, G, w32 + s0 * G, s);
+            if (e != hipSuccess) return hip_fail(e, "batched weights");
         }
         a0 += (uint64_t)(A > 0 ? A : 0);
         s0 += (uint64_t)(A > 0 ? A : 0) * (uint64_t)PNL;
@@ -1432,15 +1401,14 @@ msda_status batch_weight_prep(const msda_batch* b, char* ws, const BatchWs& w, b
 msda_status batch_softmax_grad(const msda_batch* b, char* ws, const BatchWs& w, hipStream_t s) {
     if (!(b->flags & MSDA_WEIGHT_LOGITS)) return MSDA_OK;
     const float* w32 = reinterpret_cast<const float*>(ws + w.w32);
-    float* part = reinterpret_cast<float*>(ws + w.wscratch);
     const int G = b->groups;
     uint64_t s0 = 0;
     for (int sc = 0; sc < b->num_scenes; ++sc) {
         const msda_scene& h = b->host_scenes[sc];
         const int A = h.num_anchors, PNL = b->num_points * h.num_cams * b->num_levels;
         if (A > 0 && h.grad_weights) {
-            const hipError_t e = msda::launch_softmax_grad(w32 + s0 * G, h.grad_weights, A, PNL, G,
-                                                           part, s);
+            const hipError_t e =
+                msda::launch_softmax_grad(w32 + s0 * G, h.grad_weights, A, PNL, G, s);
             if (e != hipSuccess) return hip_fail(e, "batched gradient through the softmax");
         }
         s0 += (uint64_t)(A > 0 ? A : 0) * (uint64_t)PNL;

@@ -272,18 +272,15 @@ hipError_t launch_backward_visible(const OpArgs& a, int dtype, int cpl, int wave
                                    float* item_dot, hipStream_t s);
 // Fused weight generation (per-group softmax of logits, BF16 weights).
 // stats[(b*A + a)*G + g] = (max, 1 / sum of exp(logit - max)) over the
-// anchor's P*N*L logits of group g; logits FP32 or bfloat16 bit patterns.
-// part: scratch of softmax_scratch_bytes (per-chunk partials).
-size_t softmax_scratch_bytes(int BA, int PNL, int G);
-hipError_t launch_softmax_stats(const void* logits, bool bf16, int BA, int PNL, int G,
-                                float2* part, float2* stats, hipStream_t s);
-// w[i] = softmax weight (stats given) or the widened weight (stats nullptr),
-// FP32, for all BA*PNL*G entries.
-hipError_t launch_weights_f32(const void* src, bool bf16, const float2* stats, int BA, int PNL,
-                              int G, float* w, hipStream_t s);
+// anchor's P*N*L logits of group g, and the softmax weights of all BA*PNL*G
+// entries, FP32; either may be nullptr. Logits FP32 or bfloat16 bit patterns.
+hipError_t launch_softmax(const void* logits, bool bf16, int BA, int PNL, int G, float2* stats,
+                          float* weights, hipStream_t s);
+// w[i] = the bfloat16 weight src[i], widened, for all BA*PNL*G entries.
+hipError_t launch_weights_f32(const void* src, int BA, int PNL, int G, float* w, hipStream_t s);
 // In place: grad[i] = w[i] * (grad[i] - sum over the anchor's group of w * grad),
-// the gradient through the per-group softmax; part: softmax_scratch_bytes.
-hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int G, float* part,
+// the gradient through the per-group softmax.
+hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int G,
                                hipStream_t s);
 hipError_t launch_view_scale(const uint8_t* visible, const float* score, int BA, int N,
                              float* vt, hipStream_t s);

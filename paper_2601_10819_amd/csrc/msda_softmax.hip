@@ -2,21 +2,33 @@
 // logits into MSDA's weights (over the P*N*L (keypoint, camera, level)
 // entries of each (batch item, anchor, group)), and its gradient.
 //
-// The forward never writes the weights: softmax_stats_kernel reduces each
-// group's logits to (max, 1/sum of exp) and the gathers apply
-// exp(logit - max) / sum while they stage the weights. The backward writes
-// the FP32 weights once (weights_f32_kernel), runs the plain backward on
-// them, and softmax_grad_kernel maps grad_weights to the logits' gradient
-// in place: d logit = w * (d w - sum over the group of w * d w).
+// The forward never writes the weights: softmax_kernel reduces each group's
+// logits to (max, 1/sum of exp) and the gathers apply exp(logit - max) / sum
+// while they stage the weights. The backward has the same kernel write the
+// FP32 weights once, runs the plain backward on them, and
+// softmax_grad_kernel maps grad_weights to the logits' gradient in place:
+// d logit = w * (d w - sum over the group of w * d w).
 //
-// Blocks of 256 threads over chunks of 4096 entries of one anchor. G is a
-// power of two <= 64, so entry e of an anchor (groups fastest) belongs to
-// group e % G and thread t sees only group t % G; partials are combined with
-// the other threads of that group, then over the chunks, in a fixed order
-// (bitwise reproducible).
+// Each pass is bound by its bytes and by how many of them are in flight, so
+// one workgroup takes an anchor's n = P*N*L*G entries (groups fastest) from
+// the first read to the last write: nothing but the result goes to memory,
+// no launch merges partials, and a second look at the entries finds them in
+// registers (the last kRound per thread) or near. A thread's kRound loads of
+// a round are unconditional -- past the end, the last entry, whose value is
+// then replaced -- so that all are in flight together; behind a branch each,
+// the compiler waits for one before it issues the next. 900 anchors of 64
+// cameras, 13 keypoints, 4 levels and 8 groups (96 MB of FP32 logits):
+// statistics 41 -> 26 us (3.7 TB/s), weights for the backward 77 -> 51 (3.8
+// TB/s), the gradient 77 -> 79 in one launch instead of three.
+//
+// G is a power of two <= 64, so entry e of an anchor belongs to group e % G
+// and thread t sees only group t % G; the threads of a group are combined in
+// a fixed order (bitwise reproducible).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "msda_common.h"
 
@@ -24,11 +36,36 @@ namespace msda {
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kRound = 16;            // entries per thread and round
+constexpr int kFlatThreads = 256;
+constexpr size_t kFlatChunk = (size_t)kRound * kFlatThreads;
 
-__device__ __forceinline__ float load_weight(const void* p, bool bf16, size_t i) {
-    return bf16 ? __uint_as_float((uint32_t) static_cast<const uint16_t*>(p)[i] << 16)
-                : static_cast<const float*>(p)[i];
+__device__ __forceinline__ float widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
+__device__ __forceinline__ float widen(float v) { return v; }
+
+// Entries t, t + THREADS, ... (kRound of them) of p[0, left), left > 0; the
+// last entry instead of those past the end.
+template <int THREADS, class T>
+__device__ __forceinline__ void load_round(const T* p, size_t left, float* x) {
+    const uint32_t t = threadIdx.x;
+    T raw[kRound];
+    if (left >= (size_t)kRound * THREADS) {
+#pragma unroll
+        for (int k = 0; k < kRound; ++k) raw[k] = p[t + (uint32_t)(k * THREADS)];
+    } else {
+        const uint32_t end = (uint32_t)left - 1;
+#pragma unroll
+        for (int k = 0; k < kRound; ++k) raw[k] = p[min(t + (uint32_t)(k * THREADS), end)];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < kRound; ++k) x[k] = widen(raw[k]);
+}
+
+// Whether entry t + k * THREADS of a round is one of the `left` that are left.
+template <int THREADS>
+__device__ __forceinline__ bool in_round(int k, size_t left) {
+    return left >= (size_t)kRound * THREADS || threadIdx.x + (uint32_t)(k * THREADS) < (uint32_t)left;
 }
 
 // (max, sum of exp(x - max)) of two disjoint sets.
@@ -39,205 +76,179 @@ __device__ __forceinline__ float2 merge(float2 a, float2 b) {
     return make_float2(m, a.y * expf(a.x - m) + b.y * expf(b.x - m));
 }
 
-// Combines the values of the threads that share a group (t % G): within the
-// wave by xor steps over the lane bits above log2(G), then the 4 waves in
-// order through LDS. Returns the group's total in threads t < G.
-template <class T, class F>
-__device__ __forceinline__ T group_total(T v, int G, T* lds, F combine) {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    for (int m = G; m < 64; m <<= 1) {
-        T o;
-        if constexpr (sizeof(T) == 8) {
-            o.x = __shfl_xor(v.x, m, 64);
-            o.y = __shfl_xor(v.y, m, 64);
-        } else {
-            o = __shfl_xor(v, m, 64);
-        }
-        // the lower lane keeps its own value first: both lanes then agree
-        v = (lane & m) ? combine(o, v) : combine(v, o);
-    }
+// The combined value of the threads that share a group (t % G), in each of
+// them: within the wave by xor steps over the lane bits above log2(G), then
+// the waves in order through LDS.
+template <int THREADS, class F>
+__device__ __forceinline__ float group_total(float v, int G, float* lds, F combine) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = t & (G - 1);
+    for (int m = G; m < 64; m <<= 1) v = combine(v, __shfl_xor(v, m, 64));
     if (lane < G) lds[wave * 64 + lane] = v;
     __syncthreads();
-    T r = v;
-    if (t < G) {
-        r = lds[t];
-        for (int w = 1; w < kThreads / 64; ++w) r = combine(r, lds[w * 64 + t]);
-    }
+    v = lds[g];
+    for (int w = 1; w < THREADS / 64; ++w) v = combine(v, lds[w * 64 + g]);
     __syncthreads();
-    return r;
+    return v;
 }
 
-// Work split: each anchor's n = P*N*L*G entries are cut into chunks of
-// kChunk; block (chunk, anchor) handles one chunk, each thread kChunk/256
-// entries of its group (independent loads, all in flight together).
-constexpr int kChunk = 4096;
-
-__host__ __device__ __forceinline__ int chunks_of(size_t n) { return (int)((n + kChunk - 1) / kChunk); }
-
-// Per (anchor, chunk, group): (max, sum of exp(x - max)) of the chunk's logits.
-__global__ void __launch_bounds__(kThreads) softmax_partial_kernel(const void* logits, int bf16,
-                                                                   int PNL, int G,
-                                                                   float2* part) {
-    __shared__ float2 lds[kThreads];
-    const size_t ba = blockIdx.y;
-    const size_t n = (size_t)PNL * G;
-    const int nch = chunks_of(n);
-    const size_t e0 = (size_t)blockIdx.x * kChunk + threadIdx.x;
-    float x[kChunk / kThreads];
-#pragma unroll
-    for (int k = 0; k < kChunk / kThreads; ++k) {
-        const size_t e = e0 + (size_t)k * kThreads;
-        x[k] = e < n ? load_weight(logits, bf16 != 0, ba * n + e) : -INFINITY;
-    }
-    float m = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < kChunk / kThreads; ++k) m = fmaxf(m, x[k]);
-    float sum = 0.f;
-    if (m != -INFINITY) {
-#pragma unroll
-        for (int k = 0; k < kChunk / kThreads; ++k) sum += expf(x[k] - m);   // exp(-inf) = 0
-    }
-    const float2 tot = group_total(make_float2(m, sum), G, lds, merge);
-    if ((int)threadIdx.x < G) part[(ba * nch + blockIdx.x) * G + threadIdx.x] = tot;
-}
-
-// stats[anchor][g] = (max, 1/sum) from the chunks' partials, in chunk order.
-__global__ void __launch_bounds__(kThreads) softmax_merge_kernel(const float2* part, int BA,
-                                                                 int nch, int G,
-                                                                 float2* stats) {
-    const size_t t = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (t >= (size_t)BA * G) return;
-    const size_t ba = t / G, g = t % G;
+// One anchor per block: the groups' (max, 1/sum of exp) to `stats` and the
+// weights to `weights`, either of which may be nullptr.
+template <class T, int THREADS>
+__global__ void __launch_bounds__(THREADS) softmax_kernel(const T* logits, size_t n, int G,
+                                                          float2* stats, float* weights) {
+    __shared__ float lds[THREADS];
+    const size_t ba = blockIdx.x, t = threadIdx.x;
+    const T* p = logits + ba * n;
+    constexpr size_t kStep = (size_t)kRound * THREADS;
+    const size_t last = (n - 1) / kStep * kStep;      // the last round's first entry
+    float x[kRound];
     float2 acc = make_float2(-INFINITY, 0.f);
-    for (int c = 0; c < nch; ++c) acc = merge(acc, part[(ba * nch + c) * G + g]);
-    stats[t] = make_float2(acc.x, 1.f / acc.y);
-}
-
-// w = softmax weight (stats given) or the widened weight (stats nullptr).
-__global__ void __launch_bounds__(kThreads) weights_f32_kernel(const void* src, int bf16,
-                                                               const float2* stats, int PNL,
-                                                               int G, float* w) {
-    const size_t ba = blockIdx.y;
-    const size_t n = (size_t)PNL * G;
-    const size_t e0 = (size_t)blockIdx.x * kChunk + threadIdx.x;
-    const float2 st = stats ? stats[ba * G + (threadIdx.x & (G - 1))] : make_float2(0.f, 1.f);
+    for (size_t r = 0;; r += kStep) {
+        load_round<THREADS>(p + r, n - r, x);
+        float m = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < kChunk / kThreads; ++k) {
-        const size_t e = e0 + (size_t)k * kThreads;
-        if (e < n) {
-            float x = load_weight(src, bf16 != 0, ba * n + e);
-            if (stats) x = expf(x - st.x) * st.y;
-            w[ba * n + e] = x;
+        for (int k = 0; k < kRound; ++k) {
+            if (!in_round<THREADS>(k, n - r)) x[k] = -INFINITY;
+            m = fmaxf(m, x[k]);
         }
+        float sum = 0.f;
+        // exp(-inf) = 0; only masked entries: nothing to add, but a NaN stays one
+#pragma unroll
+        for (int k = 0; k < kRound; ++k)
+            sum += m != -INFINITY ? expf(x[k] - m) : (x[k] == x[k] ? 0.f : x[k]);
+        acc = merge(acc, make_float2(m, sum));
+        if (r == last) break;
+    }
+    const float m = group_total<THREADS>(acc.x, G, lds, [](float a, float b) { return fmaxf(a, b); });
+    const float mine = acc.y == 0.f ? 0.f : acc.y * expf(acc.x - m);
+    const float sum = group_total<THREADS>(mine, G, lds, [](float a, float b) { return a + b; });
+    const float inv = 1.f / sum;
+    if (stats && t < (size_t)G) stats[ba * G + t] = make_float2(m, inv);
+    if (!weights) return;
+    float* w = weights + ba * n;
+    for (size_t r = last;; r -= kStep) {              // x holds the last round's logits
+#pragma unroll
+        for (int k = 0; k < kRound; ++k) {
+            const float v = expf(x[k] - m) * inv;
+            if (in_round<THREADS>(k, n - r)) w[r + t + (uint32_t)(k * THREADS)] = v;
+        }
+        if (r == 0) break;
+        load_round<THREADS>(p + r - kStep, kStep, x);
     }
 }
 
-// Per (anchor, chunk, group): sum of w * grad over the chunk.
-__global__ void __launch_bounds__(kThreads) softmax_dot_kernel(const float* w, const float* grad,
-                                                               int PNL, int G, float* part) {
-    __shared__ float lds[kThreads];
-    const size_t ba = blockIdx.y;
-    const size_t n = (size_t)PNL * G;
-    const int nch = chunks_of(n);
-    const size_t e0 = (size_t)blockIdx.x * kChunk + threadIdx.x;
+// BF16 weights widened to FP32, all `n` of them.
+__global__ void __launch_bounds__(kFlatThreads) weights_f32_kernel(const uint16_t* src, size_t n,
+                                                                    float* w) {
+    const size_t e0 = (size_t)blockIdx.x * kFlatChunk + threadIdx.x;
+    float x[kRound];
+    load_round<kFlatThreads>(src + (size_t)blockIdx.x * kFlatChunk,
+                              n - (size_t)blockIdx.x * kFlatChunk, x);
+#pragma unroll
+    for (int k = 0; k < kRound; ++k) {
+        const size_t e = e0 + (size_t)k * kFlatThreads;
+        if (e < n) w[e] = x[k];
+    }
+}
+
+// One anchor per block: grad = w * (grad - D), D the group's sum of w * grad.
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) softmax_grad_kernel(const float* weights, float* grads,
+                                                               size_t n, int G) {
+    __shared__ float lds[THREADS];
+    const size_t ba = blockIdx.x, t = threadIdx.x;
+    const float* w = weights + ba * n;
+    float* grad = grads + ba * n;
+    constexpr size_t kStep = (size_t)kRound * THREADS;
+    const size_t last = (n - 1) / kStep * kStep;
+    float x[kRound], y[kRound];
     float acc = 0.f;
+    for (size_t r = 0;; r += kStep) {
+        load_round<THREADS>(w + r, n - r, x);
+        load_round<THREADS>(grad + r, n - r, y);
 #pragma unroll
-    for (int k = 0; k < kChunk / kThreads; ++k) {
-        const size_t e = e0 + (size_t)k * kThreads;
-        if (e < n) acc = fmaf(w[ba * n + e], grad[ba * n + e], acc);
+        for (int k = 0; k < kRound; ++k)
+            if (in_round<THREADS>(k, n - r)) acc = fmaf(x[k], y[k], acc);
+        if (r == last) break;
     }
-    const float tot = group_total(acc, G, lds, [](float a, float b) { return a + b; });
-    if ((int)threadIdx.x < G) part[(ba * nch + blockIdx.x) * G + threadIdx.x] = tot;
-}
-
-// dot[anchor][g] = the chunk partials' sum, in chunk order.
-__global__ void __launch_bounds__(kThreads) softmax_dot_merge_kernel(const float* part, int BA,
-                                                                     int nch, int G,
-                                                                     float* dot) {
-    const size_t t = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (t >= (size_t)BA * G) return;
-    const size_t ba = t / G, g = t % G;
-    float d = 0.f;
-    for (int c = 0; c < nch; ++c) d += part[(ba * nch + c) * G + g];
-    dot[t] = d;
-}
-
-// grad = w * (grad - D), D the group's sum of w * grad.
-__global__ void __launch_bounds__(kThreads) softmax_apply_kernel(const float* w, float* grad,
-                                                                 const float* dot, int PNL,
-                                                                 int G) {
-    const size_t ba = blockIdx.y;
-    const size_t n = (size_t)PNL * G;
-    const float d = dot[ba * G + (threadIdx.x & (G - 1))];
-    const size_t e0 = (size_t)blockIdx.x * kChunk + threadIdx.x;
+    const float d = group_total<THREADS>(acc, G, lds, [](float a, float b) { return a + b; });
+    for (size_t r = last;; r -= kStep) {              // x, y hold the last round
 #pragma unroll
-    for (int k = 0; k < kChunk / kThreads; ++k) {
-        const size_t e = e0 + (size_t)k * kThreads;
-        if (e < n) grad[ba * n + e] = w[ba * n + e] * (grad[ba * n + e] - d);
+        for (int k = 0; k < kRound; ++k) {
+            if (in_round<THREADS>(k, n - r))
+                grad[r + t + (uint32_t)(k * THREADS)] = x[k] * (y[k] - d);
+        }
+        if (r == 0) break;
+        load_round<THREADS>(w + r - kStep, kStep, x);
+        load_round<THREADS>(grad + r - kStep, kStep, y);
     }
 }
 
-dim3 chunk_grid(int BA, int PNL, int G) {
-    return dim3((unsigned)chunks_of((size_t)PNL * G), (unsigned)BA);
+// Threads per anchor. Small anchors are one round of 256 threads. Otherwise
+// 1024 threads read an anchor in few rounds where there are no more anchors
+// than two per CU, and 512 where there are: 900 anchors of 26,624 entries are
+// then all resident at once (statistics 26 us, with 1024 threads 34; weights
+// 51 and 57). The gradient has two values per entry to read again if they are
+// not one round, and 1024 threads hold more of them (79 us, with 512 85).
+int threads_of(size_t n, int BA, bool gradient) {
+    if (n <= kRound * 256) return 256;
+    return BA <= 512 || (gradient && n > kRound * 512) ? 1024 : 512;
+}
+
+// f(int_c<threads>).
+template <int I>
+using int_c = std::integral_constant<int, I>;
+
+template <class F>
+void with_threads(int threads, F&& f) {
+    if (threads == 256) f(int_c<256>{});
+    else if (threads == 512) f(int_c<512>{});
+    else f(int_c<1024>{});
+}
+
+template <class T>
+void run_softmax(const void* logits, int BA, size_t n, int G, float2* stats, float* w,
+                 hipStream_t s) {
+    with_threads(threads_of(n, BA, false), [&](auto threads) {
+        constexpr int THREADS = decltype(threads)::value;
+        hipLaunchKernelGGL((softmax_kernel<T, THREADS>), dim3((unsigned)BA), dim3(THREADS), 0, s,
+                           static_cast<const T*>(logits), n, G, stats, w);
+    });
 }
 
 }  // namespace
 
-size_t softmax_scratch_bytes(int BA, int PNL, int G) {
-    // per-chunk partials, then (backward) the merged group sums
-    return (size_t)BA * chunks_of((size_t)PNL * G) * G * sizeof(float2) +
-           (size_t)BA * G * sizeof(float);
-}
-
-hipError_t launch_softmax_stats(const void* logits, bool bf16, int BA, int PNL, int G,
-                                float2* part, float2* stats, hipStream_t s) {
+hipError_t launch_softmax(const void* logits, bool bf16, int BA, int PNL, int G, float2* stats,
+                          float* weights, hipStream_t s) {
     if (BA <= 0) return hipSuccess;
-    mark_begin("softmax_partial", s);
-    hipLaunchKernelGGL(softmax_partial_kernel, chunk_grid(BA, PNL, G), dim3(kThreads), 0, s,
-                       logits, (int)bf16, PNL, G, part);
-    mark_end(s);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int nch = chunks_of((size_t)PNL * G);
-    mark_begin("softmax_merge", s);
-    hipLaunchKernelGGL(softmax_merge_kernel, dim3((unsigned)(((size_t)BA * G + kThreads - 1) /
-                                                             kThreads)),
-                       dim3(kThreads), 0, s, part, BA, nch, G, stats);
+    const size_t n = (size_t)PNL * G;
+    mark_begin("softmax", s);
+    if (bf16) run_softmax<uint16_t>(logits, BA, n, G, stats, weights, s);
+    else run_softmax<float>(logits, BA, n, G, stats, weights, s);
     mark_end(s);
     return hipGetLastError();
 }
 
-hipError_t launch_weights_f32(const void* src, bool bf16, const float2* stats, int BA, int PNL,
-                              int G, float* w, hipStream_t s) {
+hipError_t launch_weights_f32(const void* src, int BA, int PNL, int G, float* w, hipStream_t s) {
     if (BA <= 0) return hipSuccess;
+    const size_t n = (size_t)BA * PNL * G;
     mark_begin("weights_f32", s);
-    hipLaunchKernelGGL(weights_f32_kernel, chunk_grid(BA, PNL, G), dim3(kThreads), 0, s, src,
-                       (int)bf16, stats, PNL, G, w);
+    hipLaunchKernelGGL(weights_f32_kernel, dim3((unsigned)((n + kFlatChunk - 1) / kFlatChunk)),
+                       dim3(kFlatThreads), 0, s, static_cast<const uint16_t*>(src), n, w);
     mark_end(s);
     return hipGetLastError();
 }
 
-hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int G, float* part,
+hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int G,
                                hipStream_t s) {
     if (BA <= 0) return hipSuccess;
-    mark_begin("softmax_dot", s);
-    hipLaunchKernelGGL(softmax_dot_kernel, chunk_grid(BA, PNL, G), dim3(kThreads), 0, s, w, grad,
-                       PNL, G, part);
-    mark_end(s);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int nch = chunks_of((size_t)PNL * G);
-    float* dot = part + (size_t)BA * nch * G * 2;      // after the float2-sized partials
-    mark_begin("softmax_dot_merge", s);
-    hipLaunchKernelGGL(softmax_dot_merge_kernel,
-                       dim3((unsigned)(((size_t)BA * G + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, part, BA, nch, G, dot);
-    mark_end(s);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    mark_begin("softmax_apply", s);
-    hipLaunchKernelGGL(softmax_apply_kernel, chunk_grid(BA, PNL, G), dim3(kThreads), 0, s, w,
-                       grad, dot, PNL, G);
+    const size_t n = (size_t)PNL * G;
+    mark_begin("softmax_grad", s);
+    with_threads(threads_of(n, BA, true), [&](auto threads) {
+        constexpr int THREADS = decltype(threads)::value;
+        hipLaunchKernelGGL((softmax_grad_kernel<THREADS>), dim3((unsigned)BA), dim3(THREADS), 0, s,
+                           w, grad, n, G);
+    });
     mark_end(s);
     return hipGetLastError();
 }
