@@ -336,21 +336,36 @@ void cells_and_tiles(const msda_desc* d, uint64_t* cells, uint64_t* tiles) {
 // Tiles (of one batch item, in slot order: coarse levels first) of the levels
 // whose regions are at most 1/16 of the largest region's area -- the levels
 // where a pixel collects 16x or more the samples of the finest one.
-uint32_t heavy_tiles(const msda_desc* d) {
+uint32_t heavy_tiles(const msda_desc* d, uint32_t* regions) {
     const int N = d->num_cams, L = d->num_levels;
     int64_t max_area = 0;
     for (int i = 0; i < N * L; ++i)
         max_area = std::max<int64_t>(max_area, (int64_t)d->host_spatial_shapes[2 * i] *
                                                    d->host_spatial_shapes[2 * i + 1]);
     uint32_t tiles = 0;
+    *regions = 0;
     for (int o = 0; o < N * L; ++o) {            // slot o -> level L-1-o/N, camera o%N
         const int l = L - 1 - o / N, n = o % N, r = n * L + l;
         const int64_t H = d->host_spatial_shapes[2 * r], W = d->host_spatial_shapes[2 * r + 1];
         if (H * W * 16 > max_area) break;
         tiles += (uint32_t)(((H + msda::kTileH - 1) / msda::kTileH) *
                             ((W + msda::kTileW - 1) / msda::kTileW));
+        ++*regions;
     }
     return tiles;
+}
+
+// Waves per block of the tile reduction. 4, so that blocks end and make room
+// in small steps (8: 64 cameras 345 -> 367 us, the 16-camera step 317 -> 344),
+// but 8 where the chip is drained before the coarse tiles, which are as long
+// as their records are many, are done: up to two rounds of the 4096 waves
+// that are resident at once, and coarse tiles of many records (6 cameras FP32
+// 67 -> 52 us, 2 cameras of 128 x 224 29 -> 20; 5 cameras with 331 anchors,
+// 107 samples per coarse tile, 21 -> 24).
+int tile_block_waves(uint64_t heavy, uint64_t tiles, uint64_t heavy_samples) {
+    constexpr uint64_t kMaxWaves = 8192, kMinSamples = 256;
+    const uint64_t waves = 4 * heavy + (tiles - heavy);
+    return heavy && waves <= kMaxWaves && heavy_samples >= kMinSamples * heavy ? 8 : 4;
 }
 
 // 1 if the regions are pairwise disjoint; *cover = they tile [0, R) exactly.
@@ -889,11 +904,14 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     t.lps_shift = log2i(a.C / rcpl);
     divmagic((uint32_t)a.P * (uint32_t)a.N * (uint32_t)a.L, &t.magic, &t.magic_shift);
     // Tiles of coarse levels collect many more samples per pixel: they come
-    // first in slot order and get 4 waves each (partial sums added as a
+    // first in slot order and get a block each (partial sums added as a
     // tree); the rest get one wave each.
+    uint32_t heavy_regions = 0;
     t.tile_begin = 0;
-    t.tile_split = heavy_tiles(desc);
+    t.tile_split = heavy_tiles(desc, &heavy_regions);
     t.tile_end = (uint32_t)tiles;
+    t.block_waves = tile_block_waves((uint64_t)t.tile_split * a.B, tiles * a.B,
+                                     (uint64_t)heavy_regions * a.B * a.A * a.P);
     if ((e = msda::launch_gfeat_tiles(t, desc->feat_dtype, rcpl, s)) != hipSuccess)
         return hip_fail(e, "grad_feat tile reduction");
     return finish();
@@ -1189,7 +1207,7 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
 
 // Sizes of a validated batch.
 struct BatchPlan {
-    uint64_t anchors, samples, regions, cells, tiles, heavy_tiles;
+    uint64_t anchors, samples, regions, cells, tiles, heavy_tiles, heavy_samples;
     uint64_t fwd_rows, bwd_rows;  // view-order units of all scenes
     int max_cams;
     int cpl, waves;
@@ -1271,6 +1289,7 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
             if ((int64_t)d.host_spatial_shapes[2 * l] * d.host_spatial_shapes[2 * l + 1] * 16 >
                 max_area)
                 continue;
+            p->heavy_samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams;
             for (int n = 0; n < sc.num_cams; ++n) {
                 const int r = n * b->num_levels + l;
                 const uint64_t H = d.host_spatial_shapes[2 * r], W = d.host_spatial_shapes[2 * r + 1];
@@ -1601,6 +1620,7 @@ msda_status msda_backward_batched(const msda_batch* b, void* workspace, size_t w
     a.tile_begin = 0;
     a.tile_split = (uint32_t)p.heavy_tiles;
     a.tile_end = (uint32_t)p.tiles;
+    a.block_waves = tile_block_waves(p.heavy_tiles, p.tiles, p.heavy_samples);
     if ((e = msda::launch_gfeat_tiles_batched(a, b->feat_dtype, rcpl, s)) != hipSuccess)
         return hip_fail(e, "batched grad_feat tile reduction");
     return p.anchors > 0 ? batch_softmax_grad(b, ws, w, s) : ok();

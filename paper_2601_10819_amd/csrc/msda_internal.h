@@ -71,8 +71,10 @@ struct TileArgs {
     int32_t N, L;                 // cameras and levels (to find a sample's view)
     uint32_t tiles_per_item;
     // the tiles of each batch item (slot order) to reduce: [tile_begin,
-    // tile_split) coarse (4 waves each), [tile_split, tile_end) light
+    // tile_split) coarse (all waves of a block each), [tile_split, tile_end)
+    // light (one wave each)
     uint32_t tile_begin, tile_split, tile_end;
+    int32_t block_waves;          // waves per block, at most 8
     uint32_t cells_per_item;
     uint32_t nrec;                // S (records, one per sample)
     int32_t NL, B, C, G;
@@ -127,6 +129,7 @@ struct BatchArgs {
     const uint32_t* vals;
     const uint32_t* off;
     uint32_t tile_begin, tile_split, tile_end;  // as TileArgs
+    int32_t block_waves;
 };
 
 enum FeatType { kF32 = 0, kBF16 = 1, kFP8 = 2, kF16 = 3 };

@@ -158,14 +158,6 @@ __device__ __forceinline__ void cell_sample(float (&acc)[4][4][CPL], float4 f, f
 // vector).
 __host__ __device__ inline int tile_entry_floats(int G) { return 8 + ((G + 3) & ~3); }
 
-// Cell boundaries of a tile's TH+1 cell rows, (TW+2) per row.
-constexpr int kBndPerWave = (kTileH + 1) * (kTileW + 2);
-
-// LDS bytes of the boundary slots: one per wave.
-__host__ __device__ inline size_t bnd_lds_bytes(int waves) {
-    return ((size_t)waves * kBndPerWave * 4 + 15) & ~(size_t)15;
-}
-
 // Everything one tile's reduction needs (from the single-call or the
 // batched tables).
 struct TileView {
@@ -191,12 +183,15 @@ struct TileView {
     bool w16;                   // G % 4 == 0 and w 16-byte aligned
 };
 
-// grad_out row of a whole-wave record: the anchor (a table entry every lane
-// reads at the same address) taken as uniform, so the row address is scalar
-// arithmetic and each lane adds only its channel offset.
-__device__ __forceinline__ const float* go_row(const TileView& v, float anchor_bits) {
-    const u32 an = (u32)uniform((int)__float_as_uint(anchor_bits));
-    return v.grad_out + (size_t)an * (u32)v.C;
+// Lane i's value (i uniform) as a uniform one.
+__device__ __forceinline__ u32 lane_value(u32 x, int i) {
+    return (u32)__builtin_amdgcn_readlane((int)x, i);
+}
+
+// grad_out row of a whole-wave record: with a uniform anchor the row address
+// is scalar arithmetic and each lane adds only its channel offset.
+__device__ __forceinline__ const float* go_row(const TileView& v, u32 anchor) {
+    return v.grad_out + (size_t)anchor * (u32)v.C;
 }
 
 // The reduction of one tile by `waves` waves of the block that share its
@@ -212,9 +207,9 @@ __device__ __forceinline__ const float* go_row(const TileView& v, float anchor_b
 // rows are loaded together.
 template <class OT, int CPL, bool WHOLE, int QB>
 __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shift,
-                                            const int waves, const int wt, u32* bnd_lds,
-                                            float* work) {
+                                            const int waves, const int wt, float* work) {
     constexpr int TH = kTileH, TW = kTileW;
+    constexpr bool FIRST = WHOLE && QB == 2;
     // the wave index is uniform: chunk bounds and cell runs below stay scalar
     const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
     const int spw = WHOLE ? 1 : 64 >> lps_shift;            // sub-waves
@@ -229,35 +224,28 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shi
     const int g = c0 / (v.C / v.G);
 
     // The tile's cells are TH+1 rows of TW+1 consecutive cells; each row's
-    // records are one contiguous range of the sorted order. The wave stores
-    // the (TH+1) x (TW+2) cell boundaries of those rows in its LDS slot.
-    constexpr int NB = kBndPerWave;
-    u32* bslot = bnd_lds + (size_t)wave * NB;
-    static_assert(NB <= 64, "one boundary per lane");
-    if (lane < NB) {
-        const int k = lane;
-        const int dy = k / (TW + 2), dx = k % (TW + 2);
-        u32 bv = 0u;
+    // records are one contiguous range of the sorted order. Lane k holds
+    // boundary k of those rows, TW+2 per row.
+    static_assert((TH + 1) * (TW + 2) <= 64, "one boundary per lane");
+    u32 bound = 0u;
+    if (lane < (TH + 1) * (TW + 2)) {
+        const int dy = lane / (TW + 2), dx = lane % (TW + 2);
         if (active && ty + dy <= H) {
             // cells past W+1 clamp to the row's end
             const u32 cell = cbase + (u32)(ty + dy) * (u32)(W + 1) + (u32)min(tx + dx, W + 1);
-            bv = min(v.off[cell], v.nrec);
+            bound = min(v.off[cell], v.nrec);
         }
-        bslot[k] = bv;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    u32 rs[TH + 1], rn[TH + 1];                     // row range start and length
+    // a row's first record and number of records (none past the region: the
+    // boundaries are all 0 there)
+    auto row_start = [&](int dy) { return lane_value(bound, dy * (TW + 2)); };
+    auto row_len = [&](int dy) {
+        const u32 a0 = row_start(dy), a1 = lane_value(bound, dy * (TW + 2) + TW + 1);
+        return a1 > a0 ? a1 - a0 : 0u;
+    };
     u32 total = 0;
 #pragma unroll
-    for (int dy = 0; dy <= TH; ++dy) {
-        const u32 a0 = bslot[dy * (TW + 2)];
-        const u32 a1 = bslot[dy * (TW + 2) + TW + 1];
-        rs[dy] = a0;
-        rn[dy] = active && ty + dy <= H && a1 > a0 ? a1 - a0 : 0u;
-        total += rn[dy];
-    }
+    for (int dy = 0; dy <= TH; ++dy) total += row_len(dy);
 
     float acc[TH][TW][CPL];
 #pragma unroll
@@ -272,17 +260,21 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shi
     // in flight together), then the wave walks the chunk.
     for (u32 base = (u32)(wt * 64); base < total; base += (u32)(waves * 64)) {
         const int n = (int)min(64u, total - base);
+        // the boundaries are read from the lanes again in every chunk: kept
+        // over the loop they take the scalar registers of everything else
+        asm("" : "+v"(bound));
+        u32 an = 0u;                                // lane k: the anchor of the chunk's record k
         if (lane < n) {
             // flat index -> (row dy, sorted position e)
             u32 f = base + (u32)lane;
             int dy = 0;
 #pragma unroll
             for (int k = 0; k < TH; ++k)
-                if (dy == k && f >= rn[k]) { f -= rn[k]; dy = k + 1; }
-            u32 e = rs[0] + f;
+                if (dy == k && f >= row_len(k)) { f -= row_len(k); dy = k + 1; }
+            u32 e = row_start(0) + f;
 #pragma unroll
             for (int k = 1; k <= TH; ++k)
-                if (dy == k) e = rs[k] + f;
+                if (dy == k) e = row_start(k) + f;
             const u32 s = min(v.vals[e], v.nrec - 1u);
             const float2 fr = v.frac[s];
             float* ent = tab + lane * stride;
@@ -290,7 +282,7 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shi
             // sort could only give wrong sums, never a read outside it)
             const u32 ls = s - v.sample_offset < v.sample_count ? s - v.sample_offset : 0u;
             const float* ws = v.w + (size_t)ls * v.G;
-            const u32 an = fast_div(ls, v.magic, v.magic_shift);
+            an = fast_div(ls, v.magic, v.magic_shift);
             if (v.vscale) {
                 // the fused form: the sample's weights times its view's factor
                 const u32 n = (ls / (u32)v.L) % (u32)v.N;
@@ -320,25 +312,46 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shi
         u32 f0 = 0;
         static_for<TH + 1>([&](auto dyc) {
             constexpr int DY = decltype(dyc)::value;
-            const u32 rlen = (u32)uniform((int)rn[DY]);
+            const u32 rlen = row_len(DY);
             if (rlen) {
-                const u32 rstart = (u32)uniform((int)rs[DY]);
+                const u32 rstart = row_start(DY);
+                // a cell's run [lo, hi) of the chunk
+                auto lo = [&](int dx) {
+                    const u32 e = lane_value(bound, DY * (TW + 2) + dx);
+                    return (int)max(f0 + (e - rstart), base) - (int)base;
+                };
+                auto hi = [&](int dx) {
+                    const u32 e = lane_value(bound, DY * (TW + 2) + dx + 1);
+                    return (int)min(f0 + (e - rstart), base + (u32)n) - (int)base;
+                };
+                float first[TW + 1][CPL];
+                if constexpr (FIRST) {
+#pragma unroll
+                    for (int dx = 0; dx <= TW; ++dx)
+                        if (lo(dx) < hi(dx))
+                            load_go<CPL>(go_row(v, lane_value(an, lo(dx))) + (u32)c0, first[dx]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 static_for<TW + 1>([&](auto dxc) {
                     constexpr int DX = decltype(dxc)::value;
-                    const u32 e0 = (u32)uniform((int)bslot[DY * (TW + 2) + DX]);
-                    const u32 e1 = (u32)uniform((int)bslot[DY * (TW + 2) + DX + 1]);
-                    const u32 lo = max(f0 + (e0 - rstart), base);
-                    const u32 hi = min(f0 + (e1 - rstart), base + (u32)n);
-                    int qq = (int)lo - (int)base;
-                    const int qe = (int)hi - (int)base;
+                    int qq = lo(DX);
+                    const int qe = hi(DX);
                     if constexpr (WHOLE) {
+                        if constexpr (FIRST) {
+                            if (qq < qe) {
+                                const float* ent = tab + qq * stride;
+                                cell_sample<DY, DX, CPL>(acc,
+                                                         *reinterpret_cast<const float4*>(ent),
+                                                         ent[8 + g], first[DX]);
+                                ++qq;
+                            }
+                        }
                         for (; qq + QB <= qe; qq += QB) {
                             float gv[QB][CPL];
 #pragma unroll
-                            for (int k = 0; k < QB; ++k) {
-                                const float* ent = tab + (qq + k) * stride;
-                                load_go<CPL>(go_row(v, ent[4]) + (u32)c0, gv[k]);
-                            }
+                            for (int k = 0; k < QB; ++k)
+                                load_go<CPL>(go_row(v, lane_value(an, qq + k)) + (u32)c0, gv[k]);
+                            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                             for (int k = 0; k < QB; ++k) {
                                 const float* ent = tab + (qq + k) * stride;
@@ -349,7 +362,7 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shi
                         for (; qq < qe; ++qq) {
                             const float* ent = tab + qq * stride;
                             float gv[CPL];
-                            load_go<CPL>(go_row(v, ent[4]) + (u32)c0, gv);
+                            load_go<CPL>(go_row(v, lane_value(an, qq)) + (u32)c0, gv);
                             cell_sample<DY, DX, CPL>(acc, *reinterpret_cast<const float4*>(ent),
                                                      ent[8 + g], gv);
                         }
@@ -453,14 +466,12 @@ template <class OT, int CPL, bool WHOLE, int QB>
 __device__ __forceinline__ void gfeat_tile_body(const TileArgs& t, const u32 gt, const int waves,
                                                 const int wt) {
     static_assert(kTileH == 4 && kTileW == 4, "the cell dispatch is written for 4x4 tiles");
-    // LDS: per wave its tile's cell boundaries and a record table (64 entries
+    // LDS: per wave a record table (64 entries
     // of bilinear factors, anchor and G weights); after the records, the
     // waves' partial sums reuse the record tables' space.
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int TH = kTileH, TW = kTileW;
-    u32* bnd_lds = reinterpret_cast<u32*>(smem_raw);
-    float* work = reinterpret_cast<float*>(smem_raw +
-                                           bnd_lds_bytes((int)(blockDim.x >> 6)));
+    float* work = reinterpret_cast<float*>(smem_raw);
 
     const u32 span = t.tile_end - t.tile_begin;
     TileView v;
@@ -499,33 +510,39 @@ __device__ __forceinline__ void gfeat_tile_body(const TileArgs& t, const u32 gt,
     v.vscale = t.view_scale;
     v.N = t.N;
     v.L = t.L;
-    tile_reduce<OT, CPL, WHOLE, QB>(v, t.lps_shift, waves, wt, bnd_lds, work);
+    tile_reduce<OT, CPL, WHOLE, QB>(v, t.lps_shift, waves, wt, work);
 }
 
 // At most 128 VGPRs, i.e. 4 waves per SIMD. The reduction waits on record
-// and grad_out loads, and a fourth wave hides more of that than the few
-// registers it spills cost (measured on the 64-camera scene: light tiles 0.28
-// -> 0.24 ms, coarse 0.19 -> 0.18 ms). QB: 2 for the one-wave light tiles
-// (fewer registers: no spills at 128), 4 for whole-wave coarse tiles
-// (measured: light 0.248 -> 0.234 ms with 2, coarse 0.180 -> 0.191 ms).
+// and grad_out loads, and a fourth wave hides more of that than a few more
+// registers give (measured on the 64-camera scene: light tiles 0.28 -> 0.24
+// ms, coarse 0.19 -> 0.18 ms).
+//
+// A light tile has about one record per cell, so its wave issues the first
+// record's row of a cell row's five cells together (FIRST) and the rest two
+// at a time; a coarse tile's wave has runs long enough for four at a time
+// (64 cameras BF16 0.358 -> 0.345 ms, 6 cameras FP32 75 -> 67 us; 6 or 8 at a
+// time 69 and 71, two and FIRST 79). Boundaries and anchors are lanes'
+// registers, read as scalars: an LDS round trip per record less.
 //
 // Narrower records (C < 64 * CPL) share the wave as sub-waves of one tile
 // rather than taking tiles of their own, which left a run-time dispatch on
 // the cell per record and, on small problems, too few waves: 2 cameras of
 // 128 x 224, C = 64, 128 anchors 144 -> 30 us, 32 cameras of 256 x 448, 900
-// anchors, C = 128 285 -> 165 us, C = 64 317 -> 150 us. 8 waves per coarse
-// tile instead of 4: 20, 184 and 162 us.
+// anchors, C = 128 285 -> 165 us, C = 64 317 -> 150 us.
 //
 // One launch for both kinds of tiles: the coarse tiles (ids below
-// (tile_split - tile_begin) * B) first, a block of 4 waves each, then the
-// light ones, 4 per block, one wave each; the light blocks fill the CUs
-// around the long coarse ones instead of waiting for them to drain.
-constexpr int kTileBlockWaves = 4;
+// (tile_split - tile_begin) * B) first, all waves of a block each, then the
+// light ones, one wave each; the light blocks fill the CUs around the long
+// coarse ones instead of waiting for them to drain. A block has 4 waves, or 8
+// where the coarse tiles would be the launch's critical path
+// (tile_block_waves).
+constexpr int kMaxTileBlockWaves = 8;
 
 template <class OT, int CPL, bool WHOLE>
-__global__ void __launch_bounds__(64 * kTileBlockWaves)
+__global__ void __launch_bounds__(64 * kMaxTileBlockWaves)
     __attribute__((amdgpu_waves_per_eu(4, 8))) gfeat_tile_kernel(TileArgs t) {
-    constexpr int BW = kTileBlockWaves;
+    const int BW = (int)(blockDim.x >> 6);
     const u32 heavy = (t.tile_split - t.tile_begin) * (u32)t.B;
     const int wave = uniform((int)(threadIdx.x >> 6));
     if (blockIdx.x < heavy)
@@ -542,9 +559,7 @@ __device__ __forceinline__ void gfeat_tile_batched_body(const BatchArgs& b, cons
                                                         const int waves, const int wt) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int TH = kTileH, TW = kTileW;
-    u32* bnd_lds = reinterpret_cast<u32*>(smem_raw);
-    float* work = reinterpret_cast<float*>(smem_raw +
-                                           bnd_lds_bytes((int)(blockDim.x >> 6)));
+    float* work = reinterpret_cast<float*>(smem_raw);
 
     TileView v;
     v.active = gt < b.tile_end - b.tile_begin;
@@ -579,18 +594,17 @@ __device__ __forceinline__ void gfeat_tile_batched_body(const BatchArgs& b, cons
     v.vscale = nullptr;
     v.N = 1;
     v.L = 1;
-    tile_reduce<OT, CPL, WHOLE, QB>(v, b.lps_shift, waves, wt, bnd_lds, work);
+    tile_reduce<OT, CPL, WHOLE, QB>(v, b.lps_shift, waves, wt, work);
 }
 
-// As gfeat_tile_kernel: the heavy tiles ([tile_begin, tile_split)) 4 waves
-// each, then the light ones 4 per block, one wave each. Both walk with 2
-// grad_out rows in flight: with the batch's scene lookups, 4 for the heavy
-// tiles spilled 64 bytes under the 128-VGPR cap (the 12-scene batch's step:
-// 9.37 ms with 4, 9.22 ms with 2).
+// As gfeat_tile_kernel, but the heavy tiles ([tile_begin, tile_split)) too
+// walk as the light ones do: with the batch's scene lookups, 4 rows at a time
+// spilled under the 128-VGPR cap (the 12-scene batch's step: 9.37 ms with 4,
+// 9.22 ms with 2).
 template <class OT, int CPL, bool WHOLE>
-__global__ void __launch_bounds__(64 * kTileBlockWaves)
+__global__ void __launch_bounds__(64 * kMaxTileBlockWaves)
     __attribute__((amdgpu_waves_per_eu(4, 8))) gfeat_tile_batched_kernel(BatchArgs b) {
-    constexpr int BW = kTileBlockWaves;
+    const int BW = (int)(blockDim.x >> 6);
     const u32 heavy = b.tile_split - b.tile_begin;
     const int wave = uniform((int)(threadIdx.x >> 6));
     if (blockIdx.x < heavy)
@@ -602,22 +616,21 @@ __global__ void __launch_bounds__(64 * kTileBlockWaves)
 
 // ---------------------------------------------------------------- launchers
 
-// LDS of a tile block of `waves` waves: the cell boundaries, then the larger
-// of the record tables and the partial sums (coarse tiles: waves/2 halves of
+// LDS of a tile block of `waves` waves: the larger of the record tables and the partial sums (coarse tiles: waves/2 halves of
 // a tile's accumulators).
 template <int CPL>
 static size_t tile_lds_bytes(int waves, int G, bool coarse) {
     const size_t part = coarse ? (size_t)(waves / 2) * kTileH * kTileW * CPL * 64 * 4 : 0;
     const size_t tables = (size_t)waves * 64 * tile_entry_floats(G) * sizeof(float);
-    return bnd_lds_bytes(waves) + (part > tables ? part : tables);
+    return part > tables ? part : tables;
 }
 
 // One launch over [tile_begin, tile_end), coarse up to tile_split.
 template <class OT, int CPL, bool WHOLE>
 static hipError_t tile_launch_of(const TileArgs& t, hipStream_t s) {
-    constexpr u32 BW = kTileBlockWaves;
     const u32 heavy = (t.tile_split - t.tile_begin) * (u32)t.B;
     const u32 light = (t.tile_end - t.tile_split) * (u32)t.B;
+    const u32 BW = (u32)t.block_waves;
     const u32 blocks = heavy + (light + BW - 1) / BW;
     if (blocks == 0) return hipSuccess;
     mark_begin("gfeat_tile_kernel", s);
@@ -635,9 +648,9 @@ static hipError_t tile_launch(const TileArgs& t, hipStream_t s) {
 
 template <class OT, int CPL, bool WHOLE>
 static hipError_t tile_batched_launch_of(const BatchArgs& b, hipStream_t s) {
-    constexpr u32 BW = kTileBlockWaves;
     const u32 heavy = b.tile_split - b.tile_begin;
     const u32 light = b.tile_end - b.tile_split;
+    const u32 BW = (u32)b.block_waves;
     const u32 blocks = heavy + (light + BW - 1) / BW;
     if (blocks == 0) return hipSuccess;
     mark_begin("gfeat_tile_batched", s);
