@@ -110,6 +110,7 @@ class MSDAError(RuntimeError):
 
 
 _lib = None
+_torch_side = None
 
 
 def load(path: str = LIB_PATH):
@@ -187,6 +188,25 @@ def load(path: str = LIB_PATH):
         raise RuntimeError(f"libmsda ABI {lib.msda_abi_version()} != binding ABI {ABI_VERSION}")
     _lib = lib
     return lib
+
+
+def torch_side():
+    """_msda_torch (checks, outputs, workspace and autograd node of the single
+    call in native code), bound to the loaded library's functions."""
+    global _torch_side
+    if _torch_side is None:
+        lib = load()
+        try:
+            from . import _msda_torch
+        except ImportError as e:
+            raise RuntimeError(
+                "_msda_torch.so is missing or does not load: build the library first "
+                "(python -m paper_2601_10819_amd.build)") from e
+        _msda_torch.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.msda_forward_ws, lib.msda_forward_workspace_size, lib.msda_backward,
+            lib.msda_backward_workspace_size)))
+        _torch_side = _msda_torch
+    return _torch_side
 
 
 def check(status: int):

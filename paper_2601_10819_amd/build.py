@@ -1,4 +1,5 @@
-"""Build libmsda.so (the HIP kernels and the C ABI) in-tree with hipcc for gfx950.
+"""Build libmsda.so (the HIP kernels and the C ABI) in-tree with hipcc for gfx950,
+and _msda_torch.so (the PyTorch side of the single call) with g++.
 
     python -m paper_2601_10819_amd.build
 """
@@ -20,6 +21,9 @@ HEADERS = [os.path.join(CSRC, "msda_internal.h"), os.path.join(CSRC, "msda_commo
            os.path.join(CSRC, "msda_rows.h"), os.path.join(CSRC, "msda_grads.h"),
            os.path.join(ROOT, "include", "msda.h")]
 
+TORCH_SOURCE = os.path.join(CSRC, "msda_torch.cpp")
+TORCH_LIB = os.path.join(PKG, "_msda_torch.so")
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -35,6 +39,22 @@ FLAGS = [
 ]
 
 
+def torch_command(out: str):
+    """The g++ line of _msda_torch.so (host code only)."""
+    import sysconfig
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            "-Wno-unused-function", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I", os.path.join(ROOT, "include"), "-isystem", inc,
+            "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+            "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+            TORCH_SOURCE, "-o", out, "-L", lib, "-lc10", "-lc10_hip", "-ltorch_cpu",
+            "-ltorch_python", f"-Wl,-rpath,{lib}"]
+
+
 def _run(cmd):
     res = subprocess.run(cmd, capture_output=True, text=True)
     out = "\n".join(l for l in (res.stdout + res.stderr).splitlines()
@@ -44,7 +64,8 @@ def _run(cmd):
 
 def build(verbose: bool = False) -> str:
     """Compile every HIP source into libmsda.so (always recompiles): one
-    object per source, compiled in parallel, then one link."""
+    object per source, compiled in parallel, then one link; and
+    _msda_torch.so beside it."""
     import shutil
     import tempfile
     from concurrent.futures import ThreadPoolExecutor
@@ -54,15 +75,17 @@ def build(verbose: bool = False) -> str:
         objs = [os.path.join(tmpdir, os.path.basename(src) + ".o") for src in SOURCES]
         cflags = [f for f in FLAGS if f != "-shared"]
         cmds = [[HIPCC] + cflags + ["-c", src, "-o", obj] for src, obj in zip(SOURCES, objs)]
+        torch_tmp = TORCH_LIB + ".tmp%d" % os.getpid()
+        cmds.append(torch_command(torch_tmp))
         if verbose:
             for c in cmds:
                 print(" ".join(c), flush=True)
         jobs = max(1, min(len(cmds), int(os.environ.get("MAX_JOBS", os.cpu_count() or 4))))
         with ThreadPoolExecutor(jobs) as pool:
             results = list(pool.map(_run, cmds))
-        for (rc, out), src in zip(results, SOURCES):
+        for (rc, out), src in zip(results, SOURCES + [TORCH_SOURCE]):
             if rc != 0:
-                raise RuntimeError(f"hipcc failed on {os.path.basename(src)} ({rc}):\n{out}")
+                raise RuntimeError(f"the compiler failed on {os.path.basename(src)} ({rc}):\n{out}")
             if verbose and out:
                 print(out)
         tmp = LIB + ".tmp%d" % os.getpid()
@@ -73,16 +96,17 @@ def build(verbose: bool = False) -> str:
         if rc != 0:
             raise RuntimeError(f"link failed ({rc}):\n{out}")
         os.replace(tmp, LIB)
+        os.replace(torch_tmp, TORCH_LIB)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
     return LIB
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(TORCH_LIB)):
         return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(s) > t for s in SOURCES + HEADERS)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(TORCH_LIB))
+    return any(os.path.getmtime(s) > t for s in SOURCES + HEADERS + [TORCH_SOURCE])
 
 
 if __name__ == "__main__":

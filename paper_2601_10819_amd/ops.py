@@ -83,6 +83,14 @@ def tile_struct(tile: dict, into=None):
     return t
 
 
+def _tile_ints(tile: Optional[dict]):
+    """The fields of tile_struct as a tuple for the native calls, None without a tile."""
+    if not tile:
+        return None
+    return (int(tile.get("waves_per_anchor", 0)), int(tile.get("chans_per_lane", 0)),
+            _order_code(tile.get("order", 0)), int(tile.get("scatter", 0)))
+
+
 def make_desc(feat: torch.Tensor, layout: Layout, sampling_loc: torch.Tensor,
               weights: torch.Tensor, level_scale: Optional[torch.Tensor] = None,
               deterministic: bool = False, tile: Optional[dict] = None, logits: bool = False):
@@ -128,7 +136,7 @@ def _need_weights(weights):
 def _resolve_tile(tile, which, feat, sampling_loc, weights):
     """tile="auto": the autotuner's cached shape for this workload (or the
     library's own choice when nothing is cached)."""
-    if tile != "auto":
+    if tile is None or tile != "auto":
         return tile
     from . import autotune
     B, _, C = feat.shape
@@ -170,23 +178,10 @@ def forward(feat, layout: Layout, sampling_loc, weights, level_scale=None, tile=
     is allocated when needed and not given). weights: FP32 or BF16; logits:
     they are logits and the per-group softmax over (keypoint, camera, level)
     is applied inside."""
-    lib = _lib.load()
-    tile = _resolve_tile(tile, "forward", feat, sampling_loc, weights)
-    _need_cuda_contig("feat", feat)
-    _need_cuda_contig("sampling_loc", sampling_loc, torch.float32)
-    _need_weights(weights)
-    if level_scale is not None:
-        _need_cuda_contig("level_scale", level_scale, torch.float32)
-    d = make_desc(feat, layout, sampling_loc, weights, level_scale, tile=tile, logits=logits)
-    if out is None:
-        out = torch.empty(d.batch, d.num_anchors, d.channels, device=feat.device,
-                          dtype=torch.float32)
-    ws_ptr, ws_len, workspace = _workspace(int(lib.msda_forward_workspace_size(ctypes.byref(d))),
-                                           workspace, feat.device)
-    _lib.check(lib.msda_forward_ws(_ptr(feat), _ptr(layout.shapes), _ptr(layout.starts),
-                                   _ptr(sampling_loc), _ptr(weights), _ptr(out), ws_ptr, ws_len,
-                                   ctypes.byref(d), _stream(stream)))
-    return out
+    return _lib.torch_side().forward(
+        feat, layout, sampling_loc, weights, level_scale,
+        _tile_ints(_resolve_tile(tile, "forward", feat, sampling_loc, weights)), out, workspace,
+        None if stream is None else int(stream.cuda_stream), logits)
 
 
 def forward_noalloc(feat, layout: Layout, sampling_loc, weights, out: torch.Tensor,
@@ -225,26 +220,11 @@ def backward(feat, layout: Layout, sampling_loc, weights, grad_out,
              ) -> Tuple[Optional[torch.Tensor], Optional[torch.Tensor], Optional[torch.Tensor]]:
     """(grad_feat, grad_sampling_loc, grad_weights); an unrequested one is None.
     grad_weights is FP32 (with logits=True: the gradient of the logits)."""
-    lib = _lib.load()
-    tile = _resolve_tile(tile, "backward", feat, sampling_loc, weights)
-    _need_cuda_contig("feat", feat)
-    _need_cuda_contig("sampling_loc", sampling_loc, torch.float32)
-    _need_weights(weights)
-    _need_cuda_contig("grad_out", grad_out, torch.float32)
-    d = make_desc(feat, layout, sampling_loc, weights, level_scale, deterministic=deterministic,
-                  tile=tile, logits=logits)
-    gf = torch.empty_like(feat) if need_feat else None
-    gl = torch.empty_like(sampling_loc) if need_loc else None
-    gw = torch.empty(weights.shape, dtype=torch.float32, device=weights.device) if need_w else None
-    weight_flags = logits or weights.dtype == torch.bfloat16
-    ws_bytes = (int(lib.msda_backward_workspace_size(ctypes.byref(d)))
-                if need_feat or weight_flags else 0)
-    ws_ptr, ws_len, workspace = _workspace(ws_bytes, workspace, feat.device)
-    _lib.check(lib.msda_backward(_ptr(feat), _ptr(layout.shapes), _ptr(layout.starts),
-                                 _ptr(sampling_loc), _ptr(weights), _ptr(grad_out), _ptr(gf),
-                                 _ptr(gl), _ptr(gw), ws_ptr, ws_len, ctypes.byref(d),
-                                 _stream(stream)))
-    return gf, gl, gw
+    return _lib.torch_side().backward(
+        feat, layout, sampling_loc, weights, grad_out, bool(need_feat), bool(need_loc),
+        bool(need_w), bool(deterministic),
+        _tile_ints(_resolve_tile(tile, "backward", feat, sampling_loc, weights)), workspace,
+        level_scale, None if stream is None else int(stream.cuda_stream), logits)
 
 
 def project_keypoints(anchors, keypoints, projection, image_hw, dt: float, stream=None):
@@ -476,11 +456,33 @@ class MSDAFunction(torch.autograd.Function):
         return gf, gl, gw, None, None, None, None, None
 
 
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
+
+
+def _plain_call(feat, sampling_loc, weights) -> bool:
+    """Plain tensors, and nothing that follows the call from outside: no
+    torch.func transform, forward-mode level, tracer, compiler, dispatch or
+    function mode."""
+    return (type(feat) in _PLAIN and type(sampling_loc) in _PLAIN and type(weights) in _PLAIN and
+            torch._C._functorch.peek_interpreter_stack() is None and
+            not torch._C._len_torch_dispatch_stack() and
+            not torch._C._len_torch_function_stack() and
+            torch._C._get_tracing_state() is None and not torch.compiler.is_compiling() and
+            torch.autograd.forward_ad._current_level < 0)
+
+
 def msda(feat, layout: Layout, sampling_loc, weights, level_scale=None, deterministic=False,
          tile=None, logits=False):
-    """Autograd-aware MSDA (logits=True: weights are per-group softmax logits)."""
-    return MSDAFunction.apply(feat, sampling_loc, weights, layout, level_scale, deterministic,
-                              tile, logits)
+    """Autograd-aware MSDA (logits=True: weights are per-group softmax logits).
+    The native node where nothing but autograd looks on, MSDAFunction where a
+    transform, a mode or a tracer does; both run the same forward and backward."""
+    if not _plain_call(feat, sampling_loc, weights):
+        return MSDAFunction.apply(feat, sampling_loc, weights, layout, level_scale, deterministic,
+                                  tile, logits)
+    return _lib.torch_side().msda(
+        feat, layout, sampling_loc, weights, level_scale, bool(deterministic),
+        _tile_ints(_resolve_tile(tile, "forward", feat, sampling_loc, weights)),
+        _tile_ints(_resolve_tile(tile, "backward", feat, sampling_loc, weights)), logits)
 
 
 class SceneBatch:
