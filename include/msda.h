@@ -424,7 +424,7 @@ msda_status msda_forward_batched(const msda_batch* batch, void* workspace,
 /*
  * Backward of every scene: one gather launch for all anchors of all scenes
  * (in the forward's work order), one sort of all scenes' grad_feat records,
- * one tiled reduction over all scenes' pixels (two launches: coarse, fine). A
+ * one tiled reduction over all scenes' pixels (in one or two launches). A
  * gradient pointer must be NULL in every scene or in none. Only the sorted
  * grad_feat form is available here. workspace: >=
  * msda_batched_workspace_size(batch, 1).

@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <iterator>
 #include <string>
 #include <utility>
 #include <vector>
@@ -335,7 +336,8 @@ void cells_and_tiles(const msda_desc* d, uint64_t* cells, uint64_t* tiles) {
 
 // Tiles (of one batch item, in slot order: coarse levels first) of the levels
 // whose regions are at most 1/16 of the largest region's area -- the levels
-// where a pixel collects 16x or more the samples of the finest one.
+// where a pixel collects 16x or more the samples of the finest one -- and how
+// many regions that is.
 uint32_t heavy_tiles(const msda_desc* d, uint32_t* regions) {
     const int N = d->num_cams, L = d->num_levels;
     int64_t max_area = 0;
@@ -355,17 +357,22 @@ uint32_t heavy_tiles(const msda_desc* d, uint32_t* regions) {
     return tiles;
 }
 
-// Waves per block of the tile reduction. 4, so that blocks end and make room
-// in small steps (8: 64 cameras 345 -> 367 us, the 16-camera step 317 -> 344),
-// but 8 where the chip is drained before the coarse tiles, which are as long
-// as their records are many, are done: up to two rounds of the 4096 waves
-// that are resident at once, and coarse tiles of many records (6 cameras FP32
-// 67 -> 52 us, 2 cameras of 128 x 224 29 -> 20; 5 cameras with 331 anchors,
-// 107 samples per coarse tile, 21 -> 24).
-int tile_block_waves(uint64_t heavy, uint64_t tiles, uint64_t heavy_samples) {
+// Whether 8 waves share a coarse tile's records (and make a block) instead of
+// 4. With 4, blocks end and make room in small steps (8: 64 cameras 345 -> 367
+// us, the 16-camera step 317 -> 344); 8 where the chip is drained before the
+// coarse tiles, which are as long as their records are many, are done: up to
+// two rounds of the 4096 waves that are resident at once, and coarse tiles of
+// 256 samples (C = 256: 6 cameras FP32, 418 samples per coarse tile, 67 -> 52
+// us, but 9 x 2, 106, 49 -> 60; C = 128: 8 cameras, 332, 54 -> 46, but 7
+// cameras, 181, 37 -> 38; C = 64: 2 cameras of 128 x 224, 333, 30 -> 20, but 9
+// cameras, 94, 27 -> 32). The number sets the order of the sums, so it is a
+// call's own, and a batch takes each scene's as a call on that scene does, in
+// a launch for either kind (the 12-scene step with 8-wave blocks for all 9.64
+// ms, in two launches 8.85).
+bool wide_tiles(uint64_t heavy, uint64_t tiles, uint64_t heavy_samples) {
     constexpr uint64_t kMaxWaves = 8192, kMinSamples = 256;
     const uint64_t waves = 4 * heavy + (tiles - heavy);
-    return heavy && waves <= kMaxWaves && heavy_samples >= kMinSamples * heavy ? 8 : 4;
+    return heavy && waves <= kMaxWaves && heavy_samples >= kMinSamples * heavy;
 }
 
 // 1 if the regions are pairwise disjoint; *cover = they tile [0, R) exactly.
@@ -910,8 +917,9 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     t.tile_begin = 0;
     t.tile_split = heavy_tiles(desc, &heavy_regions);
     t.tile_end = (uint32_t)tiles;
-    t.block_waves = tile_block_waves((uint64_t)t.tile_split * a.B, tiles * a.B,
-                                     (uint64_t)heavy_regions * a.B * a.A * a.P);
+    t.block_waves = wide_tiles((uint64_t)t.tile_split * a.B, tiles * a.B,
+                               (uint64_t)heavy_regions * a.B * a.A * a.P)
+                        ? 8 : 4;
     if ((e = msda::launch_gfeat_tiles(t, desc->feat_dtype, rcpl, s)) != hipSuccess)
         return hip_fail(e, "grad_feat tile reduction");
     return finish();
@@ -1207,7 +1215,7 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
 
 // Sizes of a validated batch.
 struct BatchPlan {
-    uint64_t anchors, samples, regions, cells, tiles, heavy_tiles, heavy_samples;
+    uint64_t anchors, samples, regions, cells, tiles, heavy_tiles;
     uint64_t fwd_rows, bwd_rows;  // view-order units of all scenes
     int max_cams;
     int cpl, waves;
@@ -1217,6 +1225,9 @@ struct BatchPlan {
     uint64_t part_bytes;          // view-order forward partials
     uint64_t max_ap;              // the largest A_s * P
     bool keys_fit;                // every region's cells fit the bucket sort's keys
+    // scenes whose coarse tiles take 8 waves: their bits, tiles and coarse tiles
+    uint32_t wide[msda::kMaxBatchScenes / 32];
+    uint64_t wide_tiles, wide_heavy;
 };
 
 // Validates the batch (every scene against its host mirrors) and sizes it.
@@ -1285,17 +1296,24 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
         for (int l = 0; l < b->num_levels; ++l)
             max_area = std::max<int64_t>(max_area, (int64_t)d.host_spatial_shapes[2 * l] *
                                                        d.host_spatial_shapes[2 * l + 1]);
+        uint64_t heavy = 0, heavy_samples = 0;
         for (int l = 0; l < b->num_levels; ++l) {
             if ((int64_t)d.host_spatial_shapes[2 * l] * d.host_spatial_shapes[2 * l + 1] * 16 >
                 max_area)
                 continue;
-            p->heavy_samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams;
+            heavy_samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams;
             for (int n = 0; n < sc.num_cams; ++n) {
                 const int r = n * b->num_levels + l;
                 const uint64_t H = d.host_spatial_shapes[2 * r], W = d.host_spatial_shapes[2 * r + 1];
-                p->heavy_tiles += ((H + msda::kTileH - 1) / msda::kTileH) *
-                                  ((W + msda::kTileW - 1) / msda::kTileW);
+                heavy += ((H + msda::kTileH - 1) / msda::kTileH) *
+                         ((W + msda::kTileW - 1) / msda::kTileW);
             }
+        }
+        p->heavy_tiles += heavy;
+        if (wide_tiles(heavy, tiles, heavy_samples)) {
+            p->wide[s >> 5] |= 1u << (s & 31);
+            p->wide_tiles += tiles;
+            p->wide_heavy += heavy;
         }
     }
     (void)eb;
@@ -1366,6 +1384,7 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, bool backward, cha
     a->total_samples = (uint32_t)p.samples;
     a->total_cells = (uint32_t)p.cells;
     a->total_regions = (uint32_t)p.regions;
+    std::copy(std::begin(p.wide), std::end(p.wide), a->wide);
     a->lps_shift = log2i(b->channels / p.cpl);
 }
 
@@ -1617,10 +1636,17 @@ msda_status msda_backward_batched(const msda_batch* b, void* workspace, size_t w
     a.off = off;
     a.total_samples = (uint32_t)std::max<uint64_t>(p.samples, 1);
     a.lps_shift = log2i(b->channels / rcpl);
+    // the wide scenes' tiles, then the others'
+    a.block_waves = 8;
     a.tile_begin = 0;
-    a.tile_split = (uint32_t)p.heavy_tiles;
+    a.tile_split = (uint32_t)p.wide_heavy;
+    a.tile_end = (uint32_t)p.wide_tiles;
+    if ((e = msda::launch_gfeat_tiles_batched(a, b->feat_dtype, rcpl, s)) != hipSuccess)
+        return hip_fail(e, "batched grad_feat tile reduction");
+    a.block_waves = 4;
+    a.tile_begin = (uint32_t)p.wide_tiles;
+    a.tile_split = (uint32_t)(p.wide_tiles + p.heavy_tiles - p.wide_heavy);
     a.tile_end = (uint32_t)p.tiles;
-    a.block_waves = tile_block_waves(p.heavy_tiles, p.tiles, p.heavy_samples);
     if ((e = msda::launch_gfeat_tiles_batched(a, b->feat_dtype, rcpl, s)) != hipSuccess)
         return hip_fail(e, "batched grad_feat tile reduction");
     return p.anchors > 0 ? batch_softmax_grad(b, ws, w, s) : ok();

@@ -2,8 +2,9 @@
 // that a batched call needs no host-to-device copy (and can be captured in
 // a HIP graph): per scene the first anchor, sample (record) and region; per
 // region its first bilinear cell; and the processing slots of the tiled
-// grad_feat reduction -- heavy (coarse) levels first, then coarsest level
-// first, then scene, then camera -- with the first tile of each slot.
+// grad_feat reduction -- wide scenes (BatchArgs::wide) first, then heavy
+// (coarse) levels, then coarsest level first, then scene, then camera -- with
+// the first tile of each slot.
 //
 // A (scene, level) is heavy when the level's area (camera 0) is at most
 // 1/16 of the scene's largest level area: there a pixel collects 16x or
@@ -104,16 +105,17 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
         }
     }
 
-    // slot groups: (class, level descending, scene), each holding the scene's cameras
+    // slot groups: (wide, class, level descending, scene), each holding the scene's cameras
     if (tid == 0) {
         u32 run = 0;
-        for (int cls = 0; cls < 2; ++cls)
+        for (int cls = 0; cls < 4; ++cls)              // (narrow, light)
             for (int ld = 0; ld < L; ++ld)
                 for (int s = 0; s < S; ++s) {
+                    if ((b.wide[s >> 5] >> (s & 31) & 1) == (u32)(cls >> 1)) continue;
                     const int l = L - 1 - ld;
                     const bool heavy = level_is_heavy(sh_h, sh_w, rstart, s, l, L);
-                    grp[(cls * L + ld) * S + s] = run;
-                    if (heavy == (cls == 0)) run += s_cams[s];
+                    grp[((cls & 1) * L + ld) * S + s] = run;
+                    if (heavy == ((cls & 1) == 0)) run += s_cams[s];
                 }
     }
     __syncthreads();

@@ -74,7 +74,7 @@ struct TileArgs {
     // tile_split) coarse (all waves of a block each), [tile_split, tile_end)
     // light (one wave each)
     uint32_t tile_begin, tile_split, tile_end;
-    int32_t block_waves;          // waves per block, at most 8
+    int32_t block_waves;          // waves per block, 4 or 8
     uint32_t cells_per_item;
     uint32_t nrec;                // S (records, one per sample)
     int32_t NL, B, C, G;
@@ -87,8 +87,9 @@ struct TileArgs {
 // Batched form: tables over all scenes, built on the device from the scene
 // table by batch_tables_kernel. Regions are numbered scene by scene (scene
 // s owns regions [region_start[s], region_start[s+1]), camera-major); slots
-// order the regions for the tiled reduction: heavy (coarse) levels first,
-// then by level (coarsest first), scene and camera.
+// order the regions for the tiled reduction: the scenes whose coarse tiles
+// take 8 waves (a launch of their own) before the others, heavy (coarse)
+// levels first, then by level (coarsest first), scene and camera.
 constexpr int kMaxBatchScenes = 256;
 constexpr int kMaxBatchRegions = 4096;
 
@@ -130,6 +131,7 @@ struct BatchArgs {
     const uint32_t* off;
     uint32_t tile_begin, tile_split, tile_end;  // as TileArgs
     int32_t block_waves;
+    uint32_t wide[kMaxBatchScenes / 32];   // bit s: scene s's coarse tiles take 8 waves
 };
 
 enum FeatType { kF32 = 0, kBF16 = 1, kFP8 = 2, kF16 = 3 };
