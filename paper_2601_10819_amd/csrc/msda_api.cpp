@@ -589,7 +589,7 @@ VisibleWs visible_layout(const msda_desc* d, size_t at) {
     VisibleWs w;
     w.place = at;
     w.partial = w.place + align256((V + 1) * 4);
-    w.items = w.partial + align256(msda::scan_scratch_words((uint32_t)(V + 1)) * 4);
+    w.items = w.partial + align256(msda::visible_partial_words(V) * 4);
     w.rec_count = w.items + align256(V * 4 + 4);
     w.vt = w.rec_count + 256;                 // the fused form's per-view weights
     w.dot = w.vt + align256(V * 4);           // and its per-item score products

@@ -253,18 +253,17 @@ hipError_t launch_bucket_sort(const uint32_t* keys, const int32_t* shapes, int32
 // bucket_sort_lds_bytes(max_ap)).
 hipError_t launch_bucket_sort_batched(const BatchArgs& b, uint32_t max_ap, uint32_t* vals,
                                       uint32_t* off, hipStream_t s);
-// In-place exclusive scan of n words; partial: scan_scratch_words(n) words.
-hipError_t launch_exclusive_scan(uint32_t* x, uint32_t n, uint32_t* partial, hipStream_t s);
-size_t scan_scratch_words(uint32_t n);
 
 // Keypoint projection and the visible-view form (msda_vis.hip).
 hipError_t launch_project_keypoints(const ProjArgs& p, hipStream_t s);
 // place[0..V] = exclusive scan of the view-major visibility flags (place[V]
 // = the number of visible items), items[place[v]] = v, and *rec_count =
-// place[V] * per_item (or nothing when rec_count is nullptr).
+// place[V] * per_item (or nothing when rec_count is nullptr); partial:
+// visible_partial_words(V) words. V = B * N * A > 0.
+size_t visible_partial_words(size_t V);
 hipError_t launch_visible_items(const uint8_t* visible, int B, int N, int A, uint32_t per_item,
                                 uint32_t* place, uint32_t* items, uint32_t* rec_count,
-                                uint32_t* scan_partial, hipStream_t s);
+                                uint32_t* partial, hipStream_t s);
 // vt (or nullptr): the fused form's per-view weights [B][A][N].
 hipError_t launch_forward_visible(const OpArgs& a, int dtype, int cpl, int waves,
                                   const uint32_t* items, const uint32_t* count,

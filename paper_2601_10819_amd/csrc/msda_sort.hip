@@ -29,7 +29,6 @@ constexpr int kSortTile = kSortThreads * kSortItems;   // elements per tile
 constexpr int kMaxDigitBits = 8;
 constexpr int kMaxDigits = 1 << kMaxDigitBits;         // one thread per digit below
 constexpr int kBand = 32;                              // tiles per band of the offset scan
-constexpr int kScanTile = 4096;                          // scan: 256 threads x 16
 
 __global__ void __launch_bounds__(kSortThreads)
 radix_hist_kernel(const u32* __restrict__ keys, u32 n, const u32* n_dev, int shift, int bits,
@@ -111,59 +110,6 @@ __global__ void __launch_bounds__(kMaxDigits) digit_offsets_kernel(u32* __restri
             table[(size_t)(t0 + k) * digits + d] = off;
             off += c[k];
         }
-    }
-}
-
-// Scan, phase 1: per-tile sums.
-__global__ void __launch_bounds__(256) scan_reduce_kernel(const u32* __restrict__ x, u32 n,
-                                                          u32* __restrict__ partial) {
-    __shared__ u32 lds4[4];
-    const u32 base = blockIdx.x * (u32)kScanTile + threadIdx.x * 16u;
-    u32 s = 0;
-    for (int i = 0; i < 16; ++i)
-        if (base + i < n) s += x[base + i];
-    u32 total;
-    block_inclusive_scan(s, lds4, &total);
-    if (threadIdx.x == 0) partial[blockIdx.x] = total;
-}
-
-// Scan, phase 2: exclusive scan of the tile sums in one block.
-__global__ void __launch_bounds__(256) scan_partials_kernel(u32* partial, u32 np) {
-    __shared__ u32 lds4[4];
-    const u32 per = (np + 255) / 256;
-    const u32 b0 = threadIdx.x * per;
-    u32 s = 0;
-    for (u32 i = 0; i < per; ++i)
-        if (b0 + i < np) s += partial[b0 + i];
-    u32 total;
-    const u32 incl = block_inclusive_scan(s, lds4, &total);
-    u32 run = incl - s;
-    for (u32 i = 0; i < per; ++i) {
-        if (b0 + i < np) {
-            const u32 v = partial[b0 + i];
-            partial[b0 + i] = run;
-            run += v;
-        }
-    }
-}
-
-// Scan, phase 3: exclusive scan within each tile, offset by its tile sum.
-__global__ void __launch_bounds__(256) scan_apply_kernel(u32* x, u32 n,
-                                                         const u32* __restrict__ partial) {
-    __shared__ u32 lds4[4];
-    const u32 base = blockIdx.x * (u32)kScanTile + threadIdx.x * 16u;
-    u32 v[16];
-    u32 s = 0;
-    for (int i = 0; i < 16; ++i) {
-        v[i] = base + i < n ? x[base + i] : 0u;
-        s += v[i];
-    }
-    u32 total;
-    const u32 incl = block_inclusive_scan(s, lds4, &total);
-    u32 run = incl - s + partial[blockIdx.x];
-    for (int i = 0; i < 16; ++i) {
-        if (base + i < n) x[base + i] = run;
-        run += v[i];
     }
 }
 
@@ -734,23 +680,6 @@ __global__ void segment_bounds_search_kernel(const u32* __restrict__ keys, u32 n
     }
     off[r] = lo;
 }
-
-hipError_t launch_exclusive_scan(u32* x, u32 n, u32* partial, hipStream_t s) {
-    const u32 tiles = (n + kScanTile - 1) / kScanTile;
-    if (tiles == 0) return hipSuccess;
-    mark_begin("scan_reduce", s);
-    hipLaunchKernelGGL(scan_reduce_kernel, dim3(tiles), dim3(256), 0, s, x, n, partial);
-    mark_end(s);
-    mark_begin("scan_partials", s);
-    hipLaunchKernelGGL(scan_partials_kernel, dim3(1), dim3(256), 0, s, partial, tiles);
-    mark_end(s);
-    mark_begin("scan_apply", s);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3(tiles), dim3(256), 0, s, x, n, partial);
-    mark_end(s);
-    return hipGetLastError();
-}
-
-size_t scan_scratch_words(u32 n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
 static u32 bands_of(u32 ntiles) { return (ntiles + kBand - 1) / kBand; }
 
