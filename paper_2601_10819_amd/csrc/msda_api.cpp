@@ -497,7 +497,7 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
     const size_t stats = stats_bytes(desc);
     int part_rows = 0;
     if (order == MSDA_ORDER_VIEW) {
-        part_rows = std::max(msda::fwd_rows(a.N), msda::kMinFwdRows);
+        part_rows = std::max(msda::max_fwd_rows(a.N), msda::kMinFwdRows);
         while (part_rows > msda::kMinFwdRows &&
                part_bytes(desc, part_rows) + stats > workspace_bytes)
             --part_rows;
@@ -560,7 +560,7 @@ static size_t forward_bytes(const msda_desc* d, int part_rows) {
 }
 
 size_t msda_forward_workspace_size(const msda_desc* d) {
-    return forward_bytes(d, d ? std::max(msda::fwd_rows(d->num_cams), msda::kMinFwdRows) : 0);
+    return forward_bytes(d, d ? std::max(msda::max_fwd_rows(d->num_cams), msda::kMinFwdRows) : 0);
 }
 
 }  // extern "C"
@@ -1274,10 +1274,10 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
         if (!aligned(sc.feat, 16))
             return fail(MSDA_ERR_UNSUPPORTED, "scene %d: feat must be 16-byte aligned", s);
         p->anchors += (uint64_t)sc.num_anchors;
-        p->fwd_rows += (uint64_t)sc.num_anchors * (uint64_t)msda::fwd_rows(sc.num_cams);
+        p->fwd_rows += (uint64_t)sc.num_anchors * (uint64_t)msda::fwd_rows(sc.num_cams, b->num_points, b->num_levels);
         // sized as for the single call: at least kMinFwdRows rows an anchor
         p->part_bytes += (uint64_t)sc.num_anchors *
-                         (uint64_t)std::max(msda::fwd_rows(sc.num_cams), msda::kMinFwdRows);
+                         (uint64_t)std::max(msda::max_fwd_rows(sc.num_cams), msda::kMinFwdRows);
         p->bwd_rows += (uint64_t)sc.num_anchors *
                        (uint64_t)msda::bwd_rows(sc.num_cams, b->num_points);
         p->samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams * b->num_levels;

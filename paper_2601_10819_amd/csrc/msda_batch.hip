@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
             b.t.region_start[s] = reg;
             rstart[s] = reg;
             b.t.row_start[s] = rows;
-            rows += (u64)(backward ? bwd_rows((int)s_cams[s], b.P) : fwd_rows((int)s_cams[s])) *
+            rows += (u64)(backward ? bwd_rows((int)s_cams[s], b.P) : fwd_rows((int)s_cams[s], b.P, L)) *
                     s_anchors[s];
             a += s_anchors[s];
             const u32 per_anchor = (u32)b.P * s_cams[s] * (u32)L;

@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(512) msda_fwd_batched_view_kernel(BatchArgs b,
     const int s = scene_of_row(b.t.row_start, b.S, u);
     const OpArgs a = scene_view(b, s, FT::kBytes);
     const RowUnit t = row_unit(u - b.t.row_start[s], a.A);
-    const CamRange n = row_cams(a.N, (int)t.row, fwd_rows(a.N));
+    const CamRange n = row_cams(a.N, (int)t.row, fwd_rows(a.N, a.P, a.L));
     const Lanes q = lanes_of<FT, CPL>(a);
     const rsrc_t feat = make_rsrc(a.feat, a.batch_bytes);
     const int NS = a.P * a.L;
@@ -186,7 +186,7 @@ __global__ void __launch_bounds__(256) fwd_batched_view_reduce(BatchArgs b, cons
     const int sc = scene_of(b.t.anchor_start, b.S, g);
     const u32 a = g - b.t.anchor_start[sc];
     const size_t AC = (size_t)b.scenes[sc].num_anchors * b.C;
-    const int rows = fwd_rows(b.scenes[sc].num_cams);
+    const int rows = fwd_rows(b.scenes[sc].num_cams, b.P, b.L);
     const float* p = part + (b.t.row_start[sc] + a) * (u32)b.C + c;
     float s[V];
 #pragma unroll
@@ -255,7 +255,7 @@ static hipError_t fwd_launch(const OpArgs& a, int waves, hipStream_t s) {
 template <class FT, int CPL>
 static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, float* part,
                                   hipStream_t s) {
-    const int rows = fwd_rows(a.N), chunk = fwd_chunk_samples(waves, a.G);
+    const int rows = fwd_rows(a.N, a.P, a.L), chunk = fwd_chunk_samples(waves, a.G);
     const size_t AC = (size_t)a.A * a.C, total = AC * a.B;
     for (int row0 = 0; row0 < rows; row0 += part_rows) {
         const int nrows = part_rows < rows - row0 ? part_rows : rows - row0;

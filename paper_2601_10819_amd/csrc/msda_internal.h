@@ -170,11 +170,21 @@ inline unsigned slot_blocks(uint64_t T, int waves) {
 // to grow: one camera for a multiple of 8 up to 64 cameras (a wave per camera
 // took 0.325 ms at the 64-camera scene in BF16, 2 cameras 0.332, 4 0.366, 8
 // 0.385; FP32 0.577, 0.649, 0.752), and at most 64 rows so that the
-// workspace stays bounded.
-constexpr int kMinFwdRows = 8, kMaxFwdRows = 64;
+// workspace stays bounded (max_fwd_rows). Where a camera has few samples,
+// rather as many cameras as hold kMinRowSamples: a wave stages 64 samples at a
+// time, and every row is written and read once more. 49 cameras of 7 x 3
+// samples 70 -> 50 us, 63 of 7 x 4 45 -> 35, 26 of 11 x 4 173 -> 159, 53 of 11
+// x 4 355 -> 343 (with 32 samples 57, 35, 176, 348); 13 x 4 are a row.
+constexpr int kMinFwdRows = 8, kMaxFwdRows = 64, kMinRowSamples = 48;
 
-__host__ __device__ inline int fwd_rows(int N) {
+__host__ __device__ inline int max_fwd_rows(int N) {
     return N < kMinFwdRows ? N : N >= kMaxFwdRows ? kMaxFwdRows : N / 8 * 8;
+}
+
+__host__ __device__ inline int fwd_rows(int N, int P, int L) {
+    const int rows = max_fwd_rows(N), cams = (kMinRowSamples + P * L - 1) / (P * L);
+    const int few = ((N + cams - 1) / cams + 7) / 8 * 8;
+    return few < rows ? few : rows;
 }
 
 // The backward, whose rows need no combining: one camera per row, or as many
@@ -200,7 +210,7 @@ hipError_t launch_forward(const OpArgs& a, int dtype, int cpl, int waves, hipStr
 hipError_t launch_backward(const OpArgs& a, int dtype, int cpl, int waves, hipStream_t s);
 // View order: `waves` waves per workgroup, each its own unit. The forward
 // writes partial rows to part and adds them into out in row order, part_rows
-// (>= min(fwd_rows(N), kMinFwdRows)) rows [B][part_rows][A][C] FP32 at a
+// (>= min(fwd_rows, kMinFwdRows)) rows [B][part_rows][A][C] FP32 at a
 // time; the sums do not depend on part_rows.
 hipError_t launch_forward_view(const OpArgs& a, int dtype, int cpl, int waves, int part_rows,
                                float* part, hipStream_t s);
