@@ -360,17 +360,17 @@ uint32_t heavy_tiles(const msda_desc* d, uint32_t* regions) {
 // Whether 8 waves share a coarse tile's records (and make a block) instead of
 // 4. With 4, blocks end and make room in small steps (8: 64 cameras 345 -> 367
 // us, the 16-camera step 317 -> 344); 8 where the chip is drained before the
-// coarse tiles, which are as long as their records are many, are done: up to
-// two rounds of the 4096 waves that are resident at once, and coarse tiles of
-// 256 samples (C = 256: 6 cameras FP32, 418 samples per coarse tile, 67 -> 52
-// us, but 9 x 2, 106, 49 -> 60; C = 128: 8 cameras, 332, 54 -> 46, but 7
-// cameras, 181, 37 -> 38; C = 64: 2 cameras of 128 x 224, 333, 30 -> 20, but 9
-// cameras, 94, 27 -> 32). The number sets the order of the sums, so it is a
-// call's own, and a batch takes each scene's as a call on that scene does, in
-// a launch for either kind (the 12-scene step with 8-wave blocks for all 9.64
-// ms, in two launches 8.85).
+// coarse tiles, which are as long as their records are many, are done: at most
+// a quarter of the 4096 waves that are resident at once, and coarse tiles of
+// 256 samples (C = 64, 2 cameras of 128 x 224, 333 samples per coarse tile, 30
+// -> 20 us; below 200 samples 8 waves were no faster or slower). Up to 8192
+// waves a call alone gains too (6 cameras FP32 67 -> 52), but the number sets
+// the order of the sums, so it is a scene's own: a batch takes it over and
+// needs a launch for either kind, which costs a batch of two scenes, one on
+// each side of the line, 20 to 28 us (468 -> 496, 355 -> 378), and scenes of
+// so many tiles come in such batches.
 bool wide_tiles(uint64_t heavy, uint64_t tiles, uint64_t heavy_samples) {
-    constexpr uint64_t kMaxWaves = 8192, kMinSamples = 256;
+    constexpr uint64_t kMaxWaves = 1024, kMinSamples = 256;
     const uint64_t waves = 4 * heavy + (tiles - heavy);
     return heavy && waves <= kMaxWaves && heavy_samples >= kMinSamples * heavy;
 }
