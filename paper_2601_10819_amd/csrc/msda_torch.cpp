@@ -12,13 +12,13 @@
 // library called is the one the Python side has loaded.
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
-#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/functions/utils.h>
-#include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/utils/pybind.h>
 #include <torch/extension.h>
 
 #include <array>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -258,60 +258,114 @@ py::tuple py_backward(const Tensor& feat, const py::handle& layout, const Tensor
     return py::make_tuple(or_none(g.feat), or_none(g.loc), or_none(g.w));
 }
 
-// The autograd node of one call. The operands are saved variables (versions
-// are checked, saved-tensor hooks run); nothing else refers to their memory.
-struct MsdaBackward : torch::autograd::Node {
+// Raised on an engine's thread, which holds no interpreter lock: the Python
+// error is set under it and travels with the exception.
+[[noreturn]] void raise_python(msda_status st, const std::string& bad) {
+    py::gil_scoped_acquire lock;
+    if (!bad.empty()) {
+        PyErr_SetString(PyExc_ValueError, bad.c_str());
+    } else {
+        try {
+            check(st);
+        } catch (py::error_already_set& e) {
+            e.restore();
+        }
+    }
+    python_error e;
+    e.persist();
+    throw e;
+}
+
+torch::autograd::variable_list call_backward(const Call& c, const Tensor& feat, const Tensor& loc,
+                                             const Tensor& w, const Tensor& grad_out,
+                                             bool need_feat, bool need_loc, bool need_w) {
+    Grads g;
+    if (need_feat || need_loc || need_w) {
+        std::string bad;
+        msda_status st = MSDA_OK;
+        try {
+            st = run_backward(c, feat, loc, w, grad_out.contiguous(), need_feat, need_loc, need_w,
+                              {}, current_stream(), &g);
+        } catch (const py::builtin_exception& e) {
+            bad = e.what();
+        }
+        if (st != MSDA_OK || !bad.empty()) raise_python(st, bad);
+        if (g.w.defined() && g.w.scalar_type() != w.scalar_type()) g.w = g.w.to(w.scalar_type());
+    }
+    return {g.feat, g.loc, g.w};
+}
+
+// The backward as compiled autograd calls it from its graph: the call's
+// description taken from the node's saved data, where save put it.
+struct MsdaBackward : torch::autograd::Function<MsdaBackward> {
+    static void save(const Call& c, torch::autograd::AutogradContext* ctx) {
+        std::vector<int64_t> v = {c.num_cams, c.num_levels, c.deterministic, c.logits, c.has_tile,
+                                  c.tile.waves_per_anchor, c.tile.chans_per_lane, c.tile.order,
+                                  c.tile.scatter};
+        v.insert(v.end(), c.host_shapes.begin(), c.host_shapes.end());
+        v.insert(v.end(), c.host_starts.begin(), c.host_starts.end());
+        ctx->saved_data["call"] = std::move(v);
+        ctx->saved_data["shapes"] = c.shapes;
+        ctx->saved_data["starts"] = c.starts;
+        if (c.level_scale) ctx->saved_data["level_scale"] = *c.level_scale;
+    }
+
+    static Call saved(torch::autograd::AutogradContext* ctx) {
+        const auto v = ctx->saved_data["call"].toIntVector();
+        Call c;
+        c.num_cams = (int)v[0];
+        c.num_levels = (int)v[1];
+        c.deterministic = v[2];
+        c.logits = v[3];
+        c.has_tile = v[4];
+        c.tile = msda_tile{};
+        c.tile.waves_per_anchor = (int32_t)v[5];
+        c.tile.chans_per_lane = (int32_t)v[6];
+        c.tile.order = (int32_t)v[7];
+        c.tile.scatter = (int32_t)v[8];
+        const auto host = v.begin() + 9;
+        const size_t n = (size_t)c.num_cams * (size_t)c.num_levels;
+        c.host_shapes.assign(host, host + 2 * n);
+        c.host_starts.assign(host + 2 * n, v.end());
+        c.shapes = ctx->saved_data["shapes"].toTensor();
+        c.starts = ctx->saved_data["starts"].toTensor();
+        const auto scale = ctx->saved_data.find("level_scale");
+        if (scale != ctx->saved_data.end()) c.level_scale = scale->second.toTensor();
+        return c;
+    }
+
+    static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx,
+                                                   torch::autograd::variable_list grads) {
+        const auto t = ctx->get_saved_variables();
+        return call_backward(saved(ctx), t[0], t[1], t[2], grads[0], ctx->needs_input_grad(0),
+                             ctx->needs_input_grad(1), ctx->needs_input_grad(2));
+    }
+};
+
+// The autograd node of one call: torch's node of a C++ function (saved-tensor
+// hooks, version checks, compiled autograd), the call's description beside it.
+// The plain engine's pass reads that; it becomes saved data (a table of boxed
+// values) only for compiled autograd, which takes the node apart: filling and
+// reading the table on every call took 4.5 of a small step's 72 us.
+struct MsdaNode : torch::autograd::CppNode<MsdaBackward> {
     Call call;
-    torch::autograd::SavedVariable feat, loc, w;
-    std::vector<int64_t> out_sizes;
-    at::TensorOptions out_options;
 
     std::string name() const override { return "MSDABackward"; }
 
-    void release_variables() override {
-        feat.reset_data();
-        loc.reset_data();
-        w.reset_data();
-    }
-
     torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
-        const Tensor f = feat.unpack(), l = loc.unpack(), x = w.unpack();
-        const bool nf = should_compute_output(0), nl = should_compute_output(1),
-                   nw = should_compute_output(2);
-        Grads g;
-        if (nf || nl || nw) {
-            const Tensor go =
-                grads[0].defined() ? grads[0].contiguous() : at::zeros(out_sizes, out_options);
-            std::string bad;
-            msda_status st = MSDA_OK;
-            try {
-                st = run_backward(call, f, l, x, go, nf, nl, nw, {}, current_stream(), &g);
-            } catch (const py::builtin_exception& e) {
-                bad = e.what();
-            }
-            if (st != MSDA_OK || !bad.empty()) raise(st, bad);
-            if (g.w.defined() && g.w.scalar_type() != x.scalar_type())
-                g.w = g.w.to(x.scalar_type());
-        }
-        return {g.feat, g.loc, g.w};
+        std::lock_guard<std::mutex> lock(mutex_);      // as release_variables takes it
+        const auto t = ctx_.get_saved_variables();
+        const Tensor go = grads[0].defined()
+                              ? grads[0]
+                              : at::zeros({t[1].size(0), t[1].size(1), t[0].size(2)},
+                                          t[1].options());
+        return call_backward(call, t[0], t[1], t[2], go, should_compute_output(0),
+                             should_compute_output(1), should_compute_output(2));
     }
 
-    // The engine's threads hold no interpreter lock: the Python error is set
-    // under it and travels with the exception.
-    [[noreturn]] static void raise(msda_status st, const std::string& bad) {
-        py::gil_scoped_acquire lock;
-        if (!bad.empty()) {
-            PyErr_SetString(PyExc_ValueError, bad.c_str());
-        } else {
-            try {
-                check(st);
-            } catch (py::error_already_set& e) {
-                e.restore();
-            }
-        }
-        python_error e;
-        e.persist();
-        throw e;
+    void compiled_args(torch::dynamo::autograd::CompiledNodeArgs& args) const override {
+        MsdaBackward::save(call, const_cast<torch::autograd::AutogradContext*>(&ctx_));
+        CppNode::compiled_args(args);
     }
 };
 
@@ -325,17 +379,18 @@ Tensor py_msda(const Tensor& feat, const py::handle& layout, const Tensor& loc, 
     c.deterministic = false;                    // the forward knows no such flag
     check(run_forward(c, feat, loc, w, {}, current_stream(), &out));
     if (torch::autograd::compute_requires_grad(feat, loc, w)) {
-        auto node = std::shared_ptr<MsdaBackward>(new MsdaBackward(), torch::autograd::deleteNode);
+        auto node = std::shared_ptr<MsdaNode>(new MsdaNode(), torch::autograd::deleteNode);
         node->set_next_edges(torch::autograd::collect_next_edges(feat, loc, w));
+        node->set_ctx_grad_fn(node);
         c.deterministic = deterministic;
+        set_tile(&c, tile_backward);
         node->call = std::move(c);
-        set_tile(&node->call, tile_backward);
-        node->feat = torch::autograd::SavedVariable(feat, false);
-        node->loc = torch::autograd::SavedVariable(loc, false);
-        node->w = torch::autograd::SavedVariable(w, false);
-        node->out_sizes = out.sizes().vec();
-        node->out_options = out.options();
+        node->ctx_.save_for_backward({feat, loc, w});
+        node->is_variable_input_ = {true, true, true};
+        for (const Tensor& t : {feat, loc, w}) node->input_info_.emplace_back(t);
         torch::autograd::set_history(out, node);
+        node->output_info_.emplace_back(out);
+        node->save_variables_to_ctx();
     }
     return out;
 }
