@@ -232,6 +232,14 @@ Call make_call(const py::handle& layout, optional<Tensor> level_scale, bool dete
     return c;
 }
 
+// f() without the interpreter lock: allocating and enqueueing can wait for the
+// device, and other Python threads need not.
+template <class F>
+auto unlocked(F&& f) {
+    py::gil_scoped_release free;
+    return f();
+}
+
 void* stream_or_current(optional<int64_t> s) { return s ? (void*)*s : current_stream(); }
 
 Tensor py_forward(const Tensor& feat, const py::handle& layout, const Tensor& loc, const Tensor& w,
@@ -241,7 +249,9 @@ Tensor py_forward(const Tensor& feat, const py::handle& layout, const Tensor& lo
     if (level_scale) need("level_scale", *level_scale, at::kFloat);
     const Call c = make_call(layout, std::move(level_scale), false, logits, tile);
     Tensor result = out ? *out : Tensor();
-    check(run_forward(c, feat, loc, w, workspace, stream_or_current(stream), &result));
+    check(unlocked([&] {
+        return run_forward(c, feat, loc, w, workspace, stream_or_current(stream), &result);
+    }));
     return result;
 }
 
@@ -252,8 +262,10 @@ py::tuple py_backward(const Tensor& feat, const py::handle& layout, const Tensor
                       optional<int64_t> stream, bool logits) {
     const Call c = make_call(layout, std::move(level_scale), deterministic, logits, tile);
     Grads g;
-    check(run_backward(c, feat, loc, w, grad_out, need_feat, need_loc, need_w, workspace,
-                       stream_or_current(stream), &g));
+    check(unlocked([&] {
+        return run_backward(c, feat, loc, w, grad_out, need_feat, need_loc, need_w, workspace,
+                            stream_or_current(stream), &g);
+    }));
     auto or_none = [](const Tensor& t) { return t.defined() ? py::cast(t) : py::none(); };
     return py::make_tuple(or_none(g.feat), or_none(g.loc), or_none(g.w));
 }
@@ -377,7 +389,7 @@ Tensor py_msda(const Tensor& feat, const py::handle& layout, const Tensor& loc, 
     Call c = make_call(layout, std::move(level_scale), deterministic, logits, tile_forward);
     Tensor out;
     c.deterministic = false;                    // the forward knows no such flag
-    check(run_forward(c, feat, loc, w, {}, current_stream(), &out));
+    check(unlocked([&] { return run_forward(c, feat, loc, w, {}, current_stream(), &out); }));
     if (torch::autograd::compute_requires_grad(feat, loc, w)) {
         auto node = std::shared_ptr<MsdaNode>(new MsdaNode(), torch::autograd::deleteNode);
         node->set_next_edges(torch::autograd::collect_next_edges(feat, loc, w));

@@ -1,5 +1,8 @@
 """The native autograd node where something other than the plain engine runs
-it: compiled autograd gives the engine's own gradients."""
+it: compiled autograd gives the engine's own gradients. And no call of the
+library is made with the interpreter lock held."""
+import ctypes
+
 import pytest
 import torch
 
@@ -43,3 +46,20 @@ def test_compiled_autograd(ops, needs, kw):
             out.backward(go)
         for x, y in zip(ask, ref):
             assert torch.equal(x.grad, y)
+
+
+def test_interpreter_lock_is_free_in_the_library(ops):
+    t, layout, go = operands()
+    feat, loc, w = (x.detach() for x in t)
+    lib = ops._lib.load()
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    sizes = address(lib.msda_forward_workspace_size), address(lib.msda_backward_workspace_size)
+    holds = address(ctypes.pythonapi.PyGILState_Check)     # as a status: 0 is OK, 1 an error
+    side = ops._lib.torch_side()
+    side.bind(holds, sizes[0], holds, sizes[1])
+    try:
+        ops.forward(feat, layout, loc, w)
+        ops.backward(feat, layout, loc, w, go)
+        torch.autograd.grad(ops.msda(t[0], layout, t[1], t[2]), t, go)
+    finally:
+        side.bind(address(lib.msda_forward_ws), sizes[0], address(lib.msda_backward), sizes[1])
