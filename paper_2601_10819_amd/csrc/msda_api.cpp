@@ -1169,8 +1169,8 @@ msda_status msda_quantize_fp8(const float* feat_f32, const int32_t* spatial_shap
 namespace {
 
 struct BatchWs {
-    size_t anchor_start, sample_start, region_start, row_start, cell_start, slot_scene,
-        slot_region, tile_start, magic, magic_shift, keys_a, keys_b, vals_a, vals_b, frac, off, scratch, part,
+    size_t anchor_start, sample_start, region_start, row_start, slot_start, slot_first, cell_start,
+        slot_scene, slot_region, tile_start, magic, magic_shift, keys_a, keys_b, vals_a, vals_b, frac, off, scratch, part,
         wstats, w32, total;
 };
 
@@ -1191,6 +1191,8 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
     w.sample_start = take((S + 1) * 4);
     w.region_start = take((S + 1) * 4);
     w.row_start = take((S + 1) * 8);
+    w.slot_start = take(msda::kSlots * (S + 1) * 8);
+    w.slot_first = take(msda::kSlots * S * 8);
     w.cell_start = take(regions * 4);
     w.slot_scene = take(regions * 4);
     w.slot_region = take(regions * 4);
@@ -1216,7 +1218,7 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
 // Sizes of a validated batch.
 struct BatchPlan {
     uint64_t anchors, samples, regions, cells, tiles, heavy_tiles;
-    uint64_t fwd_rows, bwd_rows;  // view-order units of all scenes
+    uint64_t slot_units;          // view-order units in a slot, at most
     int max_cams;
     int cpl, waves;
     int64_t max_batch_bytes;
@@ -1243,6 +1245,7 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
     *p = BatchPlan{};
     p->keys_fit = true;
     const int eb = elem_bytes(b->feat_dtype);
+    uint64_t slot_units[msda::kSlots] = {};
     for (int s = 0; s < b->num_scenes; ++s) {
         const msda_scene& sc = b->host_scenes[s];
         msda_desc d = {};
@@ -1274,12 +1277,14 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
         if (!aligned(sc.feat, 16))
             return fail(MSDA_ERR_UNSUPPORTED, "scene %d: feat must be 16-byte aligned", s);
         p->anchors += (uint64_t)sc.num_anchors;
-        p->fwd_rows += (uint64_t)sc.num_anchors * (uint64_t)msda::fwd_rows(sc.num_cams, b->num_points, b->num_levels);
+        const int rows = backward ? msda::bwd_rows(sc.num_cams, b->num_points)
+                                  : msda::fwd_rows(sc.num_cams, b->num_points, b->num_levels);
+        const msda::SlotCuts cuts =
+            msda::UnitGroup{1, sc.num_cams, sc.num_anchors, rows, 0, rows}.cuts();
+        for (int x = 0; x < msda::kSlots; ++x) slot_units[x] += cuts.first[x + 1] - cuts.first[x];
         // sized as for the single call: at least kMinFwdRows rows an anchor
         p->part_bytes += (uint64_t)sc.num_anchors *
                          (uint64_t)std::max(msda::max_fwd_rows(sc.num_cams), msda::kMinFwdRows);
-        p->bwd_rows += (uint64_t)sc.num_anchors *
-                       (uint64_t)msda::bwd_rows(sc.num_cams, b->num_points);
         p->samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams * b->num_levels;
         p->regions += (uint64_t)sc.num_cams * b->num_levels;
         p->max_cams = std::max(p->max_cams, sc.num_cams);
@@ -1317,6 +1322,7 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
         }
     }
     (void)eb;
+    p->slot_units = *std::max_element(std::begin(slot_units), std::end(slot_units));
     if (p->regions > (uint64_t)msda::kMaxBatchRegions)
         return fail(MSDA_ERR_UNSUPPORTED, "%llu (camera, level) regions in the batch (limit %d)",
                     (unsigned long long)p->regions, msda::kMaxBatchRegions);
@@ -1373,6 +1379,8 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, bool backward, cha
     a->t.sample_start = reinterpret_cast<uint32_t*>(ws + w.sample_start);
     a->t.region_start = reinterpret_cast<uint32_t*>(ws + w.region_start);
     a->t.row_start = reinterpret_cast<uint64_t*>(ws + w.row_start);
+    a->t.slot_start = reinterpret_cast<uint64_t*>(ws + w.slot_start);
+    a->t.slot_first = reinterpret_cast<uint64_t*>(ws + w.slot_first);
     a->t.cell_start = reinterpret_cast<uint32_t*>(ws + w.cell_start);
     a->t.slot_scene = reinterpret_cast<uint32_t*>(ws + w.slot_scene);
     a->t.slot_region = reinterpret_cast<uint32_t*>(ws + w.slot_region);
@@ -1380,7 +1388,7 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, bool backward, cha
     a->t.magic = reinterpret_cast<uint64_t*>(ws + w.magic);
     a->t.magic_shift = reinterpret_cast<uint32_t*>(ws + w.magic_shift);
     a->total_anchors = (uint32_t)p.anchors;
-    a->total_rows = backward ? p.bwd_rows : p.fwd_rows;
+    a->slot_units = p.slot_units;
     a->total_samples = (uint32_t)p.samples;
     a->total_cells = (uint32_t)p.cells;
     a->total_regions = (uint32_t)p.regions;

@@ -33,8 +33,10 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
     __shared__ uint16_t sh_h[kMaxBatchRegions];
     __shared__ uint16_t sh_w[kMaxBatchRegions];
     __shared__ u32 grp[2 * 8 * kMaxBatchScenes];    // first slot of (class, level, scene)
-    __shared__ u32 tiles[kMaxBatchRegions];         // tiles of each slot, then their scan
+    __shared__ __align__(8) u32 tiles[kMaxBatchRegions];   // tiles of each slot, then their scan
     __shared__ u32 lds4[4];
+    static_assert(2 * kSlots * kMaxBatchScenes <= kMaxBatchRegions, "slot_first shares tiles' space");
+    u64* const slot_first = reinterpret_cast<u64*>(tiles); // first unit of (XCD slot, scene)
     const int S = b.S, L = b.L, tid = threadIdx.x;
 
     for (int s = tid; s < S; s += blockDim.x) {
@@ -54,15 +56,8 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
             rows += (u64)(backward ? bwd_rows((int)s_cams[s], b.P) : fwd_rows((int)s_cams[s], b.P, L)) *
                     s_anchors[s];
             a += s_anchors[s];
-            const u32 per_anchor = (u32)b.P * s_cams[s] * (u32)L;
-            smp += s_anchors[s] * per_anchor;
+            smp += s_anchors[s] * ((u32)b.P * s_cams[s] * (u32)L);
             reg += s_cams[s] * (u32)L;
-            // s / per_anchor for s < 2^30 as (s * m) >> k, m = ceil(2^k / d)
-            int lg = 0;
-            while ((1u << lg) < per_anchor) ++lg;
-            const int k = 32 + lg;
-            b.t.magic[s] = ((1ull << k) + per_anchor - 1) / per_anchor;
-            b.t.magic_shift[s] = (u32)k;
         }
         b.t.anchor_start[S] = a;
         b.t.sample_start[S] = smp;
@@ -71,7 +66,53 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
         rstart[S] = reg;
     }
     __syncthreads();
+    // the XCD slots' ranges, every scene cut on its own: its first unit in each
+    // slot, and (32 threads a slot) a slot's units before each scene
+    auto scene_units = [&](int s) {
+        const int N = (int)s_cams[s];
+        const int rows = backward ? bwd_rows(N, b.P) : fwd_rows(N, b.P, L);
+        return UnitGroup{1, N, (int)s_anchors[s], rows, 0, rows};
+    };
+    for (int i = tid; i < kSlots * S; i += blockDim.x) {
+        slot_first[i] = scene_units(i % S).first(i / S);
+        b.t.slot_first[i] = slot_first[i];
+    }
+    __syncthreads();
+    {
+        static_assert(kSlots * 32 == 256, "32 threads a slot");
+        const int x = tid >> 5, sl = tid & 31, per = (S + 31) / 32;
+        const int s0 = min(sl * per, S), s1 = min(s0 + per, S);
+        auto units = [&](int s) {
+            return (x + 1 < kSlots ? slot_first[(x + 1) * S + s] : scene_units(s).units()) -
+                   slot_first[x * S + s];
+        };
+        u64 sum = 0;
+        for (int s = s0; s < s1; ++s) sum += units(s);
+        u64 run = sum;
+#pragma unroll
+        for (int d = 1; d < 32; d <<= 1) {
+            const u64 t = __shfl_up(run, d, 32);
+            if (sl >= d) run += t;
+        }
+        u64* start = b.t.slot_start + x * (S + 1);
+        if (sl == 31) start[S] = run;
+        run -= sum;
+        for (int s = s0; s < s1; ++s) {
+            start[s] = run;
+            run += units(s);
+        }
+    }
     if (!backward) return;
+    for (int s = tid; s < S; s += blockDim.x) {
+        // sample / per_anchor for a sample < 2^30 as (sample * m) >> k, m = ceil(2^k / d)
+        const u32 per_anchor = (u32)b.P * s_cams[s] * (u32)L;
+        int lg = 0;
+        while ((1u << lg) < per_anchor) ++lg;
+        const int k = 32 + lg;
+        b.t.magic[s] = ((1ull << k) + per_anchor - 1) / per_anchor;
+        b.t.magic_shift[s] = (u32)k;
+    }
+    __syncthreads();
 
     const u32 R = rstart[S];
     // (H, W) of every region

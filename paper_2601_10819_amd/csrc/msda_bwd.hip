@@ -43,12 +43,12 @@ __global__ void __launch_bounds__(512) msda_bwd_kernel(OpArgs a) {
 // cameras of batch item b (bwd_rows), cut camera-major into one range per XCD.
 // Every output is per sample or per pair, so the rows need no combining.
 template <class FT, int CPL>
-__global__ void __launch_bounds__(512) msda_bwd_view_kernel(OpArgs a, int rows) {
+__global__ void __launch_bounds__(512) msda_bwd_view_kernel(OpArgs a, SlotCuts cuts,
+                                                            int rows) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
-    const u64 T = (u64)a.B * (u32)rows * (u32)a.A;
-    const u64 u = slot_unit(T, blockIdx.x, wave, nwaves);
-    if (u >= T) return;
+    const u64 u = slot_unit(cuts, blockIdx.x, wave, nwaves);
+    if (u == kNoUnit) return;
     const RowUnit t = row_unit(u, a.A);
     const int b = (int)(t.row / (u32)rows);
     const CamRange n = row_cams(a.N, (int)(t.row % (u32)rows), rows);
@@ -70,17 +70,16 @@ __global__ void __launch_bounds__(512) msda_bwd_batched_kernel(BatchArgs b) {
     }
 }
 
-// Batched backward gather in view order: the units of all scenes, scene by
-// scene, cut into one range per XCD.
+// Batched backward gather in view order: each scene's units cut into one range
+// per XCD, an XCD's ranges one after the other.
 template <class FT, int CPL>
 __global__ void __launch_bounds__(512) msda_bwd_batched_view_kernel(BatchArgs b) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
-    const u64 u = slot_unit(b.total_rows, blockIdx.x, wave, nwaves);
-    if (u >= b.total_rows) return;
-    const int s = scene_of_row(b.t.row_start, b.S, u);
-    const OpArgs a = scene_view(b, s, FT::kBytes);
-    const RowUnit t = row_unit(u - b.t.row_start[s], a.A);
+    const SceneUnit su = scene_unit(b, blockIdx.x, wave, nwaves);
+    if (su.s < 0) return;
+    const OpArgs a = scene_view(b, su.s, FT::kBytes);
+    const RowUnit t = row_unit(su.u, a.A);
     const CamRange n = row_cams(a.N, (int)t.row, bwd_rows(a.N, a.P));
     const int np = (n.hi - n.lo) * a.P;
     grads_of<FT, CPL>(a, grad_anchor<FT>(a, 0, t.a),
@@ -123,10 +122,10 @@ hipError_t launch_backward(const OpArgs& a, int dtype, int cpl, int waves, hipSt
 template <class FT, int CPL>
 static hipError_t bwd_view_launch(const OpArgs& a, int waves, hipStream_t s) {
     const int rows = bwd_rows(a.N, a.P);
+    const SlotCuts cuts = UnitGroup{a.B, a.N, a.A, rows, 0, rows}.cuts();
     mark_begin("msda_bwd_view_kernel", s);
-    hipLaunchKernelGGL((msda_bwd_view_kernel<FT, CPL>),
-                       dim3(slot_blocks((uint64_t)a.B * (uint32_t)rows * (uint32_t)a.A, waves)),
-                       dim3(64 * waves), (size_t)waves * grads_lds_bytes(a.G), s, a, rows);
+    hipLaunchKernelGGL((msda_bwd_view_kernel<FT, CPL>), dim3(slot_blocks(cuts.most(), waves)),
+                       dim3(64 * waves), (size_t)waves * grads_lds_bytes(a.G), s, a, cuts, rows);
     mark_end(s);
     return hipGetLastError();
 }
@@ -159,7 +158,7 @@ template <class FT, int CPL>
 static hipError_t bwd_batched_view_launch(const BatchArgs& b, int waves, hipStream_t s) {
     mark_begin("msda_bwd_batched_view_kernel", s);
     hipLaunchKernelGGL((msda_bwd_batched_view_kernel<FT, CPL>),
-                       dim3(slot_blocks(b.total_rows, waves)), dim3(64 * waves),
+                       dim3(slot_blocks(b.slot_units, waves)), dim3(64 * waves),
                        (size_t)waves * grads_lds_bytes(b.G), s, b);
     mark_end(s);
     return hipGetLastError();

@@ -376,13 +376,20 @@ __device__ __forceinline__ u32 block_inclusive_scan(u32 v, u32* lds4, u32* total
 
 // ---------------------------------------------------------------- view order
 
-// The XCD slot x of a workgroup (the hardware hands workgroups to the XCDs
-// round-robin) takes the x-th of kSlots equal ranges of T units: this wave's
-// unit, or T.
-__device__ __forceinline__ u64 slot_unit(u64 T, u32 block, int wave, int nwaves) {
+constexpr u64 kNoUnit = ~(u64)0;
+
+// This wave's unit in the range of its workgroup's XCD slot x (the hardware
+// hands workgroups to the XCDs round-robin), or kNoUnit.
+__device__ __forceinline__ u64 slot_unit(const SlotCuts& cuts, u32 block, int wave, int nwaves) {
     const u32 x = block % kSlots;
-    const u64 u = T * x / kSlots + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
-    return u < T * (x + 1) / kSlots ? u : T;
+    u64 first = cuts.first[0], end = cuts.first[1];
+#pragma unroll
+    for (u32 k = 1; k < kSlots; ++k) {
+        first = x == k ? cuts.first[k] : first;
+        end = x == k ? cuts.first[k + 1] : end;
+    }
+    const u64 u = first + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
+    return u < end ? u : kNoUnit;
 }
 
 // Unit u of a view-order launch as (row, anchor), units row-major: both the
@@ -417,14 +424,24 @@ __device__ __forceinline__ int scene_of(const u32* start, int S, u32 item) {
     return lo;
 }
 
-// The same for a row index (start: 64-bit prefix table), wave-uniform.
-__device__ __forceinline__ int scene_of_row(const u64* start, int S, u64 u) {
-    int lo = 0, hi = S - 1;
+// This wave's unit of a batch: its scene and the unit's number in the scene, both
+// the same across the wave; scene -1 past the slot's end. A slot's units are
+// its ranges of the scenes, one after the other.
+struct SceneUnit { int s; u64 u; };
+
+__device__ __forceinline__ SceneUnit scene_unit(const BatchArgs& b, u32 block, int wave,
+                                                int nwaves) {
+    const u32 x = block % kSlots;
+    const u64 i = (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
+    const u64* start = b.t.slot_start + x * (u32)(b.S + 1);
+    if (i >= start[b.S]) return SceneUnit{-1, 0};
+    int lo = 0, hi = b.S - 1;                       // the last scene with start <= i
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (start[mid] <= u) lo = mid; else hi = mid - 1;
+        if (start[mid] <= i) lo = mid; else hi = mid - 1;
     }
-    return uniform(lo);
+    const int s = uniform(lo);
+    return SceneUnit{s, b.t.slot_first[x * (u32)b.S + (u32)s] + (i - start[s])};
 }
 
 // Scene s of a batch as a single-call argument set with B = 1.

@@ -82,13 +82,13 @@ __global__ void __launch_bounds__(512) msda_fwd_kernel(OpArgs a, int chunk) {
 // View order: rows [row0, row0 + nrows) of every batch item, of `rows` in
 // all; unit (b*nrows + j)*A + a, the partial row of that index in part.
 template <class FT, int CPL>
-__global__ void __launch_bounds__(512) msda_fwd_view_kernel(OpArgs a, int rows, int row0,
-                                                            int nrows, int chunk, float* part) {
+__global__ void __launch_bounds__(512) msda_fwd_view_kernel(OpArgs a, SlotCuts cuts,
+                                                            int rows, int row0, int nrows,
+                                                            int chunk, float* part) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
-    const u64 T = (u64)a.B * (u32)nrows * (u32)a.A;
-    const u64 u = slot_unit(T, blockIdx.x, wave, nwaves);
-    if (u >= T) return;
+    const u64 u = slot_unit(cuts, blockIdx.x, wave, nwaves);
+    if (u == kNoUnit) return;
     const RowUnit t = row_unit(u, a.A);
     const int b = (int)(t.row / (u32)nrows);
     const CamRange n = row_cams(a.N, row0 + (int)(t.row % (u32)nrows), rows);
@@ -147,19 +147,21 @@ __global__ void __launch_bounds__(512) msda_fwd_batched_kernel(BatchArgs b, int 
     }
 }
 
-// Batched forward in view order: the units of all scenes, scene by scene,
-// cut into one range per XCD. Per anchor the arithmetic is the single call's
-// view order with B = 1.
+// Batched forward in view order: each scene's units cut into one range per XCD,
+// as the single call's, and an XCD's ranges one after the other (one cut
+// through all scenes left the XCDs whose scenes have larger maps behind: the
+// 12-scene step 8.93 -> 8.62 ms, five scenes of 5 to 25 cameras FP32 135 ->
+// 114 us, BF16 317 -> 263). Per anchor the arithmetic is the single call's view
+// order with B = 1.
 template <class FT, int CPL>
 __global__ void __launch_bounds__(512) msda_fwd_batched_view_kernel(BatchArgs b, int chunk,
                                                                     float* part) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
-    const u64 u = slot_unit(b.total_rows, blockIdx.x, wave, nwaves);
-    if (u >= b.total_rows) return;
-    const int s = scene_of_row(b.t.row_start, b.S, u);
-    const OpArgs a = scene_view(b, s, FT::kBytes);
-    const RowUnit t = row_unit(u - b.t.row_start[s], a.A);
+    const SceneUnit su = scene_unit(b, blockIdx.x, wave, nwaves);
+    if (su.s < 0) return;
+    const OpArgs a = scene_view(b, su.s, FT::kBytes);
+    const RowUnit t = row_unit(su.u, a.A);
     const CamRange n = row_cams(a.N, (int)t.row, fwd_rows(a.N, a.P, a.L));
     const Lanes q = lanes_of<FT, CPL>(a);
     const rsrc_t feat = make_rsrc(a.feat, a.batch_bytes);
@@ -168,7 +170,7 @@ __global__ void __launch_bounds__(512) msda_fwd_batched_view_kernel(BatchArgs b,
     row_sum<FT, CPL>(a, (size_t)t.a, feat, n.lo * NS, n.hi * NS, q, chunk,
                      smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
     if (q.sub == 0) {
-        float* dst = part + u * (u32)b.C + q.c0;
+        float* dst = part + (b.t.row_start[su.s] + su.u) * (u32)b.C + q.c0;
 #pragma unroll
         for (int i = 0; i < CPL; ++i) dst[i] = acc[i];
     }
@@ -214,7 +216,7 @@ static hipError_t fwd_batched_view_launch(const BatchArgs& b, int waves, float* 
     const int chunk = fwd_chunk_samples(waves, b.G);
     mark_begin("msda_fwd_batched_view_kernel", s);
     hipLaunchKernelGGL((msda_fwd_batched_view_kernel<FT, CPL>),
-                       dim3(slot_blocks(b.total_rows, waves)), dim3(64 * waves),
+                       dim3(slot_blocks(b.slot_units, waves)), dim3(64 * waves),
                        (size_t)waves * row_lds_bytes(chunk, b.G), s, b, chunk, part);
     mark_end(s);
     hipError_t e = hipGetLastError();
@@ -259,11 +261,11 @@ static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, flo
     const size_t AC = (size_t)a.A * a.C, total = AC * a.B;
     for (int row0 = 0; row0 < rows; row0 += part_rows) {
         const int nrows = part_rows < rows - row0 ? part_rows : rows - row0;
+        const SlotCuts cuts = UnitGroup{a.B, a.N, a.A, rows, row0, nrows}.cuts();
         mark_begin("msda_fwd_view_kernel", s);
-        hipLaunchKernelGGL((msda_fwd_view_kernel<FT, CPL>),
-                           dim3(slot_blocks((u64)a.B * (u32)nrows * (u32)a.A, waves)),
-                           dim3(64 * waves), (size_t)waves * row_lds_bytes(chunk, a.G), s, a, rows,
-                           row0, nrows, chunk, part);
+        hipLaunchKernelGGL((msda_fwd_view_kernel<FT, CPL>), dim3(slot_blocks(cuts.most(), waves)),
+                           dim3(64 * waves), (size_t)waves * row_lds_bytes(chunk, a.G), s, a, cuts,
+                           rows, row0, nrows, chunk, part);
         mark_end(s);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -18,6 +18,114 @@ namespace msda {
 constexpr uint32_t kMaxRowBytes = 4096u;
 constexpr uint32_t kOOB = 0xFFFFE000u;
 
+// ---------------------------------------------------------------- view order
+//
+// In view order the work of a call is cut, camera-major, into kSlots
+// contiguous ranges of equal work. Range x runs on the workgroups whose index
+// is x modulo kSlots: the hardware hands workgroups to the chip's kSlots XCDs
+// round-robin, so a range stays on one XCD and its L2 holds the pyramids of
+// the few cameras the range is working through instead of every camera's. A
+// unit of work, one wave's, is one anchor over a row of cameras.
+constexpr int kSlots = 8;
+
+// The units of slot x: [first[x], first[x + 1]).
+struct SlotCuts {
+    uint64_t first[kSlots + 1];
+
+    // the most of a slot
+    uint64_t most() const {
+        uint64_t m = 0;
+        for (int x = 0; x < kSlots; ++x) {
+            const uint64_t n = first[x + 1] - first[x];
+            if (n > m) m = n;
+        }
+        return m;
+    }
+};
+
+// Units numbered row by row: those of B batch items of N cameras and A anchors,
+// rows [row0, row0 + nrows) of `rows`, row j the cameras [N*j/rows,
+// N*(j+1)/rows). They are cut into ranges of equal work, not of equal numbers
+// of units: where the cameras are no multiple of the rows, rows differ in
+// length, and the slots that got the long ones ended the launch (900 anchors,
+// 9 cameras of 256 x 448, FP32 forward 133 -> 89 us, 12 of 512 x 704 with 5
+// levels 224 -> 185). A camera of an anchor counts kCamWork and a unit by
+// itself kUnitWork: 10, 17 and 25 cameras take 96, 158 and 229 us with 4 and 1,
+// 103, 148 and 221 with the cameras alone; 133, 192 and 274 by units.
+constexpr uint32_t kCamWork = 4, kUnitWork = 1;
+
+struct UnitGroup {
+    int B, N, A, rows, row0, nrows;
+    __host__ __device__ uint64_t units() const {
+        return (uint64_t)B * (uint32_t)nrows * (uint32_t)A;
+    }
+    // of an anchor's units in the rows before j
+    __host__ __device__ uint32_t before(int j) const {
+        const uint32_t cams = (uint32_t)(N * j) / (uint32_t)rows -
+                              (uint32_t)(N * row0) / (uint32_t)rows;
+        return kCamWork * cams + kUnitWork * (uint32_t)(j - row0);
+    }
+    // the first unit of slot x
+    __host__ __device__ uint64_t first(int x) const {
+        if (x >= kSlots) return units();
+        const uint64_t item = (uint64_t)before(row0 + nrows) * (uint32_t)A;
+        const uint64_t w = (uint64_t)B * item / kSlots * (uint32_t)x;
+        if (w == 0) return 0;
+        const uint64_t b = B == 1 ? 0 : w / item, in = w - b * item;
+        int lo = row0, hi = row0 + nrows - 1;       // the last row with no more than `in` before it
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if ((uint64_t)before(mid) * (uint32_t)A <= in) lo = mid; else hi = mid - 1;
+        }
+        const uint64_t left = in - (uint64_t)before(lo) * (uint32_t)A;
+        const uint32_t unit = before(lo + 1) - before(lo);
+        return (b * (uint32_t)nrows + (uint32_t)(lo - row0)) * (uint32_t)A +
+               (left + unit - 1) / unit;
+    }
+    SlotCuts cuts() const {
+        SlotCuts c;
+        for (int x = 0; x <= kSlots; ++x) c.first[x] = first(x);
+        return c;
+    }
+};
+
+// Workgroups of `waves` waves for `most` units in every slot.
+inline unsigned slot_blocks(uint64_t most, int waves) {
+    return (unsigned)(kSlots * ((most + (uint64_t)waves - 1) / (uint64_t)waves));
+}
+
+// The forward: partial row j of a batch item with N cameras
+// covers cameras [N*j/rows, N*(j+1)/rows), and one wave sums one anchor over
+// one row. Rows are as short as the workspace's 8 rows per batch item allow
+// to grow: one camera for a multiple of 8 up to 64 cameras (a wave per camera
+// took 0.325 ms at the 64-camera scene in BF16, 2 cameras 0.332, 4 0.366, 8
+// 0.385; FP32 0.577, 0.649, 0.752), and at most 64 rows so that the
+// workspace stays bounded (max_fwd_rows). Where a camera has few samples,
+// rather as many cameras as hold kMinRowSamples: a wave stages 64 samples at a
+// time, and every row is written and read once more. 49 cameras of 7 x 3
+// samples 70 -> 50 us, 63 of 7 x 4 45 -> 35, 26 of 11 x 4 173 -> 159, 53 of 11
+// x 4 355 -> 343 (with 32 samples 57, 35, 176, 348); 13 x 4 are a row.
+constexpr int kMinFwdRows = 8, kMaxFwdRows = 64, kMinRowSamples = 48;
+
+__host__ __device__ inline int max_fwd_rows(int N) {
+    return N < kMinFwdRows ? N : N >= kMaxFwdRows ? kMaxFwdRows : N / 8 * 8;
+}
+
+__host__ __device__ inline int fwd_rows(int N, int P, int L) {
+    const int rows = max_fwd_rows(N), cams = (kMinRowSamples + P * L - 1) / (P * L);
+    const int few = ((N + cams - 1) / cams + 7) / 8 * 8;
+    return few < rows ? few : rows;
+}
+
+// The backward, whose rows need no combining: one camera per row, or as many
+// as hold kMinRowPairs pairs where anchors have few keypoints.
+constexpr int kMinRowPairs = 7;
+
+__host__ __device__ inline int bwd_rows(int N, int P) {
+    const int cams = P >= kMinRowPairs ? 1 : (kMinRowPairs + P - 1) / P;
+    return (N + cams - 1) / cams;
+}
+
 // Everything one forward/backward launch needs. Pointers are device memory.
 struct OpArgs {
     const void* feat;             // [B][R][C], dtype below
@@ -98,6 +206,8 @@ struct BatchTables {
     uint32_t* sample_start;       // [S+1] first sample / record of each scene
     uint32_t* region_start;       // [S+1] first region of each scene
     uint64_t* row_start;          // [S+1] first view-order unit of each scene
+    uint64_t* slot_start;         // [kSlots][S+1] a slot's units before each scene
+    uint64_t* slot_first;         // [kSlots][S] the scene's first unit in the slot
     uint32_t* cell_start;         // [regions] first cell of each region (global)
     uint32_t* slot_scene;         // [regions] scene of each slot
     uint32_t* slot_region;        // [regions] region (within its scene) of each slot
@@ -112,7 +222,7 @@ struct BatchArgs {
     const float* level_scale;
     BatchTables t;
     uint32_t total_anchors;
-    uint64_t total_rows;          // view-order units: sum of fwd_rows (bwd_rows) * A
+    uint64_t slot_units;          // view-order units of all scenes in a slot, at most
     uint32_t total_samples;
     uint32_t total_cells;
     uint32_t total_regions;
@@ -147,54 +257,6 @@ struct ProjArgs {
     int32_t B, A, P, N;
     float dt;
 };
-
-// ---------------------------------------------------------------- view order
-//
-// In view order the work of a call is cut, camera-major, into kSlots
-// contiguous ranges of equal size. Range x runs on the workgroups whose index
-// is x modulo kSlots: the hardware hands workgroups to the chip's kSlots XCDs
-// round-robin, so a range stays on one XCD and its L2 holds the pyramids of
-// the few cameras the range is working through instead of every camera's. A
-// unit of work, one wave's, is one anchor over a row of cameras.
-constexpr int kSlots = 8;
-
-// Workgroups of `waves` waves for T units, a multiple of kSlots.
-inline unsigned slot_blocks(uint64_t T, int waves) {
-    const uint64_t per_slot = (T + kSlots - 1) / kSlots;
-    return (unsigned)(kSlots * ((per_slot + (uint64_t)waves - 1) / (uint64_t)waves));
-}
-
-// The forward: partial row j of a batch item with N cameras
-// covers cameras [N*j/rows, N*(j+1)/rows), and one wave sums one anchor over
-// one row. Rows are as short as the workspace's 8 rows per batch item allow
-// to grow: one camera for a multiple of 8 up to 64 cameras (a wave per camera
-// took 0.325 ms at the 64-camera scene in BF16, 2 cameras 0.332, 4 0.366, 8
-// 0.385; FP32 0.577, 0.649, 0.752), and at most 64 rows so that the
-// workspace stays bounded (max_fwd_rows). Where a camera has few samples,
-// rather as many cameras as hold kMinRowSamples: a wave stages 64 samples at a
-// time, and every row is written and read once more. 49 cameras of 7 x 3
-// samples 70 -> 50 us, 63 of 7 x 4 45 -> 35, 26 of 11 x 4 173 -> 159, 53 of 11
-// x 4 355 -> 343 (with 32 samples 57, 35, 176, 348); 13 x 4 are a row.
-constexpr int kMinFwdRows = 8, kMaxFwdRows = 64, kMinRowSamples = 48;
-
-__host__ __device__ inline int max_fwd_rows(int N) {
-    return N < kMinFwdRows ? N : N >= kMaxFwdRows ? kMaxFwdRows : N / 8 * 8;
-}
-
-__host__ __device__ inline int fwd_rows(int N, int P, int L) {
-    const int rows = max_fwd_rows(N), cams = (kMinRowSamples + P * L - 1) / (P * L);
-    const int few = ((N + cams - 1) / cams + 7) / 8 * 8;
-    return few < rows ? few : rows;
-}
-
-// The backward, whose rows need no combining: one camera per row, or as many
-// as hold kMinRowPairs pairs where anchors have few keypoints.
-constexpr int kMinRowPairs = 7;
-
-__host__ __device__ inline int bwd_rows(int N, int P) {
-    const int cams = P >= kMinRowPairs ? 1 : (kMinRowPairs + P - 1) / P;
-    return (N + cams - 1) / cams;
-}
 
 // Samples a wave of the forward stages at a time: 64 while `waves` waves' staging fits 64
 // KiB, else the largest power of two that does. At least 64 / lanes per
@@ -309,7 +371,7 @@ hipError_t launch_forward_batched(const BatchArgs& b, int dtype, int cpl, int wa
 hipError_t launch_backward_batched(const BatchArgs& b, int dtype, int cpl, int waves, int blocks,
                                    hipStream_t s);
 // Batched gathers in view order: one wave per unit of every scene, scenes in
-// order. The forward's partial rows go to part ([total_rows][C] FP32) and are
+// order. The forward's partial rows go to part ([units][C] FP32) and are
 // added into each scene's out.
 hipError_t launch_forward_batched_view(const BatchArgs& b, int dtype, int cpl, int waves,
                                        float* part, hipStream_t s);
