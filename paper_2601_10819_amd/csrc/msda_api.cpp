@@ -1281,7 +1281,7 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
                                   : msda::fwd_rows(sc.num_cams, b->num_points, b->num_levels);
         const msda::SlotCuts cuts =
             msda::UnitGroup{1, sc.num_cams, sc.num_anchors, rows, 0, rows}.cuts();
-        for (int x = 0; x < msda::kSlots; ++x) slot_units[x] += cuts.first[x + 1] - cuts.first[x];
+        for (int x = 0; x < msda::kSlots; ++x) slot_units[x] += cuts.end[x] - cuts.first[x];
         // sized as for the single call: at least kMinFwdRows rows an anchor
         p->part_bytes += (uint64_t)sc.num_anchors *
                          (uint64_t)std::max(msda::max_fwd_rows(sc.num_cams), msda::kMinFwdRows);

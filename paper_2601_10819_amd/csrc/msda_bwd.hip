@@ -123,11 +123,16 @@ template <class FT, int CPL>
 static hipError_t bwd_view_launch(const OpArgs& a, int waves, hipStream_t s) {
     const int rows = bwd_rows(a.N, a.P);
     const SlotCuts cuts = UnitGroup{a.B, a.N, a.A, rows, 0, rows}.cuts();
-    mark_begin("msda_bwd_view_kernel", s);
-    hipLaunchKernelGGL((msda_bwd_view_kernel<FT, CPL>), dim3(slot_blocks(cuts.most(), waves)),
-                       dim3(64 * waves), (size_t)waves * grads_lds_bytes(a.G), s, a, cuts, rows);
-    mark_end(s);
-    return hipGetLastError();
+    for (u64 at = 0; at < cuts.most(); at += kMaxSlotUnits) {
+        mark_begin("msda_bwd_view_kernel", s);
+        hipLaunchKernelGGL((msda_bwd_view_kernel<FT, CPL>),
+                           dim3(slot_blocks(cuts.most() - at, waves)), dim3(64 * waves),
+                           (size_t)waves * grads_lds_bytes(a.G), s, a, cuts.part(at), rows);
+        mark_end(s);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_backward_view(const OpArgs& a, int dtype, int cpl, int waves, hipStream_t s) {
@@ -155,13 +160,17 @@ static hipError_t bwd_batched_launch(const BatchArgs& b, int waves, int blocks, 
 }
 
 template <class FT, int CPL>
-static hipError_t bwd_batched_view_launch(const BatchArgs& b, int waves, hipStream_t s) {
-    mark_begin("msda_bwd_batched_view_kernel", s);
-    hipLaunchKernelGGL((msda_bwd_batched_view_kernel<FT, CPL>),
-                       dim3(slot_blocks(b.slot_units, waves)), dim3(64 * waves),
-                       (size_t)waves * grads_lds_bytes(b.G), s, b);
-    mark_end(s);
-    return hipGetLastError();
+static hipError_t bwd_batched_view_launch(BatchArgs b, int waves, hipStream_t s) {
+    for (b.slot_begin = 0; b.slot_begin < b.slot_units; b.slot_begin += kMaxSlotUnits) {
+        mark_begin("msda_bwd_batched_view_kernel", s);
+        hipLaunchKernelGGL((msda_bwd_batched_view_kernel<FT, CPL>),
+                           dim3(slot_blocks(b.slot_units - b.slot_begin, waves)),
+                           dim3(64 * waves), (size_t)waves * grads_lds_bytes(b.G), s, b);
+        mark_end(s);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_backward_batched_view(const BatchArgs& b, int dtype, int cpl, int waves,

@@ -382,11 +382,11 @@ constexpr u64 kNoUnit = ~(u64)0;
 // hands workgroups to the XCDs round-robin), or kNoUnit.
 __device__ __forceinline__ u64 slot_unit(const SlotCuts& cuts, u32 block, int wave, int nwaves) {
     const u32 x = block % kSlots;
-    u64 first = cuts.first[0], end = cuts.first[1];
+    u64 first = cuts.first[0], end = cuts.end[0];
 #pragma unroll
     for (u32 k = 1; k < kSlots; ++k) {
         first = x == k ? cuts.first[k] : first;
-        end = x == k ? cuts.first[k + 1] : end;
+        end = x == k ? cuts.end[k] : end;
     }
     const u64 u = first + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
     return u < end ? u : kNoUnit;
@@ -432,7 +432,7 @@ struct SceneUnit { int s; u64 u; };
 __device__ __forceinline__ SceneUnit scene_unit(const BatchArgs& b, u32 block, int wave,
                                                 int nwaves) {
     const u32 x = block % kSlots;
-    const u64 i = (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
+    const u64 i = b.slot_begin + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
     const u64* start = b.t.slot_start + x * (u32)(b.S + 1);
     if (i >= start[b.S]) return SceneUnit{-1, 0};
     int lo = 0, hi = b.S - 1;                       // the last scene with start <= i

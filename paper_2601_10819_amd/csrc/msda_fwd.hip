@@ -211,16 +211,18 @@ __global__ void __launch_bounds__(256) fwd_batched_view_reduce(BatchArgs b, cons
 }
 
 template <class FT, int CPL>
-static hipError_t fwd_batched_view_launch(const BatchArgs& b, int waves, float* part,
-                                          hipStream_t s) {
+static hipError_t fwd_batched_view_launch(BatchArgs b, int waves, float* part, hipStream_t s) {
     const int chunk = fwd_chunk_samples(waves, b.G);
-    mark_begin("msda_fwd_batched_view_kernel", s);
-    hipLaunchKernelGGL((msda_fwd_batched_view_kernel<FT, CPL>),
-                       dim3(slot_blocks(b.slot_units, waves)), dim3(64 * waves),
-                       (size_t)waves * row_lds_bytes(chunk, b.G), s, b, chunk, part);
-    mark_end(s);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    for (b.slot_begin = 0; b.slot_begin < b.slot_units; b.slot_begin += kMaxSlotUnits) {
+        mark_begin("msda_fwd_batched_view_kernel", s);
+        hipLaunchKernelGGL((msda_fwd_batched_view_kernel<FT, CPL>),
+                           dim3(slot_blocks(b.slot_units - b.slot_begin, waves)),
+                           dim3(64 * waves), (size_t)waves * row_lds_bytes(chunk, b.G), s, b,
+                           chunk, part);
+        mark_end(s);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     const size_t total = (size_t)b.total_anchors * b.C;
     mark_begin("fwd_batched_view_reduce", s);
     if (b.C % 4 == 0) {
@@ -262,13 +264,16 @@ static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, flo
     for (int row0 = 0; row0 < rows; row0 += part_rows) {
         const int nrows = part_rows < rows - row0 ? part_rows : rows - row0;
         const SlotCuts cuts = UnitGroup{a.B, a.N, a.A, rows, row0, nrows}.cuts();
-        mark_begin("msda_fwd_view_kernel", s);
-        hipLaunchKernelGGL((msda_fwd_view_kernel<FT, CPL>), dim3(slot_blocks(cuts.most(), waves)),
-                           dim3(64 * waves), (size_t)waves * row_lds_bytes(chunk, a.G), s, a, cuts,
-                           rows, row0, nrows, chunk, part);
-        mark_end(s);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        for (u64 at = 0; at < cuts.most(); at += kMaxSlotUnits) {
+            mark_begin("msda_fwd_view_kernel", s);
+            hipLaunchKernelGGL((msda_fwd_view_kernel<FT, CPL>),
+                               dim3(slot_blocks(cuts.most() - at, waves)), dim3(64 * waves),
+                               (size_t)waves * row_lds_bytes(chunk, a.G), s, a, cuts.part(at),
+                               rows, row0, nrows, chunk, part);
+            mark_end(s);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
         mark_begin("fwd_view_reduce", s);
         if (a.C % 4 == 0) {
             hipLaunchKernelGGL(fwd_rows_reduce<4>, dim3((unsigned)((total / 4 + 255) / 256)),
@@ -278,7 +283,8 @@ static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, flo
                                dim3(256), 0, s, part, a.out, a.B, nrows, AC, row0 > 0);
         }
         mark_end(s);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }

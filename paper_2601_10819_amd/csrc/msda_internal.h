@@ -28,18 +28,29 @@ constexpr uint32_t kOOB = 0xFFFFE000u;
 // unit of work, one wave's, is one anchor over a row of cameras.
 constexpr int kSlots = 8;
 
-// The units of slot x: [first[x], first[x + 1]).
+// A launch has fewer than 2^32 work-items; one of more waves than this goes in
+// parts.
+constexpr uint64_t kMaxLaunchWaves = 1u << 25, kMaxSlotUnits = kMaxLaunchWaves / kSlots;
+
+// The units of slot x: [first[x], end[x]).
 struct SlotCuts {
-    uint64_t first[kSlots + 1];
+    uint64_t first[kSlots], end[kSlots];
 
     // the most of a slot
     uint64_t most() const {
         uint64_t m = 0;
-        for (int x = 0; x < kSlots; ++x) {
-            const uint64_t n = first[x + 1] - first[x];
-            if (n > m) m = n;
-        }
+        for (int x = 0; x < kSlots; ++x)
+            if (end[x] - first[x] > m) m = end[x] - first[x];
         return m;
+    }
+    // the slots' units from the at-th on, as many as a launch takes
+    SlotCuts part(uint64_t at) const {
+        SlotCuts c;
+        for (int x = 0; x < kSlots; ++x) {
+            c.first[x] = first[x] + at < end[x] ? first[x] + at : end[x];
+            c.end[x] = end[x] - c.first[x] < kMaxSlotUnits ? end[x] : c.first[x] + kMaxSlotUnits;
+        }
+        return c;
     }
 };
 
@@ -84,13 +95,18 @@ struct UnitGroup {
     }
     SlotCuts cuts() const {
         SlotCuts c;
-        for (int x = 0; x <= kSlots; ++x) c.first[x] = first(x);
+        for (int x = 0; x < kSlots; ++x) {
+            c.first[x] = first(x);
+            c.end[x] = first(x + 1);
+        }
         return c;
     }
 };
 
-// Workgroups of `waves` waves for `most` units in every slot.
+// Workgroups of `waves` waves for `most` units in every slot (a launch's share
+// of them).
 inline unsigned slot_blocks(uint64_t most, int waves) {
+    if (most > kMaxSlotUnits) most = kMaxSlotUnits;
     return (unsigned)(kSlots * ((most + (uint64_t)waves - 1) / (uint64_t)waves));
 }
 
@@ -223,6 +239,7 @@ struct BatchArgs {
     BatchTables t;
     uint32_t total_anchors;
     uint64_t slot_units;          // view-order units of all scenes in a slot, at most
+    uint64_t slot_begin;          // the first of them in this launch
     uint32_t total_samples;
     uint32_t total_cells;
     uint32_t total_regions;

@@ -206,13 +206,23 @@ void with_threads(int threads, F&& f) {
     else f(int_c<1024>{});
 }
 
+// f(first anchor, anchors) over parts of fewer than 2^32 threads.
+template <class F>
+void in_parts(int BA, F&& f) {
+    constexpr int kPart = 1 << 21;
+    for (int64_t at = 0; at < BA; at += kPart) f((size_t)at, (unsigned)(BA - at < kPart ? BA - at : kPart));
+}
+
 template <class T>
 void run_softmax(const void* logits, int BA, size_t n, int G, float2* stats, float* w,
                  hipStream_t s) {
     with_threads(threads_of(n, BA, false), [&](auto threads) {
         constexpr int THREADS = decltype(threads)::value;
-        hipLaunchKernelGGL((softmax_kernel<T, THREADS>), dim3((unsigned)BA), dim3(THREADS), 0, s,
-                           static_cast<const T*>(logits), n, G, stats, w);
+        in_parts(BA, [&](size_t at, unsigned anchors) {
+            hipLaunchKernelGGL((softmax_kernel<T, THREADS>), dim3(anchors), dim3(THREADS), 0, s,
+                               static_cast<const T*>(logits) + at * n, n, G,
+                               stats ? stats + at * (size_t)G : nullptr, w ? w + at * n : nullptr);
+        });
     });
 }
 
@@ -246,8 +256,10 @@ hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int
     mark_begin("softmax_grad", s);
     with_threads(threads_of(n, BA, true), [&](auto threads) {
         constexpr int THREADS = decltype(threads)::value;
-        hipLaunchKernelGGL((softmax_grad_kernel<THREADS>), dim3((unsigned)BA), dim3(THREADS), 0, s,
-                           w, grad, n, G);
+        in_parts(BA, [&](size_t at, unsigned anchors) {
+            hipLaunchKernelGGL((softmax_grad_kernel<THREADS>), dim3(anchors), dim3(THREADS), 0, s,
+                               w + at * n, grad + at * n, n, G);
+        });
     });
     mark_end(s);
     return hipGetLastError();

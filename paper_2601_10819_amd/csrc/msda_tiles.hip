@@ -646,19 +646,34 @@ static size_t tile_lds_bytes(int waves, int G, bool coarse) {
     return part > tables ? part : tables;
 }
 
-// One launch over [tile_begin, tile_end), coarse up to tile_split.
+// [tile_begin, tile_end), coarse up to tile_split: one launch, or as many as
+// hold the waves (a tile of each of `items` batch items takes up to block_waves).
+template <class Args, class F>
+static hipError_t tile_parts(Args t, u32 items, F&& launch) {
+    const u32 BW = (u32)t.block_waves, begin = t.tile_begin, split = t.tile_split, end = t.tile_end;
+    const u32 most = (u32)(kMaxLaunchWaves / BW / items ? kMaxLaunchWaves / BW / items : 1);
+    for (u32 at = begin; at < end; at = t.tile_end) {
+        t.tile_begin = at;
+        t.tile_end = end - at < most ? end : at + most;
+        t.tile_split = split < at ? at : split < t.tile_end ? split : t.tile_end;
+        const u32 heavy = (t.tile_split - t.tile_begin) * items;
+        const u32 light = (t.tile_end - t.tile_split) * items;
+        launch(t, heavy, heavy + (light + BW - 1) / BW);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <class OT, int CPL, bool WHOLE>
-static hipError_t tile_launch_of(const TileArgs& t, hipStream_t s) {
-    const u32 heavy = (t.tile_split - t.tile_begin) * (u32)t.B;
-    const u32 light = (t.tile_end - t.tile_split) * (u32)t.B;
-    const u32 BW = (u32)t.block_waves;
-    const u32 blocks = heavy + (light + BW - 1) / BW;
-    if (blocks == 0) return hipSuccess;
-    mark_begin("gfeat_tile_kernel", s);
-    hipLaunchKernelGGL((gfeat_tile_kernel<OT, CPL, WHOLE>), dim3(blocks), dim3(64 * BW),
-                       tile_lds_bytes<CPL>(BW, t.G, heavy > 0), s, t);
-    mark_end(s);
-    return hipGetLastError();
+static hipError_t tile_launch_of(const TileArgs& a, hipStream_t s) {
+    return tile_parts(a, (u32)a.B, [&](const TileArgs& t, u32 heavy, u32 blocks) {
+        mark_begin("gfeat_tile_kernel", s);
+        hipLaunchKernelGGL((gfeat_tile_kernel<OT, CPL, WHOLE>), dim3(blocks),
+                           dim3(64 * t.block_waves),
+                           tile_lds_bytes<CPL>(t.block_waves, t.G, heavy > 0), s, t);
+        mark_end(s);
+    });
 }
 
 template <class OT, int CPL>
@@ -668,17 +683,14 @@ static hipError_t tile_launch(const TileArgs& t, hipStream_t s) {
 }
 
 template <class OT, int CPL, bool WHOLE>
-static hipError_t tile_batched_launch_of(const BatchArgs& b, hipStream_t s) {
-    const u32 heavy = b.tile_split - b.tile_begin;
-    const u32 light = b.tile_end - b.tile_split;
-    const u32 BW = (u32)b.block_waves;
-    const u32 blocks = heavy + (light + BW - 1) / BW;
-    if (blocks == 0) return hipSuccess;
-    mark_begin("gfeat_tile_batched", s);
-    hipLaunchKernelGGL((gfeat_tile_batched_kernel<OT, CPL, WHOLE>), dim3(blocks), dim3(64 * BW),
-                       tile_lds_bytes<CPL>(BW, b.G, heavy > 0), s, b);
-    mark_end(s);
-    return hipGetLastError();
+static hipError_t tile_batched_launch_of(const BatchArgs& a, hipStream_t s) {
+    return tile_parts(a, 1, [&](const BatchArgs& b, u32 heavy, u32 blocks) {
+        mark_begin("gfeat_tile_batched", s);
+        hipLaunchKernelGGL((gfeat_tile_batched_kernel<OT, CPL, WHOLE>), dim3(blocks),
+                           dim3(64 * b.block_waves),
+                           tile_lds_bytes<CPL>(b.block_waves, b.G, heavy > 0), s, b);
+        mark_end(s);
+    });
 }
 
 template <class OT, int CPL>
