@@ -382,14 +382,8 @@ constexpr u64 kNoUnit = ~(u64)0;
 // hands workgroups to the XCDs round-robin), or kNoUnit.
 __device__ __forceinline__ u64 slot_unit(const SlotCuts& cuts, u32 block, int wave, int nwaves) {
     const u32 x = block % kSlots;
-    u64 first = cuts.first[0], end = cuts.end[0];
-#pragma unroll
-    for (u32 k = 1; k < kSlots; ++k) {
-        first = x == k ? cuts.first[k] : first;
-        end = x == k ? cuts.end[k] : end;
-    }
-    const u64 u = first + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
-    return u < end ? u : kNoUnit;
+    const u64 u = cuts.first[x] + (u64)(block / kSlots) * (u32)nwaves + (u32)wave;
+    return u < cuts.end[x] ? u : kNoUnit;
 }
 
 // Unit u of a view-order launch as (row, anchor), units row-major: both the
