@@ -34,9 +34,9 @@ __device__ __forceinline__ void bwd_anchor(const OpArgs& a, const int ba, unsign
 }
 
 template <class FT, int CPL>
-__global__ void __launch_bounds__(512) msda_bwd_kernel(OpArgs a) {
+__global__ void __launch_bounds__(512) msda_bwd_kernel(OpArgs a, int ba0) {
     extern __shared__ __align__(16) unsigned char smem[];
-    bwd_anchor<FT, CPL>(a, (int)blockIdx.x, smem);
+    bwd_anchor<FT, CPL>(a, ba0 + (int)blockIdx.x, smem);
 }
 
 // View order: unit (b*rows + j)*A + a is anchor a over row j of `rows` rows of
@@ -97,11 +97,12 @@ size_t gather_lds_bytes(int waves, int C, int G) {
 
 template <class FT, int CPL>
 static hipError_t bwd_launch(const OpArgs& a, int waves, hipStream_t s) {
-    mark_begin("msda_bwd_kernel", s);
-    hipLaunchKernelGGL((msda_bwd_kernel<FT, CPL>), dim3((unsigned)(a.B * a.A)),
-                       dim3(64 * waves), (size_t)waves * grads_lds_bytes(a.G), s, a);
-    mark_end(s);
-    return hipGetLastError();
+    return anchor_parts(a, waves, [&](int ba0, unsigned anchors) {
+        mark_begin("msda_bwd_kernel", s);
+        hipLaunchKernelGGL((msda_bwd_kernel<FT, CPL>), dim3(anchors), dim3(64 * waves),
+                           (size_t)waves * grads_lds_bytes(a.G), s, a, ba0);
+        mark_end(s);
+    });
 }
 
 hipError_t launch_backward(const OpArgs& a, int dtype, int cpl, int waves, hipStream_t s) {

@@ -374,6 +374,19 @@ __device__ __forceinline__ u32 block_inclusive_scan(u32 v, u32* lds4, u32* total
     return v + before;
 }
 
+// Anchor order: launch(first anchor, anchors) over all B*A anchors, a workgroup
+// of `waves` waves each.
+template <class F>
+hipError_t anchor_parts(const OpArgs& a, int waves, F&& launch) {
+    const int64_t total = (int64_t)a.B * a.A, part = (int64_t)(kMaxLaunchWaves / (u32)waves);
+    for (int64_t at = 0; at < total; at += part) {
+        launch((int)at, (unsigned)(total - at < part ? total - at : part));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // ---------------------------------------------------------------- view order
 
 constexpr u64 kNoUnit = ~(u64)0;

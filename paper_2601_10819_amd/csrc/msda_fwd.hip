@@ -74,9 +74,9 @@ static size_t anchor_lds_bytes(int waves, int chunk, int C, int G) {
 }
 
 template <class FT, int CPL>
-__global__ void __launch_bounds__(512) msda_fwd_kernel(OpArgs a, int chunk) {
+__global__ void __launch_bounds__(512) msda_fwd_kernel(OpArgs a, int ba0, int chunk) {
     extern __shared__ __align__(16) unsigned char smem[];
-    fwd_anchor<FT, CPL>(a, (int)blockIdx.x, chunk, smem);
+    fwd_anchor<FT, CPL>(a, ba0 + (int)blockIdx.x, chunk, smem);
 }
 
 // View order: rows [row0, row0 + nrows) of every batch item, of `rows` in
@@ -249,11 +249,12 @@ static hipError_t fwd_batched_launch(const BatchArgs& b, int waves, int blocks, 
 template <class FT, int CPL>
 static hipError_t fwd_launch(const OpArgs& a, int waves, hipStream_t s) {
     const int chunk = fwd_chunk_samples(waves, a.G);
-    mark_begin("msda_fwd_kernel", s);
-    hipLaunchKernelGGL((msda_fwd_kernel<FT, CPL>), dim3((unsigned)(a.B * a.A)),
-                       dim3(64 * waves), anchor_lds_bytes(waves, chunk, a.C, a.G), s, a, chunk);
-    mark_end(s);
-    return hipGetLastError();
+    return anchor_parts(a, waves, [&](int ba0, unsigned anchors) {
+        mark_begin("msda_fwd_kernel", s);
+        hipLaunchKernelGGL((msda_fwd_kernel<FT, CPL>), dim3(anchors), dim3(64 * waves),
+                           anchor_lds_bytes(waves, chunk, a.C, a.G), s, a, ba0, chunk);
+        mark_end(s);
+    });
 }
 
 template <class FT, int CPL>

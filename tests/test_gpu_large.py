@@ -67,3 +67,17 @@ def test_softmax_of_many_anchors(ops):
         assert torch.equal(out[:, lo:hi], ops.forward(feat, layout, *part, logits=True))
         assert torch.equal(gw[:, lo:hi], ops.backward(feat, layout, *part, go[:, lo:hi].contiguous(),
                                                       False, False, True, logits=True)[2])
+
+
+def test_anchor_order(ops):
+    A = 70_000_000                                 # a wave each
+    feat, shapes, starts, loc, w = operands(1, 1, A, 1, 2, torch.bfloat16, torch.float32)
+    layout = ops.Layout(shapes, starts)
+    go = torch.randn(1, A, 2, device="cuda")
+    out = ops.forward(feat, layout, loc, w)
+    _, gl, gw = ops.backward(feat, layout, loc, w, go, need_feat=False)
+    for lo, hi in ((0, A // 2), (A // 2, A)):
+        part = loc[:, lo:hi], w[:, lo:hi]
+        assert torch.equal(out[:, lo:hi], ops.forward(feat, layout, *part))
+        _, hl, hw = ops.backward(feat, layout, *part, go[:, lo:hi].contiguous(), need_feat=False)
+        assert torch.equal(gl[:, lo:hi], hl) and torch.equal(gw[:, lo:hi], hw)
