@@ -19,30 +19,30 @@ namespace msda {
 
 // The backward gather of one anchor (index ba = b*A + a of `a`) by the whole
 // workgroup in anchor order: equal runs of its pairs to the waves.
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __device__ __forceinline__ void bwd_anchor(const OpArgs& a, const int ba, unsigned char* smem) {
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
-    const int npairs = a.P * a.N, J = 64 >> level_shift(a.L);
+    const int npairs = a.P * a.N, J = grad_samples(a.G) >> level_shift(a.L);
     int per = (npairs + nwaves - 1) / nwaves;
     if (per > J) per = (per + J - 1) / J * J;
     const int k_lo = (int)min((int64_t)npairs, (int64_t)wave * per);
     const int b = ba / a.A;
-    grads_of<FT, CPL>(a, grad_anchor<FT>(a, b, ba - b * a.A),
+    grads_of<FT, CPL, PACKED>(a, grad_anchor<FT>(a, b, ba - b * a.A),
                       AnchorOrder{a.N, div_magic(a.N, npairs)}, k_lo,
                       min(npairs, k_lo + per), lanes_of<FT, CPL>(a),
                       smem + (size_t)wave * grads_lds_bytes(a.G));
 }
 
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_bwd_kernel(OpArgs a, int ba0) {
     extern __shared__ __align__(16) unsigned char smem[];
-    bwd_anchor<FT, CPL>(a, ba0 + (int)blockIdx.x, smem);
+    bwd_anchor<FT, CPL, PACKED>(a, ba0 + (int)blockIdx.x, smem);
 }
 
 // View order: unit (b*rows + j)*A + a is anchor a over row j of `rows` rows of
 // cameras of batch item b (bwd_rows), cut camera-major into one range per XCD.
 // Every output is per sample or per pair, so the rows need no combining.
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_bwd_view_kernel(OpArgs a, SlotCuts cuts,
                                                             int rows) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(512) msda_bwd_view_kernel(OpArgs a, SlotCuts c
     const int b = (int)(t.row / (u32)rows);
     const CamRange n = row_cams(a.N, (int)(t.row % (u32)rows), rows);
     const int np = (n.hi - n.lo) * a.P;
-    grads_of<FT, CPL>(a, grad_anchor<FT>(a, b, t.a),
+    grads_of<FT, CPL, PACKED>(a, grad_anchor<FT>(a, b, t.a),
                       ViewOrder{a.P, n.lo, div_magic(a.P, np)}, 0, np, lanes_of<FT, CPL>(a),
                       smem + (size_t)wave * grads_lds_bytes(a.G));
 }
@@ -61,18 +61,18 @@ __global__ void __launch_bounds__(512) msda_bwd_view_kernel(OpArgs a, SlotCuts c
 // Batched backward gather: persistent workgroups stride over the anchors of
 // all scenes; records go to the batch's sample space, per (scene, region)
 // bucket with local cells or at the sample index with batch-global cells.
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_bwd_batched_kernel(BatchArgs b) {
     extern __shared__ __align__(16) unsigned char smem[];
     for (u32 item = blockIdx.x; item < b.total_anchors; item += gridDim.x) {
         const int s = scene_of(b.t.anchor_start, b.S, item);
-        bwd_anchor<FT, CPL>(scene_view(b, s, FT::kBytes), (int)(item - b.t.anchor_start[s]), smem);
+        bwd_anchor<FT, CPL, PACKED>(scene_view(b, s, FT::kBytes), (int)(item - b.t.anchor_start[s]), smem);
     }
 }
 
 // Batched backward gather in view order: each scene's units cut into one range
 // per XCD, an XCD's ranges one after the other.
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_bwd_batched_view_kernel(BatchArgs b) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(512) msda_bwd_batched_view_kernel(BatchArgs b)
     const RowUnit t = row_unit(su.u, a.A);
     const CamRange n = row_cams(a.N, (int)t.row, bwd_rows(a.N, a.P));
     const int np = (n.hi - n.lo) * a.P;
-    grads_of<FT, CPL>(a, grad_anchor<FT>(a, 0, t.a),
+    grads_of<FT, CPL, PACKED>(a, grad_anchor<FT>(a, 0, t.a),
                       ViewOrder{a.P, n.lo, div_magic(a.P, np)}, 0, np, lanes_of<FT, CPL>(a),
                       smem + (size_t)wave * grads_lds_bytes(a.G));
 }
@@ -97,9 +97,11 @@ size_t gather_lds_bytes(int waves, int C, int G) {
 
 template <class FT, int CPL>
 static hipError_t bwd_launch(const OpArgs& a, int waves, hipStream_t s) {
+    const auto kernel = a.G <= kPackedGroups ? msda_bwd_kernel<FT, CPL, true>
+                                              : msda_bwd_kernel<FT, CPL, false>;
     return anchor_parts(a, waves, [&](int ba0, unsigned anchors) {
         mark_begin("msda_bwd_kernel", s);
-        hipLaunchKernelGGL((msda_bwd_kernel<FT, CPL>), dim3(anchors), dim3(64 * waves),
+        hipLaunchKernelGGL(kernel, dim3(anchors), dim3(64 * waves),
                            (size_t)waves * grads_lds_bytes(a.G), s, a, ba0);
         mark_end(s);
     });
@@ -122,12 +124,13 @@ hipError_t launch_backward(const OpArgs& a, int dtype, int cpl, int waves, hipSt
 
 template <class FT, int CPL>
 static hipError_t bwd_view_launch(const OpArgs& a, int waves, hipStream_t s) {
+    const auto kernel = a.G <= kPackedGroups ? msda_bwd_view_kernel<FT, CPL, true>
+                                              : msda_bwd_view_kernel<FT, CPL, false>;
     const int rows = bwd_rows(a.N, a.P);
     const SlotCuts cuts = UnitGroup{a.B, a.N, a.A, rows, 0, rows}.cuts();
     for (u64 at = 0; at < cuts.most(); at += kMaxSlotUnits) {
         mark_begin("msda_bwd_view_kernel", s);
-        hipLaunchKernelGGL((msda_bwd_view_kernel<FT, CPL>),
-                           dim3(slot_blocks(cuts.most() - at, waves)), dim3(64 * waves),
+        hipLaunchKernelGGL(kernel, dim3(slot_blocks(cuts.most() - at, waves)), dim3(64 * waves),
                            (size_t)waves * grads_lds_bytes(a.G), s, a, cuts.part(at), rows);
         mark_end(s);
         const hipError_t e = hipGetLastError();
@@ -153,8 +156,10 @@ hipError_t launch_backward_view(const OpArgs& a, int dtype, int cpl, int waves, 
 
 template <class FT, int CPL>
 static hipError_t bwd_batched_launch(const BatchArgs& b, int waves, int blocks, hipStream_t s) {
+    const auto kernel = b.G <= kPackedGroups ? msda_bwd_batched_kernel<FT, CPL, true>
+                                              : msda_bwd_batched_kernel<FT, CPL, false>;
     mark_begin("msda_bwd_batched_kernel", s);
-    hipLaunchKernelGGL((msda_bwd_batched_kernel<FT, CPL>), dim3(blocks), dim3(64 * waves),
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * waves),
                        (size_t)waves * grads_lds_bytes(b.G), s, b);
     mark_end(s);
     return hipGetLastError();
@@ -162,10 +167,11 @@ static hipError_t bwd_batched_launch(const BatchArgs& b, int waves, int blocks, 
 
 template <class FT, int CPL>
 static hipError_t bwd_batched_view_launch(BatchArgs b, int waves, hipStream_t s) {
+    const auto kernel = b.G <= kPackedGroups ? msda_bwd_batched_view_kernel<FT, CPL, true>
+                                              : msda_bwd_batched_view_kernel<FT, CPL, false>;
     for (b.slot_begin = 0; b.slot_begin < b.slot_units; b.slot_begin += kMaxSlotUnits) {
         mark_begin("msda_bwd_batched_view_kernel", s);
-        hipLaunchKernelGGL((msda_bwd_batched_view_kernel<FT, CPL>),
-                           dim3(slot_blocks(b.slot_units - b.slot_begin, waves)),
+        hipLaunchKernelGGL(kernel, dim3(slot_blocks(b.slot_units - b.slot_begin, waves)),
                            dim3(64 * waves), (size_t)waves * grads_lds_bytes(b.G), s, b);
         mark_end(s);
         const hipError_t e = hipGetLastError();

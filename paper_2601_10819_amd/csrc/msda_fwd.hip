@@ -26,7 +26,7 @@ namespace msda {
 // The forward of one anchor (index ba = b*A + a of `a`) by the whole
 // workgroup in anchor order. Called by every thread of the block (it ends
 // with block-wide barriers).
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __device__ __forceinline__ void fwd_anchor(const OpArgs& a, const int ba, int chunk,
                                            unsigned char* smem) {
     const int wave = wave_index(), nwaves = blockDim.x >> 6;
@@ -40,7 +40,7 @@ __device__ __forceinline__ void fwd_anchor(const OpArgs& a, const int ba, int ch
     if (per > 64) per = (per + 63) & ~63;
     const int s_lo = (int)min((int64_t)total, (int64_t)wave * per);
     float acc[CPL];
-    row_sum<FT, CPL>(a, (size_t)ba, feat, s_lo, min(total, s_lo + per), q, chunk,
+    row_sum<FT, CPL, PACKED>(a, (size_t)ba, feat, s_lo, min(total, s_lo + per), q, chunk,
                      smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
 
     float* out = a.out + (size_t)ba * a.C;
@@ -73,15 +73,15 @@ static size_t anchor_lds_bytes(int waves, int chunk, int C, int G) {
     return stage > red ? stage : red;
 }
 
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_fwd_kernel(OpArgs a, int ba0, int chunk) {
     extern __shared__ __align__(16) unsigned char smem[];
-    fwd_anchor<FT, CPL>(a, ba0 + (int)blockIdx.x, chunk, smem);
+    fwd_anchor<FT, CPL, PACKED>(a, ba0 + (int)blockIdx.x, chunk, smem);
 }
 
 // View order: rows [row0, row0 + nrows) of every batch item, of `rows` in
 // all; unit (b*nrows + j)*A + a, the partial row of that index in part.
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_fwd_view_kernel(OpArgs a, SlotCuts cuts,
                                                             int rows, int row0, int nrows,
                                                             int chunk, float* part) {
@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(512) msda_fwd_view_kernel(OpArgs a, SlotCuts c
         static_cast<const char*>(a.feat) + (size_t)b * a.batch_bytes, a.batch_bytes);
     const int NS = a.P * a.L;
     float acc[CPL];
-    row_sum<FT, CPL>(a, (size_t)b * a.A + t.a, feat, n.lo * NS, n.hi * NS, q, chunk,
+    row_sum<FT, CPL, PACKED>(a, (size_t)b * a.A + t.a, feat, n.lo * NS, n.hi * NS, q, chunk,
                      smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
     if (q.sub == 0) {
         float* dst = part + u * (u32)a.C + q.c0;
@@ -137,13 +137,13 @@ __global__ void __launch_bounds__(256) fwd_rows_reduce(const float* part, float*
 
 // Batched forward: persistent workgroups stride over the anchors of all
 // scenes.
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_fwd_batched_kernel(BatchArgs b, int chunk) {
     extern __shared__ __align__(16) unsigned char smem[];
     for (u32 item = blockIdx.x; item < b.total_anchors; item += gridDim.x) {
         const int s = scene_of(b.t.anchor_start, b.S, item);
         const OpArgs a = scene_view(b, s, FT::kBytes);
-        fwd_anchor<FT, CPL>(a, (int)(item - b.t.anchor_start[s]), chunk, smem);
+        fwd_anchor<FT, CPL, PACKED>(a, (int)(item - b.t.anchor_start[s]), chunk, smem);
     }
 }
 
@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(512) msda_fwd_batched_kernel(BatchArgs b, int 
 // 12-scene step 8.93 -> 8.62 ms, five scenes of 5 to 25 cameras FP32 135 ->
 // 114 us, BF16 317 -> 263). Per anchor the arithmetic is the single call's view
 // order with B = 1.
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_fwd_batched_view_kernel(BatchArgs b, int chunk,
                                                                     float* part) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -167,7 +167,7 @@ __global__ void __launch_bounds__(512) msda_fwd_batched_view_kernel(BatchArgs b,
     const rsrc_t feat = make_rsrc(a.feat, a.batch_bytes);
     const int NS = a.P * a.L;
     float acc[CPL];
-    row_sum<FT, CPL>(a, (size_t)t.a, feat, n.lo * NS, n.hi * NS, q, chunk,
+    row_sum<FT, CPL, PACKED>(a, (size_t)t.a, feat, n.lo * NS, n.hi * NS, q, chunk,
                      smem + (size_t)wave * row_lds_bytes(chunk, a.G), acc);
     if (q.sub == 0) {
         float* dst = part + (b.t.row_start[su.s] + su.u) * (u32)b.C + q.c0;
@@ -212,11 +212,12 @@ __global__ void __launch_bounds__(256) fwd_batched_view_reduce(BatchArgs b, cons
 
 template <class FT, int CPL>
 static hipError_t fwd_batched_view_launch(BatchArgs b, int waves, float* part, hipStream_t s) {
+    const auto kernel = b.G <= kPackedGroups ? msda_fwd_batched_view_kernel<FT, CPL, true>
+                                              : msda_fwd_batched_view_kernel<FT, CPL, false>;
     const int chunk = fwd_chunk_samples(waves, b.G);
     for (b.slot_begin = 0; b.slot_begin < b.slot_units; b.slot_begin += kMaxSlotUnits) {
         mark_begin("msda_fwd_batched_view_kernel", s);
-        hipLaunchKernelGGL((msda_fwd_batched_view_kernel<FT, CPL>),
-                           dim3(slot_blocks(b.slot_units - b.slot_begin, waves)),
+        hipLaunchKernelGGL(kernel, dim3(slot_blocks(b.slot_units - b.slot_begin, waves)),
                            dim3(64 * waves), (size_t)waves * row_lds_bytes(chunk, b.G), s, b,
                            chunk, part);
         mark_end(s);
@@ -239,8 +240,10 @@ static hipError_t fwd_batched_view_launch(BatchArgs b, int waves, float* part, h
 template <class FT, int CPL>
 static hipError_t fwd_batched_launch(const BatchArgs& b, int waves, int blocks, hipStream_t s) {
     const int chunk = fwd_chunk_samples(waves, b.G);
+    const auto kernel = b.G <= kPackedGroups ? msda_fwd_batched_kernel<FT, CPL, true>
+                                              : msda_fwd_batched_kernel<FT, CPL, false>;
     mark_begin("msda_fwd_batched_kernel", s);
-    hipLaunchKernelGGL((msda_fwd_batched_kernel<FT, CPL>), dim3(blocks), dim3(64 * waves),
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * waves),
                        anchor_lds_bytes(waves, chunk, b.C, b.G), s, b, chunk);
     mark_end(s);
     return hipGetLastError();
@@ -248,10 +251,12 @@ static hipError_t fwd_batched_launch(const BatchArgs& b, int waves, int blocks, 
 
 template <class FT, int CPL>
 static hipError_t fwd_launch(const OpArgs& a, int waves, hipStream_t s) {
+    const auto kernel = a.G <= kPackedGroups ? msda_fwd_kernel<FT, CPL, true>
+                                              : msda_fwd_kernel<FT, CPL, false>;
     const int chunk = fwd_chunk_samples(waves, a.G);
     return anchor_parts(a, waves, [&](int ba0, unsigned anchors) {
         mark_begin("msda_fwd_kernel", s);
-        hipLaunchKernelGGL((msda_fwd_kernel<FT, CPL>), dim3(anchors), dim3(64 * waves),
+        hipLaunchKernelGGL(kernel, dim3(anchors), dim3(64 * waves),
                            anchor_lds_bytes(waves, chunk, a.C, a.G), s, a, ba0, chunk);
         mark_end(s);
     });
@@ -260,6 +265,8 @@ static hipError_t fwd_launch(const OpArgs& a, int waves, hipStream_t s) {
 template <class FT, int CPL>
 static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, float* part,
                                   hipStream_t s) {
+    const auto kernel = a.G <= kPackedGroups ? msda_fwd_view_kernel<FT, CPL, true>
+                                              : msda_fwd_view_kernel<FT, CPL, false>;
     const int rows = fwd_rows(a.N, a.P, a.L), chunk = fwd_chunk_samples(waves, a.G);
     const size_t AC = (size_t)a.A * a.C, total = AC * a.B;
     for (int row0 = 0; row0 < rows; row0 += part_rows) {
@@ -267,8 +274,7 @@ static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, flo
         const SlotCuts cuts = UnitGroup{a.B, a.N, a.A, rows, row0, nrows}.cuts();
         for (u64 at = 0; at < cuts.most(); at += kMaxSlotUnits) {
             mark_begin("msda_fwd_view_kernel", s);
-            hipLaunchKernelGGL((msda_fwd_view_kernel<FT, CPL>),
-                               dim3(slot_blocks(cuts.most() - at, waves)), dim3(64 * waves),
+            hipLaunchKernelGGL(kernel, dim3(slot_blocks(cuts.most() - at, waves)), dim3(64 * waves),
                                (size_t)waves * row_lds_bytes(chunk, a.G), s, a, cuts.part(at),
                                rows, row0, nrows, chunk, part);
             mark_end(s);

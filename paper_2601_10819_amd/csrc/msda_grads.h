@@ -23,14 +23,17 @@
 namespace msda {
 
 // Staging: one sample per lane, lane = pair * Lp + level with the levels
-// padded to a power of two, so 64 / Lp pairs at a time. Per sample in LDS:
+// padded to a power of two, so grad_samples / Lp pairs at a time. With 64 groups
+// half a wave's lanes, whose LDS leaves room for 16 waves per CU instead of 8
+// (16 cameras of 256 x 448, 900 anchors, FP32: 376 -> 264 us). Per sample in LDS:
 // corner offsets, corner weights, location-derivative factors (W(1-ly), W ly,
 // H(1-lx), H lx), and its G weights, which its grad_w replaces.
 __host__ __device__ constexpr int level_shift(int L) {
     return L > 4 ? 3 : L > 2 ? 2 : L > 1 ? 1 : 0;
 }
+__host__ __device__ constexpr int grad_samples(int G) { return G > 32 ? 32 : 64; }
 __host__ __device__ constexpr size_t grads_lds_bytes(int G) {
-    return 64 * (3 * 16 + 4 * (size_t)G) + 64 * 4;
+    return (size_t)grad_samples(G) * (3 * 16 + 4 * (size_t)G + 4);
 }
 
 struct GradLds {
@@ -42,12 +45,13 @@ struct GradLds {
 };
 
 __device__ __forceinline__ GradLds grads_lds(unsigned char* p, int G) {
+    const int n = grad_samples(G);
     GradLds s;
     s.off = reinterpret_cast<u32x4*>(p);
-    s.cw = reinterpret_cast<float4*>(p + 64 * 16);
-    s.dk = reinterpret_cast<float4*>(p + 64 * 32);
-    s.w = reinterpret_cast<float*>(p + 64 * 48);
-    s.src = reinterpret_cast<u32*>(s.w + 64 * G);
+    s.cw = reinterpret_cast<float4*>(s.off + n);
+    s.dk = s.cw + n;
+    s.w = reinterpret_cast<float*>(s.dk + n);
+    s.src = reinterpret_cast<u32*>(s.w + n * G);
     return s;
 }
 
@@ -132,7 +136,7 @@ struct ViewOrder {
 
 // Stages pairs [k0, k0 + nj) and writes their records; lanes past the last
 // sample stage zeros that read no memory.
-template <class FT, class Order>
+template <class FT, bool PACKED, class Order>
 __device__ __forceinline__ void stage_grads(const OpArgs& a, const GradAnchor& x,
                                             const Order& order, int k0, int nj, int lane,
                                             const GradLds& s) {
@@ -141,7 +145,7 @@ __device__ __forceinline__ void stage_grads(const OpArgs& a, const GradAnchor& x
     u32x4 off = {kOOB, kOOB, kOOB, kOOB};
     float4 cw = make_float4(0.f, 0.f, 0.f, 0.f), dk = cw;
     const bool live = jj < nj && l < L;
-    const float* w = nullptr;
+    u32 row = 0;                                    // the sample's row of G weights
     if (live) {
         int p, n;
         order(k0 + jj, &p, &n);
@@ -151,7 +155,7 @@ __device__ __forceinline__ void stage_grads(const OpArgs& a, const GradAnchor& x
         gm.H = a.shapes[2 * r];
         gm.W = a.shapes[2 * r + 1];
         gm.start = a.starts[r];
-        w = x.gw + ((size_t)src * L + l) * G;
+        row = src * (u32)L + (u32)l;
         const Corners c = corners_of(x.gl[2 * (size_t)src], x.gl[2 * (size_t)src + 1], gm,
                                      (u32)a.C * FT::kBytes, 0u);
         off = u32x4{c.off[0], c.off[1], c.off[2], c.off[3]};
@@ -178,10 +182,31 @@ __device__ __forceinline__ void stage_grads(const OpArgs& a, const GradAnchor& x
             x.rec.frac[smp] = make_float2(c.lx, c.ly);
         }
     }
-    s.off[lane] = off;
-    s.cw[lane] = cw;
-    s.dk[lane] = dk;
-    if (G == 8) {
+    const int ns = PACKED ? 64 : grad_samples(G);
+    if (lane < ns) {
+        s.off[lane] = off;
+        s.cw[lane] = cw;
+        s.dk[lane] = dk;
+    }
+    if constexpr (!PACKED) {
+        // lane after lane across a sample's groups (64 % G == 0): the loads and LDS
+        // stores of a lane's own sample would be G entries apart in the wave
+        const u32 r = live ? row : ~0u;
+        const int gs = __builtin_ctz(G), g = lane & (G - 1);
+        for (int e0 = lane; e0 - lane < ns * G; e0 += 64 * 8) {      // ns * G >= 1024
+            float t[8];
+            bool in[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const u32 i = (u32)__shfl((int)r, (e0 + 64 * k) >> gs, 64);
+                in[k] = i != ~0u;
+                t[k] = x.gw[(size_t)(in[k] ? i : 0u) * (u32)G + (u32)g];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s.w[e0 + 64 * k] = in[k] ? t[k] : 0.f;
+        }
+    } else if (G == 8) {
+        const float* w = x.gw + (size_t)row * (u32)G;
         float t[8];
 #pragma unroll
         for (int g = 0; g < 8; ++g) t[g] = live ? w[g] : 0.f;
@@ -189,6 +214,7 @@ __device__ __forceinline__ void stage_grads(const OpArgs& a, const GradAnchor& x
         d[0] = make_float4(t[0], t[1], t[2], t[3]);
         d[1] = make_float4(t[4], t[5], t[6], t[7]);
     } else {
+        const float* w = x.gw + (size_t)row * (u32)G;
         for (int g = 0; g < G; ++g) s.w[lane * G + g] = live ? w[g] : 0.f;
     }
 }
@@ -207,7 +233,7 @@ __device__ __forceinline__ void pairs_grads(const OpArgs& a, const GradAnchor& x
                                             float out_scale, float* dot) {
     using RowT = Row<FT, CPL>;
     constexpr int LU = kGradLevels;
-    const int L = a.L, G = a.G, ls = level_shift(L), J = 64 >> ls;
+    const int L = a.L, G = a.G, ls = level_shift(L), J = grad_samples(G) >> ls;
     const int lpg = (a.C / G) / CPL;               // lanes of one group (a power of two)
     for (int j0 = 0; j0 < nj; j0 += q.spw) {
         // sub-waves past the last pair repeat one and write nothing
@@ -304,32 +330,40 @@ __device__ __forceinline__ void pairs_atomic(const OpArgs& a, const GradAnchor& 
 // The lane widths of the common layouts (C = 256 in G = 8 groups: 32 lanes
 // per sample in groups of 4 with 8 channels per lane, 64 in groups of 8 with
 // 4) are compile-time in their copies of the loop.
-template <class FT, int CPL, class Order>
+template <class FT, int CPL, bool PACKED, class Order>
 __device__ __forceinline__ void grads_of(const OpArgs& a, const GradAnchor& x, const Order& order,
                                          int k_lo, int k_hi, const Lanes& q, unsigned char* lds,
                                          float out_scale = 1.f, float* dot = nullptr) {
     const GradLds s = grads_lds(lds, a.G);
-    const int G = a.G, L = a.L, ls = level_shift(L), J = 64 >> ls;
+    const int G = a.G, L = a.L, ls = level_shift(L), J = grad_samples(G) >> ls;
     const int lpg = (a.C / G) / CPL;
     float go[CPL];
 #pragma unroll
     for (int i = 0; i < CPL; ++i) go[i] = x.go[q.c0 + i];
     for (int k0 = k_lo; k0 < k_hi; k0 += J) {
         const int nj = min(J, k_hi - k0);
-        stage_grads<FT>(a, x, order, k0, nj, q.lane, s);
+        stage_grads<FT, PACKED>(a, x, order, k0, nj, q.lane, s);
         wave_lds_sync();
         if (x.gacc) pairs_atomic<FT, CPL>(a, x, s, nj, q);
         if (x.gwout || x.glout || dot) {
-            if (lpg == 4 && q.lps == 32)
+            if (PACKED && lpg == 4 && q.lps == 32)
                 pairs_grads<FT, CPL, 4, 32>(a, x, s, nj, q, go, out_scale, dot);
-            else if (lpg == 8 && q.lps == 64)
+            else if (PACKED && lpg == 8 && q.lps == 64)
                 pairs_grads<FT, CPL, 8, 64>(a, x, s, nj, q, go, out_scale, dot);
             else
                 pairs_grads<FT, CPL, 0, 0>(a, x, s, nj, q, go, out_scale, dot);
             wave_lds_sync();
-            // grad_w, a sample's groups by the lane that staged it
+            // grad_w, a sample's groups by the lane that staged it, or (many) lane
+            // after lane
             const int jj = q.lane >> ls, l = q.lane & ((1 << ls) - 1);
-            if (x.gwout && jj < nj && l < L) {
+            if (!PACKED && x.gwout) {
+                const int gs = __builtin_ctz(G);
+                for (int e = q.lane; e < grad_samples(G) * G; e += 64) {
+                    const int je = e >> gs >> ls, le = (e >> gs) & ((1 << ls) - 1);
+                    if (je < nj && le < L)
+                        x.gwout[((size_t)s.src[je] * L + le) * G + (e & (G - 1))] = s.w[e];
+                }
+            } else if (x.gwout && jj < nj && l < L) {
                 float* o = x.gwout + ((size_t)s.src[jj] * L + l) * G;
                 const float* t = s.w + q.lane * G;
                 if (G == 8) {

@@ -216,7 +216,7 @@ __device__ __forceinline__ void for_each_visible_item(const OpArgs& a, const u32
     }
 }
 
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_fwd_visible_kernel(OpArgs a, const u32* items,
                                                                const u32* count, int chunk,
                                                                float* part) {
@@ -228,7 +228,8 @@ __global__ void __launch_bounds__(512) msda_fwd_visible_kernel(OpArgs a, const u
         const rsrc_t feat = make_rsrc(static_cast<const char*>(a.feat) + (size_t)b * a.batch_bytes,
                                       a.batch_bytes);
         float acc[CPL];
-        row_sum<FT, CPL>(a, (size_t)b * a.A + an, feat, n * NS, (n + 1) * NS, q, chunk, lds, acc);
+        row_sum<FT, CPL, PACKED>(a, (size_t)b * a.A + an, feat, n * NS, (n + 1) * NS, q, chunk,
+                                 lds, acc);
         if (q.sub == 0) {
             float* dst = part + (size_t)i * a.C + q.c0;
 #pragma unroll
@@ -296,7 +297,7 @@ __global__ void __launch_bounds__(256) fwd_visible_reduce(const float* __restric
     }
 }
 
-template <class FT, int CPL>
+template <class FT, int CPL, bool PACKED>
 __global__ void __launch_bounds__(512) msda_bwd_visible_kernel(OpArgs a, const u32* items,
                                                                const u32* place,
                                                                const u32* count,
@@ -323,7 +324,7 @@ __global__ void __launch_bounds__(512) msda_bwd_visible_kernel(OpArgs a, const u
         }
         const float scale = vt ? vt[((size_t)b * a.A + an) * a.N + n] : 1.f;
         float dot = 0.f;
-        grads_of<FT, CPL>(a, x, ViewOrder{a.P, n, mP}, 0, a.P, q, lds, scale,
+        grads_of<FT, CPL, PACKED>(a, x, ViewOrder{a.P, n, mP}, 0, a.P, q, lds, scale,
                           item_dot ? &dot : nullptr);
         if (item_dot) {
             dot = group_sum(dot, 64);
@@ -344,8 +345,10 @@ static hipError_t fwd_visible_launch(const OpArgs& a, int waves, const u32* item
                                      const u32* count, const u32* place, const uint8_t* visible,
                                      const float* vt, float* part, hipStream_t s) {
     const int chunk = fwd_chunk_samples(waves, a.G);
+    const auto kernel = a.G <= kPackedGroups ? msda_fwd_visible_kernel<FT, CPL, true>
+                                              : msda_fwd_visible_kernel<FT, CPL, false>;
     mark_begin("msda_fwd_visible_kernel", s);
-    hipLaunchKernelGGL((msda_fwd_visible_kernel<FT, CPL>), dim3(visible_blocks(waves)),
+    hipLaunchKernelGGL(kernel, dim3(visible_blocks(waves)),
                        dim3(64 * waves), (size_t)waves * row_lds_bytes(chunk, a.G), s, a, items,
                        count, chunk, part);
     mark_end(s);
@@ -363,8 +366,10 @@ template <class FT, int CPL>
 static hipError_t bwd_visible_launch(const OpArgs& a, int waves, const u32* items,
                                      const u32* place, const u32* count, u32* rec_val,
                                      const float* vt, float* item_dot, hipStream_t s) {
+    const auto kernel = a.G <= kPackedGroups ? msda_bwd_visible_kernel<FT, CPL, true>
+                                              : msda_bwd_visible_kernel<FT, CPL, false>;
     mark_begin("msda_bwd_visible_kernel", s);
-    hipLaunchKernelGGL((msda_bwd_visible_kernel<FT, CPL>), dim3(visible_blocks(waves)),
+    hipLaunchKernelGGL(kernel, dim3(visible_blocks(waves)),
                        dim3(64 * waves), (size_t)waves * grads_lds_bytes(a.G), s, a, items, place,
                        count, rec_val, vt, item_dot);
     mark_end(s);
