@@ -375,6 +375,32 @@ bool wide_tiles(uint64_t heavy, uint64_t tiles, uint64_t heavy_samples) {
     return heavy && waves <= kMaxWaves && heavy_samples >= kMinSamples * heavy;
 }
 
+// Whether light tiles are sparse: of `tiles` with `samples` samples, so few that
+// a wave takes a tile per sub-wave, with a run-time dispatch per record, rather
+// than one tile with all sub-waves and a static walk of its 25 cells, which
+// costs the wave the same with one record as with twenty (narrow records only:
+// a C = 256 record is a whole wave's). grad_feat of 25 cameras of 256 x 704, 3
+// levels, FP32, by samples per tile, one tile a wave / one a sub-wave: C = 64
+// 3.2 112 / 66 us, 9.5 142 / 90, 20.7 191 / 141, 41 280 / 245; C = 8 6.4 147 /
+// 97, 20.7 206 / 202, 28.6 230 / 248. With fewer tiles than two rounds of the
+// 4096 resident waves the chip has room for a wave a tile, and the line falls
+// with them: C = 64, 8 samples a tile, 6160 tiles 56 / 51, 3520 46 / 41, 1760 38 /
+// 40, 840 31 / 34; 16 samples 70 / 69, 58 / 60, 47 / 58, 33 / 45. The sums' order
+// is the rule's, so the rule is a scene's own, by its sizes alone.
+bool sparse_tiles(uint64_t tiles, uint64_t samples) {
+    constexpr uint64_t kMaxSamples = 24, kFullTiles = 8192;
+    return tiles && samples * kFullTiles < kMaxSamples * tiles * std::min(tiles, kFullTiles);
+}
+
+// Sparse tiles a wave takes: a power of two up to its sub-waves, as many as
+// leave the chip full (4096 waves are resident at once). It does not change the
+// sums.
+int tiles_per_wave(uint64_t tiles, int lps_shift) {
+    int n = 1;
+    while (n < 64 >> lps_shift && tiles / (uint64_t)(2 * n) >= 4096) n *= 2;
+    return n;
+}
+
 // 1 if the regions are pairwise disjoint; *cover = they tile [0, R) exactly.
 bool regions_disjoint(const msda_desc* d, bool* cover) {
     const int64_t NL = (int64_t)d->num_cams * d->num_levels;
@@ -920,6 +946,9 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     t.block_waves = wide_tiles((uint64_t)t.tile_split * a.B, tiles * a.B,
                                (uint64_t)heavy_regions * a.B * a.A * a.P)
                         ? 8 : 4;
+    const uint64_t light = (tiles - t.tile_split) * a.B;
+    if (t.lps_shift < 6 && sparse_tiles(light, ((uint64_t)a.N * a.L - heavy_regions) * a.B * a.A * a.P))
+        t.sparse = tiles_per_wave(light, t.lps_shift);
     if ((e = msda::launch_gfeat_tiles(t, desc->feat_dtype, rcpl, s)) != hipSuccess)
         return hip_fail(e, "grad_feat tile reduction");
     return finish();
@@ -1227,9 +1256,13 @@ struct BatchPlan {
     uint64_t part_bytes;          // view-order forward partials
     uint64_t max_ap;              // the largest A_s * P
     bool keys_fit;                // every region's cells fit the bucket sort's keys
-    // scenes whose coarse tiles take 8 waves: their bits, tiles and coarse tiles
+    // scenes whose coarse tiles take 8 waves: their bits, tiles (without sparse
+    // ones) and coarse tiles
     uint32_t wide[msda::kMaxBatchScenes / 32];
     uint64_t wide_tiles, wide_heavy;
+    // scenes whose light tiles are sparse: their bits and light tiles
+    uint32_t thin[msda::kMaxBatchScenes / 32];
+    uint64_t thin_tiles;
 };
 
 // Validates the batch (every scene against its host mirrors) and sizes it.
@@ -1246,6 +1279,10 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
     p->keys_fit = true;
     const int eb = elem_bytes(b->feat_dtype);
     uint64_t slot_units[msda::kSlots] = {};
+    int rcpl = 0;                 // the reduction's channels per lane (see backward_impl)
+    if (b->channels > 0 && b->groups > 0 && b->channels % b->groups == 0)
+        for (int c : {4, 2, 1})
+            if (cpl_fits(c, b->channels, b->groups)) { rcpl = c; break; }
     for (int s = 0; s < b->num_scenes; ++s) {
         const msda_scene& sc = b->host_scenes[s];
         msda_desc d = {};
@@ -1315,10 +1352,19 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
             }
         }
         p->heavy_tiles += heavy;
-        if (wide_tiles(heavy, tiles, heavy_samples)) {
+        const uint64_t samples = (uint64_t)sc.num_anchors * b->num_points * sc.num_cams *
+                                 b->num_levels;
+        const bool wide = wide_tiles(heavy, tiles, heavy_samples);
+        const bool thin = rcpl && b->channels < 64 * rcpl &&
+                          sparse_tiles(tiles - heavy, samples - heavy_samples);
+        if (wide) {
             p->wide[s >> 5] |= 1u << (s & 31);
-            p->wide_tiles += tiles;
+            p->wide_tiles += thin ? heavy : tiles;
             p->wide_heavy += heavy;
+        }
+        if (thin) {
+            p->thin[s >> 5] |= 1u << (s & 31);
+            p->thin_tiles += tiles - heavy;
         }
     }
     (void)eb;
@@ -1393,6 +1439,7 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, bool backward, cha
     a->total_cells = (uint32_t)p.cells;
     a->total_regions = (uint32_t)p.regions;
     std::copy(std::begin(p.wide), std::end(p.wide), a->wide);
+    std::copy(std::begin(p.thin), std::end(p.thin), a->thin);
     a->lps_shift = log2i(b->channels / p.cpl);
 }
 
@@ -1644,18 +1691,23 @@ msda_status msda_backward_batched(const msda_batch* b, void* workspace, size_t w
     a.off = off;
     a.total_samples = (uint32_t)std::max<uint64_t>(p.samples, 1);
     a.lps_shift = log2i(b->channels / rcpl);
-    // the wide scenes' tiles, then the others'
-    a.block_waves = 8;
-    a.tile_begin = 0;
-    a.tile_split = (uint32_t)p.wide_heavy;
-    a.tile_end = (uint32_t)p.wide_tiles;
-    if ((e = msda::launch_gfeat_tiles_batched(a, b->feat_dtype, rcpl, s)) != hipSuccess)
-        return hip_fail(e, "batched grad_feat tile reduction");
-    a.block_waves = 4;
-    a.tile_begin = (uint32_t)p.wide_tiles;
-    a.tile_split = (uint32_t)(p.wide_tiles + p.heavy_tiles - p.wide_heavy);
-    a.tile_end = (uint32_t)p.tiles;
-    if ((e = msda::launch_gfeat_tiles_batched(a, b->feat_dtype, rcpl, s)) != hipSuccess)
+    // the wide scenes' tiles, then the others', then the sparse light ones (with
+    // the others' coarse ones where no other light tile is between)
+    auto tiles = [&](int waves, uint64_t begin, uint64_t split, uint64_t end, bool sparse) {
+        a.block_waves = waves;
+        a.tile_begin = (uint32_t)begin;
+        a.tile_split = (uint32_t)split;
+        a.tile_end = (uint32_t)end;
+        a.sparse = sparse ? tiles_per_wave(p.thin_tiles, a.lps_shift) : 0;
+        return msda::launch_gfeat_tiles_batched(a, b->feat_dtype, rcpl, s);
+    };
+    const uint64_t split = p.wide_tiles + p.heavy_tiles - p.wide_heavy, thin = p.tiles - p.thin_tiles;
+    const bool between = thin > split || !p.thin_tiles;
+    if ((e = tiles(8, 0, p.wide_heavy, p.wide_tiles, false)) != hipSuccess ||
+        (between && (e = tiles(4, p.wide_tiles, split, thin, false)) != hipSuccess) ||
+        (p.thin_tiles &&
+         (e = tiles(4, between ? thin : p.wide_tiles, between ? thin : split, p.tiles, true)) !=
+             hipSuccess))
         return hip_fail(e, "batched grad_feat tile reduction");
     return p.anchors > 0 ? batch_softmax_grad(b, ws, w, s) : ok();
 }

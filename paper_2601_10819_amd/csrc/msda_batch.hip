@@ -2,9 +2,9 @@
 // that a batched call needs no host-to-device copy (and can be captured in
 // a HIP graph): per scene the first anchor, sample (record) and region; per
 // region its first bilinear cell; and the processing slots of the tiled
-// grad_feat reduction -- wide scenes (BatchArgs::wide) first, then heavy
-// (coarse) levels, then coarsest level first, then scene, then camera -- with
-// the first tile of each slot.
+// grad_feat reduction -- sparse light levels last, of the rest wide scenes
+// (BatchArgs::wide) first, then heavy (coarse) levels, then coarsest level
+// first, then scene, then camera -- with the first tile of each slot.
 //
 // A (scene, level) is heavy when the level's area (camera 0) is at most
 // 1/16 of the scene's largest level area: there a pixel collects 16x or
@@ -146,18 +146,20 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
         }
     }
 
-    // slot groups: (wide, class, level descending, scene), each holding the
-    // scene's cameras; their first slots by a scan over all groups in that
+    // slot groups: (class, level descending, scene), each holding the scene's
+    // cameras; their first slots by a scan over all groups in that
     // order (one thread walking them took most of the kernel's 45 us for 12
     // scenes of 4 levels)
     {
-        const int groups = 4 * L * S;                  // class 0..3: (narrow, light)
+        const int groups = 5 * L * S;
+        auto bit = [&](const uint32_t* m, int s) { return (int)(m[s >> 5] >> (s & 31) & 1); };
+        // classes: wide heavy, wide light, heavy, light, sparse light
         auto value = [&](int i, int* at) {
             const int cls = i / (L * S), rest = i - cls * (L * S), ld = rest / S, s = rest - ld * S;
-            const bool mine = (b.wide[s >> 5] >> (s & 31) & 1) != (u32)(cls >> 1);
-            *at = mine ? ((cls & 1) * L + ld) * S + s : -1;
-            const bool heavy = level_is_heavy(sh_h, sh_w, rstart, s, L - 1 - ld, L);
-            return mine && heavy == ((cls & 1) == 0) ? s_cams[s] : 0u;
+            const int light = !level_is_heavy(sh_h, sh_w, rstart, s, L - 1 - ld, L);
+            const bool mine = cls == (light && bit(b.thin, s) ? 4 : 2 * !bit(b.wide, s) + light);
+            *at = mine ? (light * L + ld) * S + s : -1;
+            return mine ? s_cams[s] : 0u;
         };
         const int per = (groups + blockDim.x - 1) / blockDim.x;
         const int i0 = tid * per, i1 = min(i0 + per, groups);

@@ -199,6 +199,7 @@ struct TileArgs {
     // light (one wave each)
     uint32_t tile_begin, tile_split, tile_end;
     int32_t block_waves;          // waves per block, 4 or 8
+    int32_t sparse;               // 0, or the sparse light tiles a wave takes, one per sub-wave
     uint32_t cells_per_item;
     uint32_t nrec;                // S (records, one per sample)
     int32_t NL, B, C, G;
@@ -213,7 +214,8 @@ struct TileArgs {
 // s owns regions [region_start[s], region_start[s+1]), camera-major); slots
 // order the regions for the tiled reduction: the scenes whose coarse tiles
 // take 8 waves (a launch of their own) before the others, heavy (coarse)
-// levels first, then by level (coarsest first), scene and camera.
+// levels first, then by level (coarsest first), scene and camera; sparse light
+// tiles of all scenes (a launch of their own, too) last.
 constexpr int kMaxBatchScenes = 256;
 constexpr int kMaxBatchRegions = 4096;
 
@@ -258,7 +260,9 @@ struct BatchArgs {
     const uint32_t* off;
     uint32_t tile_begin, tile_split, tile_end;  // as TileArgs
     int32_t block_waves;
+    int32_t sparse;
     uint32_t wide[kMaxBatchScenes / 32];   // bit s: scene s's coarse tiles take 8 waves
+    uint32_t thin[kMaxBatchScenes / 32];   // bit s: scene s's light tiles are sparse
 };
 
 enum FeatType { kF32 = 0, kBF16 = 1, kFP8 = 2, kF16 = 3 };

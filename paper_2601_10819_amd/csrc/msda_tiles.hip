@@ -153,10 +153,36 @@ __device__ __forceinline__ void cell_sample(float (&acc)[4][4][CPL], float4 f, f
     add_sample<DY, DX, 4, 4, CPL>(acc, f, wv, gv);
 }
 
-// Floats per record-table entry: the 4 bilinear factors, the anchor, 3
-// spare, then the G weights (16-byte multiple, so the factors load as one
+// One sample of the cell `at` = dy * 5 + dx, known at run time only.
+template <int CPL>
+__device__ __forceinline__ void add_sample_at(int at, float (&acc)[4][4][CPL], float4 f, float wv,
+                                              const float* gv) {
+#define MSDA_CELL(P) \
+    case P: add_sample<(P) / 5, (P) % 5, 4, 4, CPL>(acc, f, wv, gv); break;
+#define MSDA_CELLS(P) \
+    MSDA_CELL(P) MSDA_CELL(P + 1) MSDA_CELL(P + 2) MSDA_CELL(P + 3) MSDA_CELL(P + 4)
+    switch (at) {
+        MSDA_CELLS(0) MSDA_CELLS(5) MSDA_CELLS(10) MSDA_CELLS(15) MSDA_CELLS(20)
+        default: break;
+    }
+#undef MSDA_CELLS
+#undef MSDA_CELL
+}
+
+// Floats per record-table entry: the 4 bilinear factors, the anchor, the cell
+// (sparse tiles), 2 spare, then the G weights (16-byte multiple, so the factors load as one
 // vector).
 __host__ __device__ inline int tile_entry_floats(int G) { return 8 + ((G + 3) & ~3); }
+
+// Floats of a wave's LDS with sparse tiles: the record table and each sub-wave's
+// cell boundaries.
+__host__ __device__ inline int sparse_wave_floats(int lps_shift, int G) {
+    const int bounds = (64 >> lps_shift) * (kTileH + 1) * (kTileW + 2);
+    return 64 * tile_entry_floats(G) + ((bounds + 3) & ~3);
+}
+
+// Records of a sparse tile whose grad_out rows are loaded together.
+constexpr int kSparseRows = 4;
 
 // Everything one tile's reduction needs (from the single-call or the
 // batched tables).
@@ -192,6 +218,35 @@ __device__ __forceinline__ u32 lane_value(u32 x, int i) {
 // is scalar arithmetic and each lane adds only its channel offset.
 __device__ __forceinline__ const float* go_row(const TileView& v, u32 anchor) {
     return v.grad_out + (size_t)anchor * (u32)v.C;
+}
+
+// The table entry of the record at sorted position e; returns its anchor.
+__device__ __forceinline__ u32 fill_entry(const TileView& v, u32 e, float* ent) {
+    const u32 s = min(v.vals[e], v.nrec - 1u);
+    const float2 fr = v.frac[s];
+    // the scene-local sample (clamped into the scene: an inconsistent sort could
+    // only give wrong sums, never a read outside it)
+    const u32 ls = s - v.sample_offset < v.sample_count ? s - v.sample_offset : 0u;
+    const float* ws = v.w + (size_t)ls * v.G;
+    const u32 an = fast_div(ls, v.magic, v.magic_shift);
+    if (v.vscale) {
+        // the fused form: the sample's weights times its view's factor
+        const u32 n = (ls / (u32)v.L) % (u32)v.N;
+        const float sc = v.vscale[(size_t)an * v.N + n];
+        for (int k = 0; k < v.G; ++k) ent[8 + k] = ws[k] * sc;
+    } else if (v.w16) {
+        // rows of G % 4 == 0 floats from a 16-byte aligned base: 16-byte loads
+        // and LDS stores
+        const float4* ws4 = reinterpret_cast<const float4*>(ws);
+        float4* e4 = reinterpret_cast<float4*>(ent + 8);
+        for (int k = 0; k < (v.G >> 2); ++k) e4[k] = ws4[k];
+    } else {
+        for (int k = 0; k < v.G; ++k) ent[8 + k] = ws[k];
+    }
+    const float hx = 1.f - fr.x, hy = 1.f - fr.y;
+    *reinterpret_cast<float4*>(ent) = make_float4(hy * hx, hy * fr.x, fr.y * hx, fr.y * fr.x);
+    ent[4] = __uint_as_float(an);
+    return an;
 }
 
 // The reduction of one tile by `waves` waves of the block that share its
@@ -275,32 +330,7 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shi
 #pragma unroll
             for (int k = 1; k <= TH; ++k)
                 if (dy == k) e = row_start(k) + f;
-            const u32 s = min(v.vals[e], v.nrec - 1u);
-            const float2 fr = v.frac[s];
-            float* ent = tab + lane * stride;
-            // the scene-local sample (clamped into the scene: an inconsistent
-            // sort could only give wrong sums, never a read outside it)
-            const u32 ls = s - v.sample_offset < v.sample_count ? s - v.sample_offset : 0u;
-            const float* ws = v.w + (size_t)ls * v.G;
-            an = fast_div(ls, v.magic, v.magic_shift);
-            if (v.vscale) {
-                // the fused form: the sample's weights times its view's factor
-                const u32 n = (ls / (u32)v.L) % (u32)v.N;
-                const float sc = v.vscale[(size_t)an * v.N + n];
-                for (int k = 0; k < v.G; ++k) ent[8 + k] = ws[k] * sc;
-            } else if (v.w16) {
-                // rows of G % 4 == 0 floats from a 16-byte aligned base: 16-byte
-                // loads and LDS stores
-                const float4* ws4 = reinterpret_cast<const float4*>(ws);
-                float4* e4 = reinterpret_cast<float4*>(ent + 8);
-                for (int k = 0; k < (v.G >> 2); ++k) e4[k] = ws4[k];
-            } else {
-                for (int k = 0; k < v.G; ++k) ent[8 + k] = ws[k];
-            }
-            const float hx = 1.f - fr.x, hy = 1.f - fr.y;
-            *reinterpret_cast<float4*>(ent) =
-                make_float4(hy * hx, hy * fr.x, fr.y * hx, fr.y * fr.x);
-            ent[4] = __uint_as_float(an);
+            an = fill_entry(v, e, tab + lane * stride);
         }
         // LDS accesses of one wave are performed in order; keep the compiler
         // from hoisting the reads above the writes
@@ -459,6 +489,102 @@ __device__ __forceinline__ void tile_reduce(const TileView& v, const int lps_shi
     }
 }
 
+// The reduction of a sparse tile by the lanes of one sub-wave (1 << lps_shift
+// of them), so that a wave takes as many tiles as it has sub-waves: `v` is the
+// sub-wave's tile, its records one after the other, each by a run-time dispatch
+// on its cell. bnd, tab: the wave's cell boundaries and record table in LDS.
+template <class OT, int CPL>
+__device__ __forceinline__ void tile_reduce_sparse(const TileView& v, const int lps_shift,
+                                                   u32* bnd, float* tab) {
+    constexpr int TH = kTileH, TW = kTileW, NB = (TH + 1) * (TW + 2), QB = kSparseRows;
+    const int lane = threadIdx.x & 63, lps = 1 << lps_shift;
+    const int sub = lane >> lps_shift, sl = lane & (lps - 1);
+    const int stride = tile_entry_floats(v.G);
+    tab += sub * lps * stride;
+    bnd += sub * NB;
+    const int c0 = sl * CPL, g = c0 / (v.C / v.G);
+    for (int k = sl; k < NB; k += lps) {
+        const int dy = k / (TW + 2), dx = k % (TW + 2);
+        u32 x = 0u;
+        if (v.active && v.ty + dy <= v.H) {
+            const u32 cell = v.cbase + (u32)(v.ty + dy) * (u32)(v.W + 1) +
+                             (u32)min(v.tx + dx, v.W + 1);
+            x = min(v.off[cell], v.nrec);
+        }
+        bnd[k] = x;
+    }
+    wave_lds_sync();
+    u32 rs[TH + 1], rn[TH + 1], total = 0;          // the cell rows' first records and lengths
+#pragma unroll
+    for (int dy = 0; dy <= TH; ++dy) {
+        rs[dy] = bnd[dy * (TW + 2)];
+        const u32 end = bnd[dy * (TW + 2) + TW + 1];
+        rn[dy] = end > rs[dy] ? end - rs[dy] : 0u;
+        total += rn[dy];
+    }
+    float acc[TH][TW][CPL];
+#pragma unroll
+    for (int py = 0; py < TH; ++py)
+#pragma unroll
+        for (int px = 0; px < TW; ++px)
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) acc[py][px][i] = 0.f;
+
+    // the records as one flat list, a lane's entry each, lps at a time
+    for (u32 base = 0; base < total; base += (u32)lps) {
+        const int n = (int)min((u32)lps, total - base);
+        if (sl < n) {
+            u32 f = base + (u32)sl;
+            int dy = 0;
+#pragma unroll
+            for (int k = 0; k < TH; ++k)
+                if (dy == k && f >= rn[k]) { f -= rn[k]; dy = k + 1; }
+            u32 e = rs[0] + f;
+#pragma unroll
+            for (int k = 1; k <= TH; ++k)
+                if (dy == k) e = rs[k] + f;
+            int dx = 0;
+#pragma unroll
+            for (int k = 1; k <= TW; ++k)
+                if (e >= bnd[dy * (TW + 2) + k]) dx = k;
+            float* ent = tab + sl * stride;
+            fill_entry(v, e, ent);
+            ent[5] = __int_as_float(dy * (TW + 1) + dx);
+        }
+        wave_lds_sync();
+        for (int q = 0; q < n; q += QB) {
+            float gv[QB][CPL];
+#pragma unroll
+            for (int k = 0; k < QB; ++k)
+                load_go<CPL>(v.grad_out +
+                                 (size_t)__float_as_uint(tab[min(q + k, n - 1) * stride + 4]) * v.C +
+                                 c0,
+                             gv[k]);
+#pragma unroll
+            for (int k = 0; k < QB; ++k) {
+                if (q + k < n) {
+                    const float* ent = tab + (q + k) * stride;
+                    add_sample_at<CPL>(__float_as_int(ent[5]), acc,
+                                       *reinterpret_cast<const float4*>(ent), ent[8 + g], gv[k]);
+                }
+            }
+        }
+        wave_lds_sync();
+    }
+    if (!v.active) return;
+#pragma unroll
+    for (int py = 0; py < TH; ++py) {
+#pragma unroll
+        for (int px = 0; px < TW; ++px) {
+            const int y = v.ty + py, x = v.tx + px;
+            if (y < v.H && x < v.W) {
+                const size_t row = v.row_base + (size_t)(v.start + y * v.W + x);
+                store_row<OT, CPL>(v.grad_feat, row * (size_t)v.C + (size_t)c0, acc[py][px]);
+            }
+        }
+    }
+}
+
 // The last of n slots whose first tile (tile_start) is at most tt, and that
 // tile. The lanes look at n / 64 apart, then at the run between: two loads in
 // a row where a binary search takes one per halving (4 cameras of 128 x 224
@@ -482,27 +608,30 @@ __device__ __forceinline__ int slot_of(const u32* tile_start, int n, u32 tt, u32
     return uniform(slot);
 }
 
-// The tile of id gt (ids run over batch items first, then processing slots
-// within [tile_begin, tile_end)) by `waves` waves of the block, this wave the
-// wt-th of them.
-template <class OT, int CPL, bool WHOLE, int QB>
-__device__ __forceinline__ void gfeat_tile_body(const TileArgs& t, const u32 gt, const int waves,
-                                                const int wt) {
-    static_assert(kTileH == 4 && kTileW == 4, "the cell dispatch is written for 4x4 tiles");
-    // LDS: per wave a record table (64 entries
-    // of bilinear factors, anchor and G weights); after the records, the
-    // waves' partial sums reuse the record tables' space.
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    constexpr int TH = kTileH, TW = kTileW;
-    float* work = reinterpret_cast<float*>(smem_raw);
+// The slot of tile tt, at or after slot o (which starts at *first), lane by lane.
+__device__ __forceinline__ int slot_after(const u32* tile_start, int n, u32 tt, int o, u32* first) {
+    for (; o + 1 < n; ++o) {
+        const u32 next = tile_start[o + 1];
+        if (next > tt) break;
+        *first = next;
+    }
+    return o;
+}
 
+// The tile of id gt; ids run over batch items first, then processing slots
+// within [tile_begin, tile_end). WAVE: the same id in every lane, else ids from
+// the first lane's on.
+template <bool WAVE>
+__device__ __forceinline__ TileView tile_view(const TileArgs& t, const u32 gt) {
+    constexpr int TH = kTileH, TW = kTileW;
     const u32 span = t.tile_end - t.tile_begin;
     TileView v;
     v.active = gt < span * (u32)t.B;
     const u32 tt = t.tile_begin + (v.active ? gt / (u32)t.B : 0u);
     const int b = v.active ? (int)(gt % (u32)t.B) : 0;
     u32 first;
-    const int o = slot_of(t.tile_start, t.NL, tt, &first);
+    int o = slot_of(t.tile_start, t.NL, WAVE ? tt : (u32)uniform((int)tt), &first);
+    if constexpr (!WAVE) o = slot_after(t.tile_start, t.NL, tt, o, &first);
     // (as region_tables_kernel lists the slots: a division instead of a load)
     const int r = (o % t.N) * t.L + (t.L - 1 - o / t.N);
     v.H = t.shapes[2 * r];
@@ -531,61 +660,20 @@ __device__ __forceinline__ void gfeat_tile_body(const TileArgs& t, const u32 gt,
     v.vscale = t.view_scale;
     v.N = t.N;
     v.L = t.L;
-    tile_reduce<OT, CPL, WHOLE, QB>(v, t.lps_shift, waves, wt, work);
+    return v;
 }
 
-// At most 128 VGPRs, i.e. 4 waves per SIMD. The reduction waits on record
-// and grad_out loads, and a fourth wave hides more of that than a few more
-// registers give (measured on the 64-camera scene: light tiles 0.28 -> 0.24
-// ms, coarse 0.19 -> 0.18 ms).
-//
-// A light tile has about one record per cell, so its wave issues the first
-// record's row of a cell row's five cells together (FIRST) and the rest two
-// at a time; a coarse tile's wave has runs long enough for four at a time
-// (64 cameras BF16 0.358 -> 0.345 ms, 6 cameras FP32 75 -> 67 us; 6 or 8 at a
-// time 69 and 71, two and FIRST 79). Boundaries and anchors are lanes'
-// registers, read as scalars: an LDS round trip per record less.
-//
-// Narrower records (C < 64 * CPL) share the wave as sub-waves of one tile
-// rather than taking tiles of their own, which left a run-time dispatch on
-// the cell per record and, on small problems, too few waves: 2 cameras of
-// 128 x 224, C = 64, 128 anchors 144 -> 30 us, 32 cameras of 256 x 448, 900
-// anchors, C = 128 285 -> 165 us, C = 64 317 -> 150 us.
-//
-// One launch for both kinds of tiles: the coarse tiles (ids below
-// (tile_split - tile_begin) * B) first, all waves of a block each, then the
-// light ones, one wave each; the light blocks fill the CUs around the long
-// coarse ones instead of waiting for them to drain. A block has 4 waves, or 8
-// where the coarse tiles would be the launch's critical path (wide_tiles).
-constexpr int kMaxTileBlockWaves = 8;
-
-template <class OT, int CPL, bool WHOLE>
-__global__ void __launch_bounds__(64 * kMaxTileBlockWaves)
-    __attribute__((amdgpu_waves_per_eu(4, 8))) gfeat_tile_kernel(TileArgs t) {
-    const int BW = (int)(blockDim.x >> 6);
-    const u32 heavy = (t.tile_split - t.tile_begin) * (u32)t.B;
-    const int wave = uniform((int)(threadIdx.x >> 6));
-    if (blockIdx.x < heavy)
-        gfeat_tile_body<OT, CPL, WHOLE, WHOLE ? 4 : 2>(t, blockIdx.x, BW, wave);
-    else
-        gfeat_tile_body<OT, CPL, WHOLE, 2>(
-            t, heavy + (blockIdx.x - heavy) * (u32)BW + (u32)wave, 1, 0);
-}
-
-// Batched tiled reduction: tiles of all scenes' regions in slot order; the
-// tile of id gt (from tile_begin) by `waves` waves, this wave the wt-th.
-template <class OT, int CPL, bool WHOLE, int QB>
-__device__ __forceinline__ void gfeat_tile_batched_body(const BatchArgs& b, const u32 gt,
-                                                        const int waves, const int wt) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
+// The same of a batch: tiles of all scenes' regions in slot order.
+template <bool WAVE>
+__device__ __forceinline__ TileView tile_view(const BatchArgs& b, const u32 gt) {
     constexpr int TH = kTileH, TW = kTileW;
-    float* work = reinterpret_cast<float*>(smem_raw);
-
     TileView v;
     v.active = gt < b.tile_end - b.tile_begin;
     const u32 tt = b.tile_begin + (v.active ? gt : 0u);
     u32 first;
-    const int slot = slot_of(b.t.tile_start, (int)b.total_regions, tt, &first);
+    int slot = slot_of(b.t.tile_start, (int)b.total_regions, WAVE ? tt : (u32)uniform((int)tt),
+                       &first);
+    if constexpr (!WAVE) slot = slot_after(b.t.tile_start, (int)b.total_regions, tt, slot, &first);
     const int s = (int)b.t.slot_scene[slot];
     const int r = (int)b.t.slot_region[slot];
     const msda_scene& sc = b.scenes[s];
@@ -615,24 +703,88 @@ __device__ __forceinline__ void gfeat_tile_batched_body(const BatchArgs& b, cons
     v.vscale = nullptr;
     v.N = 1;
     v.L = 1;
-    tile_reduce<OT, CPL, WHOLE, QB>(v, b.lps_shift, waves, wt, work);
+    return v;
 }
 
-// As gfeat_tile_kernel, but the heavy tiles ([tile_begin, tile_split)) too
-// walk as the light ones do: with the batch's scene lookups, 4 rows at a time
-// spilled under the 128-VGPR cap (the 12-scene batch's step: 9.37 ms with 4,
-// 9.22 ms with 2).
-template <class OT, int CPL, bool WHOLE>
+// The tile of id gt by `waves` waves of the block, this wave the wt-th of them.
+template <class OT, int CPL, bool WHOLE, int QB, class Args>
+__device__ __forceinline__ void tile_body(const Args& t, const u32 gt, const int waves,
+                                          const int wt) {
+    static_assert(kTileH == 4 && kTileW == 4, "the cell dispatch is written for 4x4 tiles");
+    // LDS: per wave a record table (64 entries of bilinear factors, anchor and G
+    // weights); after the records, the waves' partial sums in its space
+    extern __shared__ __align__(16) unsigned char smem[];
+    tile_reduce<OT, CPL, WHOLE, QB>(tile_view<true>(t, gt), t.lps_shift, waves, wt,
+                                    reinterpret_cast<float*>(smem));
+}
+
+// Sparse tiles from id gt on, one per sub-wave, t.sparse of them.
+template <class OT, int CPL, class Args>
+__device__ __forceinline__ void sparse_body(const Args& t, const u32 gt, u32 end, const int wave) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int sub = (threadIdx.x & 63) >> t.lps_shift;
+    TileView v = tile_view<false>(t, min(gt + (u32)sub, end));
+    v.active = v.active && sub < t.sparse;
+    float* tab = reinterpret_cast<float*>(smem) + (size_t)wave * sparse_wave_floats(t.lps_shift, t.G);
+    tile_reduce_sparse<OT, CPL>(v, t.lps_shift,
+                                reinterpret_cast<u32*>(tab + 64 * tile_entry_floats(t.G)), tab);
+}
+
+// At most 128 VGPRs, i.e. 4 waves per SIMD. The reduction waits on record
+// and grad_out loads, and a fourth wave hides more of that than a few more
+// registers give (measured on the 64-camera scene: light tiles 0.28 -> 0.24
+// ms, coarse 0.19 -> 0.18 ms).
+//
+// A light tile has about one record per cell, so its wave issues the first
+// record's row of a cell row's five cells together (FIRST) and the rest two
+// at a time; a coarse tile's wave has runs long enough for four at a time
+// (64 cameras BF16 0.358 -> 0.345 ms, 6 cameras FP32 75 -> 67 us; 6 or 8 at a
+// time 69 and 71, two and FIRST 79). Boundaries and anchors are lanes'
+// registers, read as scalars: an LDS round trip per record less.
+//
+// Narrower records (C < 64 * CPL) share the wave as sub-waves of one tile
+// rather than taking tiles of their own, which left a run-time dispatch on
+// the cell per record and, on small problems, too few waves: 2 cameras of
+// 128 x 224, C = 64, 128 anchors 144 -> 30 us, 32 cameras of 256 x 448, 900
+// anchors, C = 128 285 -> 165 us, C = 64 317 -> 150 us. Sparse light tiles do
+// take a sub-wave each (SPARSE, see sparse_tiles).
+//
+// One launch for both kinds of tiles: the coarse tiles (ids below
+// (tile_split - tile_begin) * B) first, all waves of a block each, then the
+// light ones, one wave each; the light blocks fill the CUs around the long
+// coarse ones instead of waiting for them to drain. A block has 4 waves, or 8
+// where the coarse tiles would be the launch's critical path (wide_tiles).
+constexpr int kMaxTileBlockWaves = 8;
+
+template <class OT, int CPL, bool WHOLE, bool SPARSE, int QB, class Args>
+__device__ __forceinline__ void tile_block(const Args& t, const u32 items) {
+    const int BW = (int)(blockDim.x >> 6);
+    const u32 heavy = (t.tile_split - t.tile_begin) * items;
+    const int wave = uniform((int)(threadIdx.x >> 6));
+    if (blockIdx.x < heavy) {
+        tile_body<OT, CPL, WHOLE, QB>(t, blockIdx.x, BW, wave);
+        return;
+    }
+    const u32 w = (blockIdx.x - heavy) * (u32)BW + (u32)wave;
+    if constexpr (SPARSE)
+        sparse_body<OT, CPL>(t, heavy + w * (u32)t.sparse, (t.tile_end - t.tile_begin) * items, wave);
+    else
+        tile_body<OT, CPL, WHOLE, 2>(t, heavy + w, 1, 0);
+}
+
+template <class OT, int CPL, bool WHOLE, bool SPARSE>
+__global__ void __launch_bounds__(64 * kMaxTileBlockWaves)
+    __attribute__((amdgpu_waves_per_eu(4, 8))) gfeat_tile_kernel(TileArgs t) {
+    tile_block<OT, CPL, WHOLE, SPARSE, WHOLE ? 4 : 2>(t, (u32)t.B);
+}
+
+// The batched form; its heavy tiles ([tile_begin, tile_split)) too walk as the
+// light ones do: with the batch's scene lookups, 4 rows at a time spilled under
+// the 128-VGPR cap (the 12-scene batch's step: 9.37 ms with 4, 9.22 ms with 2).
+template <class OT, int CPL, bool WHOLE, bool SPARSE>
 __global__ void __launch_bounds__(64 * kMaxTileBlockWaves)
     __attribute__((amdgpu_waves_per_eu(4, 8))) gfeat_tile_batched_kernel(BatchArgs b) {
-    const int BW = (int)(blockDim.x >> 6);
-    const u32 heavy = b.tile_split - b.tile_begin;
-    const int wave = uniform((int)(threadIdx.x >> 6));
-    if (blockIdx.x < heavy)
-        gfeat_tile_batched_body<OT, CPL, WHOLE, 2>(b, blockIdx.x, BW, wave);
-    else
-        gfeat_tile_batched_body<OT, CPL, WHOLE, 2>(
-            b, heavy + (blockIdx.x - heavy) * (u32)BW + (u32)wave, 1, 0);
+    tile_block<OT, CPL, WHOLE, SPARSE, 2>(b, 1);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -640,9 +792,10 @@ __global__ void __launch_bounds__(64 * kMaxTileBlockWaves)
 // LDS of a tile block of `waves` waves: the larger of the record tables and the partial sums (coarse tiles: waves/2 halves of
 // a tile's accumulators).
 template <int CPL>
-static size_t tile_lds_bytes(int waves, int G, bool coarse) {
+static size_t tile_lds_bytes(int waves, int G, bool coarse, int sparse, int lps_shift) {
     const size_t part = coarse ? (size_t)(waves / 2) * kTileH * kTileW * CPL * 64 * 4 : 0;
-    const size_t tables = (size_t)waves * 64 * tile_entry_floats(G) * sizeof(float);
+    const size_t wave = sparse ? sparse_wave_floats(lps_shift, G) : 64 * tile_entry_floats(G);
+    const size_t tables = (size_t)waves * wave * sizeof(float);
     return part > tables ? part : tables;
 }
 
@@ -658,45 +811,50 @@ static hipError_t tile_parts(Args t, u32 items, F&& launch) {
         t.tile_split = split < at ? at : split < t.tile_end ? split : t.tile_end;
         const u32 heavy = (t.tile_split - t.tile_begin) * items;
         const u32 light = (t.tile_end - t.tile_split) * items;
-        launch(t, heavy, heavy + (light + BW - 1) / BW);
+        const u32 per_block = BW * (u32)(t.sparse ? t.sparse : 1);
+        launch(t, heavy, heavy + (light + per_block - 1) / per_block);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-template <class OT, int CPL, bool WHOLE>
+template <class OT, int CPL, bool WHOLE, bool SPARSE>
 static hipError_t tile_launch_of(const TileArgs& a, hipStream_t s) {
     return tile_parts(a, (u32)a.B, [&](const TileArgs& t, u32 heavy, u32 blocks) {
         mark_begin("gfeat_tile_kernel", s);
-        hipLaunchKernelGGL((gfeat_tile_kernel<OT, CPL, WHOLE>), dim3(blocks),
+        hipLaunchKernelGGL((gfeat_tile_kernel<OT, CPL, WHOLE, SPARSE>), dim3(blocks),
                            dim3(64 * t.block_waves),
-                           tile_lds_bytes<CPL>(t.block_waves, t.G, heavy > 0), s, t);
+                           tile_lds_bytes<CPL>(t.block_waves, t.G, heavy > 0, t.sparse, t.lps_shift),
+                           s, t);
         mark_end(s);
     });
 }
 
 template <class OT, int CPL>
 static hipError_t tile_launch(const TileArgs& t, hipStream_t s) {
-    return t.lps_shift == 6 ? tile_launch_of<OT, CPL, true>(t, s)
-                            : tile_launch_of<OT, CPL, false>(t, s);
+    return t.lps_shift == 6 ? tile_launch_of<OT, CPL, true, false>(t, s)
+           : t.sparse       ? tile_launch_of<OT, CPL, false, true>(t, s)
+                            : tile_launch_of<OT, CPL, false, false>(t, s);
 }
 
-template <class OT, int CPL, bool WHOLE>
+template <class OT, int CPL, bool WHOLE, bool SPARSE>
 static hipError_t tile_batched_launch_of(const BatchArgs& a, hipStream_t s) {
     return tile_parts(a, 1, [&](const BatchArgs& b, u32 heavy, u32 blocks) {
         mark_begin("gfeat_tile_batched", s);
-        hipLaunchKernelGGL((gfeat_tile_batched_kernel<OT, CPL, WHOLE>), dim3(blocks),
+        hipLaunchKernelGGL((gfeat_tile_batched_kernel<OT, CPL, WHOLE, SPARSE>), dim3(blocks),
                            dim3(64 * b.block_waves),
-                           tile_lds_bytes<CPL>(b.block_waves, b.G, heavy > 0), s, b);
+                           tile_lds_bytes<CPL>(b.block_waves, b.G, heavy > 0, b.sparse, b.lps_shift),
+                           s, b);
         mark_end(s);
     });
 }
 
 template <class OT, int CPL>
 static hipError_t tile_batched_launch(const BatchArgs& b, hipStream_t s) {
-    return b.lps_shift == 6 ? tile_batched_launch_of<OT, CPL, true>(b, s)
-                            : tile_batched_launch_of<OT, CPL, false>(b, s);
+    return b.lps_shift == 6 ? tile_batched_launch_of<OT, CPL, true, false>(b, s)
+           : b.sparse       ? tile_batched_launch_of<OT, CPL, false, true>(b, s)
+                            : tile_batched_launch_of<OT, CPL, false, false>(b, s);
 }
 
 hipError_t launch_gfeat_tiles_batched(const BatchArgs& b, int out_dtype, int cpl, hipStream_t s) {
