@@ -112,15 +112,16 @@ __device__ __forceinline__ GradAnchor grad_anchor(const OpArgs& a, int b, int an
     return x;
 }
 
-// Pair orders: the k-th pair -> keypoint p, camera n. Anchor order walks the
-// anchor's pairs as stored (keypoint-major), view order the cameras from n_lo
-// one after the other.
+// Pair orders: the k-th pair -> keypoint p, camera n. Both walk the cameras one
+// after the other: anchor order's wave all of the anchor's, taking every
+// nwaves-th pair, view order's those from n_lo on.
 struct AnchorOrder {
-    int N;
-    u32 m;                   // div_magic(N, pairs)
+    int P, nwaves, wave;
+    u32 m;                   // div_magic(P, pairs)
     __device__ __forceinline__ void operator()(int k, int* p, int* n) const {
-        *p = div_by(k, N, m);
-        *n = k - *p * N;
+        const int i = k * nwaves + wave;
+        *n = div_by(i, P, m);
+        *p = i - *n * P;
     }
 };
 
