@@ -1268,6 +1268,7 @@ struct BatchPlan {
     // scenes whose light tiles are sparse: their bits and light tiles
     uint32_t thin[msda::kMaxBatchScenes / 32];
     uint64_t thin_tiles;
+    uint16_t heavy[msda::kMaxBatchScenes];   // coarse regions of each scene
 };
 
 // Validates the batch (every scene against its host mirrors) and sizes it.
@@ -1338,24 +1339,12 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
         p->max_ap = std::max<uint64_t>(p->max_ap, (uint64_t)sc.num_anchors * b->num_points);
         if (!bucket_keys_fit(d.host_spatial_shapes, (int64_t)sc.num_cams * b->num_levels))
             p->keys_fit = false;
-        // heavy (scene, level): camera 0's area at most 1/16 of its largest level
-        int64_t max_area = 0;
-        for (int l = 0; l < b->num_levels; ++l)
-            max_area = std::max<int64_t>(max_area, (int64_t)d.host_spatial_shapes[2 * l] *
-                                                       d.host_spatial_shapes[2 * l + 1]);
-        uint64_t heavy = 0, heavy_samples = 0;
-        for (int l = 0; l < b->num_levels; ++l) {
-            if ((int64_t)d.host_spatial_shapes[2 * l] * d.host_spatial_shapes[2 * l + 1] * 16 >
-                max_area)
-                continue;
-            heavy_samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams;
-            for (int n = 0; n < sc.num_cams; ++n) {
-                const int r = n * b->num_levels + l;
-                const uint64_t H = d.host_spatial_shapes[2 * r], W = d.host_spatial_shapes[2 * r + 1];
-                heavy += ((H + msda::kTileH - 1) / msda::kTileH) *
-                         ((W + msda::kTileW - 1) / msda::kTileW);
-            }
-        }
+        // the scene's coarse tiles as the single call splits them
+        uint32_t heavy_regions = 0;
+        const uint64_t heavy = heavy_tiles(&d, &heavy_regions);
+        const uint64_t heavy_samples =
+            (uint64_t)heavy_regions * (uint64_t)sc.num_anchors * (uint64_t)b->num_points;
+        p->heavy[s] = (uint16_t)heavy_regions;
         p->heavy_tiles += heavy;
         const uint64_t samples = (uint64_t)sc.num_anchors * b->num_points * sc.num_cams *
                                  b->num_levels;
@@ -1445,6 +1434,7 @@ void fill_batch_args(const msda_batch* b, const BatchPlan& p, bool backward, cha
     a->total_regions = (uint32_t)p.regions;
     std::copy(std::begin(p.wide), std::end(p.wide), a->wide);
     std::copy(std::begin(p.thin), std::end(p.thin), a->thin);
+    std::copy(std::begin(p.heavy), std::end(p.heavy), a->heavy);
     a->lps_shift = log2i(b->channels / p.cpl);
 }
 

@@ -6,10 +6,8 @@
 // (BatchArgs::wide) first, then heavy (coarse) levels, then coarsest level
 // first, then scene, then camera -- with the first tile of each slot.
 //
-// A (scene, level) is heavy when the level's area (camera 0) is at most
-// 1/16 of the scene's largest level area: there a pixel collects 16x or
-// more the samples of the finest level. The host computes the same split
-// from its mirrors to size the two tile launches.
+// A scene's heavy regions are the first BatchArgs::heavy of its slots (coarsest
+// level first, cameras in order), as the host counts them for the single call.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -17,22 +15,13 @@
 
 namespace msda {
 
-// Heavy flag of (scene s, level l) from the LDS copy of the shapes.
-__device__ __forceinline__ bool level_is_heavy(const uint16_t* sh_h, const uint16_t* sh_w,
-                                               const u32* rstart, int s, int l, int L) {
-    const u32 r0 = rstart[s];                      // camera 0's regions: r0 + l
-    u32 max_area = 0;
-    for (int k = 0; k < L; ++k) max_area = max(max_area, (u32)sh_h[r0 + k] * (u32)sh_w[r0 + k]);
-    return (u32)sh_h[r0 + l] * (u32)sh_w[r0 + l] * 16u <= max_area;
-}
-
 __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int backward) {
     __shared__ u32 s_anchors[kMaxBatchScenes];
     __shared__ u32 s_cams[kMaxBatchScenes];
     __shared__ u32 rstart[kMaxBatchScenes + 1];
     __shared__ uint16_t sh_h[kMaxBatchRegions];
     __shared__ uint16_t sh_w[kMaxBatchRegions];
-    __shared__ u32 grp[2 * 8 * kMaxBatchScenes];    // first slot of (class, level, scene)
+    __shared__ u32 grp[2 * 8 * kMaxBatchScenes];    // first slot of (light, level, scene)
     __shared__ __align__(8) u32 tiles[kMaxBatchRegions];   // tiles of each slot, then their scan
     __shared__ u32 lds4[4];
     static_assert(2 * kSlots * kMaxBatchScenes <= kMaxBatchRegions, "slot_first shares tiles' space");
@@ -146,8 +135,12 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
         }
     }
 
+    // the heavy cameras of scene s's level L - 1 - ld: the first ones
+    auto heavy_cams = [&](int s, int ld) {
+        return min(max((int)b.heavy[s] - ld * (int)s_cams[s], 0), (int)s_cams[s]);
+    };
     // slot groups: (class, level descending, scene), each holding the scene's
-    // cameras; their first slots by a scan over all groups in that
+    // cameras of the class; their first slots by a scan over all groups in that
     // order (one thread walking them took most of the kernel's 45 us for 12
     // scenes of 4 levels)
     {
@@ -156,10 +149,10 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
         // classes: wide heavy, wide light, heavy, light, sparse light
         auto value = [&](int i, int* at) {
             const int cls = i / (L * S), rest = i - cls * (L * S), ld = rest / S, s = rest - ld * S;
-            const int light = !level_is_heavy(sh_h, sh_w, rstart, s, L - 1 - ld, L);
+            const int light = cls == 1 || cls >= 3, h = heavy_cams(s, ld);
             const bool mine = cls == (light && bit(b.thin, s) ? 4 : 2 * !bit(b.wide, s) + light);
             *at = mine ? (light * L + ld) * S + s : -1;
-            return mine ? s_cams[s] : 0u;
+            return !mine ? 0u : light ? s_cams[s] - (u32)h : (u32)h;
         };
         const int per = (groups + blockDim.x - 1) / blockDim.x;
         const int i0 = tid * per, i1 = min(i0 + per, groups);
@@ -184,8 +177,8 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
         const int s = lo;
         const u32 i = g - rstart[s];
         const int n = (int)(i / (u32)L), l = (int)(i % (u32)L);
-        const int cls = level_is_heavy(sh_h, sh_w, rstart, s, l, L) ? 0 : 1;
-        const u32 slot = grp[(cls * L + (L - 1 - l)) * S + s] + (u32)n;
+        const int h = heavy_cams(s, L - 1 - l), light = n >= h;
+        const u32 slot = grp[(light * L + (L - 1 - l)) * S + s] + (u32)(light ? n - h : n);
         b.t.slot_scene[slot] = (u32)s;
         b.t.slot_region[slot] = i;
         tiles[slot] = (((u32)sh_h[g] + kTileH - 1) / kTileH) * (((u32)sh_w[g] + kTileW - 1) / kTileW);

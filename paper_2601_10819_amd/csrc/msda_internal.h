@@ -263,6 +263,7 @@ struct BatchArgs {
     int32_t sparse;
     uint32_t wide[kMaxBatchScenes / 32];   // bit s: scene s's coarse tiles take 8 waves
     uint32_t thin[kMaxBatchScenes / 32];   // bit s: scene s's light tiles are sparse
+    uint16_t heavy[kMaxBatchScenes];       // scene s's heavy (coarse) regions
 };
 
 enum FeatType { kF32 = 0, kBF16 = 1, kFP8 = 2, kF16 = 3 };
