@@ -367,15 +367,18 @@ uint32_t heavy_tiles(const msda_desc* d, uint32_t* regions) {
 // us, the 16-camera step 317 -> 344); 8 where the chip is drained before the
 // coarse tiles, which are as long as their records are many, are done: at most
 // a quarter of the 4096 waves that are resident at once, and coarse tiles of
-// 256 samples (C = 64, 2 cameras of 128 x 224, 333 samples per coarse tile, 30
-// -> 20 us; below 200 samples 8 waves were no faster or slower). Up to 8192
-// waves a call alone gains too (6 cameras FP32 67 -> 52), but the number sets
-// the order of the sums, so it is a scene's own: a batch takes it over and
-// needs a launch for either kind, which costs a batch of two scenes, one on
-// each side of the line, 20 to 28 us (468 -> 496, 355 -> 378), and scenes of
-// so many tiles come in such batches.
+// more samples than a chunk or two of 64 (C = 256, 2 cameras of 128 x 224, whole
+// grad_feat with 4 / 8 waves, by samples per coarse tile: 65 31.6 / 32.4 us, 104
+// 36.0 / 31.2, 156 37.3 / 31.5, 338 57.5 / 42.5; C = 64 31.6 / 32.5, 33.2 / 31.4,
+// 34.0 / 31.9, 47.2 / 37.2). With many groups 8 waves' record tables leave a CU
+// one block, which is all it gets here (64 groups, 333 samples 61.6 / 51.0, 32
+// 59.2 / 46.5). Up to 8192 waves a call alone gains too (6 cameras FP32 67 -> 52),
+// but the number sets the order of the sums, so it is a scene's own: a batch
+// takes it over and needs a launch for either kind, which costs a batch of two
+// scenes, one on each side of the line, 20 to 28 us (468 -> 496, 355 -> 378), and
+// scenes of so many tiles come in such batches.
 bool wide_tiles(uint64_t heavy, uint64_t tiles, uint64_t heavy_samples) {
-    constexpr uint64_t kMaxWaves = 1024, kMinSamples = 256;
+    constexpr uint64_t kMaxWaves = 1024, kMinSamples = 96;
     const uint64_t waves = 4 * heavy + (tiles - heavy);
     return heavy && waves <= kMaxWaves && heavy_samples >= kMinSamples * heavy;
 }
