@@ -305,8 +305,7 @@ bool aligned(const void* p, size_t n) { return ((uintptr_t)p % n) == 0; }
 // values (x2), fractions, per-cell offsets, region tables and the sort's
 // histogram scratch.
 struct SortedWs {
-    size_t keys_a, keys_b, vals_a, vals_b, frac, off, cell_start, tile_start, tile_region,
-        scratch, total;
+    size_t keys_a, keys_b, vals_a, vals_b, frac, off, cell_start, tile_start, scratch, total;
 };
 
 SortedWs sorted_layout(uint64_t nrec, uint64_t ncells, uint64_t nregions) {
@@ -320,8 +319,7 @@ SortedWs sorted_layout(uint64_t nrec, uint64_t ncells, uint64_t nregions) {
     w.off = w.frac + align256(nrec * 8);
     w.cell_start = w.off + align256((ncells + 1) * 4);
     w.tile_start = w.cell_start + align256(nregions * 4);
-    w.tile_region = w.tile_start + align256((nregions + 1) * 4);
-    w.scratch = w.tile_region + align256(nregions * 4);
+    w.scratch = w.tile_start + align256((nregions + 1) * 4);
     w.total = w.scratch + align256(msda::sort_scratch_words((uint32_t)nrec) * 4);
     return w;
 }
@@ -825,12 +823,11 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     }
 
     SortedWs W = {};
-    uint32_t *cell_start = nullptr, *tile_start = nullptr, *tile_region = nullptr;
+    uint32_t *cell_start = nullptr, *tile_start = nullptr;
     if (grad_feat) {
         W = sorted_layout(nrec, ncells, (uint64_t)a.N * a.L);
         cell_start = reinterpret_cast<uint32_t*>(ws + W.cell_start);
         tile_start = reinterpret_cast<uint32_t*>(ws + W.tile_start);
-        tile_region = reinterpret_cast<uint32_t*>(ws + W.tile_region);
         // records sorted per (batch item, region) bucket in LDS when the
         // buckets fit (that launch also writes the region tables), else, or
         // when asked, by the global radix sort
@@ -838,7 +835,7 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
             a.rec_bucket_ap = (uint32_t)(a.A * a.P);
         if (!a.rec_bucket_ap &&
             (e = msda::launch_region_tables(spatial_shapes, a.N, a.L, cell_start, tile_start,
-                                            tile_region, s)) != hipSuccess)
+                                            s)) != hipSuccess)
             return hip_fail(e, "region tables");
         a.rec_key = reinterpret_cast<uint32_t*>(ws + W.keys_a);
         a.rec_frac = reinterpret_cast<float2*>(ws + W.frac);
@@ -908,7 +905,7 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
         sorted = reinterpret_cast<uint32_t*>(ws + W.vals_a);
         e = msda::launch_bucket_sort(reinterpret_cast<uint32_t*>(ws + W.keys_a), spatial_shapes,
                                      a.B, a.N, a.L, a.A, a.P, (uint32_t)cells, sorted, off,
-                                     cell_start, tile_start, tile_region, vis_place, vis_items,
+                                     cell_start, tile_start, vis_place, vis_items,
                                      s);
     } else {
         e = msda::launch_sort_records(reinterpret_cast<uint32_t*>(ws + W.keys_a),
@@ -930,8 +927,6 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     t.starts = level_start_index;
     t.cell_start = cell_start;
     t.tile_start = tile_start;
-    t.tile_region = tile_region;
-    t.tiles_per_item = (uint32_t)tiles;
     t.cells_per_item = (uint32_t)cells;
     t.nrec = (uint32_t)(nrec > 0 ? nrec : 1);
     t.NL = a.N * a.L;
@@ -1217,7 +1212,7 @@ struct BatchWeights {
     uint64_t stats_bytes, w32_bytes;
 };
 
-// part_bytes: the view-order forward's per-slot partial sums (always part of
+// part_bytes: the view-order forward's partial rows (always part of
 // the forward's workspace, so that the order can change without resizing).
 BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncells, bool records,
                      uint64_t part_bytes = 0, const BatchWeights& wb = BatchWeights{}) {

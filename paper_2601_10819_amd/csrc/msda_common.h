@@ -161,13 +161,12 @@ __device__ __forceinline__ Axis axis_of(float u, int n) {
 }
 
 // The 4 corners of one sample, in the order (y0,x0), (y0,x0+1), (y0+1,x0),
-// (y0+1,x0+1): byte offsets (kOOB when outside), bilinear weights (0 when
-// outside) and rows within the batch item (-1 when outside).
+// (y0+1,x0+1): byte offsets (kOOB when outside) and bilinear weights (0 when
+// outside).
 struct Corners {
     u32 off[4];
     float cw[4];
     float lx, ly;
-    int row[4];
     int x0, y0;     // top-left neighbour (meaningful when valid)
     bool valid;
 };
@@ -192,7 +191,6 @@ __device__ __forceinline__ Corners corners_of(float u, float v, const Geo& g, u3
     const int rows[4] = {base, base + 1, base + g.W, base + g.W + 1};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        c.row[k] = in[k] ? rows[k] : -1;
         c.off[k] = in[k] ? (u32)rows[k] * row_bytes + lane_off : kOOB;
         c.cw[k] = in[k] ? wt[k] : 0.f;
     }
@@ -213,13 +211,6 @@ __device__ __forceinline__ int wave_index() {
 // A value the caller knows to be the same in every lane, marked as such for
 // the compiler (it is then kept in scalar registers).
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-__device__ __forceinline__ const void* uniform(const void* p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo);
-}
 
 __device__ __forceinline__ float xor_shuffle(float v, int mask) {
     return __shfl_xor(v, mask, 64);
@@ -313,7 +304,6 @@ struct WSrc {
     const float2* stats;    // per group (max, 1/sum), or nullptr (plain weights)
     int G;
     bool bf16;
-    __device__ WSrc(const float* w) : p(w), stats(nullptr), G(1), bf16(false) {}
     __device__ WSrc(const void* w, const float2* st, int g, bool b)
         : p(w), stats(st), G(g), bf16(b) {}
     // entry i as stored (FP32, or bfloat16 widened exactly)

@@ -134,7 +134,13 @@ __host__ __device__ inline int fwd_rows(int N, int P, int L) {
 }
 
 // The backward, whose rows need no combining: one camera per row, or as many
-// as hold kMinRowPairs pairs where anchors have few keypoints.
+// as hold kMinRowPairs pairs where anchors have few keypoints, and a wave's start
+// is most of its work (64 cameras of 256 x 448, 900 anchors, BF16, rows of 1 / 4 /
+// 7 / 13 / 26 pairs at least: 1 keypoint, 4 levels 69 / 37 / 41 / 44 / 42 us, 1
+// level 54 / 22 / 22 / 21 / 21; 4 keypoints 127 / 127 / 123 / 128 / 136 and 70 / 70
+// / 55 / 52 / 53; 6 keypoints 180 / 180 / 178 / 186 / 196 and 87 / 87 / 72 / 72 / 74.
+// 16 cameras FP32, 6 keypoints 71 / 71 / 80 / 85 / 80: there the longer rows end
+// the launch, and a line that suits both is not in sight).
 constexpr int kMinRowPairs = 7;
 
 __host__ __device__ inline int bwd_rows(int N, int P) {
@@ -175,8 +181,8 @@ struct OpArgs {
 };
 
 // The tiled grad_feat reduction over records sorted by bilinear cell.
-// Tiles are kTileH x kTileW pixels of one region; processing slot o covers
-// region tile_region[o], regions ordered coarse levels first.
+// Tiles are kTileH x kTileW pixels of one region; processing slot o covers camera
+// o % N at level L - 1 - o / N: coarse levels first.
 constexpr int kTileH = 4, kTileW = 4;
 
 struct TileArgs {
@@ -190,10 +196,8 @@ struct TileArgs {
     const int32_t* starts;        // [N*L]
     const uint32_t* cell_start;   // [N*L]
     const uint32_t* tile_start;   // [N*L + 1], by processing slot
-    const uint32_t* tile_region;  // [N*L], region of each processing slot
     const float* view_scale;      // [B*A][N] per-view weight factor (fused form), or nullptr
     int32_t N, L;                 // cameras and levels (to find a sample's view)
-    uint32_t tiles_per_item;
     // the tiles of each batch item (slot order) to reduce: [tile_begin,
     // tile_split) coarse (all waves of a block each), [tile_split, tile_end)
     // light (one wave each)
@@ -310,9 +314,9 @@ hipError_t launch_forward_view(const OpArgs& a, int dtype, int cpl, int waves, i
                                float* part, hipStream_t s);
 hipError_t launch_backward_view(const OpArgs& a, int dtype, int cpl, int waves, hipStream_t s);
 hipError_t launch_gfeat_tiles(const TileArgs& t, int out_dtype, int cpl, hipStream_t s);
-// cell_start[N*L], tile_start[N*L + 1] and tile_region[N*L] from the shapes.
+// cell_start[N*L] and tile_start[N*L + 1] from the shapes.
 hipError_t launch_region_tables(const int32_t* shapes, int32_t N, int32_t L, uint32_t* cell_start,
-                                uint32_t* tile_start, uint32_t* tile_region, hipStream_t s);
+                                uint32_t* tile_start, hipStream_t s);
 // Stable sort of the n record keys (keys_a; values = the indices, or the
 // caller's in vals_a when vals_given) by key in [0, nrows]; *sorted_vals
 // receives the sorted values (in vals_a or vals_b) and off[0..nrows] the
@@ -331,7 +335,7 @@ size_t sort_scratch_words(uint32_t n);
 // bucket's i-th record in key order and off[] of the bucket's cells (global
 // cell b*cells_per_item + cell_start[r] + local), and off[B*cells_per_item]
 // = B*N*L*ap. Also writes the region tables of launch_region_tables
-// (cell_start, tile_start, tile_region). Requires ap <= kBucketMaxRecords,
+// (cell_start, tile_start). Requires ap <= kBucketMaxRecords,
 // (H+1)(W+1) + 1 <= kBucketMaxKeys for every region, N*L <= 1024, and
 // bucket_sort_lds_bytes(ap) of LDS. The visible-view form (place, items
 // non-null: the exclusive scan of the visible flags over the view-major items
@@ -346,8 +350,8 @@ size_t bucket_sort_lds_bytes(uint32_t ap);
 hipError_t launch_bucket_sort(const uint32_t* keys, const int32_t* shapes, int32_t B, int32_t N,
                               int32_t L, int32_t A, int32_t P, uint32_t cells_per_item,
                               uint32_t* vals, uint32_t* off, uint32_t* cell_start,
-                              uint32_t* tile_start, uint32_t* tile_region, const uint32_t* place,
-                              const uint32_t* items, hipStream_t s);
+                              uint32_t* tile_start, const uint32_t* place, const uint32_t* items,
+                              hipStream_t s);
 // The batched form's record sort: bucket k = the batch's region k (scene s,
 // region r of it), A_s*P records at sample_start[s] + r*A_s*P, keyed by
 // local cell; writes the sorted global sample indices to vals (bucket k's
@@ -424,8 +428,6 @@ hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStrea
 // The most LDS a gather's workgroup of `waves` waves takes.
 size_t gather_lds_bytes(int waves, int C, int G);
 
-// Benchmark instrumentation (msda_set_kernel_events): called around every
-// kernel launch; records the caller's events when enabled, else does nothing.
 // The least workspace msda_forward_ws takes for d: kMinFwdRows partial rows
 // per batch item in view order, where msda_forward_workspace_size has room for all.
 size_t forward_min_workspace(const msda_desc* d);
@@ -433,6 +435,8 @@ size_t forward_min_workspace(const msda_desc* d);
 // Sets the thread's last-error message (msda_last_error) and returns st.
 msda_status set_error(msda_status st, const char* message);
 
+// Benchmark instrumentation (msda_set_kernel_events): called around every
+// kernel launch; records the caller's events when enabled, else does nothing.
 void mark_begin(const char* kernel, hipStream_t s);
 void mark_end(hipStream_t s);
 

@@ -274,7 +274,6 @@ struct BucketSortArgs {
     // the tiled reduction's tables, written by block 0 (as region_tables_kernel)
     u32* cell_start;
     u32* tile_start;
-    u32* tile_region;
     int B, N, L, A, P;
     u32 ap;                     // A*P records per bucket (the visible-view form: at most)
     u32 cells_per_item;
@@ -490,13 +489,12 @@ __global__ void __launch_bounds__(kBucketThreads) bucket_sort_kernel(BucketSortA
     // of every region ((H+1)(W+1) bilinear cells and the outside cell each)
     // -- this block's own, and block 0 writes them all -- and, over the
     // processing slots (coarse levels first: slot o -> region
-    // (o % N) * L + (L - 1 - o / N)), the first tile and region of each slot.
+    // (o % N) * L + (L - 1 - o / N)), the first tile of each slot.
     {
         u32 cells = 0, tiles = 0;
-        int rs = 0;
         if (tid < NL) {
             cells = (u32)(p.shapes[2 * tid] + 1) * (u32)(p.shapes[2 * tid + 1] + 1) + 1u;
-            rs = (tid % p.N) * p.L + (p.L - 1 - tid / p.N);
+            const int rs = (tid % p.N) * p.L + (p.L - 1 - tid / p.N);
             tiles = ((u32)(p.shapes[2 * rs] + kTileH - 1) / kTileH) *
                     ((u32)(p.shapes[2 * rs + 1] + kTileW - 1) / kTileW);
         }
@@ -507,7 +505,6 @@ __global__ void __launch_bounds__(kBucketThreads) bucket_sort_kernel(BucketSortA
         if (k == 0 && tid < NL) {
             p.cell_start[tid] = cs;
             p.tile_start[tid] = ts;
-            p.tile_region[tid] = (u32)rs;
             if (tid == NL - 1) p.tile_start[NL] = tt;
         }
         __syncthreads();
@@ -585,8 +582,8 @@ __global__ void __launch_bounds__(kBucketThreads) bucket_sort_batched_kernel(Bat
 
 hipError_t launch_bucket_sort(const u32* keys, const int32_t* shapes, int32_t B, int32_t N,
                               int32_t L, int32_t A, int32_t P, u32 cells_per_item, u32* vals,
-                              u32* off, u32* cell_start, u32* tile_start, u32* tile_region,
-                              const u32* place, const u32* items, hipStream_t s) {
+                              u32* off, u32* cell_start, u32* tile_start, const u32* place,
+                              const u32* items, hipStream_t s) {
     BucketSortArgs p;
     p.keys = keys;
     p.shapes = shapes;
@@ -594,7 +591,6 @@ hipError_t launch_bucket_sort(const u32* keys, const int32_t* shapes, int32_t B,
     p.items = items;
     p.cell_start = cell_start;
     p.tile_start = tile_start;
-    p.tile_region = tile_region;
     p.vals = vals;
     p.off = off;
     p.B = B;

@@ -76,13 +76,11 @@ __device__ __forceinline__ void load_go(const float* p, float* v) {
 
 // Tables of the tiled reduction for one batch item, from the shapes: the
 // first cell of each region (regions in order, (H+1)(W+1) bilinear cells
-// each and one for the region's samples outside the level) and,
-// over processing slots (coarse levels first: slot o = (L-1-l)*N + n), the
-// first tile and the region of each slot. One block of 256 threads; N*L <=
+// each and one for the region's samples outside the level) and the first tile
+// of each processing slot (coarse levels first: slot o = (L-1-l)*N + n). One block of 256 threads; N*L <=
 // 1024 regions, 4 per thread.
 __global__ void __launch_bounds__(256) region_tables_kernel(const int32_t* shapes, int N, int L,
-                                                            u32* cell_start, u32* tile_start,
-                                                            u32* tile_region) {
+                                                            u32* cell_start, u32* tile_start) {
     __shared__ u32 lds4[4];
     const int NL = N * L;
     u32 cells[4], tiles[4], sum_c = 0, sum_t = 0;
@@ -110,7 +108,6 @@ __global__ void __launch_bounds__(256) region_tables_kernel(const int32_t* shape
         if (i < NL) {
             cell_start[i] = run_c;
             tile_start[i] = run_t;
-            tile_region[i] = (u32)((i % N) * L + (L - 1 - i / N));
         }
         run_c += cells[k];
         run_t += tiles[k];
@@ -888,10 +885,10 @@ hipError_t launch_gfeat_tiles(const TileArgs& t, int out_dtype, int cpl, hipStre
 }
 
 hipError_t launch_region_tables(const int32_t* shapes, int32_t N, int32_t L, u32* cell_start,
-                                u32* tile_start, u32* tile_region, hipStream_t s) {
+                                u32* tile_start, hipStream_t s) {
     mark_begin("region_tables", s);
     hipLaunchKernelGGL(region_tables_kernel, dim3(1), dim3(256), 0, s, shapes, N, L, cell_start,
-                       tile_start, tile_region);
+                       tile_start);
     mark_end(s);
     return hipGetLastError();
 }
