@@ -62,6 +62,20 @@ def _run(cmd):
     return res.returncode, out
 
 
+def _replace(built: str, target: str):
+    """target replaced by the built file at once (also across file systems);
+    a copy that fails leaves nothing beside it."""
+    import shutil
+    tmp = target + ".tmp%d" % os.getpid()
+    try:
+        shutil.copyfile(built, tmp)
+        shutil.copymode(built, tmp)
+        os.replace(tmp, target)
+    finally:
+        if os.path.exists(tmp):
+            os.unlink(tmp)
+
+
 def build(verbose: bool = False) -> str:
     """Compile every HIP source into libmsda.so (always recompiles): one
     object per source, compiled in parallel, then one link; and
@@ -75,8 +89,8 @@ def build(verbose: bool = False) -> str:
         objs = [os.path.join(tmpdir, os.path.basename(src) + ".o") for src in SOURCES]
         cflags = [f for f in FLAGS if f != "-shared"]
         cmds = [[HIPCC] + cflags + ["-c", src, "-o", obj] for src, obj in zip(SOURCES, objs)]
-        torch_tmp = TORCH_LIB + ".tmp%d" % os.getpid()
-        cmds.append(torch_command(torch_tmp))
+        torch_obj = os.path.join(tmpdir, os.path.basename(TORCH_LIB))
+        cmds.append(torch_command(torch_obj))
         if verbose:
             for c in cmds:
                 print(" ".join(c), flush=True)
@@ -88,15 +102,15 @@ def build(verbose: bool = False) -> str:
                 raise RuntimeError(f"the compiler failed on {os.path.basename(src)} ({rc}):\n{out}")
             if verbose and out:
                 print(out)
-        tmp = LIB + ".tmp%d" % os.getpid()
-        link = [HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}"] + objs + ["-o", tmp]
+        lib_obj = os.path.join(tmpdir, os.path.basename(LIB))
+        link = [HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}"] + objs + ["-o", lib_obj]
         if verbose:
             print(" ".join(link), flush=True)
         rc, out = _run(link)
         if rc != 0:
             raise RuntimeError(f"link failed ({rc}):\n{out}")
-        os.replace(tmp, LIB)
-        os.replace(torch_tmp, TORCH_LIB)
+        for obj, target in ((lib_obj, LIB), (torch_obj, TORCH_LIB)):
+            _replace(obj, target)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
     return LIB
