@@ -414,7 +414,9 @@ size_t msda_batched_workspace_size(const msda_batch* batch, int32_t backward);
  * workgroups stride over all anchors of all scenes (bitwise the single
  * call's in anchor order). workspace: device, 256-byte aligned, >=
  * msda_batched_workspace_size(batch, 0) (it includes the view order's FP32
- * partial rows, R * anchors * C per scene, in either order). Validation as for
+ * partial rows, R * anchors * C per scene, in either order; R as for
+ * msda_forward_workspace_size, or fewer, at least 8, where a row holds several
+ * cameras). Validation as for
  * msda_forward, per scene; in addition at most 4096 (camera, level)
  * regions over all scenes.
  */

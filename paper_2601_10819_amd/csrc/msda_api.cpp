@@ -1323,9 +1323,11 @@ msda_status plan_batch(const msda_batch* b, bool backward, BatchPlan* p) {
         const msda::SlotCuts cuts =
             msda::UnitGroup{1, sc.num_cams, sc.num_anchors, rows, 0, rows}.cuts();
         for (int x = 0; x < msda::kSlots; ++x) slot_units[x] += cuts.end[x] - cuts.first[x];
-        // sized as for the single call: at least kMinFwdRows rows an anchor
-        p->part_bytes += (uint64_t)sc.num_anchors *
-                         (uint64_t)std::max(msda::max_fwd_rows(sc.num_cams), msda::kMinFwdRows);
+        // the rows the scene takes, at least kMinFwdRows an anchor
+        p->part_bytes +=
+            (uint64_t)sc.num_anchors *
+            (uint64_t)std::max(msda::fwd_rows(sc.num_cams, b->num_points, b->num_levels),
+                               msda::kMinFwdRows);
         p->samples += (uint64_t)sc.num_anchors * b->num_points * sc.num_cams * b->num_levels;
         p->regions += (uint64_t)sc.num_cams * b->num_levels;
         p->max_cams = std::max(p->max_cams, sc.num_cams);

@@ -281,7 +281,7 @@ static hipError_t fwd_view_launch(const OpArgs& a, int waves, int part_rows, flo
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        mark_begin("fwd_view_reduce", s);
+        mark_begin("fwd_rows_reduce", s);
         if (a.C % 4 == 0) {
             hipLaunchKernelGGL(fwd_rows_reduce<4>, dim3((unsigned)((total / 4 + 255) / 256)),
                                dim3(256), 0, s, part, a.out, a.B, nrows, AC, row0 > 0);

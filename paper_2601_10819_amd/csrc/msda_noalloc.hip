@@ -1,14 +1,13 @@
 // msda_forward_noalloc: the forward for callers that cannot allocate device
 // memory (code under HIP graph capture, serving loops, harnesses that forbid
 // hipMalloc). The workspace msda_forward_ws takes from its caller -- the
-// view-order forward's per-XCD-slot partial sums, and the softmax statistics
-// when the weights are logits -- lives here in a fixed device array of
+// view-order forward's partial rows (as many as fit, at least eight an anchor),
+// and the softmax statistics when the weights are logits -- lives here in a fixed device array of
 // MSDA_NOALLOC_SCRATCH_BYTES instead. Each GPU the library runs on holds its
 // own copy of the array until the process ends; every call on that GPU uses
 // it, so calls that overlap on one GPU (two streams, two threads) race.
 // Nothing in it needs to start at zero: the forward overwrites every partial
-// row it later reads (zeros for an anchor with no camera in a slot) and
-// recomputes the statistics on every call.
+// row it later reads and recomputes the statistics on every call.
 #include <hip/hip_runtime.h>
 #include <stdio.h>
 
