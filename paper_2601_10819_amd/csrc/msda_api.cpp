@@ -548,7 +548,8 @@ static msda_status forward_impl(const void* feat, const int32_t* spatial_shapes,
         char* base = static_cast<char*>(workspace) + stats_off;
         float2* stats = reinterpret_cast<float2*>(base);
         const hipError_t e = msda::launch_softmax(weights, wbf16, a.B * a.A, a.P * a.N * a.L,
-                                                  a.G, stats, nullptr, (hipStream_t)stream);
+                                                  a.G, stats, nullptr, nullptr,
+                                                  (hipStream_t)stream);
         if (e != hipSuccess) return hip_fail(e, "softmax statistics");
         a.wstats = stats;
     }
@@ -675,9 +676,17 @@ static size_t weights_f32_bytes(const msda_desc* d) {
     return (d->flags & kWeightFlags) ? align256(num_samples(d) * (size_t)d->groups * 4) : 0;
 }
 
+// and the softmax's partial results behind them.
+static size_t softmax_scratch(const msda_desc* d) {
+    if (!(d->flags & MSDA_WEIGHT_LOGITS) || d->num_anchors < 1) return 0;
+    const int64_t BA = (int64_t)d->batch * d->num_anchors;
+    return align256(msda::softmax_scratch_bytes(
+        BA, (size_t)(num_samples(d) / (uint64_t)BA) * (size_t)d->groups, d->groups));
+}
+
 size_t msda_backward_workspace_size(const msda_desc* d) {
     if (!d || d->batch < 1 || d->rows < 1 || d->channels < 1 || d->num_anchors < 0) return 0;
-    return align256(base_backward_bytes(d)) + weights_f32_bytes(d);
+    return align256(base_backward_bytes(d)) + weights_f32_bytes(d) + softmax_scratch(d);
 }
 
 // The backward, dense (visible == nullptr) or over the visible views only.
@@ -752,7 +761,7 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     // weight flags: the FP32 weights after the rest
     const size_t base_need = visible && a.A > 0 ? VW.total : sorted_need;
     const size_t wx_off = align256(base_need);
-    const size_t wx_bytes = a.A > 0 ? weights_f32_bytes(desc) : 0;
+    const size_t wx_bytes = a.A > 0 ? weights_f32_bytes(desc) + softmax_scratch(desc) : 0;
     const size_t need = wx_bytes ? wx_off + wx_bytes : base_need;
     if (need) {
         if (!workspace || workspace_bytes < need)
@@ -775,11 +784,14 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     const bool logits = (desc->flags & MSDA_WEIGHT_LOGITS) && a.A > 0;
     const float* weff = weights;
     float* w32 = nullptr;
+    float2* runs = nullptr;
     if (wx_bytes) {
         w32 = reinterpret_cast<float*>(ws + wx_off);
+        if (softmax_scratch(desc))
+            runs = reinterpret_cast<float2*>(ws + wx_off + weights_f32_bytes(desc));
         const int BA = a.B * a.A, PNL = a.P * a.N * a.L;
         e = logits ? msda::launch_softmax(weights, desc->flags & MSDA_WEIGHTS_BF16, BA, PNL, a.G,
-                                          nullptr, w32, s)
+                                          nullptr, w32, runs, s)
                    : msda::launch_weights_f32(weights, BA, PNL, a.G, w32, s);
         if (e != hipSuccess)
             return hip_fail(e, "weights from logits");
@@ -788,7 +800,7 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     auto finish = [&]() -> msda_status {
         if (logits && grad_weights) {
             const hipError_t ee = msda::launch_softmax_grad(w32, grad_weights, a.B * a.A,
-                                                            a.P * a.N * a.L, a.G, s);
+                                                            a.P * a.N * a.L, a.G, runs, s);
             if (ee != hipSuccess) return hip_fail(ee, "gradient through the softmax");
         }
         return ok();
@@ -1007,7 +1019,7 @@ size_t msda_backward_fused_workspace_size(const msda_desc* d) {
 size_t msda_backward_visible_workspace_size(const msda_desc* d) {
     if (!d || d->batch < 1 || d->rows < 1 || d->channels < 1 || d->num_anchors < 0) return 0;
     const size_t base = visible_layout(d, align256(base_backward_bytes(d))).total;
-    const size_t extra = weights_f32_bytes(d);
+    const size_t extra = weights_f32_bytes(d) + softmax_scratch(d);
     return extra ? align256(base) + extra : base;
 }
 
@@ -1071,7 +1083,7 @@ static msda_status forward_visible_impl(const void* feat, const int32_t* spatial
     if (desc->flags & MSDA_WEIGHT_LOGITS) {
         float2* stats = reinterpret_cast<float2*>(ws + stats_off);
         const hipError_t es = msda::launch_softmax(weights, wbf16, a.B * a.A, a.P * a.N * a.L,
-                                                   a.G, stats, nullptr, s);
+                                                   a.G, stats, nullptr, nullptr, s);
         if (es != hipSuccess) return hip_fail(es, "softmax statistics");
         a.wstats = stats;
     }
@@ -1202,14 +1214,14 @@ namespace {
 
 struct BatchWs {
     size_t anchor_start, sample_start, region_start, row_start, slot_start, slot_first, cell_start,
-        slot_scene, slot_region, tile_start, magic, magic_shift, keys_a, keys_b, vals_a, vals_b, frac, off, scratch, part,
-        wstats, w32, total;
+        slot_scene, slot_region, tile_start, magic, magic_shift, keys_a, keys_b, vals_a, vals_b,
+        frac, off, scratch, part, wstats, w32, runs, total;
 };
 
 // Weight-flag buffers of a batch: forward, softmax statistics per anchor of
 // every scene; backward, the FP32 weights of every sample.
 struct BatchWeights {
-    uint64_t stats_bytes, w32_bytes;
+    uint64_t stats_bytes, w32_bytes, runs_bytes;
 };
 
 // part_bytes: the view-order forward's partial rows (always part of
@@ -1243,6 +1255,7 @@ BatchWs batch_layout(uint64_t S, uint64_t regions, uint64_t nsamp, uint64_t ncel
     if (part_bytes) w.part = take(part_bytes);
     if (wb.stats_bytes) w.wstats = take(wb.stats_bytes);
     if (wb.w32_bytes) w.w32 = take(wb.w32_bytes);
+    if (wb.runs_bytes) w.runs = take(wb.runs_bytes);
     w.total = at;
     return w;
 }
@@ -1444,6 +1457,15 @@ BatchWeights batch_weights(const msda_batch* b, const BatchPlan& p, bool backwar
     if (!backward && (b->flags & MSDA_WEIGHT_LOGITS))
         w.stats_bytes = p.anchors * (uint64_t)b->groups * sizeof(float2);
     if (backward && (b->flags & kWeightFlags)) w.w32_bytes = p.samples * (uint64_t)b->groups * 4;
+    // the softmax's partial results, of one scene after the other
+    if (backward && (b->flags & MSDA_WEIGHT_LOGITS))
+        for (int sc = 0; sc < b->num_scenes; ++sc) {
+            const msda_scene& h = b->host_scenes[sc];
+            const size_t n = (size_t)b->num_points * (size_t)h.num_cams * (size_t)b->num_levels *
+                             (size_t)b->groups;
+            w.runs_bytes = std::max<uint64_t>(
+                w.runs_bytes, msda::softmax_scratch_bytes(h.num_anchors, n, b->groups));
+        }
     return w;
 }
 
@@ -1467,7 +1489,9 @@ msda_status batch_weight_prep(const msda_batch* b, char* ws, const BatchWs& w, b
             if (logits)
                 e = msda::launch_softmax(h.weights, wbf16, A, PNL, G,
                                          stats ? stats + a0 * G : nullptr,
-                                         w32 ? w32 + s0 * G : nullptr, s);
+                                         w32 ? w32 + s0 * G : nullptr,
+                                         w.runs ? reinterpret_cast<float2*>(ws + w.runs) : nullptr,
+                                         s);
             else if (w32)
                 e = msda::launch_weights_f32(h.weights, A, PNL, G, w32 + s0 * G, s);
             if (e != hipSuccess) return hip_fail(e, "batched weights");
@@ -1489,6 +1513,7 @@ msda_status batch_weight_prep(const msda_batch* b, char* ws, const BatchWs& w, b
 msda_status batch_softmax_grad(const msda_batch* b, char* ws, const BatchWs& w, hipStream_t s) {
     if (!(b->flags & MSDA_WEIGHT_LOGITS)) return MSDA_OK;
     const float* w32 = reinterpret_cast<const float*>(ws + w.w32);
+    float2* runs = w.runs ? reinterpret_cast<float2*>(ws + w.runs) : nullptr;
     const int G = b->groups;
     uint64_t s0 = 0;
     for (int sc = 0; sc < b->num_scenes; ++sc) {
@@ -1496,7 +1521,7 @@ msda_status batch_softmax_grad(const msda_batch* b, char* ws, const BatchWs& w, 
         const int A = h.num_anchors, PNL = b->num_points * h.num_cams * b->num_levels;
         if (A > 0 && h.grad_weights) {
             const hipError_t e =
-                msda::launch_softmax_grad(w32 + s0 * G, h.grad_weights, A, PNL, G, s);
+                msda::launch_softmax_grad(w32 + s0 * G, h.grad_weights, A, PNL, G, runs, s);
             if (e != hipSuccess) return hip_fail(e, "batched gradient through the softmax");
         }
         s0 += (uint64_t)(A > 0 ? A : 0) * (uint64_t)PNL;

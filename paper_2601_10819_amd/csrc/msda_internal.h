@@ -386,13 +386,15 @@ hipError_t launch_backward_visible(const OpArgs& a, int dtype, int cpl, int wave
 // stats[(b*A + a)*G + g] = (max, 1 / sum of exp(logit - max)) over the
 // anchor's P*N*L logits of group g, and the softmax weights of all BA*PNL*G
 // entries, FP32; either may be nullptr. Logits FP32 or bfloat16 bit patterns.
+// scratch: softmax_scratch_bytes, used (if given) for weights alone.
+size_t softmax_scratch_bytes(int64_t BA, size_t n, int G);    // n = PNL*G
 hipError_t launch_softmax(const void* logits, bool bf16, int BA, int PNL, int G, float2* stats,
-                          float* weights, hipStream_t s);
+                          float* weights, float2* scratch, hipStream_t s);
 // w[i] = the bfloat16 weight src[i], widened, for all BA*PNL*G entries.
 hipError_t launch_weights_f32(const void* src, int BA, int PNL, int G, float* w, hipStream_t s);
 // In place: grad[i] = w[i] * (grad[i] - sum over the anchor's group of w * grad),
-// the gradient through the per-group softmax.
-hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int G,
+// the gradient through the per-group softmax. scratch: as for launch_softmax.
+hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int G, float2* scratch,
                                hipStream_t s);
 hipError_t launch_view_scale(const uint8_t* visible, const float* score, int BA, int N,
                              float* vt, hipStream_t s);

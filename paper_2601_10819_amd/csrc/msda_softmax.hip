@@ -91,6 +91,31 @@ __device__ __forceinline__ float group_total(float v, int G, float* lds, F combi
     return v;
 }
 
+// (max, sum of exp(x - max)) of a thread's entries of a round with `left` left.
+template <int THREADS>
+__device__ __forceinline__ float2 round_stats(float* x, size_t left) {
+    float m = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < kRound; ++k) {
+        if (!in_round<THREADS>(k, left)) x[k] = -INFINITY;
+        m = fmaxf(m, x[k]);
+    }
+    float sum = 0.f;
+    // exp(-inf) = 0; only masked entries: nothing to add, but a NaN stays one
+#pragma unroll
+    for (int k = 0; k < kRound; ++k)
+        sum += m != -INFINITY ? expf(x[k] - m) : (x[k] == x[k] ? 0.f : x[k]);
+    return make_float2(m, sum);
+}
+
+// A block's (max, sum of exp) per group, in each of the group's threads.
+template <int THREADS>
+__device__ __forceinline__ float2 group_stats(float2 acc, int G, float* lds) {
+    const float m = group_total<THREADS>(acc.x, G, lds, [](float a, float b) { return fmaxf(a, b); });
+    const float mine = acc.y == 0.f ? 0.f : acc.y * expf(acc.x - m);
+    return make_float2(m, group_total<THREADS>(mine, G, lds, [](float a, float b) { return a + b; }));
+}
+
 // One anchor per block: the groups' (max, 1/sum of exp) to `stats` and the
 // weights to `weights`, either of which may be nullptr.
 template <class T, int THREADS>
@@ -105,24 +130,11 @@ __global__ void __launch_bounds__(THREADS) softmax_kernel(const T* logits, size_
     float2 acc = make_float2(-INFINITY, 0.f);
     for (size_t r = 0;; r += kStep) {
         load_round<THREADS>(p + r, n - r, x);
-        float m = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < kRound; ++k) {
-            if (!in_round<THREADS>(k, n - r)) x[k] = -INFINITY;
-            m = fmaxf(m, x[k]);
-        }
-        float sum = 0.f;
-        // exp(-inf) = 0; only masked entries: nothing to add, but a NaN stays one
-#pragma unroll
-        for (int k = 0; k < kRound; ++k)
-            sum += m != -INFINITY ? expf(x[k] - m) : (x[k] == x[k] ? 0.f : x[k]);
-        acc = merge(acc, make_float2(m, sum));
+        acc = merge(acc, round_stats<THREADS>(x, n - r));
         if (r == last) break;
     }
-    const float m = group_total<THREADS>(acc.x, G, lds, [](float a, float b) { return fmaxf(a, b); });
-    const float mine = acc.y == 0.f ? 0.f : acc.y * expf(acc.x - m);
-    const float sum = group_total<THREADS>(mine, G, lds, [](float a, float b) { return a + b; });
-    const float inv = 1.f / sum;
+    const float2 all = group_stats<THREADS>(acc, G, lds);
+    const float m = all.x, inv = 1.f / all.y;
     if (stats && t < (size_t)G) stats[ba * G + t] = make_float2(m, inv);
     if (!weights) return;
     float* w = weights + ba * n;
@@ -184,6 +196,99 @@ __global__ void __launch_bounds__(THREADS) softmax_grad_kernel(const float* weig
     }
 }
 
+// Few anchors of many entries: an anchor's entries in `parts` runs of `per`, a
+// block each (blockIdx.x), whose partial results go through `part`, [anchor][run]
+// [group], to a second launch.
+template <class T>
+__global__ void __launch_bounds__(kFlatThreads) softmax_part_kernel(const T* logits, size_t n, int G,
+                                                                    size_t per, float2* part) {
+    __shared__ float lds[kFlatThreads];
+    const size_t ba = blockIdx.y, lo = blockIdx.x * per, hi = min(lo + per, n);
+    float x[kRound];
+    float2 acc = make_float2(-INFINITY, 0.f);
+    for (size_t r = lo; r < hi; r += kFlatChunk) {
+        load_round<kFlatThreads>(logits + ba * n + r, hi - r, x);
+        acc = merge(acc, round_stats<kFlatThreads>(x, hi - r));
+    }
+    acc = group_stats<kFlatThreads>(acc, G, lds);
+    if (threadIdx.x < (unsigned)G) part[(ba * gridDim.x + blockIdx.x) * G + threadIdx.x] = acc;
+}
+
+template <class T>
+__global__ void __launch_bounds__(kFlatThreads) softmax_weights_kernel(const T* logits, size_t n,
+                                                                       int G, size_t per,
+                                                                       const float2* part,
+                                                                       float* weights) {
+    const size_t ba = blockIdx.y, lo = blockIdx.x * per, hi = min(lo + per, n);
+    const float2* mine = part + ba * gridDim.x * G + (threadIdx.x & (unsigned)(G - 1));
+    float2 all = make_float2(-INFINITY, 0.f);
+    for (unsigned k = 0; k < gridDim.x; ++k) all = merge(all, mine[(size_t)k * G]);
+    const float inv = 1.f / all.y;
+    float x[kRound];
+    for (size_t r = lo; r < hi; r += kFlatChunk) {
+        load_round<kFlatThreads>(logits + ba * n + r, hi - r, x);
+#pragma unroll
+        for (int k = 0; k < kRound; ++k)
+            if (in_round<kFlatThreads>(k, hi - r))
+                weights[ba * n + r + threadIdx.x + (uint32_t)(k * kFlatThreads)] =
+                    expf(x[k] - all.x) * inv;
+    }
+}
+
+__global__ void __launch_bounds__(kFlatThreads) softmax_dot_kernel(const float* weights,
+                                                                   const float* grads, size_t n,
+                                                                   int G, size_t per, float* part) {
+    __shared__ float lds[kFlatThreads];
+    const size_t ba = blockIdx.y, lo = blockIdx.x * per, hi = min(lo + per, n);
+    float x[kRound], y[kRound], acc = 0.f;
+    for (size_t r = lo; r < hi; r += kFlatChunk) {
+        load_round<kFlatThreads>(weights + ba * n + r, hi - r, x);
+        load_round<kFlatThreads>(grads + ba * n + r, hi - r, y);
+#pragma unroll
+        for (int k = 0; k < kRound; ++k)
+            if (in_round<kFlatThreads>(k, hi - r)) acc = fmaf(x[k], y[k], acc);
+    }
+    acc = group_total<kFlatThreads>(acc, G, lds, [](float a, float b) { return a + b; });
+    if (threadIdx.x < (unsigned)G) part[(ba * gridDim.x + blockIdx.x) * G + threadIdx.x] = acc;
+}
+
+__global__ void __launch_bounds__(kFlatThreads) softmax_apply_kernel(const float* weights,
+                                                                     float* grads, size_t n, int G,
+                                                                     size_t per,
+                                                                     const float* part) {
+    const size_t ba = blockIdx.y, lo = blockIdx.x * per, hi = min(lo + per, n);
+    const float* mine = part + ba * gridDim.x * G + (threadIdx.x & (unsigned)(G - 1));
+    float d = 0.f;
+    for (unsigned k = 0; k < gridDim.x; ++k) d += mine[(size_t)k * G];
+    float x[kRound], y[kRound];
+    for (size_t r = lo; r < hi; r += kFlatChunk) {
+        load_round<kFlatThreads>(weights + ba * n + r, hi - r, x);
+        load_round<kFlatThreads>(grads + ba * n + r, hi - r, y);
+#pragma unroll
+        for (int k = 0; k < kRound; ++k)
+            if (in_round<kFlatThreads>(k, hi - r))
+                grads[ba * n + r + threadIdx.x + (uint32_t)(k * kFlatThreads)] = x[k] * (y[k] - d);
+    }
+}
+
+// Runs an anchor is cut into, and their length: where a block per anchor leaves
+// most of the 256 CUs without one and an anchor is many rounds long, as many as
+// give every CU two blocks (64 cameras, 13 keypoints, 4 levels, 64 groups, logits,
+// backward of weights: 4 anchors 138 us in one block each, 82 in
+// runs; 32 182 and 95; 100 359 and 247; 8 groups, 7 rounds, are one block).
+struct Runs {
+    unsigned parts;
+    size_t per;
+};
+
+Runs runs_of(int64_t BA, size_t n) {
+    const size_t rounds = (n + kFlatChunk - 1) / kFlatChunk;
+    if (BA >= 128 || rounds < 8) return Runs{1, n};
+    const size_t want = (size_t)(512 / BA);
+    const size_t per = (rounds + want - 1) / want;
+    return Runs{(unsigned)((rounds + per - 1) / per), per * kFlatChunk};
+}
+
 // Threads per anchor. Small anchors are one round of 256 threads. Otherwise
 // 1024 threads read an anchor in few rounds where there are no more anchors
 // than two per CU, and 512 where there are: 900 anchors of 26,624 entries are
@@ -228,10 +333,36 @@ void run_softmax(const void* logits, int BA, size_t n, int G, float2* stats, flo
 
 }  // namespace
 
+size_t softmax_scratch_bytes(int64_t BA, size_t n, int G) {
+    if (BA <= 0) return 0;
+    const Runs runs = runs_of(BA, n);
+    return runs.parts > 1 ? (size_t)BA * runs.parts * (size_t)G * sizeof(float2) : 0;
+}
+
 hipError_t launch_softmax(const void* logits, bool bf16, int BA, int PNL, int G, float2* stats,
-                          float* weights, hipStream_t s) {
+                          float* weights, float2* scratch, hipStream_t s) {
     if (BA <= 0) return hipSuccess;
     const size_t n = (size_t)PNL * G;
+    const Runs runs = runs_of(BA, n);
+    if (!stats && scratch && runs.parts > 1) {
+        const dim3 grid(runs.parts, (unsigned)BA);
+        auto both = [&](auto* p) -> hipError_t {
+            using T = std::remove_const_t<std::remove_pointer_t<decltype(p)>>;
+            mark_begin("softmax_part", s);
+            hipLaunchKernelGGL((softmax_part_kernel<T>), grid, dim3(kFlatThreads), 0, s, p, n, G,
+                               runs.per, scratch);
+            mark_end(s);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            mark_begin("softmax", s);
+            hipLaunchKernelGGL((softmax_weights_kernel<T>), grid, dim3(kFlatThreads), 0, s, p, n, G,
+                               runs.per, scratch, weights);
+            mark_end(s);
+            return hipGetLastError();
+        };
+        return bf16 ? both(static_cast<const uint16_t*>(logits))
+                    : both(static_cast<const float*>(logits));
+    }
     mark_begin("softmax", s);
     if (bf16) run_softmax<uint16_t>(logits, BA, n, G, stats, weights, s);
     else run_softmax<float>(logits, BA, n, G, stats, weights, s);
@@ -249,10 +380,26 @@ hipError_t launch_weights_f32(const void* src, int BA, int PNL, int G, float* w,
     return hipGetLastError();
 }
 
-hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int G,
+hipError_t launch_softmax_grad(const float* w, float* grad, int BA, int PNL, int G, float2* scratch,
                                hipStream_t s) {
     if (BA <= 0) return hipSuccess;
     const size_t n = (size_t)PNL * G;
+    const Runs runs = runs_of(BA, n);
+    if (scratch && runs.parts > 1) {
+        const dim3 grid(runs.parts, (unsigned)BA);
+        float* part = reinterpret_cast<float*>(scratch);
+        mark_begin("softmax_dot", s);
+        hipLaunchKernelGGL(softmax_dot_kernel, grid, dim3(kFlatThreads), 0, s, w, grad, n, G,
+                           runs.per, part);
+        mark_end(s);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        mark_begin("softmax_grad", s);
+        hipLaunchKernelGGL(softmax_apply_kernel, grid, dim3(kFlatThreads), 0, s, w, grad, n, G,
+                           runs.per, part);
+        mark_end(s);
+        return hipGetLastError();
+    }
     mark_begin("softmax_grad", s);
     with_threads(threads_of(n, BA, true), [&](auto threads) {
         constexpr int THREADS = decltype(threads)::value;
