@@ -32,6 +32,9 @@ __host__ __device__ constexpr int level_shift(int L) {
     return L > 4 ? 3 : L > 2 ? 2 : L > 1 ? 1 : 0;
 }
 __host__ __device__ constexpr int grad_samples(int G) { return G > 32 ? 32 : 64; }
+// (of a PACKED kernel, with no more than kPackedGroups groups: a constant)
+template <bool PACKED>
+__host__ __device__ constexpr int grad_samples_of(int G) { return PACKED ? 64 : grad_samples(G); }
 __host__ __device__ constexpr size_t grads_lds_bytes(int G) {
     return (size_t)grad_samples(G) * (3 * 16 + 4 * (size_t)G + 4);
 }
@@ -44,8 +47,9 @@ struct GradLds {
     u32* src;                // per pair: its index p*N + n among the anchor's pairs
 };
 
+template <bool PACKED>
 __device__ __forceinline__ GradLds grads_lds(unsigned char* p, int G) {
-    const int n = grad_samples(G);
+    const int n = grad_samples_of<PACKED>(G);
     GradLds s;
     s.off = reinterpret_cast<u32x4*>(p);
     s.cw = reinterpret_cast<float4*>(s.off + n);
@@ -183,7 +187,7 @@ __device__ __forceinline__ void stage_grads(const OpArgs& a, const GradAnchor& x
             x.rec.frac[smp] = make_float2(c.lx, c.ly);
         }
     }
-    const int ns = PACKED ? 64 : grad_samples(G);
+    const int ns = grad_samples_of<PACKED>(G);
     if (lane < ns) {
         s.off[lane] = off;
         s.cw[lane] = cw;
@@ -228,13 +232,13 @@ constexpr int kGradLevels = 2;
 // grad_loc to memory. out_scale multiplies both (the fused form's per-view
 // weight); dot (or nullptr) accumulates, on each group's first lane,
 // <grad_out, the pairs' feature>.
-template <class FT, int CPL, int LPG, int LPS>
+template <class FT, int CPL, bool PACKED, int LPG, int LPS>
 __device__ __forceinline__ void pairs_grads(const OpArgs& a, const GradAnchor& x, const GradLds& s,
                                             int nj, const Lanes& q, const float* go,
                                             float out_scale, float* dot) {
     using RowT = Row<FT, CPL>;
     constexpr int LU = kGradLevels;
-    const int L = a.L, G = a.G, ls = level_shift(L), J = grad_samples(G) >> ls;
+    const int L = a.L, G = a.G, ls = level_shift(L), J = grad_samples_of<PACKED>(G) >> ls;
     const int lpg = (a.C / G) / CPL;               // lanes of one group (a power of two)
     for (int j0 = 0; j0 < nj; j0 += q.spw) {
         // sub-waves past the last pair repeat one and write nothing
@@ -335,8 +339,8 @@ template <class FT, int CPL, bool PACKED, class Order>
 __device__ __forceinline__ void grads_of(const OpArgs& a, const GradAnchor& x, const Order& order,
                                          int k_lo, int k_hi, const Lanes& q, unsigned char* lds,
                                          float out_scale = 1.f, float* dot = nullptr) {
-    const GradLds s = grads_lds(lds, a.G);
-    const int G = a.G, L = a.L, ls = level_shift(L), J = grad_samples(G) >> ls;
+    const GradLds s = grads_lds<PACKED>(lds, a.G);
+    const int G = a.G, L = a.L, ls = level_shift(L), J = grad_samples_of<PACKED>(G) >> ls;
     const int lpg = (a.C / G) / CPL;
     float go[CPL];
 #pragma unroll
@@ -348,11 +352,11 @@ __device__ __forceinline__ void grads_of(const OpArgs& a, const GradAnchor& x, c
         if (x.gacc) pairs_atomic<FT, CPL>(a, x, s, nj, q);
         if (x.gwout || x.glout || dot) {
             if (PACKED && lpg == 4 && q.lps == 32)
-                pairs_grads<FT, CPL, 4, 32>(a, x, s, nj, q, go, out_scale, dot);
+                pairs_grads<FT, CPL, PACKED, 4, 32>(a, x, s, nj, q, go, out_scale, dot);
             else if (PACKED && lpg == 8 && q.lps == 64)
-                pairs_grads<FT, CPL, 8, 64>(a, x, s, nj, q, go, out_scale, dot);
+                pairs_grads<FT, CPL, PACKED, 8, 64>(a, x, s, nj, q, go, out_scale, dot);
             else
-                pairs_grads<FT, CPL, 0, 0>(a, x, s, nj, q, go, out_scale, dot);
+                pairs_grads<FT, CPL, PACKED, 0, 0>(a, x, s, nj, q, go, out_scale, dot);
             wave_lds_sync();
             // grad_w, a sample's groups by the lane that staged it, or (many) lane
             // after lane
