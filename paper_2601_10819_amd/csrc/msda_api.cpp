@@ -225,7 +225,7 @@ size_t device_lds_limit() {
 // Validates everything and chooses the launch shape for the given order;
 // fills `a` except pointers.
 msda_status prepare(const msda_desc* d, int order, msda::OpArgs* a, int* cpl_out,
-                    int* waves_out, bool backward = false) {
+                    int* waves_out) {
     int64_t batch_bytes = 0;
     msda_status st = check_regions(d, &batch_bytes);
     if (st != MSDA_OK) return st;
@@ -269,14 +269,16 @@ msda_status prepare(const msda_desc* d, int order, msda::OpArgs* a, int* cpl_out
     } else if (order == MSDA_ORDER_VIEW) {
         waves = 4;
     } else {
-        // Aim for about 8 waves per SIMD across the chip (256 CUs x 4 SIMDs),
-        // with at least 4 pairs each; the backward's anchors for 4, beyond two
-        // waves, so that fewer of them are at different cameras (900 anchors FP32
-        // with 8 / 4 waves: 64 cameras 1136 / 1030 us, 16 249 / 216, 6 97 / 84; 1800
-        // anchors of 16 BF16 with 4 / 2 230 / 183; 300 of 16 with 8 / 4 93 / 107)
+        // Two waves an anchor while that is no more than 8 per SIMD (256 CUs x 4
+        // SIMDs), more while it is no more than 4, with at least 4 pairs each: more
+        // waves are at more cameras at once. Backward, 900 anchors FP32 with 8 / 4
+        // waves: 64 cameras 1136 / 1030 us, 16 249 / 216, 6 97 / 84; 1800 anchors of 16
+        // BF16 with 4 / 2 230 / 183; 300 of 16 with 8 / 4 93 / 107. Forward, 4 cameras,
+        // C = 64, BF16: 1050 anchors with 4 / 2 16.1 / 14.3; 2 cameras 1800 anchors with
+        // 4 / 2 / 1 16.8 / 11.0 / 11.1; 6 cameras 500 anchors with 8 / 4 10.4 / 11.1.
         const int64_t blocks = (int64_t)d->batch * d->num_anchors;
         waves = 1;
-        while (waves < 8 && blocks * waves * 2 <= (backward && waves > 1 ? 4096 : 8192) &&
+        while (waves < 8 && blocks * waves * 2 <= (waves > 1 ? 4096 : 8192) &&
                waves * 2 * 4 <= npairs)
             waves *= 2;
     }
@@ -709,7 +711,7 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
     const int order = visible ? MSDA_ORDER_VIEW : resolve_order(desc, true);
     msda::OpArgs a = {};
     int cpl = 0, waves = 0;
-    msda_status st = prepare(desc, order, &a, &cpl, &waves, true);
+    msda_status st = prepare(desc, order, &a, &cpl, &waves);
     if (st != MSDA_OK) return st;
     // sampling_loc, weights and grad_out hold zero elements when A == 0 and may be NULL then
     if (!feat || !spatial_shapes || !level_start_index ||
