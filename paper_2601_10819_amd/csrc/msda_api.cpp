@@ -964,7 +964,8 @@ static msda_status backward_impl(const void* feat, const int32_t* spatial_shapes
                                (uint64_t)heavy_regions * a.B * a.A * a.P)
                         ? 8 : 4;
     const uint64_t light = (tiles - t.tile_split) * a.B;
-    if (t.lps_shift < 6 && sparse_tiles(light, ((uint64_t)a.N * a.L - heavy_regions) * a.B * a.A * a.P))
+    if (t.lps_shift < 6 &&
+        sparse_tiles(light, ((uint64_t)a.N * a.L - heavy_regions) * a.B * a.A * a.P))
         t.sparse = tiles_per_wave(light, t.lps_shift);
     if ((e = msda::launch_gfeat_tiles(t, desc->feat_dtype, rcpl, s)) != hipSuccess)
         return hip_fail(e, "grad_feat tile reduction");
@@ -1723,7 +1724,8 @@ msda_status msda_backward_batched(const msda_batch* b, void* workspace, size_t w
         a.sparse = sparse ? tiles_per_wave(p.thin_tiles, a.lps_shift) : 0;
         return msda::launch_gfeat_tiles_batched(a, b->feat_dtype, rcpl, s);
     };
-    const uint64_t split = p.wide_tiles + p.heavy_tiles - p.wide_heavy, thin = p.tiles - p.thin_tiles;
+    const uint64_t split = p.wide_tiles + p.heavy_tiles - p.wide_heavy;
+    const uint64_t thin = p.tiles - p.thin_tiles;
     const bool between = thin > split || !p.thin_tiles;
     if ((e = tiles(8, 0, p.wide_heavy, p.wide_tiles, false)) != hipSuccess ||
         (between && (e = tiles(4, p.wide_tiles, split, thin, false)) != hipSuccess) ||

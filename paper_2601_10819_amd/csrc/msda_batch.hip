@@ -24,7 +24,7 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
     __shared__ u32 grp[2 * 8 * kMaxBatchScenes];    // first slot of (light, level, scene)
     __shared__ __align__(8) u32 tiles[kMaxBatchRegions];   // tiles of each slot, then their scan
     __shared__ u32 lds4[4];
-    static_assert(2 * kSlots * kMaxBatchScenes <= kMaxBatchRegions, "slot_first shares tiles' space");
+    static_assert(2 * kSlots * kMaxBatchScenes <= kMaxBatchRegions, "slot_first is in tiles");
     u64* const slot_first = reinterpret_cast<u64*>(tiles); // first unit of (XCD slot, scene)
     const int S = b.S, L = b.L, tid = threadIdx.x;
 
@@ -42,8 +42,8 @@ __global__ void __launch_bounds__(256) batch_tables_kernel(BatchArgs b, int back
             b.t.region_start[s] = reg;
             rstart[s] = reg;
             b.t.row_start[s] = rows;
-            rows += (u64)(backward ? bwd_rows((int)s_cams[s], b.P) : fwd_rows((int)s_cams[s], b.P, L)) *
-                    s_anchors[s];
+            const int N = (int)s_cams[s];
+            rows += (u64)(backward ? bwd_rows(N, b.P) : fwd_rows(N, b.P, L)) * s_anchors[s];
             a += s_anchors[s];
             smp += s_anchors[s] * ((u32)b.P * s_cams[s] * (u32)L);
             reg += s_cams[s] * (u32)L;

@@ -1,10 +1,10 @@
 // The backward gather's unit of work, shared by every work order: the
 // gradients of a run of one anchor's (keypoint, camera) pairs, by one wave.
 //
-// What bounds it: at the 64-camera scene in BF16 the vector ALU is busy 87% of
+// What bounds it: at the 64-camera scene in BF16 the vector ALU is busy 86% of
 // the launch (61 instructions per sample: 32 widen and multiply-add the
 // corners, 12 form the sums, the rest stages and reduces) and the vector
-// cache's address path 80%. One camera per unit keeps an XCD's waves on one
+// cache's address path 92%. One camera per unit keeps an XCD's waves on one
 // camera's pyramid, each sample is staged by one lane with its record, and
 // grad_w leaves by whole samples: 0.44 -> 0.39 ms. Products on the matrix
 // cores (grad_out split exactly into three bfloat16 parts, the diagonal of

@@ -128,8 +128,9 @@ __device__ __forceinline__ void reduce_subwaves(const Lanes& q, float* acc) {
 // then keypoint, then level; they go through LDS `chunk` at a time (a power of two from
 // the sub-waves' count to 64; it does not change the sum's order), one per
 // lane: corner offsets, and per group the corner weights times the sample's
-// weight (and the FP8 level scale; many groups: apart, see row_lds_bytes). Geometry is read from memory: a camera's
-// few words stay in the caches, and nothing is staged block-wide.
+// weight (and the FP8 level scale; many groups: apart, see row_lds_bytes).
+// Geometry is read from memory: a camera's few words stay in the caches, and
+// nothing is staged block-wide.
 template <class FT, int CPL, bool PACKED>
 __device__ __forceinline__ void row_sum(const OpArgs& a, size_t ba, rsrc_t feat, int s_lo,
                                         int s_hi, const Lanes& q, int chunk, unsigned char* lds,

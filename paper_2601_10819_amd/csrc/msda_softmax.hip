@@ -273,9 +273,10 @@ __global__ void __launch_bounds__(kFlatThreads) softmax_apply_kernel(const float
 
 // Runs an anchor is cut into, and their length: where a block per anchor leaves
 // most of the 256 CUs without one and an anchor is many rounds long, as many as
-// give every CU two blocks (64 cameras, 13 keypoints, 4 levels, 64 groups, logits,
-// backward of weights: 4 anchors 138 us in one block each, 82 in
-// runs; 32 182 and 95; 100 359 and 247; 8 groups, 7 rounds, are one block).
+// give every CU two blocks (64 cameras, 13 keypoints, 4 levels, 64 groups, 52
+// rounds, whole gradient of the logits: 4 anchors 138 us in one block each, 82 in
+// runs; 32 182 and 95; 100 359 and 247; 8 groups, 7 rounds, were no slower than
+// two launches: 4 anchors 40 us).
 struct Runs {
     unsigned parts;
     size_t per;
@@ -315,7 +316,8 @@ void with_threads(int threads, F&& f) {
 template <class F>
 void in_parts(int BA, F&& f) {
     constexpr int kPart = 1 << 21;
-    for (int64_t at = 0; at < BA; at += kPart) f((size_t)at, (unsigned)(BA - at < kPart ? BA - at : kPart));
+    for (int64_t at = 0; at < BA; at += kPart)
+        f((size_t)at, (unsigned)(BA - at < kPart ? BA - at : kPart));
 }
 
 template <class T>

@@ -77,8 +77,8 @@ __device__ __forceinline__ void load_go(const float* p, float* v) {
 // Tables of the tiled reduction for one batch item, from the shapes: the
 // first cell of each region (regions in order, (H+1)(W+1) bilinear cells
 // each and one for the region's samples outside the level) and the first tile
-// of each processing slot (coarse levels first: slot o = (L-1-l)*N + n). One block of 256 threads; N*L <=
-// 1024 regions, 4 per thread.
+// of each processing slot (coarse levels first: slot o = (L-1-l)*N + n). One
+// block of 256 threads; N*L <= 1024 regions, 4 per thread.
 __global__ void __launch_bounds__(256) region_tables_kernel(const int32_t* shapes, int N, int L,
                                                             u32* cell_start, u32* tile_start) {
     __shared__ u32 lds4[4];
@@ -722,7 +722,8 @@ __device__ __forceinline__ void sparse_body(const Args& t, const u32 gt, u32 end
     const int sub = (threadIdx.x & 63) >> t.lps_shift;
     TileView v = tile_view<false>(t, min(gt + (u32)sub, end));
     v.active = v.active && sub < t.sparse;
-    float* tab = reinterpret_cast<float*>(smem) + (size_t)wave * sparse_wave_floats(t.lps_shift, t.G);
+    float* tab =
+        reinterpret_cast<float*>(smem) + (size_t)wave * sparse_wave_floats(t.lps_shift, t.G);
     tile_reduce_sparse<OT, CPL>(v, t.lps_shift,
                                 reinterpret_cast<u32*>(tab + 64 * tile_entry_floats(t.G)), tab);
 }
@@ -764,7 +765,8 @@ __device__ __forceinline__ void tile_block(const Args& t, const u32 items) {
     }
     const u32 w = (blockIdx.x - heavy) * (u32)BW + (u32)wave;
     if constexpr (SPARSE)
-        sparse_body<OT, CPL>(t, heavy + w * (u32)t.sparse, (t.tile_end - t.tile_begin) * items, wave);
+        sparse_body<OT, CPL>(t, heavy + w * (u32)t.sparse, (t.tile_end - t.tile_begin) * items,
+                             wave);
     else
         tile_body<OT, CPL, WHOLE, 2>(t, heavy + w, 1, 0);
 }
@@ -786,8 +788,9 @@ __global__ void __launch_bounds__(64 * kMaxTileBlockWaves)
 
 // ---------------------------------------------------------------- launchers
 
-// LDS of a tile block of `waves` waves: the larger of the record tables and the partial sums (coarse tiles: waves/2 halves of
-// a tile's accumulators).
+// LDS of a tile block of `waves` waves: the larger of the record tables (sparse
+// tiles: with the cell boundaries) and the partial sums (coarse tiles: waves/2
+// halves of a tile's accumulators).
 template <int CPL>
 static size_t tile_lds_bytes(int waves, int G, bool coarse, int sparse, int lps_shift) {
     const size_t part = coarse ? (size_t)(waves / 2) * kTileH * kTileW * CPL * 64 * 4 : 0;
